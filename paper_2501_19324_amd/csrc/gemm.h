@@ -800,17 +800,44 @@ static void gemm_launch(hipStream_t st, int epi, const float* W, int N, int K, c
 
 // ---------------------------------------------------------------- bf16 MFMA, many rows, pre-split activations
 // Y[m][n] (+)= sum_k (Xh + Xl)[m][k] * W[n][k] for more than 64 rows (prefill chunks, large decode batches).
-// Block tile BM (128 or 256 rows of X) x 256 (rows of W), BM / 32 waves of 64 x 128 (2 x 4 MFMA tiles of
-// 32x32x16, hi and lo pass on each: 32 MFMAs against 16 operand reads of 16 bytes per K block of 32).
-// The copies from L2 into LDS, not the MFMAs, bound this kernel (they alone take 85 % of its time at
-// BM = 128): per K block a tile pulls 64 B x (2 BM + 256) through L2, so the larger tile moves 25 %
-// fewer bytes per flop and is used whenever it still gives every compute unit two blocks.  LDS holds two stages of
-// [rows][32 k] tiles (Xh, Xl, W), chunks of 16 bytes permuted by (row / 4) % 4 so that both the
-// line-wise writes and the operand reads are conflict-free without padding.  While one stage is
-// multiplied the next one is already on its way from global memory in registers.  gridDim.z > 1 cuts K into
-// slices whose partial tiles go to part[z][M][N] (finished by rows_finish_kernel).
-template <int EPI, int BM>
-__global__ __launch_bounds__(BM * 2, BM == 128 ? 2 : 1) void gemm_tile_kernel(const bf16_t* __restrict__ W, int N, int K,
+// Block tile BM rows of X x BN rows of W on eight waves, MFMA tiles of 32x32x16, lo pass then hi pass on each.
+//
+// What bounds it: MFMA issue, and behind that the power the chip may draw.  The K loop is built so that the matrix
+// cores never wait for operands:
+//   * LDS holds a ring of three stages of 32 k ([rows][32 k] tiles of Xh, Xl and W; chunks of 16 bytes permuted by
+//     (row / 4) % 4, which makes the operand reads conflict-free without padding).  The copies go straight from
+//     global memory into LDS (global_load_lds, 1 KB per wave request, the permutation applied to the source address)
+//     and are requested more than two K blocks before they are used;
+//   * the operands of the next half K block (16 k) are read from LDS into a second register set between the MFMAs of
+//     the half being multiplied, so neither a barrier nor an LDS round trip stands between two MFMAs;
+//   * one barrier per K block, in its middle: before it every wave has its own copies of the next block landed
+//     (vmcnt) and has read the rest of this block (lgkmcnt), so behind it the next block may be read and the ring's
+//     oldest stage overwritten.
+// The order inside the loop is pinned with sched_barrier; the requests are inline assembly because the compiler would
+// otherwise drain them (vmcnt(0)) in front of every LDS read.  They write no registers.
+// Measured at 8192 x 37888 x 3584 (256 x 256 tile): 2130 shader cycles per K block against 2048 of MFMA issue; the chip
+// then holds 1.50 GHz (the register-staged, two-stage predecessor: 2610 cycles at 1.71 GHz), 3.95 -> 3.23 ms = 1.38 PFLOP/s
+// executed, what a library bf16 product of this shape reaches on this part.  Fewer, larger waves (four of 128 x 128,
+// a quarter less LDS traffic) leave the barrier exposed: 2610 cycles, 3.44 ms.
+// Thread blocks go to the XCDs round-robin by index; they are renumbered so that an XCD works on consecutive tiles in
+// groups of four row tiles (32 resident blocks = 4 x 8 tiles share their operands in that XCD's L2): 3.50 -> 3.23 ms.
+// gridDim.z > 1 cuts K into slices whose partial tiles go to part[z][M][N] (finished by rows_finish_kernel).
+__device__ __forceinline__ void copy16_to_lds(uint32_t lds_off, uint32_t voff, const char* base) {
+    // lane l: 16 bytes at base + voff -> LDS byte lds_off + 16 l  (M0 holds the wave's LDS address; one wait state behind its write)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_off), "v"(voff), "s"(base) : "memory");
+}
+template <int BM, int BN>
+struct TileCfg {
+    static constexpr int BK = 32, NS = 3;
+    static constexpr int WN = 2, WM = 4;                                 // waves along the columns / rows of the tile
+    static constexpr int TM = BM / 32 / WM, TN = BN / 32 / WN;           // MFMA tiles of a wave
+    static constexpr int STAGE = (2 * BM + BN) * BK;                     // bf16 elements of a stage
+    static constexpr int LDS = NS * STAGE * 2;
+    static constexpr int NA = BM / 128;                                  // 16-row requests of a wave per X half
+    static constexpr int NB = BN / 128, NBX = (BN / 16) % 8;             // ... of W: NB, one more for the first NBX waves
+};
+template <int EPI, int BM, int BN>
+__global__ __launch_bounds__(512, 2) void gemm_tile_kernel(const bf16_t* __restrict__ W, int N, int K,
                                                            const uint16_t* __restrict__ Xh,
                                                            const uint16_t* __restrict__ Xl, int M,
                                                            float* __restrict__ Y, int ldy,
@@ -822,129 +849,132 @@ __global__ __launch_bounds__(BM * 2, BM == 128 ? 2 : 1) void gemm_tile_kernel(co
     // launches} are added to clk[0..2], which gives the clock the chip sustains while this kernel runs
     long long clk_c0 = 0, clk_w0 = 0;
     if (clk) { clk_c0 = clock64(); clk_w0 = wall_clock64(); }
-    constexpr int BN = 256, BK = 32, CR = BM / 2;        // CR: rows covered by one round of copies (threads / 4)
-    __shared__ __attribute__((aligned(16))) uint16_t Ah[2][BM * BK];
-    __shared__ __attribute__((aligned(16))) uint16_t Al[2][BM * BK];
-    __shared__ __attribute__((aligned(16))) uint16_t Bs[2][BN * BK];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;                 // wave tile: rows wm*64.., columns wn*128..
-    // (K-sliced launches only: without slices the plain order already keeps an activation tile's blocks together)
-    int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
-    if (gridDim.z > 1) {
-        const int nxy = gridDim.x * gridDim.y;
-        const int lin = xcd_major(bx + gridDim.x * by + nxy * bz, nxy * gridDim.z, M, N);
-        bz = lin / nxy; by = (lin - bz * nxy) / gridDim.x; bx = lin - bz * nxy - by * gridDim.x;
+    using C = TileCfg<BM, BN>;
+    constexpr int BK = C::BK, TM = C::TM, TN = C::TN, STAGE = C::STAGE, NA = C::NA, NB = C::NB, NBX = C::NBX;
+    constexpr int ND = 2 * NA + NB;                          // requests of a wave per K block (waves below NBX: one more)
+    extern __shared__ __attribute__((aligned(16))) uint16_t tile_sm[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / C::WN, wn = wave % C::WN;
+    int bx, by, bz;
+    {
+        constexpr int GM = 4;
+        const int nxy = gridDim.x * gridDim.y, nb = nxy * gridDim.z;
+        const int id = blockIdx.x + gridDim.x * blockIdx.y + nxy * blockIdx.z;
+        const int k = id % 8, j = id / 8, q = nb / 8, r = nb % 8;
+        int lin = k * q + min(k, r) + j;
+        bz = lin / nxy; lin -= bz * nxy;
+        const int per = GM * gridDim.x, g = lin / per, rem = lin - g * per;
+        const int gm = min(GM, (int)gridDim.y - g * GM);
+        by = g * GM + rem % gm; bx = rem / gm;
+        // (the divisions leave them in vector registers; the copies below need their base addresses in scalar ones)
+        bx = __builtin_amdgcn_readfirstlane(bx); by = __builtin_amdgcn_readfirstlane(by); bz = __builtin_amdgcn_readfirstlane(bz);
     }
     const int m0 = by * BM, n0 = bx * BN;
-    const int nkb = K / BK;
-    const int per = (nkb + gridDim.z - 1) / gridDim.z;
-    const int kb0 = bz * per, kb1 = min(nkb, kb0 + per);
-    const int nk = kb1 - kb0;
-    const int kb_last = max(kb1 - 1, 0);
-    // LDS offset (in bf16) of 16-byte chunk c (0..3) of row r
-    auto sw = [](int r, int c) { return r * BK + ((c ^ ((r >> 2) & 3)) << 3); };
-    // global -> LDS copies: thread -> chunk tid % 4 of rows tid / 4 + CR i (two rounds cover the X tile;
-    // the W tile takes four rounds at BM = 128, two at BM = 256)
-    const int crow = tid >> 2, cch = tid & 3;
-    const uint16_t* ah0 = Xh + (size_t)min(m0 + crow, M - 1) * K + cch * 8;
-    const uint16_t* ah1 = Xh + (size_t)min(m0 + crow + CR, M - 1) * K + cch * 8;
-    const uint16_t* al0 = Xl + (size_t)min(m0 + crow, M - 1) * K + cch * 8;
-    const uint16_t* al1 = Xl + (size_t)min(m0 + crow + CR, M - 1) * K + cch * 8;
-    // W row behind tile column r.  EPI_SWIGLU (W = [gate | up], N = 2F, never K-sliced): the tile's columns are 128
-    // gate rows and the 128 up rows of the same units, arranged so that a wave's column groups j and j + 2 hold
-    // gate and up of one unit: columns 128 w + 64 h + i (w = wave column, h = 0 gate / 1 up) <- row h F + 128 bx + 64 w + i
-    auto wrow = [&](int r) {
-        if (EPI == EPI_SWIGLU) return min(((r >> 6) & 1) * (N / 2) + bx * 128 + (r >> 7) * 64 + (r & 63), N - 1);
-        return min(n0 + r, N - 1);
-    };
-    const bf16_t* b0 = W + (size_t)wrow(crow) * K + cch * 8;
-    const bf16_t* b1 = W + (size_t)wrow(crow + CR) * K + cch * 8;
-    const bf16_t* b2 = W + (size_t)wrow(crow + 128) * K + cch * 8;       // BM = 128 only
-    const bf16_t* b3 = W + (size_t)wrow(crow + 192) * K + cch * 8;
-    const int st0 = sw(crow, cch), st1 = sw(crow + CR, cch), st2 = sw(crow + 128, cch), st3 = sw(crow + 192, cch);
+    const int nkb_all = K / BK;
+    const int per = __builtin_amdgcn_readfirstlane((nkb_all + gridDim.z - 1) / gridDim.z);
+    const int nk = min(nkb_all, bz * per + per) - bz * per, kb0 = min(bz * per, nkb_all - 1);     // K blocks of this slice (an empty one: nk <= 0, zeros)
 
-    f32x16_t acc[2][4];
+    // copies: lane -> row lane / 4 of a 16-row group, LDS chunk lane % 4, which holds source chunk (lane % 4) ^ ((row / 4) % 4)
+    const int lrow = lane >> 2, lch = (lane & 3) ^ ((lane >> 4) & 3);
+    // W row behind tile row r.  EPI_SWIGLU (W = [gate | up], N = 2F, never K-sliced): a 32-row group is 16 gate rows and the
+    // 16 up rows of the same units
+    const int F = N / 2;
+    auto wrow = [&](int r) { return EPI == EPI_SWIGLU ? ((r >> 4) & 1) * F + min(bx * (BN / 2) + (r >> 5) * 16 + (r & 15), F - 1) : min(n0 + r, N - 1); };
+    const char *pa_h[NA], *pa_l[NA], *pb[NB + 1];
+    uint32_t va[NA], vb[NB + 1];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NA; ++i) {
+        const int r = m0 + (i * 8 + wave) * 16, b = min(r, M - 1);
+        va[i] = (uint32_t)(min(r + lrow, M - 1) - b) * (uint32_t)K * 2u + lch * 16u;
+        pa_h[i] = reinterpret_cast<const char*>(Xh + (size_t)b * K + (size_t)kb0 * BK);
+        pa_l[i] = reinterpret_cast<const char*>(Xl + (size_t)b * K + (size_t)kb0 * BK);
+    }
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+    for (int i = 0; i < NB + 1; ++i) {                       // (the last one is used by the waves below NBX only)
+        const int r = min((i * 8 + wave) * 16, BN - 16), b = wrow(r);
+        vb[i] = (uint32_t)(wrow(r + lrow) - b) * (uint32_t)K * 2u + lch * 16u;
+        pb[i] = reinterpret_cast<const char*>(W + (size_t)b * K + (size_t)kb0 * BK);
+    }
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)tile_sm + wave * 1024;
+    // request d of a wave for K block kb into stage s; past the end the last block is requested again (never used)
+    auto request = [&](int kb, int s, int d) {
+        const size_t ko = (size_t)max(min(kb, nk - 1), 0) * (BK * 2);
+        const uint32_t l = lds0 + s * (STAGE * 2);
+        if (d < NA) copy16_to_lds(l + d * 8192, va[d], pa_h[d] + ko);
+        else if (d < 2 * NA) copy16_to_lds(l + BM * 64 + (d - NA) * 8192, va[d - NA], pa_l[d - NA] + ko);
+        else copy16_to_lds(l + 2 * BM * 64 + (d - 2 * NA) * 8192, vb[d - 2 * NA], pb[d - 2 * NA] + ko);
+    };
+    const bool extra = NBX > 0 && wave < NBX;
+
+    f32x16_t acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-
-    // two register sets named member by member: a K block is requested two steps before it moves into LDS
-    struct Regs { u32x4_t h0, h1, l0, l1, b0, b1, b2, b3; };
-    Regs ra, rb;
-#define RSD_FETCH(kb, R)                                                                         \
-    {                                                                                            \
-        const size_t k0_ = (size_t)min((kb), kb_last) * BK;                                      \
-        R.h0 = *reinterpret_cast<const u32x4_t*>(ah0 + k0_);                                     \
-        R.h1 = *reinterpret_cast<const u32x4_t*>(ah1 + k0_);                                     \
-        R.l0 = *reinterpret_cast<const u32x4_t*>(al0 + k0_);                                     \
-        R.l1 = *reinterpret_cast<const u32x4_t*>(al1 + k0_);                                     \
-        R.b0 = *reinterpret_cast<const u32x4_t*>(b0 + k0_);                                      \
-        R.b1 = *reinterpret_cast<const u32x4_t*>(b1 + k0_);                                      \
-        if (BM == 128) {                                                                         \
-            R.b2 = *reinterpret_cast<const u32x4_t*>(b2 + k0_);                                  \
-            R.b3 = *reinterpret_cast<const u32x4_t*>(b3 + k0_);                                  \
-        }                                                                                        \
-    }
-#define RSD_STAGE(buf, R)                                                                        \
-    {                                                                                            \
-        *reinterpret_cast<u32x4_t*>(&Ah[(buf)][st0]) = R.h0;                                     \
-        *reinterpret_cast<u32x4_t*>(&Ah[(buf)][st1]) = R.h1;                                     \
-        *reinterpret_cast<u32x4_t*>(&Al[(buf)][st0]) = R.l0;                                     \
-        *reinterpret_cast<u32x4_t*>(&Al[(buf)][st1]) = R.l1;                                     \
-        *reinterpret_cast<u32x4_t*>(&Bs[(buf)][st0]) = R.b0;                                     \
-        *reinterpret_cast<u32x4_t*>(&Bs[(buf)][st1]) = R.b1;                                     \
-        if (BM == 128) {                                                                         \
-            *reinterpret_cast<u32x4_t*>(&Bs[(buf)][st2]) = R.b2;                                 \
-            *reinterpret_cast<u32x4_t*>(&Bs[(buf)][st3]) = R.b3;                                 \
-        }                                                                                        \
-    }
     const int l32 = lane & 31, kg = lane >> 5;
-#define RSD_COMPUTE(buf)                                                                         \
-    {                                                                                            \
-        _Pragma("unroll") for (int kk_ = 0; kk_ < 2; ++kk_) {                                    \
-            bf16x8_t a_[2], l_[2], b_[4];                                                        \
-            _Pragma("unroll") for (int i_ = 0; i_ < 2; ++i_) {                                   \
-                const int off_ = sw(wm * 64 + i_ * 32 + l32, kk_ * 2 + kg);                      \
-                a_[i_] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(&Ah[(buf)][off_])); \
-                l_[i_] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(&Al[(buf)][off_])); \
-            }                                                                                    \
-            _Pragma("unroll") for (int j_ = 0; j_ < 4; ++j_)                                     \
-                b_[j_] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(&Bs[(buf)][sw(wn * 128 + j_ * 32 + l32, kk_ * 2 + kg)])); \
-            /* all lo passes, then all hi passes: two MFMAs on one accumulator are eight apart */ \
-            _Pragma("unroll") for (int i_ = 0; i_ < 2; ++i_)                                     \
-                _Pragma("unroll") for (int j_ = 0; j_ < 4; ++j_)                                 \
-                    acc[i_][j_] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(l_[i_], b_[j_], acc[i_][j_], 0, 0, 0); \
-            _Pragma("unroll") for (int i_ = 0; i_ < 2; ++i_)                                     \
-                _Pragma("unroll") for (int j_ = 0; j_ < 4; ++j_)                                 \
-                    acc[i_][j_] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_[i_], b_[j_], acc[i_][j_], 0, 0, 0); \
-        }                                                                                        \
+    // operand reads: rows of a wave's tiles start at multiples of 32, so the permutation depends on the lane alone
+    const int swz = (l32 >> 2) & 3;
+    const int o0 = l32 * BK + ((kg ^ swz) << 3), o1 = l32 * BK + (((2 + kg) ^ swz) << 3);      // first / second 16 k of a block
+    const uint16_t* A = tile_sm + wm * TM * 32 * BK;
+    const uint16_t* B = tile_sm + 2 * BM * BK + wn * TN * 32 * BK;
+    struct Ops { u32x4_t h[TM], l[TM], b[TN]; };
+    Ops P, Q;
+    constexpr int NR = 2 * TM + TN, NM = 2 * TM * TN;        // operand reads and MFMAs of a half block
+    // read number r of a half block, in the order in which the MFMAs need them: lo row 0, W, lo rows, hi rows
+    auto read = [&](Ops& d, const uint16_t* a, const uint16_t* b, int r) {
+        if (r == 0) d.l[0] = *reinterpret_cast<const u32x4_t*>(a + BM * BK);
+        else if (r <= TN) d.b[r - 1] = *reinterpret_cast<const u32x4_t*>(b + (r - 1) * 32 * BK);
+        else if (r < TN + TM) d.l[r - TN] = *reinterpret_cast<const u32x4_t*>(a + BM * BK + (r - TN) * 32 * BK);
+        else d.h[r - TN - TM] = *reinterpret_cast<const u32x4_t*>(a + (r - TN - TM) * 32 * BK);
+    };
+    auto mfma = [&](const Ops& o, int t) {
+        const int u = t % (TM * TN), i = u / TN, j = u % TN;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, t < TM * TN ? o.l[i] : o.h[i]),
+                                                            __builtin_bit_cast(bf16x8_t, o.b[j]), acc[i][j], 0, 0, 0);
+    };
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+#pragma unroll
+        for (int d = 0; d < ND; ++d) request(s, s, d);
+        if (extra) request(s, s, ND);
     }
-    RSD_FETCH(kb0, ra)
-    RSD_FETCH(kb0 + 1, rb)
-    RSD_STAGE(0, ra)
-    __syncthreads();
-    // step i: block i + 2 is requested into the set F that block i came from, block i is multiplied,
-    // block i + 1 (set S, requested a step ago) moves into the LDS buffer block i - 1 has left
-#define RSD_STEP(i_step, F, S)                                                                   \
-    {                                                                                            \
-        RSD_FETCH(kb0 + (i_step) + 2, F)                                                         \
-        RSD_COMPUTE((i_step) & 1)                                                                \
-        RSD_STAGE(((i_step) + 1) & 1, S)                                                         \
-        __syncthreads();                                                                         \
+    // the first stage has landed when at most the requests of the two others are outstanding
+    if (extra) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * ND + 2) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * ND) : "memory");
+#pragma unroll
+    for (int r = 0; r < NR; ++r) read(P, A + o0, B + o0, r);
+    int stg = 0;
+    for (int kb = 0; kb < nk; ++kb) {
+        const uint16_t *a = A + stg * STAGE + o1, *b = B + stg * STAGE + o1;
+#pragma unroll
+        for (int t = 0; t < NM; ++t) {                       // first half: multiply P, read the second half into Q
+            mfma(P, t);
+            if (t < NR) read(Q, a, b, t);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // the next block's copies have landed (only the block after it may be outstanding) and this block is read
+        if (extra) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(ND + 1) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(ND) : "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        const int nst = stg == 2 ? 0 : stg + 1;
+        a = A + nst * STAGE + o0; b = B + nst * STAGE + o0;
+#pragma unroll
+        for (int t = 0; t < NM; ++t) {                       // second half: multiply Q, read the next block's first half, request block kb + 3
+            mfma(Q, t);
+            constexpr int IT = NR + ND;
+#pragma unroll
+            for (int k = t * IT / NM; k < (t + 1) * IT / NM; ++k) {
+                if (k < NR) read(P, a, b, k);
+                else request(kb + 3, stg, k - NR);
+            }
+            if (t == NM - 1 && extra) request(kb + 3, stg, ND);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        stg = nst;
     }
-    int i = 0;
-    for (; i + 1 < nk; i += 2) {
-        RSD_STEP(i, ra, rb)
-        RSD_STEP(i + 1, rb, ra)
-    }
-    if (i < nk) RSD_STEP(i, ra, rb)
-#undef RSD_STEP
-#undef RSD_FETCH
-#undef RSD_STAGE
-#undef RSD_COMPUTE
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");      // nothing is in flight into LDS when the block ends
     if (clk && tid == 0 && blockIdx.x == gridDim.x / 2 && blockIdx.y == gridDim.y / 2 && blockIdx.z == 0) {
         atomicAdd(&clk[0], (unsigned long long)(clock64() - clk_c0));
         atomicAdd(&clk[1], (unsigned long long)(wall_clock64() - clk_w0));
@@ -952,18 +982,19 @@ __global__ __launch_bounds__(BM * 2, BM == 128 ? 2 : 1) void gemm_tile_kernel(co
     }
 
     if (EPI == EPI_SWIGLU) {
-        // silu(gate) * up of the units this wave holds, straight into the hi / lo halves the down projection reads
-        const int F = N / 2;
+        // silu(gate) * up straight into the hi / lo halves the down projection reads.  Lanes 0..15 of a 32-lane half hold
+        // gate, 16..31 up of the same 16 units; a row swap of two accumulator registers gives every lane both of one row
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int col = bx * 128 + wn * 64 + j * 32 + l32;
+            for (int j = 0; j < TN; ++j) {
+                const int col = bx * (BN / 2) + (wn * TN + j) * 16 + (lane & 15);
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int m = m0 + wm * 64 + i * 32 + 8 * (v >> 2) + 4 * kg + (v & 3);
+                for (int v = 0; v < 8; ++v) {
+                    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[i][j][v]), __float_as_uint(acc[i][j][v + 8]), false, false);
+                    const float g = __uint_as_float(s[0]), u = __uint_as_float(s[1]);
+                    const int m = m0 + (wm * TM + i) * 32 + 8 * (v >> 2) + 4 * kg + (v & 3) + ((lane & 16) ? 16 : 0);
                     if (m < M && col < F) {
-                        const float g = acc[i][j][v], u = acc[i][j + 2][v];
                         const float x = g / (1.0f + expf(-g)) * u;
                         const uint16_t hi = f2bf(x);
                         Oh[(size_t)m * F + col] = hi;
@@ -974,112 +1005,91 @@ __global__ __launch_bounds__(BM * 2, BM == 128 ? 2 : 1) void gemm_tile_kernel(co
         return;
     }
     const bool sliced = gridDim.z > 1;
+    float res[2][16];        // EPI_RESID: the residual values of a tile are requested while the tile before it is stored
+    auto fetch_res = [&](int t, float* r) {
+        const int i = t / TN, j = t % TN, n = min(n0 + (wn * TN + j) * 32 + l32, N - 1);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int v = 0; v < 16; ++v)
+            r[v] = Y[(size_t)min(m0 + (wm * TM + i) * 32 + 8 * (v >> 2) + 4 * kg + (v & 3), M - 1) * ldy + n];
+    };
+    if (EPI == EPI_RESID && !sliced) fetch_res(0, res[0]);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + wn * 128 + j * 32 + l32;
+    for (int t = 0; t < TM * TN; ++t) {
+        if (EPI == EPI_RESID && !sliced && t + 1 < TM * TN) fetch_res(t + 1, res[(t + 1) & 1]);
+        const int i = t / TN, j = t % TN, n = n0 + (wn * TN + j) * 32 + l32;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int m = m0 + wm * 64 + i * 32 + 8 * (v >> 2) + 4 * kg + (v & 3);
-                if (m < M && n < N) {
-                    if (sliced) {
-                        part[((size_t)bz * M + m) * N + n] = acc[i][j][v];
-                    } else {
-                        float* yp = Y + (size_t)m * ldy + n;
-                        *yp = (EPI == EPI_RESID) ? (*yp + acc[i][j][v]) : acc[i][j][v];
-                    }
-                }
+        for (int v = 0; v < 16; ++v) {
+            const int m = m0 + (wm * TM + i) * 32 + 8 * (v >> 2) + 4 * kg + (v & 3);
+            if (m < M && n < N) {
+                if (sliced) part[((size_t)bz * M + m) * N + n] = acc[i][j][v];
+                else Y[(size_t)m * ldy + n] = EPI == EPI_RESID ? res[t & 1][v] + acc[i][j][v] : acc[i][j][v];
             }
         }
+    }
 }
 
-// Block tile and K slices for gemm_tile_kernel.
-// Many rows (chunked passes): gemm_tile_plan_chunked below.
-// 65..256 rows (the decode iteration of a large batch: one row tile): the kernel is MFMA-bound there, two
-// co-resident 128-row blocks run no faster than one (measured per K block of 32: 0.97 us for a 128-row block
-// alone on its unit, 2.2 us each for two, 1.37 us for a 256-row block), so the grid is kept to one round of at
-// most 256 blocks and filled with K slices: [3584][18944] at 256 rows 98 -> 72 us, [17920][1536] 53 -> 39 us,
-// [37888][3584] (148 column tiles: no slices, no finish kernel) 178 + 18 -> 170 us.
-static bool gemm_tile_decode_rows(int M) { return M <= 256; }
-// Decode-size launches (one row tile of the batch): the 256-row tile wherever its N tiles x K slices (at least six
-// K blocks each) give 128 blocks or more, else two 128-row tiles (small matrices: the 1.5B attention projections
-// at 256 rows 22 -> 17 us).  A compute unit holds one block of the 256-row tile or two of the 128-row tile.
-// Chunked passes (more than 256 rows): tile height and K slices by a small cost model in units of the measured
-// time per K block (1.37 us for a 256-row block, one per compute unit; 2.2 us for two co-resident 128-row blocks,
-// 0.97 us for one alone): rounds of resident blocks x K blocks per slice (+ 3 for filling and draining the
-// pipeline), plus what the finish kernel pays to read the slices' partial sums back.
-struct TilePlan { int bm, ks; };
-static TilePlan gemm_tile_plan_chunked(int N, int K, int M, size_t part_floats) {
-    const int tn = (N + 255) / 256, nkb = K / 32;
-    TilePlan best{256, 1};
-    double best_t = 1e30;
-    for (int bm : {256, 128})
-        for (int ks = 1; ks <= 32; ks *= 2) {
-            if (ks > 1 && (nkb / ks < 8 || (size_t)ks * M * N > part_floats)) break;
-            const long long blocks = (long long)tn * ((M + bm - 1) / bm) * ks;
-            const double kb = (nkb + ks - 1) / ks + 3;
-            double us;
-            if (bm == 256) us = (double)((blocks + 255) / 256) * kb * 1.37;
-            else {
-                const long long rem = blocks % 512;
-                us = (double)(blocks / 512) * kb * 2.2 + (rem == 0 ? 0.0 : rem <= 256 ? kb * 0.97 : kb * 2.2);
-            }
-            if (ks > 1) us += 4.0 + (double)ks * M * N * 8.0 / 5.0e6;
-            if (us < best_t) { best_t = us; best = TilePlan{bm, ks}; }
+// Block tile and K slices of a many-row product: the plan for which a cost model is smallest.  The model was fitted to
+// 4456 timings (12 projection shapes of the 1.5B / 7B / 72B models x 14 row counts from 70 to 8192 x all tiles and slice
+// counts; rms error 9 %, the plans it picks are 1.4 % slower than the best measured ones on average): a round of thread
+// blocks that fills the chip costs `full` per K block of 32, one that occupies the share x of it `light` + x (`full` -
+// `light`) (fewer busy units clock higher), and every round `over` for filling the ring and storing the tile.  K slices
+// pay a finish kernel that reads their partial sums back; a residual product without slices pays the separate kernel
+// that leaves the normalised halves for the next projection.
+struct TilePlan { int bm, bn, ks; };
+struct TileCost { int bm, bn, per_cu; float full, light, over; };        // microseconds
+static constexpr TileCost kTileCosts[] = {
+    {256, 256, 1, 1.596f, 0.856f, 8.7f}, {256, 192, 1, 1.279f, 0.690f, 6.7f}, {128, 256, 1, 0.903f, 0.435f, 5.0f},
+    {128, 192, 1, 0.718f, 0.382f, 4.3f}, {128, 128, 2, 1.106f, 0.194f, 3.3f}};
+static TilePlan gemm_tile_plan(int epi, int N, int K, int M, size_t part_floats) {
+    const int nkb = K / 32;
+    const float mn = 1e-6f * (float)M * (float)N;
+    TilePlan best{256, 256, 1};
+    float best_us = 1e30f;
+    for (const TileCost& c : kTileCosts)
+        for (int ks : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
+            const int kb = (nkb + ks - 1) / ks;
+            // slices: whole columns of four (finish kernels), at least six K blocks each, none empty, room for the partial sums
+            if (ks > 1 && (N % 4 || kb < 6 || (ks - 1) * kb >= nkb || (size_t)ks * M * N > part_floats)) continue;
+            const long long blocks = (long long)((N + c.bn - 1) / c.bn) * ((M + c.bm - 1) / c.bm) * ks, cap = 256 * c.per_cu;
+            const float part = (float)(blocks % cap) / (float)cap;
+            float us = (float)(blocks / cap) * (kb * c.full + c.over);
+            if (part > 0.0f) us += kb * (c.light + part * (c.full - c.light)) + c.over;
+            if (ks > 1) us += 5.4f + 1.03f * ks * mn;
+            else if (epi == EPI_RESID) us += 8.7f + 0.69f * mn;
+            if (us < best_us) { best_us = us; best = TilePlan{c.bm, c.bn, ks}; }
         }
     return best;
 }
-static int gemm_tile_bm(int N, int K, int M, int ks) {
-    if (gemm_tile_decode_rows(M)) {
-        const int tn = (N + 255) / 256, nkb = K / 32;
-        if (M <= 128) return 128;
-        return tn * std::max(1, std::min(std::min(256 / tn, nkb / 6), 32)) >= 128 ? 256 : 128;
-    }
-    // (chunked: the height the plan chose for this slice count)
-    TilePlan best{256, ks};
-    double best_t = 1e30;
-    const int tn = (N + 255) / 256, nkb = K / 32;
-    for (int bm : {256, 128}) {
-        const long long blocks = (long long)tn * ((M + bm - 1) / bm) * ks;
-        const double kb = (nkb + ks - 1) / ks + 3;
-        double us;
-        if (bm == 256) us = (double)((blocks + 255) / 256) * kb * 1.37;
-        else {
-            const long long rem = blocks % 512;
-            us = (double)(blocks / 512) * kb * 2.2 + (rem == 0 ? 0.0 : rem <= 256 ? kb * 0.97 : kb * 2.2);
-        }
-        if (us < best_t) { best_t = us; best.bm = bm; }
-    }
-    return best.bm;
-}
-static int gemm_tile_slices(int N, int K, int M, size_t part_floats) {
-    if (gemm_tile_decode_rows(M)) {
-        const int tn = (N + 255) / 256, nkb = K / 32;
-        const int bm = gemm_tile_bm(N, K, M, 1);
-        const int room = bm == 256 ? 256 / tn : 512 / (tn * ((M + 127) / 128));
-        int ks = std::max(1, std::min(std::min(room, nkb / 6), 32));
-        while (ks > 1 && ((size_t)ks * M * N > part_floats || (ks - 1) * ((nkb + ks - 1) / ks) >= nkb)) --ks;
-        return ks;
-    }
-    return gemm_tile_plan_chunked(N, K, M, part_floats).ks;
+
+#define RSD_TILE_SIZES(X) X(256, 256) X(256, 192) X(128, 256) X(128, 192) X(128, 128)
+
+// The tiles need more than 64 KB of LDS: allowed once per context on its device (never from inside a launch, which may
+// be recording a graph).
+static hipError_t gemm_tile_raise() {
+    hipError_t e = hipSuccess;
+#define RSD_TILE_RAISE(BM, BN)                                                                                               \
+    for (const void* f : {reinterpret_cast<const void*>(gemm_tile_kernel<EPI_STORE, BM, BN>),                                \
+                          reinterpret_cast<const void*>(gemm_tile_kernel<EPI_RESID, BM, BN>),                                \
+                          reinterpret_cast<const void*>(gemm_tile_kernel<EPI_SWIGLU, BM, BN>)})                              \
+        if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, TileCfg<BM, BN>::LDS);
+    RSD_TILE_SIZES(RSD_TILE_RAISE)
+#undef RSD_TILE_RAISE
+    return e;
 }
 
 // epi == EPI_SWIGLU (W = [gate | up], ks = 1): the activated values go to Oh / Ol [M][N / 2] as hi / lo halves
-static void gemm_tile_launch(hipStream_t st, int epi, const bf16_t* W, int N, int K, const uint16_t* Xh,
-                             const uint16_t* Xl, int M, float* Y, int ldy, float* part, int ks,
+static void gemm_tile_launch(hipStream_t st, int epi, TilePlan pl, const bf16_t* W, int N, int K, const uint16_t* Xh,
+                             const uint16_t* Xl, int M, float* Y, int ldy, float* part,
                              uint16_t* Oh = nullptr, uint16_t* Ol = nullptr, unsigned long long* clk = nullptr) {
-    const int tn = (N + 255) / 256;
-    if (gemm_tile_bm(N, K, M, ks) == 256) {
-        const dim3 grid(tn, (M + 255) / 256, ks), block(512);
-        if (epi == EPI_SWIGLU)     hipLaunchKernelGGL((gemm_tile_kernel<EPI_SWIGLU, 256>), grid, block, 0, st, W, N, K, Xh, Xl, M, Y, ldy, part, Oh, Ol, clk);
-        else if (epi == EPI_RESID) hipLaunchKernelGGL((gemm_tile_kernel<EPI_RESID, 256>), grid, block, 0, st, W, N, K, Xh, Xl, M, Y, ldy, part, Oh, Ol, clk);
-        else                       hipLaunchKernelGGL((gemm_tile_kernel<EPI_STORE, 256>), grid, block, 0, st, W, N, K, Xh, Xl, M, Y, ldy, part, Oh, Ol, clk);
-        return;
+    const dim3 grid((N + pl.bn - 1) / pl.bn, (M + pl.bm - 1) / pl.bm, pl.ks), block(512);
+#define RSD_TILE_CASE(BM, BN)                                                                                                \
+    if (pl.bm == BM && pl.bn == BN) {                                                                                        \
+        constexpr size_t lds = TileCfg<BM, BN>::LDS;                                                                         \
+        if (epi == EPI_SWIGLU)     hipLaunchKernelGGL((gemm_tile_kernel<EPI_SWIGLU, BM, BN>), grid, block, lds, st, W, N, K, Xh, Xl, M, Y, ldy, part, Oh, Ol, clk); \
+        else if (epi == EPI_RESID) hipLaunchKernelGGL((gemm_tile_kernel<EPI_RESID, BM, BN>), grid, block, lds, st, W, N, K, Xh, Xl, M, Y, ldy, part, Oh, Ol, clk);  \
+        else                       hipLaunchKernelGGL((gemm_tile_kernel<EPI_STORE, BM, BN>), grid, block, lds, st, W, N, K, Xh, Xl, M, Y, ldy, part, Oh, Ol, clk);  \
+        return;                                                                                                              \
     }
-    const dim3 grid(tn, (M + 127) / 128, ks), block(256);
-    if (epi == EPI_SWIGLU)     hipLaunchKernelGGL((gemm_tile_kernel<EPI_SWIGLU, 128>), grid, block, 0, st, W, N, K, Xh, Xl, M, Y, ldy, part, Oh, Ol, clk);
-    else if (epi == EPI_RESID) hipLaunchKernelGGL((gemm_tile_kernel<EPI_RESID, 128>), grid, block, 0, st, W, N, K, Xh, Xl, M, Y, ldy, part, Oh, Ol, clk);
-    else                       hipLaunchKernelGGL((gemm_tile_kernel<EPI_STORE, 128>), grid, block, 0, st, W, N, K, Xh, Xl, M, Y, ldy, part, Oh, Ol, clk);
+    RSD_TILE_SIZES(RSD_TILE_CASE)
+#undef RSD_TILE_CASE
 }
-

@@ -530,7 +530,8 @@ void rows_gemm(rsd_ctx* c, const Model& m, int op, int epi, const bf16_t* W, int
         ProbeScope ps(c, m, op, pb, pf);
         gemm_rows_launch(c->st, W, N, K, Xh, Xl, M, c->part_k, ks);
     } else {
-        ks = N % 4 ? 1 : gemm_tile_slices(N, K, M, c->part_k_floats);
+        const TilePlan pl = gemm_tile_plan(epi, N, K, M, c->part_k_floats);
+        ks = pl.ks;
         if (ks == 1) {      // the tile kernel finishes by itself
             if (epi == EPI_SWIGLU) {
                 // the kernel activates in its epilogue; the halves cannot go to xs_h / xs_l, which other blocks still
@@ -539,19 +540,19 @@ void rows_gemm(rsd_ctx* c, const Model& m, int op, int epi, const bf16_t* W, int
                 uint16_t* oh = reinterpret_cast<uint16_t*>(c->gu);
                 uint16_t* ol = oh + (size_t)M * (N / 2);
                 ProbeScope ps(c, m, op, pb, pf);
-                gemm_tile_launch(c->st, EPI_SWIGLU, W, N, K, Xh, Xl, M, nullptr, 0, nullptr, 1, oh, ol, ps.clk());
+                gemm_tile_launch(c->st, EPI_SWIGLU, pl, W, N, K, Xh, Xl, M, nullptr, 0, nullptr, oh, ol, ps.clk());
                 c->xin_h = oh; c->xin_l = ol;
             } else {
                 {
                     ProbeScope ps(c, m, op, pb, pf);
-                    gemm_tile_launch(c->st, epi, W, N, K, Xh, Xl, M, Y, ldy, nullptr, 1, nullptr, nullptr, ps.clk());
+                    gemm_tile_launch(c->st, epi, pl, W, N, K, Xh, Xl, M, Y, ldy, nullptr, nullptr, nullptr, ps.clk());
                 }
                 if (next_gain) rows_split(c, Y, ldy, M, N, next_gain, eps);
             }
             return;
         }
         ProbeScope ps(c, m, op, pb, pf);
-        gemm_tile_launch(c->st, EPI_STORE, W, N, K, Xh, Xl, M, nullptr, 0, c->part_k, ks, nullptr, nullptr, ps.clk());
+        gemm_tile_launch(c->st, EPI_STORE, pl, W, N, K, Xh, Xl, M, nullptr, 0, c->part_k, nullptr, nullptr, ps.clk());
     }
     if (defer && geo.G == 0 && ldy == N) {
         *defer = QkvParts{c->part_k, ks, (size_t)rows * N};
@@ -1287,6 +1288,7 @@ int rsd_init(rsd_ctx** out, const rsd_model_shape shape[3], const rsd_weights w[
         int rc = setup_kv(c, c->m[i], i);
         if (rc) return rc;
     }
+    HIPCHK(c, gemm_tile_raise());
     const int B = batch;
     const size_t mc = p->max_ctx;
     c->sb_ints = (size_t)18 * B + 4;

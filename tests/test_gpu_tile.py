@@ -1,0 +1,52 @@
+"""The many-row GEMM (chunked passes of more than 64 rows) at the edges of its tiles: row counts around multiples of 128
+and 256, matrices whose sides are no multiple of any tile, an odd vocabulary, K sliced and not.
+
+Small model: against the fp64 checker.  Full widths: against the same model evaluated in passes of 64 rows, which other
+kernels serve.  Both sides keep 16 bits of every activation, so they differ by the flips of single bf16 cache entries only:
+a flip moves one key or value by 2^-8 of itself, which the softmax average and the projections spread to less than the
+2e-2 the bf16 tests allow; a wrong row or column of a tile is off by the logits' own size (0.5 rms and more)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-2
+
+
+def build(shape, vocab, max_ctx, batch=1):
+    import torch
+    from dataclasses import replace
+    from rsd_inputs import ModelShape, model_blob_torch
+    from paper_2501_19324_amd import binding as R
+    stub = ModelShape(1, 128, 1, 1, 64, vocab)
+    shapes = [shape, stub, replace(stub, head_kind="reward")]
+    blobs = [model_blob_torch(7, i, s, torch.device("cuda")) for i, s in enumerate(shapes)]
+    torch.cuda.synchronize()
+    ctx = R.rsd_init(shapes, blobs, batch=batch, delta=0.5, sep_id=vocab - 1, step_cap=1, max_steps=1, max_ctx=max_ctx)
+    return R, ctx
+
+
+@pytest.mark.parametrize("rows", [65, 128, 129, 255, 257, 390])
+def test_small_model_against_the_checker(rows):
+    from oracle import rsd_oracle as O
+    from rsd_inputs import ModelShape, model_weights_np
+    shape = ModelShape(2, 640, 5, 5, 448, 1001)          # N = 1920, 640, 896, 1001; K = 640, 448
+    R, ctx = build(shape, 1001, 400)
+    toks = np.random.default_rng(rows).integers(0, 1001, size=(1, rows)).astype(np.int32)
+    out = R.rsd_forward(ctx, 0, toks, np.array([rows], np.int32), 8192).cpu().numpy()[0]
+    m = O.OracleModel(shape, model_weights_np(7, 0, shape))
+    ref = O.lm_logits(m, O.forward_full(m, [int(t) for t in toks[0]], "bf16"))
+    assert np.max(np.abs(out - ref)) < TOL
+    R.rsd_destroy(ctx)
+
+
+@pytest.mark.parametrize("width,rows", [("7B", 129), ("7B", 700), ("7B", 2049), ("1.5B", 257), ("1.5B", 1100)])
+def test_full_width_against_few_row_passes(width, rows):
+    from rsd_inputs import ModelShape
+    dims = {"7B": (3584, 28, 4, 18944), "1.5B": (1536, 12, 2, 8960)}[width]
+    R, ctx = build(ModelShape(1, *dims, 4097), 4097, rows)
+    toks = np.random.default_rng(rows).integers(0, 4097, size=(1, rows)).astype(np.int32)
+    lens = np.array([rows], np.int32)
+    whole = R.rsd_forward(ctx, 0, toks, lens, 8192)
+    pieces = R.rsd_forward(ctx, 0, toks, lens, 64)
+    assert float((whole - pieces).abs().max()) < TOL
+    R.rsd_destroy(ctx)
