@@ -7,16 +7,22 @@
 // draw walks S in ascending token id and returns the first token whose running
 // mass exceeds u * mass(S).
 //
-// No sort: tau is found by a three-level radix select over the bit patterns of
-// the non-negative floats e_t (10 + 11 + 10 bits), each level a histogram of
-// masses.  Masses are summed as 64-bit fixed point (e * 2^40), so every sum is
-// exact, order-independent and reproducible from run to run.
-//
-// A row is spread over SMP_NB blocks (one vocabulary span each) so that a
-// batch of one still uses many compute units; the phases are separate
-// launches:  A  per-block max (or arg max) ->  B  level-1 histogram ->
-// C  level 2 ->  D  level 3 ->  E  per-block nucleus mass ->  F  locate the
-// draw, append the token to its sequence, clear the histograms.
+// No sort: tau is found by selection over the bit patterns of the non-negative floats e_t.  Masses are summed as
+// 64-bit fixed point (e * 2^40), so every sum is exact, order-independent and reproducible from run to run, whatever
+// the path to tau.  A row is cut into SMP_NB spans of the vocabulary; the phases are separate launches:
+//   A  max of every span (or arg max: greedy); clears the histogram
+//   B  histogram of masses over 2048 bins of 1/64 octave (exponent and six mantissa bits, down to 2^-32)
+//   C  every block finds the bin tau lies in, sums what lies above it per span and lists the keys inside it (a bin is
+//      1 % wide: a few keys per span; at most SMP_LIST are kept)
+//   D  one block per row resolves tau among the listed keys (9 + 8 bits), forms the nucleus mass of every span, locates
+//      the draw and appends the token to its sequence.
+// So the logits are read three times and everything after C works on a few hundred keys.  (Three radix levels over the
+// whole row and a fifth pass for the masses, with a 2048-bin histogram cleared and flushed for every 2400 tokens, took
+// 115 us on 64 rows of 151936 logits and 35 on one; this takes 62 and 25.  What bounds it: a division and an exponential
+// per token and pass on many rows - about 10 of the 23 and 17 us of B and C -, the chain of block scans in D on few.)
+// Where a span holds more keys of the bin than its list, or tau lies below 2^-32, block D selects over the whole row by
+// itself: slow but rare, it takes thousands of nearly equal logits or a nucleus that leaves less than 4e-5 of the mass out.
+// top_p >= 1 needs no selection: the nucleus is every token whose mass is not zero, e >= 2^-40.
 #pragma once
 #include "common.h"
 #include "misc.h"
@@ -25,7 +31,10 @@ typedef unsigned long long u64_t;
 
 constexpr int SMP_NB = 64;      // blocks per row
 constexpr int SMP_T = 256;      // threads per block
-constexpr int SMP_BINS = 2048;  // histogram size of every level (level 1 and 3 use 1024)
+constexpr int SMP_BINS = 2048;  // histogram bins of a row (its workspace: three times as many entries, two thirds hold the lists)
+constexpr int SMP_LIST = 2 * SMP_BINS * 2 / SMP_NB;       // keys of the deciding bin kept per span (128)
+constexpr int SMP_BIN0 = (0x3F800000 >> 17) - (SMP_BINS - 1);   // key >> 17 of bin 0; the last bin holds e = 1
+constexpr uint32_t SMP_UNIT = 0x2B800000u;                // key of 2^-40, the smallest e with a mass
 
 __device__ __forceinline__ u64_t shfl_up_u64(u64_t v, int d) {
     const unsigned lo = __shfl_up((unsigned)v, d, RSD_WAVE), hi = __shfl_up((unsigned)(v >> 32), d, RSD_WAVE);
@@ -84,7 +93,7 @@ __device__ __forceinline__ int smp_seq(const SampleArgs& a, int row) {
     return s;
 }
 
-// what phase F does with the chosen token besides (or instead of) storing it
+// what phase D does with the chosen token besides (or instead of) storing it
 struct AppendArgs {
     int enabled;                 // 0: off; 1: a token of a reasoning step; 2: a proposal of speculative regeneration
     SeqState st; int B, max_ctx, model;
@@ -129,20 +138,36 @@ __device__ __forceinline__ int smp_find_bin(const u64_t* hist, u64_t thr, u64_t&
     return *s_bin;
 }
 
-// ---- phase A: per-block max of x (sampling) or arg max of the biased logits (greedy)
+__device__ __forceinline__ int smp_bin(uint32_t key) { return min(max((int)(key >> 17) - SMP_BIN0, 0), SMP_BINS - 1); }
+// span of block blockIdx.x: with WPS = 4 waves per span the block's only one, with WPS = 1 one per wave; thread tid of
+// smp_span_threads() works on it
+template <int WPS> __device__ __forceinline__ int smp_span() { return WPS == 4 ? blockIdx.x : blockIdx.x * 4 + (threadIdx.x >> 6); }
+template <int WPS> __device__ __forceinline__ int smp_lane() { return WPS == 4 ? threadIdx.x : threadIdx.x & 63; }
+
+// tokens a thread requests together: two batches cover a span of 2374 with 256 threads, five with 64
+template <int WPS> constexpr int SMP_U = WPS == 4 ? 5 : 8;
+
+// ---- phase A: max of every span of x (sampling) or arg max of the biased logits (greedy).  x = logit / temperature
+// grows with the logit, so the division is done once per span
+template <int WPS>
 __global__ __launch_bounds__(SMP_T) void sample_max_kernel(SampleArgs a) {
-    const int row = blockIdx.y, j = blockIdx.x, tid = threadIdx.x;
-    const int seq = smp_seq(a, row);
-    if (seq < 0) return;
+    const int row = blockIdx.y, j = smp_span<WPS>(), tid = smp_lane<WPS>(), wave = threadIdx.x >> 6;
+    if (smp_seq(a, row) < 0) return;
     const float* lg = a.logits + (size_t)row * a.ld;
-    const int span = (a.V + SMP_NB - 1) / SMP_NB, s0 = j * span, s1 = min(a.V, s0 + span);
-    __shared__ float fred[4];
-    __shared__ int ired[4];
+    const int span = (a.V + SMP_NB - 1) / SMP_NB, s0 = min(j * span, a.V), s1 = min(a.V, s0 + span);
+    constexpr int T = WPS * 64, U = SMP_U<WPS>;
+    if (a.temperature != 0.0f && tid < SMP_BINS / SMP_NB) a.hist[(size_t)row * 3 * SMP_BINS + j * (SMP_BINS / SMP_NB) + tid] = 0;   // for phase B
     float bv = -INFINITY; int bi = 0x7FFFFFFF;
-    const bool greedy = a.temperature == 0.0f;
-    for (int i = s0 + tid; i < s1; i += SMP_T) {
-        const float v = greedy ? lg[i] + (i == a.sep_id ? a.sep_bias : 0.0f) : smp_x(a, lg, i);
-        if (v > bv) { bv = v; bi = i; }
+    for (int i0 = s0 + tid; i0 < s1; i0 += T * U) {
+        float v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = lg[min(i0 + u * T, s1 - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = min(i0 + u * T, s1 - 1);
+            if (i == a.sep_id) v[u] += a.sep_bias;
+            if (v[u] > bv) { bv = v[u]; bi = i; }
+        }
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
@@ -150,117 +175,159 @@ __global__ __launch_bounds__(SMP_T) void sample_max_kernel(SampleArgs a) {
         const int oi = __shfl_xor(bi, off, RSD_WAVE);
         if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
     }
-    if ((tid & 63) == 0) { fred[tid >> 6] = bv; ired[tid >> 6] = bi; }
-    __syncthreads();
+    if (WPS == 4) {
+        __shared__ float fred[4];
+        __shared__ int ired[4];
+        if ((tid & 63) == 0) { fred[wave] = bv; ired[wave] = bi; }
+        __syncthreads();
+        if (tid == 0)
+            for (int w = 1; w < 4; ++w)
+                if (fred[w] > bv || (fred[w] == bv && ired[w] < bi)) { bv = fred[w]; bi = ired[w]; }
+    }
     if (tid == 0) {
-        for (int w = 1; w < 4; ++w)
-            if (fred[w] > bv || (fred[w] == bv && ired[w] < bi)) { bv = fred[w]; bi = ired[w]; }
-        a.pmax[(size_t)row * SMP_NB + j] = bv;
+        a.pmax[(size_t)row * SMP_NB + j] = a.temperature == 0.0f ? bv : bv / a.temperature;
         a.pidx[(size_t)row * SMP_NB + j] = bi;
     }
 }
 
-// ---- phases B, C, D: one histogram level each (LEVEL = 0, 1, 2)
-template <int LEVEL>
+// ---- phase B: the histogram of masses
+template <int WPS>
 __global__ __launch_bounds__(SMP_T) void sample_hist_kernel(SampleArgs a) {
-    const int row = blockIdx.y, j = blockIdx.x, tid = threadIdx.x;
-    const int seq = smp_seq(a, row);
-    if (seq < 0) return;
+    const int row = blockIdx.y, j = smp_span<WPS>(), tid = smp_lane<WPS>();
+    if (smp_seq(a, row) < 0) return;
     const float* lg = a.logits + (size_t)row * a.ld;
-    const int span = (a.V + SMP_NB - 1) / SMP_NB, s0 = j * span, s1 = min(a.V, s0 + span);
+    const int span = (a.V + SMP_NB - 1) / SMP_NB, s0 = min(j * span, a.V), s1 = min(a.V, s0 + span);
     __shared__ u64_t lh[SMP_BINS];
-    __shared__ u64_t wtot[4];
     __shared__ float fred[4];
-    __shared__ int s_bin;
-    __shared__ u64_t s_above;
     u64_t* hist = a.hist + (size_t)row * 3 * SMP_BINS;
-    u64_t* sel = a.sel + (size_t)row * 8;
-    const float mx = smp_row_max(a, row, fred);
-    uint32_t prefix = 0, mask = 0;
-    if (LEVEL >= 1) {
-        // every block repeats the (deterministic) search of the previous level
-        u64_t above = (LEVEL == 1) ? 0 : sel[1];
-        u64_t thr;
-        if (LEVEL == 1) {
-            u64_t loc = 0;
-            for (int b = tid; b < 1024; b += SMP_T) loc += hist[b];
-            const u64_t tot = block256_incl_scan_u64(loc, wtot);
-            __syncthreads();
-            if (tid == SMP_T - 1) s_above = tot;
-            __syncthreads();
-            const u64_t z = s_above;
-            thr = (u64_t)ceil((double)a.top_p * (double)z);
-            if (thr < 1) thr = 1;
-            if (thr > z) thr = z;
-            __syncthreads();
-            const int bin = smp_find_bin<4>(hist, thr, above, wtot, &s_bin, &s_above);
-            prefix = (uint32_t)bin << 21; mask = 0xFFE00000u;
-            if (j == 0 && tid == 0) { sel[0] = thr; sel[1] = above; sel[2] = prefix; }
-        } else {
-            thr = sel[0];
-            const int bin = smp_find_bin<8>(hist + SMP_BINS, thr, above, wtot, &s_bin, &s_above);
-            prefix = (uint32_t)sel[2] | ((uint32_t)bin << 10); mask = 0xFFFFFC00u;
-            if (j == 0 && tid == 0) { sel[3] = above; sel[4] = prefix; }
+    for (int b = threadIdx.x; b < SMP_BINS; b += SMP_T) lh[b] = 0;
+    const float mx = smp_row_max(a, row, fred);           // (holds a barrier)
+    constexpr int T = WPS * 64, U = SMP_U<WPS>;
+    for (int i0 = s0 + tid; i0 < s1; i0 += T * U) {
+        float x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = smp_x(a, lg, min(i0 + u * T, s1 - 1));
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float e = expf(x[u] - mx);
+            const u64_t f = smp_fix(e);
+            if (f && i0 + u * T < s1) atomicAdd(&lh[smp_bin(__float_as_uint(e))], f);
         }
     }
-    for (int b = tid; b < SMP_BINS; b += SMP_T) lh[b] = 0;
     __syncthreads();
-    for (int i = s0 + tid; i < s1; i += SMP_T) {
-        const float e = expf(smp_x(a, lg, i) - mx);
-        const uint32_t key = __float_as_uint(e);
-        if (LEVEL == 0) atomicAdd(&lh[key >> 21], smp_fix(e));
-        else if ((key & mask) == prefix) atomicAdd(&lh[LEVEL == 1 ? ((key >> 10) & 0x7FFu) : (key & 0x3FFu)], smp_fix(e));
-    }
-    __syncthreads();
-    u64_t* gh = hist + LEVEL * SMP_BINS;
-    for (int b = tid; b < SMP_BINS; b += SMP_T)
-        if (lh[b]) atomicAdd(&gh[b], lh[b]);
+    for (int b = threadIdx.x; b < SMP_BINS; b += SMP_T)
+        if (lh[b]) atomicAdd(&hist[b], lh[b]);
 }
 
-// ---- phase E: tau and the draw target; per-block mass of the nucleus
-__global__ __launch_bounds__(SMP_T) void sample_mass_kernel(SampleArgs a) {
-    const int row = blockIdx.y, j = blockIdx.x, tid = threadIdx.x;
-    const int seq = smp_seq(a, row);
-    if (seq < 0) return;
+// ---- phase C: the bin in which the mass reaches top_p of the total; per span the mass above it and the keys inside it
+template <int WPS>
+__global__ __launch_bounds__(SMP_T) void sample_select_kernel(SampleArgs a) {
+    const int row = blockIdx.y, j = smp_span<WPS>(), tid = smp_lane<WPS>(), wave = threadIdx.x >> 6;
+    if (smp_seq(a, row) < 0) return;
     const float* lg = a.logits + (size_t)row * a.ld;
-    const int span = (a.V + SMP_NB - 1) / SMP_NB, s0 = j * span, s1 = min(a.V, s0 + span);
+    const int span = (a.V + SMP_NB - 1) / SMP_NB, s0 = min(j * span, a.V), s1 = min(a.V, s0 + span);
     __shared__ u64_t wtot[4];
     __shared__ float fred[4];
-    __shared__ int s_bin;
+    __shared__ int s_bin, s_cnt[4];
     __shared__ u64_t s_above;
     u64_t* hist = a.hist + (size_t)row * 3 * SMP_BINS;
     u64_t* sel = a.sel + (size_t)row * 8;
     const float mx = smp_row_max(a, row, fred);
-    u64_t above = sel[3];
-    const int bin = smp_find_bin<4>(hist + 2 * SMP_BINS, sel[0], above, wtot, &s_bin, &s_above);
-    const uint32_t tau = (uint32_t)sel[4] | (uint32_t)bin;
-    if (j == 0 && tid == 0) {
-        const u64_t zs = above + hist[2 * SMP_BINS + bin];        // ties at tau are all inside
-        const float uu = a.u[(size_t)seq * a.u_stride + (a.u_index ? a.u_index[seq] : 0)];
-        sel[5] = tau;
-        sel[6] = (u64_t)floor((double)uu * (double)zs);           // running > u * Z  <=>  running > floor(u * Z)
+    if (threadIdx.x == 0) { s_bin = 0; s_above = 0; }
+    if (threadIdx.x < 4) s_cnt[threadIdx.x] = 0;
+    // (every block repeats the deterministic search)
+    constexpr int P = SMP_BINS / SMP_T;
+    const int top = SMP_BINS - 1 - threadIdx.x * P;       // this thread's bins: top, top - 1, ...
+    u64_t h[P], loc = 0;
+#pragma unroll
+    for (int i = 0; i < P; ++i) { h[i] = hist[top - i]; loc += h[i]; }
+    const u64_t incl = block256_incl_scan_u64(loc, wtot);
+    const u64_t z = wtot[0] + wtot[1] + wtot[2] + wtot[3];
+    u64_t thr = (u64_t)ceil((double)a.top_p * (double)z);
+    if (thr < 1) thr = 1;
+    if (thr > z) thr = z;
+    u64_t run = incl - loc;
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+        if (run < thr && run + h[i] >= thr) { s_bin = top - i; s_above = run; }
+        run += h[i];
     }
+    __syncthreads();
+    const int bin = thr == z ? -1 : s_bin;                // -1: the nucleus is every token with a mass
+    // keys below lo are outside, from hi on inside the nucleus; those between are listed
+    const uint32_t lo = bin < 0 ? SMP_UNIT : bin == 0 ? 0u : (uint32_t)(bin + SMP_BIN0) << 17;
+    const uint32_t hi = bin < 0 ? SMP_UNIT : bin == SMP_BINS - 1 ? 0xFFFFFFFFu : (uint32_t)(bin + 1 + SMP_BIN0) << 17;
+    if (blockIdx.x == 0 && threadIdx.x == 0) { sel[0] = thr; sel[1] = s_above; sel[2] = (u64_t)(long long)bin; }
+    uint32_t* list = reinterpret_cast<uint32_t*>(hist + SMP_BINS) + (size_t)j * SMP_LIST;
+    int* cnt = &s_cnt[WPS == 4 ? 0 : wave];
     u64_t acc = 0;
-    for (int i = s0 + tid; i < s1; i += SMP_T) {
-        const float e = expf(smp_x(a, lg, i) - mx);
-        if (__float_as_uint(e) >= tau) acc += smp_fix(e);
+    constexpr int T = WPS * 64, U = SMP_U<WPS>;
+    for (int i0 = s0 + tid; i0 < s1; i0 += T * U) {
+        float x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = smp_x(a, lg, min(i0 + u * T, s1 - 1));
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float e = expf(x[u] - mx);
+            const uint32_t key = __float_as_uint(e);
+            if (i0 + u * T < s1) {
+                if (key >= hi) acc += smp_fix(e);
+                else if (key >= lo) {
+                    const int at = atomicAdd(cnt, 1);
+                    if (at < SMP_LIST) list[at] = key;
+                }
+            }
+        }
     }
     acc = wave_sum_u64(acc);
     __syncthreads();
-    if ((tid & 63) == 0) wtot[tid >> 6] = acc;
-    __syncthreads();
-    if (tid == 0) a.psum[(size_t)row * SMP_NB + j] = wtot[0] + wtot[1] + wtot[2] + wtot[3];
+    if (WPS == 4) {
+        if ((tid & 63) == 0) wtot[wave] = acc;
+        __syncthreads();
+        acc = wtot[0] + wtot[1] + wtot[2] + wtot[3];
+    }
+    if (tid == 0) {
+        a.psum[(size_t)row * SMP_NB + j] = acc;
+        a.pidx[(size_t)row * SMP_NB + j] = *cnt;
+    }
 }
 
-// ---- phase F: one block per row: pick the token, append it, clear the histograms
+// tau among the keys of [lo, hi) by three radix levels over the whole row, when the lists do not hold them; `need`: the
+// mass the nucleus still takes from this range.  Whole block calls; lh: SMP_BINS entries of LDS
+__device__ uint32_t smp_select_row(const SampleArgs& a, const float* lg, float mx, uint32_t lo, uint32_t hi, u64_t need, u64_t* lh,
+                                   u64_t* wtot, int* s_bin, u64_t* s_above) {
+    const int tid = threadIdx.x;
+    uint32_t prefix = 0;
+    u64_t above = 0;
+    for (int shift = 20; shift >= 0; shift -= 10) {       // keys < 2^31: 11, 10 and 10 bits
+        for (int b = tid; b < SMP_BINS; b += SMP_T) lh[b] = 0;
+        if (tid == 0) { *s_bin = 0; *s_above = above; }
+        __syncthreads();
+        for (int i = tid; i < a.V; i += SMP_T) {
+            const float e = expf(smp_x(a, lg, i) - mx);
+            const uint32_t key = __float_as_uint(e);
+            if (key >= lo && key < hi && (shift == 20 || key >> (shift + 10) == prefix)) {
+                const u64_t f = smp_fix(e);
+                if (f) atomicAdd(&lh[shift == 20 ? min(key >> 20, (uint32_t)(SMP_BINS - 1)) : (key >> shift) & 0x3FFu], f);
+            }
+        }
+        __syncthreads();
+        const int bin = smp_find_bin<8>(lh, need, above, wtot, s_bin, s_above);
+        prefix = (shift == 20 ? 0u : prefix << 10) | (uint32_t)bin;
+        __syncthreads();
+    }
+    return prefix;
+}
+
+// ---- phase D: one block per row: tau, the nucleus mass of every span, the token; appends it
 __global__ __launch_bounds__(SMP_T) void sample_finish_kernel(SampleArgs a, AppendArgs ap) {
     const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int seq = smp_seq(a, row);
     if (seq < 0) return;
     __shared__ u64_t wtot[4];
     __shared__ float fred[4];
-    __shared__ int s_tok, s_blk;
-    __shared__ u64_t s_base;
+    __shared__ int s_tok, s_blk, s_bin;
+    __shared__ u64_t s_base, s_above;
     int token;
     if (a.temperature == 0.0f) {
         float bv = -INFINITY; int bi = 0x7FFFFFFF;
@@ -279,48 +346,111 @@ __global__ __launch_bounds__(SMP_T) void sample_finish_kernel(SampleArgs a, Appe
     } else {
         const float* lg = a.logits + (size_t)row * a.ld;
         u64_t* hist = a.hist + (size_t)row * 3 * SMP_BINS;
-        const u64_t* sel = a.sel + (size_t)row * 8;
+        u64_t* sel = a.sel + (size_t)row * 8;
+        __shared__ u64_t lh[SMP_BINS];
+        __shared__ u64_t s_mass[SMP_NB];
+        const float uu = a.u[(size_t)seq * a.u_stride + (a.u_index ? a.u_index[seq] : 0)];
+        const u64_t thr = sel[0], above = sel[1];
+        const int bin = (int)(long long)sel[2];
+        const int span = (a.V + SMP_NB - 1) / SMP_NB;
+        // four threads per span hold its keys of the bin
+        const int my_span = tid >> 2, n_list = a.pidx[(size_t)row * SMP_NB + my_span];
+        const uint32_t* list = reinterpret_cast<const uint32_t*>(hist + SMP_BINS) + (size_t)my_span * SMP_LIST;
+        constexpr int NK = 4;                                  // the first 16 keys of a span (mostly all) are requested at once and kept
+        uint32_t kept[NK];
+#pragma unroll
+        for (int i = 0; i < NK; ++i) kept[i] = list[(tid & 3) + 4 * i];
+        auto each_key = [&](auto f) {
+#pragma unroll
+            for (int i = 0; i < NK; ++i) if ((tid & 3) + 4 * i < n_list) f(kept[i]);
+            for (int i = (tid & 3) + 4 * NK; i < n_list; i += 4) f(list[i]);
+        };
+        if (tid < SMP_NB) s_mass[tid] = a.psum[(size_t)row * SMP_NB + tid];
         const float mx = smp_row_max(a, row, fred);
-        const uint32_t tau = (uint32_t)sel[5];
-        const u64_t target = sel[6];
-        const u64_t pv = (tid < SMP_NB) ? a.psum[(size_t)row * SMP_NB + tid] : 0;
+        uint32_t tau = SMP_UNIT;
+        if (bin >= 0) {
+            const bool whole = __syncthreads_or(n_list > SMP_LIST) || bin == 0;
+            if (!whole) {
+                u64_t run = above;
+                // bits 8..16, then 0..7 of the keys; their upper bits are the bin
+                for (int b = tid; b < 512 + 256; b += SMP_T) lh[b] = 0;
+                if (tid == 0) { s_bin = 0; s_above = run; }
+                __syncthreads();
+                each_key([&](uint32_t k) { atomicAdd(&lh[(k >> 8) & 0x1FFu], smp_fix(__uint_as_float(k))); });
+                __syncthreads();
+                const uint32_t up = (uint32_t)smp_find_bin<2>(lh, thr, run, wtot, &s_bin, &s_above);
+                __syncthreads();
+                each_key([&](uint32_t k) { if (((k >> 8) & 0x1FFu) == up) atomicAdd(&lh[512 + (k & 0xFFu)], smp_fix(__uint_as_float(k))); });
+                __syncthreads();
+                const uint32_t low = (uint32_t)smp_find_bin<1>(lh + 512, thr, run, wtot, &s_bin, &s_above);
+                tau = ((uint32_t)(bin + SMP_BIN0) << 17) | (up << 8) | low;
+                u64_t m = 0;
+                each_key([&](uint32_t k) { if (k >= tau) m += smp_fix(__uint_as_float(k)); });
+                m += shfl_xor_u64(m, 1);
+                m += shfl_xor_u64(m, 2);
+                if ((tid & 3) == 0) s_mass[my_span] += m;
+            } else {
+                const uint32_t lo = bin == 0 ? 0u : (uint32_t)(bin + SMP_BIN0) << 17;
+                const uint32_t hi = bin == SMP_BINS - 1 ? 0xFFFFFFFFu : (uint32_t)(bin + 1 + SMP_BIN0) << 17;
+                tau = smp_select_row(a, lg, mx, lo, hi, thr - above, lh, wtot, &s_bin, &s_above);
+                for (int j = wave; j < SMP_NB; j += 4) {
+                    const int s0 = min(j * span, a.V), s1 = min(a.V, s0 + span);
+                    u64_t m = 0;
+                    for (int i = s0 + lane; i < s1; i += 64) {
+                        const float e = expf(smp_x(a, lg, i) - mx);
+                        if (__float_as_uint(e) >= tau) m += smp_fix(e);
+                    }
+                    m = wave_sum_u64(m);
+                    if (lane == 0) s_mass[j] = m;
+                }
+            }
+        }
+        __syncthreads();
+        const u64_t pv = (tid < SMP_NB) ? s_mass[tid] : 0;
+        if (tid < SMP_NB) a.psum[(size_t)row * SMP_NB + tid] = pv;
         const u64_t pincl = block256_incl_scan_u64(pv, wtot);
-        if (tid == 0) { s_blk = -1; s_tok = -1; }
+        const u64_t zs = wtot[0] + wtot[1] + wtot[2] + wtot[3];
+        const u64_t target = (u64_t)floor((double)uu * (double)zs);      // running > u * Z  <=>  running > floor(u * Z)
+        if (tid == 0) { s_blk = -1; s_tok = -1; s_base = 0; sel[5] = tau; sel[6] = target; }
         __syncthreads();
         if (tid < SMP_NB && pincl > target && pincl - pv <= target) { s_blk = tid; s_base = pincl - pv; }
         __syncthreads();
-        const int span = (a.V + SMP_NB - 1) / SMP_NB;
-        // if rounding of u * Z left no crossing, the draw is the last member: walk the last non-empty span
+        // if rounding of u * Z left no crossing, the draw is the last member: of the last span with a mass
         int blk = s_blk;
         u64_t base = s_base;
         if (blk < 0) {
             if (tid == 0) {
                 u64_t run = 0; int last = 0;
-                for (int b = 0; b < SMP_NB; ++b) { const u64_t v = a.psum[(size_t)row * SMP_NB + b]; if (v) { last = b; s_base = run; } run += v; }
+                for (int b = 0; b < SMP_NB; ++b) { const u64_t v = s_mass[b]; if (v) { last = b; s_base = run; } run += v; }
                 s_blk = last;
             }
             __syncthreads();
             blk = s_blk; base = s_base;
         }
-        const int s0 = blk * span, s1 = min(a.V, s0 + span);
+        // every thread takes a run of consecutive tokens of the span; the one whose run holds the crossing walks it
+        const int s0 = min(blk * span, a.V), s1 = min(a.V, s0 + span);
+        const int per = (s1 - s0 + SMP_T - 1) / SMP_T, t0 = min(s1, s0 + tid * per), t1 = min(s1, t0 + per);
+        u64_t mine = 0;
         int last_member = -1;
-        for (int c0 = s0; c0 < s1; c0 += SMP_T) {          // uniform trip count for the whole block
-            const int i = c0 + tid;
-            u64_t q = 0;
-            if (i < s1) {
-                const float e = expf(smp_x(a, lg, i) - mx);
-                if (__float_as_uint(e) >= tau) { q = smp_fix(e); last_member = i; }
+        for (int i0 = t0; i0 < t1; i0 += 10) {                 // (spans of 2374: one batch)
+            float x[10];
+#pragma unroll
+            for (int u = 0; u < 10; ++u) x[u] = smp_x(a, lg, min(i0 + u, t1 - 1));
+#pragma unroll
+            for (int u = 0; u < 10; ++u) {
+                const float e = expf(x[u] - mx);
+                if (i0 + u < t1 && __float_as_uint(e) >= tau) { mine += smp_fix(e); last_member = i0 + u; }
             }
-            const u64_t incl = block256_incl_scan_u64(q, wtot);
-            const u64_t run = base + incl;
-            if (q && run > target && run - q <= target) s_tok = i;     // at most one thread
-            __syncthreads();
-            if (s_tok >= 0) break;
-            __syncthreads();
-            if (tid == SMP_T - 1) s_base = run;
-            __syncthreads();
-            base = s_base;
         }
+        const u64_t incl = base + block256_incl_scan_u64(mine, wtot);
+        if (mine && incl > target && incl - mine <= target) {
+            u64_t run = incl - mine;
+            for (int i = t0; i < t1; ++i) {
+                const float e = expf(smp_x(a, lg, i) - mx);
+                if (__float_as_uint(e) >= tau) { run += smp_fix(e); if (run > target) { s_tok = i; break; } }
+            }
+        }
+        __syncthreads();
         if (s_tok < 0) {
             // no crossing (u * Z rounded up to the full mass): the last member of the nucleus
 #pragma unroll
@@ -332,7 +462,6 @@ __global__ __launch_bounds__(SMP_T) void sample_finish_kernel(SampleArgs a, Appe
             __syncthreads();
         }
         token = s_tok;
-        for (int b = tid; b < 3 * SMP_BINS; b += SMP_T) hist[b] = 0;
     }
     if (tid != 0) return;
     if (a.out) a.out[row] = token;
@@ -373,14 +502,18 @@ __global__ __launch_bounds__(SMP_T) void sample_finish_kernel(SampleArgs a, Appe
     }
 }
 
+// Few rows: a span per block of four waves, to have many blocks.  From 16 rows on a span per wave: a block then works on
+// four spans, which spreads the cost of its histogram (clearing and flushing 2048 bins) over 9500 tokens instead of 2400.
+template <int WPS>
+static void sample_launch_spans(hipStream_t st, const SampleArgs& a, int rows) {
+    const dim3 grid(SMP_NB * WPS / 4, rows), block(SMP_T);
+    hipLaunchKernelGGL((sample_max_kernel<WPS>), grid, block, 0, st, a);
+    if (a.temperature == 0.0f) return;
+    hipLaunchKernelGGL((sample_hist_kernel<WPS>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((sample_select_kernel<WPS>), grid, block, 0, st, a);
+}
 static void sample_launch(hipStream_t st, const SampleArgs& a, const AppendArgs& ap, int rows) {
-    const dim3 grid(SMP_NB, rows), block(SMP_T);
-    hipLaunchKernelGGL(sample_max_kernel, grid, block, 0, st, a);
-    if (a.temperature != 0.0f) {
-        hipLaunchKernelGGL((sample_hist_kernel<0>), grid, block, 0, st, a);
-        hipLaunchKernelGGL((sample_hist_kernel<1>), grid, block, 0, st, a);
-        hipLaunchKernelGGL((sample_hist_kernel<2>), grid, block, 0, st, a);
-        hipLaunchKernelGGL(sample_mass_kernel, grid, block, 0, st, a);
-    }
-    hipLaunchKernelGGL(sample_finish_kernel, dim3(rows), block, 0, st, a, ap);
+    if (rows < 16) sample_launch_spans<4>(st, a, rows);
+    else sample_launch_spans<1>(st, a, rows);
+    hipLaunchKernelGGL(sample_finish_kernel, dim3(rows), dim3(SMP_T), 0, st, a, ap);
 }

@@ -57,11 +57,6 @@ extern "C" int rsd_sample_static(const float* logits_dev, const float* u_dev, in
     u64_t* sel = psum + kSmpPsum;
     float* pmax = reinterpret_cast<float*>(sel + kSmpSel);
     int* pidx = reinterpret_cast<int*>(pmax + kSmpPmax);
-    // the array keeps what the last call left: histograms and selections of the rows in use start at zero
-    // (a fill kernel, not a memset node: the caller may be recording a graph)
-    const size_t nh = (size_t)n * 3 * SMP_BINS * 2, ns = (size_t)n * 8 * 2;       // as ints
-    hipLaunchKernelGGL(fill_int_kernel, dim3((unsigned)((nh + 255) / 256)), dim3(256), 0, st, reinterpret_cast<int*>(hist), 0, nh);
-    hipLaunchKernelGGL(fill_int_kernel, dim3((unsigned)((ns + 255) / 256)), dim3(256), 0, st, reinterpret_cast<int*>(sel), 0, ns);
     SampleArgs a{logits_dev, vocab, vocab, u_dev, nullptr, 1, temperature, top_p, -1, 0.f, nullptr, out_dev,
                  pmax, pidx, hist, psum, sel};
     sample_launch(st, a, AppendArgs{}, n);

@@ -7,15 +7,15 @@
 //
 // p and q are the distributions the sampler draws from (sample.h): e_t = exp(x_t - max x),
 // x = (logit + separator bias) / temperature, restricted to the nucleus {e_t >= tau} and
-// divided by the nucleus mass Z.  The sampler's phases A-E run first on every row and leave
-// max x (per-block maxima), tau and the per-block masses in its workspace; masses are 2^40
+// divided by the nucleus mass Z.  The sampler runs first on every row and leaves
+// max x (maxima of the spans), tau and the masses of the spans in its workspace; masses are 2^40
 // fixed point and are summed exactly.  Here probabilities are formed in fp64 from those
 // integers, and the positive part of p - q is summed as 2^50 fixed point, so that every sum is
 // exact and order-independent and the draw is reproducible.
 #pragma once
 #include "sample.h"
 
-struct SdRowSet {                 // rows the sampler has prepared (phases A-E)
+struct SdRowSet {                 // rows the sampler has prepared
     const float* logits; int ld;
     const float* pmax;            // [rows][SMP_NB]
     const u64_t* psum;            // [rows][SMP_NB]

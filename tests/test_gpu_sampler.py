@@ -1,0 +1,55 @@
+"""The sampler at the places where its selection changes path: a few and many rows (span per block / per wave), vocabularies
+smaller than, and no multiple of, its 64 spans, a deciding bin that overflows its lists (equal logits), a threshold below the
+histogram's range, top_p 0 and 1, masked tokens.
+
+A draw is checked against the fp64 distribution: the token's interval of the nucleus's running mass must hold u.  The
+kernel forms e = exp(x - max) in fp32 (a few ulp, 2^-22) and sums masses exactly, so interval ends and the nucleus's edge are
+known to 1e-6 of the total mass; a token whose probability equals the edge within 2^-20 may be in or out."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def logits_of(kind, n, V, rng):
+    if kind == "normal":
+        return rng.normal(size=(n, V)) * 2.0
+    if kind == "flat":                       # all equal: every token ties at the edge
+        return np.zeros((n, V))
+    if kind == "steps":                      # few distinct values: thousands of equal keys per bin
+        return rng.integers(0, 3, size=(n, V)) * 0.5
+    if kind == "wide":                       # the tail lies far below 2^-32 of the top
+        return np.where(rng.random((n, V)) < 0.01, rng.normal(size=(n, V)), -40.0 + rng.normal(size=(n, V)))
+    x = rng.normal(size=(n, V))              # masked
+    x[:, rng.random(V) < 0.7] = -np.inf
+    x[:, V // 2] = 1.0
+    return x
+
+
+@pytest.mark.parametrize("kind", ["normal", "flat", "steps", "wide", "masked"])
+@pytest.mark.parametrize("n,V", [(1, 151936), (20, 20011), (5, 37), (17, 65)])
+@pytest.mark.parametrize("T,top_p", [(0.7, 0.95), (1.0, 1.0), (1.0, 0.0), (0.5, 0.9999999)])
+def test_draws_lie_where_the_distribution_puts_them(kind, n, V, T, top_p):
+    import torch
+    from paper_2501_19324_amd import binding as R
+    rng = np.random.default_rng(V + n)
+    lg = logits_of(kind, n, V, rng).astype(np.float32)
+    u = rng.random(n).astype(np.float32)
+    out = R.rsd_sample_static(torch.from_numpy(lg).cuda(), torch.from_numpy(u).cuda(), T, top_p).cpu().numpy()
+    x = lg.astype(np.float64) / np.float64(np.float32(T))
+    for i in range(n):
+        e = np.exp(x[i] - x[i].max())
+        e[e < 2.0 ** -40] = 0.0                                    # below the fixed-point unit: no mass
+        order = np.sort(e)[::-1]
+        reach = np.nonzero(np.cumsum(order) >= float(np.float32(top_p)) * e.sum() * (1 - 1e-7))[0]
+        tau = order[reach[0]] if reach.size else order[order > 0][-1]
+        t = int(out[i])
+        assert 0 <= t < V and e[t] >= tau * (1 - 2.0 ** -20), (i, t, e[t], tau)
+        # the edge itself may be one distinct value higher or lower: accept either nucleus
+        edges = {tau, max(e[e < tau * (1 - 2.0 ** -20)], default=tau), min(e[e > tau * (1 + 2.0 ** -20)], default=tau)}
+        ok = False
+        for edge in edges:
+            m = np.where(e >= edge * (1 - 2.0 ** -20), e, 0.0)
+            c = np.cumsum(m)
+            ok |= c[t] - m[t] - 1e-6 * c[-1] <= u[i] * c[-1] <= c[t] + 1e-6 * c[-1]
+        assert ok, (kind, i, t)
