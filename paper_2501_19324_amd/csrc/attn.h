@@ -8,6 +8,7 @@
 // page p / 16, slot p % 16; block_table[seq][logical page] gives the physical page.
 #pragma once
 #include "common.h"
+#include "gemm.h"
 
 #define RSD_PAGE 16
 
@@ -744,16 +745,28 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_decode_mfma_ker
 // ---------------------------------------------------------------------------
 // MFMA chunked-prefill attention for bf16 caches, head_dim 128.
 //
-// Runs after rope_kv_kernel has rotated q in place and written the chunk's
-// keys/values to the cache.  One wave per work item = up to 4 consecutive rows
-// (query tokens) of one sequence and one kv head: two 16-column tiles, a
-// column being (row, head of the group); the wave walks every page up to the
-// last row's position once and feeds both tiles from the same K / V^T
-// registers.  Column (row, g) sees tokens <= position(row).  Same operand
-// layouts and hi + lo splitting as attn_decode_mfma_kernel.
-// gridDim.z = S > 1 (few rows over a long context): split sp walks its share of
-// the pages and leaves a partial (max, sum, accumulator) per (row, head) for
-// attn_combine_kernel, in the layout of the decode kernels.
+// Runs after rope_kv_kernel has rotated q in place and written the chunk's keys/values to the cache.  One block of four
+// waves per work item = up to 16 consecutive rows (query tokens) of one sequence and one kv head; a wave takes four rows =
+// 32 columns, a column being (row, head of the group), and keeps their rotated, scaled q as hi + lo bf16 operands in
+// registers.  The item's pages are walked once, two pages (32 tokens) per step, through a ring of three LDS stages that the
+// waves share: a page's key and value blocks of one head are 4 KB each of consecutive memory, copied straight into LDS more
+// than two steps ahead.  The one barrier per step stands in its middle, when the step's operands are all in registers; the
+// next step's keys are read between the MFMAs behind it.  Per step and wave:
+//   S^T[token][column] = K . Q^T       v_mfma_f32_32x32x16_bf16, 8 steps over head_dim, hi and lo of q
+//   online softmax per column in the accumulator layout (a lane holds 16 of its column's 32 tokens, the lane 32 further on
+//   the others: one register swap per maximum); masks are formed only where a step reaches past a row's own position
+//   O^T[dim][column] += V^T . P^T      16 tokens per MFMA, P as hi + lo; a lane's probabilities are already the operand
+// Scores are kept in units of log2 (log2 e is folded into the scaling of q).
+// What bounds it: the chain QK, softmax, PV of a step (1024 cycles of MFMA issue and about 700 of vector instructions per
+// wave; two waves per SIMD, of different blocks, overlap them to 47 % of MFMA issue).  Its predecessor (every wave on its
+// own pages and 16-column tiles, values at half the MFMA rate) spent its time in vector instructions and read each page
+// through L2 once per four rows.
+// Measured per layer: 8192 rows of 1024-token prompts 7B 382 -> 187 us, 1.5B 215 -> 107 us; 6001 rows of one context 7B
+// 1315 -> 582 us.
+// gridDim.z = S > 1 (few rows over a long context): split sp walks its share of the steps and leaves a partial (max, sum,
+// accumulator) per (row, head) for attn_combine_kernel, in the layout of the decode kernels.
+// The result is written as hi + lo bf16 halves, the input of the output projection (out: as fp32, a pass of a single row).
+constexpr int kPfItemRows = 16;
 template <int G>
 __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(const float* __restrict__ qkv, int ldq,
                                                                 const bf16_t* __restrict__ pool_layer,
@@ -761,172 +774,220 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(const float* 
                                                                 const int* __restrict__ row_seq,
                                                                 const int* __restrict__ row_pos,
                                                                 const int* __restrict__ item_row0,
-                                                                const int* __restrict__ item_n, int n_items,
+                                                                const int* __restrict__ item_n,
                                                                 int H, int Hkv, float scale,
                                                                 float* __restrict__ out, int ldo,
+                                                                uint16_t* __restrict__ out_h, uint16_t* __restrict__ out_l,
                                                                 float* __restrict__ part_acc,
                                                                 float* __restrict__ part_ml) {
-    constexpr int HD = 128, NT = 2;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int item = blockIdx.x * 4 + wave, hk = blockIdx.y, sp = blockIdx.z, S = gridDim.z;
-    if (item >= n_items) return;
+    constexpr int HD = 128, STEP = 2 * RSD_PAGE, STAGE = 2 * STEP * HD;      // bf16 elements of a stage: K and V of 32 tokens
+    __shared__ __attribute__((aligned(16))) uint16_t s_kv[3 * STAGE];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int item = gridDim.x - 1 - blockIdx.x;             // (later items have the longer contexts: they go first)
+    const int hk = blockIdx.y, sp = blockIdx.z, S = gridDim.z;
     const int r0 = item_row0[item], n = item_n[item];
     const int seq = row_seq[r0], p0 = row_pos[r0];
-    const int l16 = lane & 15, c = lane >> 4;
     const int* bt = block_table + (size_t)seq * max_pages;
     const size_t page_elts = (size_t)2 * Hkv * RSD_PAGE * HD;
     const size_t head_off = (size_t)hk * RSD_PAGE * HD, v_off = (size_t)Hkv * RSD_PAGE * HD;
-    const int p_last = p0 + n - 1, n_pages = p_last / RSD_PAGE + 1;
-    const int per = (n_pages + S - 1) / S;
-    const int pg_lo = min(n_pages, sp * per), pg_hi = min(n_pages, pg_lo + per);     // this split's pages
-    int bt_mine = ((pg_lo & ~63) + lane < n_pages) ? bt[(pg_lo & ~63) + lane] : -1;  // refreshed every 64 pages
+    const int p_last = p0 + n - 1, n_pages = p_last / RSD_PAGE + 1, n_steps = p_last / STEP + 1;
+    const int per = (n_steps + S - 1) / S;
+    const int s_lo = min(n_steps, sp * per), s_hi = min(n_steps, s_lo + per);        // this split's steps
 
-    // column l16 of tile t: row r0 + 2t + l16 / 8, head l16 % 8
-    const int g_col = l16 & 7;
-    // Q^T operands of this wave's tiles live in LDS as hi + lo bf16: [wave][tile][hi|lo][16 columns][HD + 8]
-    extern __shared__ __attribute__((aligned(16))) uint16_t s_qop[];
-    constexpr int QSTR = HD + 8;
-    uint16_t* qbase = s_qop + (size_t)wave * NT * 2 * 16 * QSTR;
-    int pos_col[NT];
+    const int col = lane & 31, h = lane >> 5;
+    const int n_w = min(max(n - 4 * wave, 0), 4);            // rows of this wave (0: it only copies)
+    const int ri = col >> 3, g = col & 7;
+    const bool live = ri < n_w && g < G;
+    const int pw = p0 + 4 * wave, pw_last = pw + n_w - 1;    // positions of its first and last row
+    const int pos_col = min(pw + ri, p_last);                // (columns without a row compute something finite that nobody reads)
+    const int row = r0 + 4 * wave + ri;
+
+    // wave w copies K (w = 0, 1) or V (w = 2, 3) of page w % 2 of a step; past the end the last page is copied again
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)s_kv + wave * (RSD_PAGE * HD * 2);
+    // (lane i holds the table entry of this wave's page of step bt_base + i; looked up afresh every 64 steps)
+    int bt_base = s_lo, bt_mine = bt[min(2 * (s_lo + lane) + (wave & 1), n_pages - 1)];
+    auto request = [&](int step, int stg) {
+        step = min(step, max(s_hi - 1, s_lo));
+        if (step - bt_base >= 64) {
+            bt_base = step;
+            bt_mine = bt[min(2 * (step + lane) + (wave & 1), n_pages - 1)];
+            asm volatile("" : "+v"(bt_mine));                // (waited for here: at the branch's end every step would wait, for the copies too)
+        }
+        const int phys = __builtin_amdgcn_readlane(bt_mine, step - bt_base);
+        const char* src = reinterpret_cast<const char*>(pool_layer + (size_t)phys * page_elts + head_off + (wave >> 1) * v_off);
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int ri = 2 * t + (l16 >> 3);
-        const bool live = ri < n && g_col < G;
-        pos_col[t] = live ? p0 + ri : -1;                   // -1: the column sees no token
-        uint16_t* qh_row = qbase + ((size_t)(t * 2 + 0) * 16 + l16) * QSTR;
-        uint16_t* ql_row = qbase + ((size_t)(t * 2 + 1) * 16 + l16) * QSTR;
+        for (int i = 0; i < 4; ++i) copy16_to_lds(lds0 + stg * (STAGE * 2) + i * 1024, (uint32_t)(i * 1024 + lane * 16), src);
+    };
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            float qv[8];
-            if (live) {
-                load8(qkv + (size_t)(r0 + ri) * ldq + (hk * G + g_col) * HD + j * 32 + c * 8, qv);
+    for (int i = 0; i < 3; ++i) request(s_lo + i, i);
+
+    // q of this lane's column: dims 16 j + 8 h .. + 7
+    abf16x8_t qh[8], ql[8];
+    {
+        const float* q = qkv + (size_t)(live ? row : r0) * ldq + (hk * G + (live ? g : 0)) * HD + h * 8;
+        const float sc_q = live ? scale : 0.0f;
+        float qv[8][8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) qv[e] *= scale;
-            } else {
+        for (int j = 0; j < 8; ++j) load8(q + j * 16, qv[j]);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) qv[e] = 0.0f;
-            }
-            abf16x8_t h8, l8;
-            split_hi_lo8(qv, h8, l8);
-            *reinterpret_cast<uint4*>(qh_row + j * 32 + c * 8) = __builtin_bit_cast(uint4, h8);
-            *reinterpret_cast<uint4*>(ql_row + j * 32 + c * 8) = __builtin_bit_cast(uint4, l8);
+        for (int j = 0; j < 8; ++j) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) qv[j][e] = live ? qv[j][e] * sc_q : 0.0f;
+            split_hi_lo8(qv[j], qh[j], ql[j]);
         }
     }
-    // (each wave reads back only what it wrote itself: no block barrier needed)
-    float m_run[NT], l_run[NT];
-    af32x4_t o[NT][8];
+    float m_run = -INFINITY, l_run = 0.0f;
+    f32x16_t o[4];                                           // o[m][v] = O[column][32 m + 8 (v / 4) + 4 h + v % 4]
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        m_run[t] = -INFINITY; l_run[t] = 0.0f;
+    for (int m = 0; m < 4; ++m)
 #pragma unroll
-        for (int nb = 0; nb < 8; ++nb) o[t][nb] = af32x4_t{0.f, 0.f, 0.f, 0.f};
-    }
+        for (int v = 0; v < 16; ++v) o[m][v] = 0.0f;
 
-    uint4 kc[4], kn[4];
-    uint4 vc[4], vn[4];
-    auto fetch = [&](int pg, uint4 k[4], uint4 v[4]) {
-        const int phys = __shfl(bt_mine, pg & 63, RSD_WAVE);
-        const bf16_t* kb = pool_layer + (size_t)phys * page_elts + head_off;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) k[j] = *reinterpret_cast<const uint4*>(kb + (j * 64 + lane) * 8);
-#pragma unroll
-        for (int m = 0; m < 4; ++m) v[m] = *reinterpret_cast<const uint4*>(kb + v_off + (m * 64 + lane) * 8);
+    // operand addresses inside a stage.  K: token col of the step, dims 16 j + 8 h .. : 16 bytes (tiled page layout, KvTiled)
+    const int k_addr = (col >> 4) * (RSD_PAGE * HD) + (h * 16 + (col & 15)) * 8;              // + j * 256
+    // V: dim 32 m + col, tokens 4 h .. + 3 and 8 + 4 h .. + 3 of page a: 8 bytes each
+    const int v_addr_ = 2 * RSD_PAGE * HD + h * 128 + (col & 15) * 8 + (col >> 4) * 4;        // + a * 2048 + m * 512 (+ 256)
+    typedef __attribute__((ext_vector_type(2))) float f2_t;
+    typedef __attribute__((ext_vector_type(2))) __bf16 b2_t;
+    uint4 kf[8], vf[8];                                      // operands: K chunk j; V of page a, dims 32 m (vf[4 a + m])
+    auto read_k = [&](const uint16_t* kv, int j) { kf[j] = *reinterpret_cast<const uint4*>(kv + k_addr + j * 256); };
+    auto read_v = [&](const uint16_t* kv, int i) {
+        const uint16_t* p = kv + v_addr_ + (i >> 2) * 2048 + (i & 3) * 512;
+        const uint2 x = *reinterpret_cast<const uint2*>(p), y = *reinterpret_cast<const uint2*>(p + 256);
+        vf[i] = make_uint4(x.x, x.y, y.x, y.y);
     };
-    auto do_page = [&](int pg, const uint4 k[4], const uint4 v[4]) {
-        // slots past the last row's position hold whatever the pool held: zero those values
-        int smask = 0;
+    // the first step has landed when at most the requests of the two others are outstanding
+    asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
 #pragma unroll
-        for (int i = 0; i < 4; ++i) smask |= (pg * RSD_PAGE + c * 4 + i <= p_last) ? (1 << i) : 0;
-        const uint32_t mk0 = ((smask & 1) ? 0xFFFFu : 0u) | ((smask & 2) ? 0xFFFF0000u : 0u);
-        const uint32_t mk1 = ((smask & 4) ? 0xFFFFu : 0u) | ((smask & 8) ? 0xFFFF0000u : 0u);
+    for (int j = 0; j < 8; ++j) read_k(s_kv, j);
+    int stg = 0;
+    // in the middle of a step: the next one's copies have landed and this one's operands are all in registers, so behind the
+    // barrier the next step may be read and this one's stage overwritten
+    auto turn = [&](int s) {
+        asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        request(s + 3, stg);
+        stg = stg == 2 ? 0 : stg + 1;
+    };
+    const int s_w = n_w ? min(s_hi, pw_last / STEP + 1) : s_lo;         // steps of which some row of this wave sees a token
+    int s = s_lo;
+    for (; s < s_w; ++s) {
+        const uint16_t* kv = s_kv + stg * STAGE;
+        f32x16_t sc, s2;                                     // scores: hi part, lo part
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            af32x4_t s = {0.f, 0.f, 0.f, 0.f};
+        for (int v = 0; v < 16; ++v) { sc[v] = 0.0f; s2[v] = 0.0f; }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const abf16x8_t ka = __builtin_bit_cast(abf16x8_t, k[j]);
-                const abf16x8_t qhi = __builtin_bit_cast(abf16x8_t, *reinterpret_cast<const uint4*>(
-                    qbase + ((size_t)(t * 2 + 0) * 16 + l16) * QSTR + j * 32 + c * 8));
-                const abf16x8_t qlo = __builtin_bit_cast(abf16x8_t, *reinterpret_cast<const uint4*>(
-                    qbase + ((size_t)(t * 2 + 1) * 16 + l16) * QSTR + j * 32 + c * 8));
-                s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qlo, s, 0, 0, 0);
-                s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qhi, s, 0, 0, 0);
-            }
-            int vmask = 0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) vmask |= (pg * RSD_PAGE + c * 4 + i <= pos_col[t]) ? (1 << i) : 0;
-            float mloc = -INFINITY;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) if ((vmask >> i) & 1) mloc = fmaxf(mloc, s[i]);
-            mloc = fmaxf(mloc, __shfl_xor(mloc, 16, RSD_WAVE));
-            mloc = fmaxf(mloc, __shfl_xor(mloc, 32, RSD_WAVE));
-            const float m_new = fmaxf(m_run[t], mloc);
-            const float corr = (m_run[t] == -INFINITY) ? 0.0f : __expf(m_run[t] - m_new);
-            float p[4], lsum = 0.0f;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                p[i] = (((vmask >> i) & 1) && m_new > -INFINITY) ? __expf(s[i] - m_new) : 0.0f;
-                lsum += p[i];
-            }
-            lsum += __shfl_xor(lsum, 16, RSD_WAVE);
-            lsum += __shfl_xor(lsum, 32, RSD_WAVE);
-            l_run[t] = l_run[t] * corr + lsum;
-            m_run[t] = m_new;
-            uint16_t ph[4], pl[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) { ph[i] = f2bf(p[i]); pl[i] = f2bf(p[i] - bf2f(ph[i])); }
-            const as16x4_t pa = __builtin_bit_cast(as16x4_t, make_uint2((uint32_t)ph[0] | ((uint32_t)ph[1] << 16), (uint32_t)ph[2] | ((uint32_t)ph[3] << 16)));
-            const as16x4_t pb = __builtin_bit_cast(as16x4_t, make_uint2((uint32_t)pl[0] | ((uint32_t)pl[1] << 16), (uint32_t)pl[2] | ((uint32_t)pl[3] << 16)));
-            float cr[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) cr[i] = __shfl(corr, c * 4 + i, RSD_WAVE);
-#pragma unroll
-            for (int nb = 0; nb < 8; ++nb) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) o[t][nb][i] *= cr[i];
-                const uint32_t vx = (nb & 1) ? v[nb >> 1].z : v[nb >> 1].x, vy = (nb & 1) ? v[nb >> 1].w : v[nb >> 1].y;
-                const as16x4_t vb = __builtin_bit_cast(as16x4_t, make_uint2(vx & mk0, vy & mk1));
-                o[t][nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pb, vb, o[t][nb], 0, 0, 0);
-                o[t][nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa, vb, o[t][nb], 0, 0, 0);
-            }
+        for (int j = 0; j < 8; ++j) {
+            const abf16x8_t k = __builtin_bit_cast(abf16x8_t, kf[j]);
+            s2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k, ql[j], s2, 0, 0, 0);
+            sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k, qh[j], sc, 0, 0, 0);
+            read_v(kv, j);
+            __builtin_amdgcn_sched_barrier(0);
         }
-    };
-    auto prefetch = [&](int pg, uint4 k[4], uint4 v[4]) {     // pg < n_pages
-        if ((pg & 63) == 0) bt_mine = (pg + lane < n_pages) ? bt[pg + lane] : -1;
-        fetch(pg, k, v);
-    };
-    // two register buffers take turns (no copies between them: a copy would wait for the load)
-    if (pg_lo < pg_hi) fetch(pg_lo, kc, vc);
-    for (int pg = pg_lo; pg < pg_hi; pg += 2) {
-        if (pg + 1 < pg_hi) prefetch(pg + 1, kn, vn);
-        do_page(pg, kc, vc);
-        if (pg + 1 >= pg_hi) break;
-        if (pg + 2 < pg_hi) prefetch(pg + 2, kc, vc);
-        do_page(pg + 1, kn, vn);
-    }
-    // accumulator row c*4+i of tile t is column (row r0 + 2t + (c*4+i)/8, head (c*4+i)%8)
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
+        for (int v = 0; v < 16; ++v) sc[v] += s2[v];
+        if (s * STEP + STEP - 1 > pw) {                      // some row of the wave does not see all tokens
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int col = c * 4 + i;
-            const float den = __shfl(l_run[t], col, RSD_WAVE);
-            const float mx = __shfl(m_run[t], col, RSD_WAVE);
-            const int ri = 2 * t + (col >> 3), g = col & 7;
-            if (ri < n && g < G) {
-                if (S == 1) {
-                    float* dst = out + (size_t)(r0 + ri) * ldo + (hk * G + g) * HD + l16;
-                    const float inv = 1.0f / den;
+            for (int v = 0; v < 16; ++v)
+                if (s * STEP + 8 * (v >> 2) + 4 * h + (v & 3) > pos_col) sc[v] = -INFINITY;
+        }
+        float mx = sc[0];
 #pragma unroll
-                    for (int nb = 0; nb < 8; ++nb) dst[nb * 16] = o[t][nb][i] * inv;
-                } else {
-                    const size_t pi = ((size_t)(r0 + ri) * H + hk * G + g) * S + sp;
-                    float* dst = part_acc + pi * HD + l16;
+        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, sc[v]);
+        {
+            const auto w2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+            mx = fmaxf(__uint_as_float(w2[0]), __uint_as_float(w2[1]));
+        }
+        // the reference m_run only moves when a score exceeds it by more than 2^6: weights stay below 2^6 (no precision is
+        // lost, they are floating point) and the accumulators are rarely rescaled
+        if (__any(mx > m_run + 6.0f)) {
+            const float m_new = mx > m_run + 6.0f ? mx : m_run;
+            const float corr = m_run == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m_run - m_new);
+            m_run = m_new;
+            l_run *= corr;
 #pragma unroll
-                    for (int nb = 0; nb < 8; ++nb) dst[nb * 16] = o[t][nb][i];
-                    if (l16 == 0) { part_ml[pi * 2] = mx; part_ml[pi * 2 + 1] = den; }
+            for (int m = 0; m < 4; ++m)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[m][v] *= corr;
+        }
+        const float m_use = m_run == -INFINITY ? 0.0f : m_run;         // (no token of the column seen yet: all weights 0)
+        float lsum = 0.0f;
+        uint32_t ph[8], pl[8];                               // probabilities of tokens v = 2 i, 2 i + 1
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float a = __builtin_amdgcn_exp2f(sc[2 * i] - m_use), b = __builtin_amdgcn_exp2f(sc[2 * i + 1] - m_use);
+            lsum += a + b;
+            ph[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2_t{a, b}, b2_t));
+            pl[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2_t{a - __uint_as_float(ph[i] << 16), b - __uint_as_float(ph[i] & 0xFFFF0000u)}, b2_t));
+        }
+        l_run += lsum;                                       // (each half of the wave sums its own tokens; added up at the end)
+        if (s * STEP + STEP - 1 > p_last) {                  // slots behind the last row hold whatever the pool held: zero those values
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                uint32_t mk[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int t = s * STEP + a * RSD_PAGE + 4 * h + (i >> 1) * 8 + (i & 1) * 2;
+                    mk[i] = (t <= p_last ? 0xFFFFu : 0u) | (t + 1 <= p_last ? 0xFFFF0000u : 0u);
+                }
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    vf[4 * a + m].x &= mk[0]; vf[4 * a + m].y &= mk[1]; vf[4 * a + m].z &= mk[2]; vf[4 * a + m].w &= mk[3];
                 }
             }
         }
+        turn(s);
+        kv = s_kv + stg * STAGE;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {                       // page a, lo then hi, dims 32 m; the next step's K in between
+            const int a = i >> 3, hi = (i >> 2) & 1, m = i & 3;
+            const uint32_t* p = hi ? ph : pl;
+            const abf16x8_t pa = __builtin_bit_cast(abf16x8_t, make_uint4(p[4 * a], p[4 * a + 1], p[4 * a + 2], p[4 * a + 3]));
+            o[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(abf16x8_t, vf[4 * a + m]), pa, o[m], 0, 0, 0);
+            if (i & 1) read_k(kv, i >> 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    for (; s < s_hi; ++s) turn(s);                           // (the other waves still need this one's copies)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // nothing is in flight into LDS when the block ends
+    {
+        const auto w2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
+        l_run = __uint_as_float(w2[0]) + __uint_as_float(w2[1]);
+    }
+    if (!live) return;
+    if (S == 1) {
+        const float inv = 1.0f / l_run;
+        const size_t at = (size_t)row * ldo + (hk * G + g) * HD + 4 * h;
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (out) {
+                    *reinterpret_cast<float4*>(out + at + 32 * m + 8 * q) =
+                        make_float4(o[m][4 * q] * inv, o[m][4 * q + 1] * inv, o[m][4 * q + 2] * inv, o[m][4 * q + 3] * inv);
+                    continue;
+                }
+                uint16_t hi[4], lo[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float y = o[m][4 * q + e] * inv;
+                    hi[e] = f2bf(y);
+                    lo[e] = f2bf(y - bf2f(hi[e]));
+                }
+                *reinterpret_cast<uint2*>(out_h + at + 32 * m + 8 * q) =
+                    make_uint2((uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16));
+                *reinterpret_cast<uint2*>(out_l + at + 32 * m + 8 * q) =
+                    make_uint2((uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16));
+            }
+    } else {
+        const size_t pi = ((size_t)row * H + hk * G + g) * S + sp;
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<float4*>(part_acc + pi * HD + 32 * m + 8 * q + 4 * h) =
+                    make_float4(o[m][4 * q], o[m][4 * q + 1], o[m][4 * q + 2], o[m][4 * q + 3]);
+        // (the merge works with natural exponentials)
+        if (h == 0) { part_ml[pi * 2] = m_run * 0.6931471805599453f; part_ml[pi * 2 + 1] = l_run; }
     }
 }

@@ -129,7 +129,7 @@ struct rsd_ctx {
     int *chk_n_pages_dev = nullptr, *chk_err_dev = nullptr, *chk_h = nullptr;
     // halves the next MFMA GEMM reads instead of xs_h / xs_l (set by a producer that could not write there; used once)
     const uint16_t *xin_h = nullptr, *xin_l = nullptr;
-    // chunked-prefill attention work items: first row and row count (<= 4 rows of one sequence)
+    // chunked-prefill attention work items: first row and row count (<= kPfItemRows rows of one sequence)
     int *item_row0_dev = nullptr, *item_n_dev = nullptr, *item_row0_h = nullptr, *item_n_h = nullptr;
     int n_items = 0;
     int pf_rows = 0, pf_max_end = 0;     // rows of the chunked pass in flight and the longest context among its pieces
@@ -446,38 +446,30 @@ void launch_attn_decode_mfma(rsd_ctx* c, const Model& m, int l, int M, int which
 }
 
 // chunked prefill over a bf16 cache: rows of the pass are described by the context's item arrays
-void launch_attn_prefill_mfma(rsd_ctx* c, const Model& m, int l, const RowMap& rm) {
+void launch_attn_prefill_mfma(rsd_ctx* c, const Model& m, int l, const RowMap& rm, bool halves) {
     const bf16_t* pool_l = reinterpret_cast<const bf16_t*>(m.pool) + (size_t)l * m.pool_pages * m.page_elts;
-    const float scale = 1.0f / std::sqrt(128.0f);
+    const float scale = (float)(1.4426950408889634 / std::sqrt(128.0));      // log2 e / sqrt(head_dim): scores in units of log2
     // few rows over long contexts (a verification pass, the scoring of one step, a short catch-up): the
     // work items alone leave most of the chip idle, so every item's pages are dealt to several splits
     int S = 1;
-    const int waves = c->n_items * m.s.n_kv_heads, pages = ceil_div(c->pf_max_end, RSD_PAGE);
-    if (waves < 512 && pages > 8 && c->pf_rows <= kPfSplitRows)
-        S = std::max(1, std::min(kPfSplits, std::min(ceil_div(pages, 4), 1024 / waves)));
-    const dim3 grid(ceil_div(c->n_items, 4), m.s.n_kv_heads, S), block(256);
-    constexpr size_t qlds = (size_t)4 * 2 * 2 * 16 * (128 + 8) * sizeof(uint16_t);     // Q operands of 4 waves
+    const int blocks = c->n_items * m.s.n_kv_heads, pages = ceil_div(c->pf_max_end, RSD_PAGE);
+    if (blocks < 256 && pages > 8 && c->pf_rows <= kPfSplitRows)
+        S = std::max(1, std::min(kPfSplits, std::min(ceil_div(pages, 4), 512 / blocks)));
+    const dim3 grid(c->n_items, m.s.n_kv_heads, S), block(256);
 #define RSD_ATTN_CASE(GG)                                                                                     \
-    case GG: {                                                                                                \
-        /* set once per process; the call is idempotent, so a race between contexts costs a repeat at most */ \
-        static std::atomic<bool> raised{false};                                                               \
-        if (!raised.load(std::memory_order_relaxed)) {                                                        \
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(attn_prefill_mfma_kernel<GG>),            \
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)qlds);                 \
-            raised.store(true, std::memory_order_relaxed);                                                    \
-        }                                                                                                     \
-        hipLaunchKernelGGL((attn_prefill_mfma_kernel<GG>), grid, block, qlds, c->st, c->qkv, m.n_qkv, pool_l, \
+    case GG:                                                                                                  \
+        hipLaunchKernelGGL((attn_prefill_mfma_kernel<GG>), grid, block, 0, c->st, c->qkv, m.n_qkv, pool_l,    \
                            m.bt_dev, m.max_pages, rm.row_seq, rm.row_pos, c->item_row0_dev, c->item_n_dev,    \
-                           c->n_items, m.s.n_heads, m.s.n_kv_heads, scale, c->att, m.q_dim, c->part_acc,      \
-                           c->part_ml);                                                                       \
-    } break;
+                           m.s.n_heads, m.s.n_kv_heads, scale, halves ? nullptr : c->att, m.q_dim, c->xs_h,   \
+                           c->xs_l, c->part_acc, c->part_ml);                                                 \
+        break;
     switch (m.G) {
         RSD_ATTN_CASE(1) RSD_ATTN_CASE(2) RSD_ATTN_CASE(4) RSD_ATTN_CASE(6) RSD_ATTN_CASE(7) RSD_ATTN_CASE(8)
     }
 #undef RSD_ATTN_CASE
     if (S > 1)
         hipLaunchKernelGGL((attn_combine_kernel<128>), dim3(c->pf_rows, m.s.n_heads), dim3(128), 0, c->st, c->part_acc,
-                           c->part_ml, rm, m.s.n_heads, S, c->att, m.q_dim, (uint16_t*)nullptr, (uint16_t*)nullptr);
+                           c->part_ml, rm, m.s.n_heads, S, c->att, m.q_dim, halves ? c->xs_h : nullptr, halves ? c->xs_l : nullptr);
 }
 
 // Two or more rows over bf16 weights: MFMA kernels on activations split into hi + lo bf16 halves, which
@@ -585,8 +577,8 @@ void run_layers(rsd_ctx* c, Model& m, int M, const RowMap& rm, bool decode) {
     const bool rows = rows_path<WT>(m, M);
     const bool fused = M <= 8 && !rows;   // few rows: norm / SwiGLU / residual folded into the weight-streaming kernels
     const bool rows_fuse_norm = rows;                        // the residual GEMMs leave RMSNorm(h) for the next projection
-    // batched decode: the attention kernel (or its merge kernel) writes the output as hi / lo halves itself
-    const bool att_halves = rows && decode && m.s.dtype == RSD_BF16 && m.hd == 128;
+    // the attention kernels over bf16 caches (or their merge kernel) write the output as hi / lo halves themselves
+    const bool att_halves = rows && m.s.dtype == RSD_BF16 && m.hd == 128;
     // single-row decode over a bf16 cache: the output projection merges the attention splits itself
     const bool parts_to_o = decode && M == 1 && S > 1 && m.s.dtype == RSD_BF16 && m.hd == 128 &&
                             (size_t)m.q_dim * sizeof(float) <= 40 * 1024;
@@ -603,7 +595,7 @@ void run_layers(rsd_ctx* c, Model& m, int M, const RowMap& rm, bool decode) {
             if (l == 0 || !rows_fuse_norm) rows_split(c, c->h, d, M, d, wptr<WT>(m, o.attn_norm), eps);
             // (the batched decode attention over a bf16 cache adds the projection's K slices itself)
             rows_gemm(c, m, 0, EPI_STORE, wptr<WT>(m, o.wqkv), m.n_qkv, d, M, c->qkv, m.n_qkv, nullptr, 0.f,
-                      att_halves ? &qkv_parts : nullptr);
+                      att_halves && decode ? &qkv_parts : nullptr);
         } else if constexpr (std::is_same<WT, float>::value) {
             hipLaunchKernelGGL((rmsnorm_kernel<WT>), dim3(M), dim3(256), 0, st, c->h, d, wptr<WT>(m, o.attn_norm), eps, c->xn);
             gemm_launch(st, EPI_STORE, wptr<WT>(m, o.wqkv), m.n_qkv, d, c->xn, d, c->qkv, m.n_qkv, M, c->part_k, c->part_k_floats);
@@ -617,7 +609,7 @@ void run_layers(rsd_ctx* c, Model& m, int M, const RowMap& rm, bool decode) {
         } else if (m.hd == 128) {
             hipLaunchKernelGGL((rope_kv_kernel<WT, 128>), dim3(M), dim3(256), 0, st, c->qkv, m.n_qkv, pool_l, m.bt_dev,
                                m.max_pages, rm, m.rope, m.s.n_heads, m.s.n_kv_heads);
-            if (m.s.dtype == RSD_BF16) launch_attn_prefill_mfma(c, m, l, rm);
+            if (m.s.dtype == RSD_BF16) launch_attn_prefill_mfma(c, m, l, rm, att_halves);
             else launch_attn_g<WT, 128>(c, m, l, M, rm, S);
         } else {
             hipLaunchKernelGGL((rope_kv_kernel<WT, 32>), dim3(M), dim3(256), 0, st, c->qkv, m.n_qkv, pool_l, m.bt_dev,
@@ -820,9 +812,9 @@ int prefill(rsd_ctx* c, int which, std::vector<Piece> pieces, AfterPass after_pa
             if (pc.end - pc.start > room) take.end = pc.start + room;
             first_row.push_back(M);
             pass.push_back(take);
-            for (int r = 0; r < take.end - take.start; r += 4) {
+            for (int r = 0; r < take.end - take.start; r += kPfItemRows) {
                 c->item_row0_h[n_items] = M + r;
-                c->item_n_h[n_items++] = std::min(4, take.end - take.start - r);
+                c->item_n_h[n_items++] = std::min(kPfItemRows, take.end - take.start - r);
             }
             for (int p = take.start; p < take.end; ++p, ++M) { c->row_seq_h[M] = take.b; c->row_pos_h[M] = p; }
             // "last row" of a sequence: the final position of its final piece

@@ -50,3 +50,21 @@ def test_full_width_against_few_row_passes(width, rows):
     pieces = R.rsd_forward(ctx, 0, toks, lens, 64)
     assert float((whole - pieces).abs().max()) < TOL
     R.rsd_destroy(ctx)
+
+
+@pytest.mark.parametrize("chunk", [2, 5, 16, 17, 33, 200])
+def test_chunked_attention_at_the_edges_of_its_work_items(chunk):
+    """Pieces that end inside a work item of 16 rows, a wave's four rows, a page and a two-page step; 8 query heads per KV
+    head; contexts split over several blocks (short passes over more than 8 pages) and not."""
+    from oracle import rsd_oracle as O
+    from rsd_inputs import ModelShape, model_weights_np
+    shape = ModelShape(1, 1024, 8, 1, 64, 501)
+    lens = np.array([200, 37, 1], np.int32)
+    R, ctx = build(shape, 501, 201, batch=3)
+    toks = np.random.default_rng(chunk).integers(0, 501, size=(3, 200)).astype(np.int32)
+    out = R.rsd_forward(ctx, 0, toks, lens, chunk).cpu().numpy()
+    m = O.OracleModel(shape, model_weights_np(7, 0, shape))
+    for b in range(3):
+        ref = O.lm_logits(m, O.forward_full(m, [int(t) for t in toks[b, :lens[b]]], "bf16"))
+        assert np.max(np.abs(out[b, :lens[b]] - ref)) < TOL, b
+    R.rsd_destroy(ctx)
