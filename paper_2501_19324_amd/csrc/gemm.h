@@ -798,6 +798,12 @@ static void gemm_launch(hipStream_t st, int epi, const float* W, int N, int K, c
     else                  hipLaunchKernelGGL((sgemm_nt_kernel<EPI_STORE>), grid, block, 0, st, W, N, K, X, ldx, Y, ldy, M);
 }
 
+// silu(g) * u with the hardware's exponential and reciprocal (a few 1e-7 relative; the result is stored with 16 bits).  The
+// library forms (expf, a full division) cost the tile kernel's epilogue about 45 instructions per value, 10 us per round of tiles.
+__device__ __forceinline__ float silu_mul(float g, float u) {
+    return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)) * u;
+}
+
 // ---------------------------------------------------------------- bf16 MFMA, many rows, pre-split activations
 // Y[m][n] (+)= sum_k (Xh + Xl)[m][k] * W[n][k] for more than 64 rows (prefill chunks, large decode batches).
 // Block tile BM rows of X x BN rows of W on eight waves, MFMA tiles of 32x32x16, lo pass then hi pass on each.
@@ -995,7 +1001,7 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(const bf16_t* __restr
                     const float g = __uint_as_float(s[0]), u = __uint_as_float(s[1]);
                     const int m = m0 + (wm * TM + i) * 32 + 8 * (v >> 2) + 4 * kg + (v & 3) + ((lane & 16) ? 16 : 0);
                     if (m < M && col < F) {
-                        const float x = g / (1.0f + expf(-g)) * u;
+                        const float x = silu_mul(g, u);
                         const uint16_t hi = f2bf(x);
                         Oh[(size_t)m * F + col] = hi;
                         Ol[(size_t)m * F + col] = f2bf(x - bf2f(hi));
@@ -1061,9 +1067,184 @@ static TilePlan gemm_tile_plan(int epi, int N, int K, int M, size_t part_floats)
     return best;
 }
 
+// ---------------------------------------------------------------- bf16 MFMA, 2..128 rows, the whole of K in one block
+// The gate/up projection with its SwiGLU, and the output head, without K slices: a block owns BN rows of W (the gate and the up
+// rows of BN / 2 units) over all of K, so there are no partial sums to write and read back and no finish kernel.  BN is
+// chosen so that the blocks make one round on 256 compute units (stream_bn).  X and W tiles of 64 k go straight into a ring
+// of up to six LDS stages, all but one of them in flight; the waves divide a K block by (32 columns, K part) and add the K
+// parts through LDS at the end.  Bound by what the copies pull through L2: W once and, per block, all of X (217 MB beside
+// 272 MB at 64 rows of the 7B shape).  Measured against K slices plus their finish kernel (us; 7B gate/up, 1.5B gate/up, a
+// head of 16384 x 1536): 16 rows 48.4 / 51.6, 14.8 / 18.3, 12.1 / 17.4; 32 rows 50.2 / 55.6, 16.7 / 20.3, 13.7 / 19.5; 64 rows 58.8 /
+// 68.6, 21.3 / 24.7, 19.2 / 25.8; 128 rows (against the tile kernel) 84.6 / 93.1, 30.3 / 35.6, 30.3 / 34.9.  Matrices that give no
+// single round of blocks stay with the slices: [59136][8192] at 16 rows 182 against 159.
+template <int MT, int BN> struct StreamCfg {
+    static constexpr int BK = 64;
+    static constexpr int TN = 1, WN = BN / 32, KW = BN == 64 ? 4 : 2, NW = WN * KW;      // waves along the columns / along K
+    static constexpr int XREQ = MT * 8, REQ = XREQ + BN / 8;          // 1 KB requests of a K block: X hi, X lo, W
+    static constexpr int NS = (160 * 1024) / (REQ * 1024) > 6 ? 6 : (160 * 1024) / (REQ * 1024);
+    static constexpr int CNT = REQ / NW, EXTRA = REQ % NW;
+    static constexpr int LDS = NS * REQ * 1024;
+    static_assert(NS >= 2 && (KW - 1) * WN * MT * TN * 4096 <= LDS, "");
+};
+template <int EPI, int MT, int BN>
+__global__ __launch_bounds__((StreamCfg<MT, BN>::NW * 64)) void gemm_stream_kernel(const bf16_t* __restrict__ W, int N, int K,
+                                                             const uint16_t* __restrict__ Xh, const uint16_t* __restrict__ Xl, int M,
+                                                             float* __restrict__ Y, int ldy,
+                                                             uint16_t* __restrict__ Oh, uint16_t* __restrict__ Ol) {
+    using C = StreamCfg<MT, BN>;
+    constexpr int BK = C::BK, TN = C::TN, WN = C::WN, KW = C::KW, NW = C::NW, NS = C::NS, CNT = C::CNT, EXTRA = C::EXTRA;
+    constexpr int STAGE = C::REQ * 512;                       // bf16 elements of a stage
+    extern __shared__ __attribute__((aligned(16))) uint16_t tile_sm[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wave % WN, kw = wave / WN;
+    const int bx = blockIdx.x, n0 = bx * BN, nk = K / BK;
+    const int F = N / 2;
+    auto wrow = [&](int r) { return EPI == EPI_SWIGLU ? ((r >> 4) & 1) * F + min(bx * (BN / 2) + (r >> 5) * 16 + (r & 15), F - 1) : min(n0 + r, N - 1); };
+    // copies (as in gemm_tile_kernel): request id = wave + NW i covers eight rows of 128 bytes; lane -> row lane / 8, LDS chunk
+    // lane % 8, which holds source chunk (lane % 8) ^ ((row / 2) % 8)
+    const char* base[CNT + 1];
+    uint32_t voff[CNT + 1];
+#pragma unroll
+    for (int i = 0; i <= CNT; ++i) {
+        const int id = min(wave + NW * i, C::REQ - 1);
+        const int x = id < MT * 4 ? id : id - MT * 4;         // 8-row group of an X half
+        const bool isx = id < C::XREQ;
+        const int g8 = isx ? x : id - C::XREQ;
+        const int rl = g8 * 8 + (lane >> 3);
+        const uint32_t ch = ((lane & 7) ^ (((g8 & 1) * 4 + (lane >> 4)) & 7)) * 16;
+        const int b = isx ? min(g8 * 8, M - 1) : wrow(g8 * 8), r = isx ? min(rl, M - 1) : wrow(rl);
+        base[i] = reinterpret_cast<const char*>((isx ? (id < MT * 4 ? Xh : Xl) : reinterpret_cast<const uint16_t*>(W)) + (size_t)b * K);
+        voff[i] = (uint32_t)(r - b) * (uint32_t)K * 2u + ch;
+    }
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)tile_sm + wave * 1024;
+    const bool extra = EXTRA > 0 && wave < EXTRA;
+    auto request = [&](int kb, int s) {
+        const size_t ko = (size_t)min(kb, nk - 1) * (BK * 2);
+#pragma unroll
+        for (int i = 0; i < CNT; ++i) copy16_to_lds(lds0 + s * (STAGE * 2) + i * (NW * 1024), voff[i], base[i] + ko);
+        if (extra) copy16_to_lds(lds0 + s * (STAGE * 2) + CNT * (NW * 1024), voff[CNT], base[CNT] + ko);
+    };
+    f32x16_t acc[MT][TN];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+    const int l32 = lane & 31, kg = lane >> 5, swz = (l32 >> 1) & 7;
+    const uint16_t* B = tile_sm + C::XREQ * 512 + wn * TN * 32 * BK;
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s) request(s, s);
+    int cur = 0, prev = NS - 1;
+    // block kb has landed when at most the requests of the NS - 2 blocks behind it are outstanding; behind the barrier that holds
+    // for every wave, and everybody has read block kb - 1, whose stage takes block kb + NS - 1
+    for (int kb = 0; kb < nk; ++kb) {
+        if (extra) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NS - 2) * (CNT + 1)) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NS - 2) * CNT) : "memory");
+        request(kb + NS - 1, prev);
+        const uint16_t *a = tile_sm + cur * STAGE, *b = B + cur * STAGE;
+#pragma unroll
+        for (int q = 0; q < 4 / KW; ++q) {
+            const int off = l32 * BK + (((2 * (kw * (4 / KW) + q) + kg) ^ swz) << 3);
+            bf16x8_t w[TN];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) w[j] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(b + j * 32 * BK + off));
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                const bf16x8_t xl = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(a + (MT + i) * 32 * BK + off));
+                const bf16x8_t xh = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(a + i * 32 * BK + off));
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl, w[j], acc[i][j], 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh, w[j], acc[i][j], 0, 0, 0);
+            }
+        }
+        prev = cur;
+        cur = cur == NS - 1 ? 0 : cur + 1;
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    // add the K parts in ascending order through LDS
+    float* red = reinterpret_cast<float*>(tile_sm);
+    if (kw > 0) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) red[((((kw - 1) * WN + wn) * MT + i) * TN + j) * 1024 + v * 64 + lane] = acc[i][j][v];
+    }
+    __syncthreads();
+    if (kw > 0) return;
+#pragma unroll
+    for (int p = 0; p < KW - 1; ++p)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][j][v] += red[(((p * WN + wn) * MT + i) * TN + j) * 1024 + v * 64 + lane];
+    if (EPI == EPI_SWIGLU) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int col = bx * (BN / 2) + (wn * TN + j) * 16 + (lane & 15);
+#pragma unroll
+                for (int v = 0; v < 8; ++v) {
+                    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[i][j][v]), __float_as_uint(acc[i][j][v + 8]), false, false);
+                    const float g = __uint_as_float(s[0]), u = __uint_as_float(s[1]);
+                    const int m = i * 32 + 8 * (v >> 2) + 4 * kg + (v & 3) + ((lane & 16) ? 16 : 0);
+                    if (m < M && col < F) {
+                        const float x = silu_mul(g, u);
+                        const uint16_t hi = f2bf(x);
+                        Oh[(size_t)m * F + col] = hi;
+                        Ol[(size_t)m * F + col] = f2bf(x - bf2f(hi));
+                    }
+                }
+            }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int n = n0 + (wn * TN + j) * 32 + l32;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int m = i * 32 + 8 * (v >> 2) + 4 * kg + (v & 3);
+                if (m < M && n < N) Y[(size_t)m * ldy + n] = acc[i][j][v];
+            }
+        }
+}
+
+// BN for which an [N][K] matrix gives 160..256 blocks, as many as possible; 0: none
+static int stream_bn(int N) {
+    for (int bn : {64, 96, 160}) {
+        const int blocks = (N + bn - 1) / bn;
+        if (blocks >= 160 && blocks <= 256) return bn;
+    }
+    return 0;
+}
+#define RSD_STREAM_SIZES(X) X(1, 64) X(1, 96) X(1, 160) X(2, 64) X(2, 96) X(2, 160) X(4, 64) X(4, 96) X(4, 160)
+static void gemm_stream_launch(hipStream_t st, int epi, int bn, const bf16_t* W, int N, int K, const uint16_t* Xh, const uint16_t* Xl, int M,
+                               float* Y, int ldy, uint16_t* Oh, uint16_t* Ol) {
+    const int mt = M <= 32 ? 1 : M <= 64 ? 2 : 4;
+    const dim3 grid((N + bn - 1) / bn);
+#define RSD_STREAM_CASE(MT, BN)                                                                                              \
+    if (mt == MT && bn == BN) {                                                                                              \
+        constexpr size_t lds = StreamCfg<MT, BN>::LDS;                                                                       \
+        const dim3 block(StreamCfg<MT, BN>::NW * 64);                                                                        \
+        if (epi == EPI_SWIGLU) hipLaunchKernelGGL((gemm_stream_kernel<EPI_SWIGLU, MT, BN>), grid, block, lds, st, W, N, K, Xh, Xl, M, Y, ldy, Oh, Ol); \
+        else                   hipLaunchKernelGGL((gemm_stream_kernel<EPI_STORE, MT, BN>), grid, block, lds, st, W, N, K, Xh, Xl, M, Y, ldy, Oh, Ol);  \
+        return;                                                                                                              \
+    }
+    RSD_STREAM_SIZES(RSD_STREAM_CASE)
+#undef RSD_STREAM_CASE
+}
+
 #define RSD_TILE_SIZES(X) X(256, 256) X(256, 192) X(128, 256) X(128, 192) X(128, 128)
 
-// The tiles need more than 64 KB of LDS: allowed once per context on its device (never from inside a launch, which may
+// These kernels need more than 64 KB of LDS: allowed once per context on its device (never from inside a launch, which may
 // be recording a graph).
 static hipError_t gemm_tile_raise() {
     hipError_t e = hipSuccess;
@@ -1074,6 +1255,12 @@ static hipError_t gemm_tile_raise() {
         if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, TileCfg<BM, BN>::LDS);
     RSD_TILE_SIZES(RSD_TILE_RAISE)
 #undef RSD_TILE_RAISE
+#define RSD_STREAM_RAISE(MT, BN)                                                                                             \
+    for (const void* f : {reinterpret_cast<const void*>(gemm_stream_kernel<EPI_STORE, MT, BN>),                              \
+                          reinterpret_cast<const void*>(gemm_stream_kernel<EPI_SWIGLU, MT, BN>)})                            \
+        if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, StreamCfg<MT, BN>::LDS);
+    RSD_STREAM_SIZES(RSD_STREAM_RAISE)
+#undef RSD_STREAM_RAISE
     return e;
 }
 

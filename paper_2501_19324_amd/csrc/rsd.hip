@@ -508,6 +508,15 @@ void rows_gemm(rsd_ctx* c, const Model& m, int op, int epi, const bf16_t* W, int
     // algorithmic traffic: the weights once, fp32 activations in and out (SwiGLU leaves N / 2 columns)
     const long long pb = (long long)N * K * 2 + 4LL * M * (K + (epi == EPI_SWIGLU ? N / 2 : N) + (epi == EPI_RESID ? N : 0));
     const long long pf = 2LL * M * N * K;
+    if (const int bn = M <= 128 && !defer && epi != EPI_RESID ? stream_bn(N) : 0) {
+        // (the activated halves go to the gate/up workspace: see the tile kernel below)
+        uint16_t* oh = reinterpret_cast<uint16_t*>(c->gu);
+        uint16_t* ol = oh + (size_t)M * (N / 2);
+        ProbeScope ps(c, m, op, pb, pf);
+        gemm_stream_launch(c->st, epi, bn, W, N, K, Xh, Xl, M, Y, ldy, oh, ol);
+        if (epi == EPI_SWIGLU) { c->xin_h = oh; c->xin_l = ol; }
+        return;
+    }
     int ks;
     if (few && gemm_rows_even(N, K)) {
         geo = sk_geometry(N, K, kSkBlocks);

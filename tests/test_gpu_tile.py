@@ -68,3 +68,20 @@ def test_chunked_attention_at_the_edges_of_its_work_items(chunk):
         ref = O.lm_logits(m, O.forward_full(m, [int(t) for t in toks[b, :lens[b]]], "bf16"))
         assert np.max(np.abs(out[b, :lens[b]] - ref)) < TOL, b
     R.rsd_destroy(ctx)
+
+
+@pytest.mark.parametrize("rows", [2, 31, 33, 64, 65, 127, 128])
+@pytest.mark.parametrize("ffn", [5248, 8320, 12864])
+def test_unsliced_gate_up_and_head(rows, ffn):
+    """The kernel without K slices (2..128 rows, matrices of 160..256 row blocks): gate/up pairs that its blocks of 32, 48 and
+    80 units cut evenly and not, a head of an odd vocabulary, row counts around its tiles of 32, 64 and 128."""
+    from oracle import rsd_oracle as O
+    from rsd_inputs import ModelShape, model_weights_np
+    shape = ModelShape(1, 128, 1, 1, ffn, 10241)
+    R, ctx = build(shape, 10241, 129)
+    toks = np.random.default_rng(rows).integers(0, 10241, size=(1, rows)).astype(np.int32)
+    out = R.rsd_forward(ctx, 0, toks, np.array([rows], np.int32), 128).cpu().numpy()[0]
+    m = O.OracleModel(shape, model_weights_np(7, 0, shape))
+    ref = O.lm_logits(m, O.forward_full(m, [int(t) for t in toks[0]], "bf16"))
+    assert np.max(np.abs(out - ref)) < TOL / 4           # (logits of rms 0.2)
+    R.rsd_destroy(ctx)
