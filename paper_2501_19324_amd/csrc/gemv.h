@@ -337,7 +337,25 @@ static bool gemv_launch_full(hipStream_t st, int pro, int epi, const WT* W, int 
 // which lets the compiler keep two stages of U loads in flight.  A wave finishes a row
 // (or its part of one) with a lane sum into its own LDS slot; the slots are added in wave
 // order at the end, so the result does not depend on timing.
-template <typename WT, int NW, int U, int PRO, int EPI>
+// The activations (and norm gains, or attention partials) are requested BEFORE the first weights: loads return in order, so
+// requested behind the weights they would only arrive when the first two stages of weights (for the 1.5B gate/up pair: all of
+// them) have, and staging, norm, barrier and arithmetic would follow the whole transfer instead of overlapping it.
+// XR: rounds of four floats per thread that cover K.  Measured (kernel alone, us): see gemv_launch_mt.
+template <int XR> constexpr int kAttnAhead = XR == 1 ? 8 : 2;       // PRO_ATTN: splits whose partials are requested ahead of the weights
+template <typename WT> struct Raw4;
+template <> struct Raw4<bf16_t> {
+    uint2 v;
+    __device__ __forceinline__ void load(const bf16_t* p) { v = *reinterpret_cast<const uint2*>(p); }
+    __device__ __forceinline__ float4 get() const {
+        return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xFFFF0000u));
+    }
+};
+template <> struct Raw4<float> {
+    float4 v;
+    __device__ __forceinline__ void load(const float* p) { v = *reinterpret_cast<const float4*>(p); }
+    __device__ __forceinline__ float4 get() const { return v; }
+};
+template <typename WT, int NW, int U, int XR, int PRO, int EPI>
 __global__ __launch_bounds__(NW * 64) void gemv_flat_kernel(const WT* __restrict__ W, int N, int K,
                                                             const float* __restrict__ X,
                                                             const WT* __restrict__ gain, float eps,
@@ -372,42 +390,70 @@ __global__ __launch_bounds__(NW * 64) void gemv_flat_kernel(const WT* __restrict
             for (int a = 0; a < NA; ++a) buf[u][a].load(W + ((size_t)a * N + r0 + v) * K + k);
         }
     };
+    float4 xv[XR];
+    Raw4<WT> gv[XR];
+    constexpr int AH = kAttnAhead<XR>;
+    float2 pml[PRO == PRO_ATTN ? XR : 1][AH];
+    float4 pac[PRO == PRO_ATTN ? XR : 1][AH];
+#pragma unroll
+    for (int r = 0; r < XR; ++r) {
+        const int k = min(tid * 4 + r * NW * 256, K - 4);
+        if (PRO == PRO_ATTN) {              // head k / 128, elements k % 128 .. + 3 of the splits' partials
+            const size_t at = (size_t)(k >> 7) * parts.S;
+#pragma unroll
+            for (int i = 0; i < AH; ++i) {
+                const size_t sp = at + min(i, parts.S - 1);
+                pml[r][i] = *reinterpret_cast<const float2*>(parts.ml + sp * 2);
+                pac[r][i] = *reinterpret_cast<const float4*>(parts.acc + sp * 128 + (k & 127));
+            }
+        } else {
+            xv[r] = *reinterpret_cast<const float4*>(X + k);
+            if (PRO == PRO_NORM) gv[r].load(gain + k);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
     Raw8<WT> b0[U][NA], b1[U][NA];
     fetch(b0, 0);
     fetch(b1, 1);
+    __builtin_amdgcn_sched_barrier(0);
 
     float ss = 0.0f;
-    for (int k = tid * 4; k < (CPR << 9); k += NW * 256) {
+#pragma unroll
+    for (int r = 0; r < XR; ++r) {
+        const int k = tid * 4 + r * NW * 256;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (PRO == PRO_ATTN) {
-            if (k < K) {        // head k / 128, elements k % 128 .. + 3
-                const int h = k >> 7, e = k & 127, S = parts.S;
-                const float* ml = parts.ml + (size_t)h * S * 2;
-                const float* pa = parts.acc + (size_t)h * S * 128 + e;
-                float mn = -INFINITY;
-                for (int sp = 0; sp < S; ++sp) mn = fmaxf(mn, ml[sp * 2]);
-                float ll = 0.0f;
-                for (int sp = 0; sp < S; ++sp) {
-                    const float m = ml[sp * 2];
-                    const float cc = (m == -INFINITY) ? 0.0f : __expf(m - mn);
-                    const float4 a = *reinterpret_cast<const float4*>(pa + (size_t)sp * 128);
-                    v.x += a.x * cc; v.y += a.y * cc; v.z += a.z * cc; v.w += a.w * cc;
-                    ll += ml[sp * 2 + 1] * cc;
-                }
-                v.x /= ll; v.y /= ll; v.z /= ll; v.w /= ll;
-            }
-        } else if (k < K) {
-            v = *reinterpret_cast<const float4*>(X + k);
+            float mn = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < AH; ++i) mn = fmaxf(mn, pml[r][i].x);
+            const int S = parts.S, kc = min(k, K - 4);
+            const float* ml = parts.ml + (size_t)(kc >> 7) * S * 2;
+            const float* pa = parts.acc + (size_t)(kc >> 7) * S * 128 + (kc & 127);
+            for (int sp = AH; sp < S; ++sp) mn = fmaxf(mn, ml[sp * 2]);
+            float ll = 0.0f;
+            auto add = [&](float m, float l, const float4& a) {
+                const float cc = (m == -INFINITY) ? 0.0f : __expf(m - mn);
+                v.x += a.x * cc; v.y += a.y * cc; v.z += a.z * cc; v.w += a.w * cc;
+                ll += l * cc;
+            };
+#pragma unroll
+            for (int i = 0; i < AH; ++i)
+                if (i < S) add(pml[r][i].x, pml[r][i].y, pac[r][i]);
+            for (int sp = AH; sp < S; ++sp) add(ml[sp * 2], ml[sp * 2 + 1], *reinterpret_cast<const float4*>(pa + (size_t)sp * 128));
+            v.x /= ll; v.y /= ll; v.z /= ll; v.w /= ll;
+        } else {
+            v = xv[r];
             if (PRO == PRO_NORM) {
-                ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-                const WT* gp = gain + k;
-                v.x *= ld1(gp); v.y *= ld1(gp + 1); v.z *= ld1(gp + 2); v.w *= ld1(gp + 3);
+                if (k < K) ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+                const float4 g = gv[r].get();
+                v.x *= g.x; v.y *= g.y; v.z *= g.z; v.w *= g.w;
             }
         }
+        if (k >= K) v = make_float4(0.f, 0.f, 0.f, 0.f);
         // within each 512-float chunk the two halves of every lane's 8 values are stored 1 KiB
         // apart, so that both 16-byte LDS reads of a wave are contiguous across its lanes
         const int c = k >> 9, o = k & 511;
-        *reinterpret_cast<float4*>(xs + (c << 9) + ((o >> 2) & 1) * 256 + (o >> 3) * 4) = v;
+        if (c < CPR) *reinterpret_cast<float4*>(xs + (c << 9) + ((o >> 2) & 1) * 256 + (o >> 3) * 4) = v;
     }
     for (int i = tid; i < NW * NA * V; i += NW * 64) red[i] = 0.0f;
     if (PRO == PRO_NORM) {
@@ -481,11 +527,11 @@ __global__ __launch_bounds__(NW * 64) void gemv_flat_kernel(const WT* __restrict
 
 // Launch of the single-row kernel: blocks_per_cu blocks of NW waves per compute unit (fewer when
 // LDS or the matrix is too small for that: a wave should still get min_chunks chunks).
-template <typename WT, int NW, int U>
+template <typename WT, int NW, int U, int XR>
 static bool gemv_launch_flat(hipStream_t st, int pro, int epi, const WT* W, int N, int K, const float* X,
                              const WT* gain, float eps, float* Y, int blocks_per_cu, int min_chunks,
                              AttnParts parts = AttnParts{nullptr, nullptr, 0}) {
-    if (pro == PRO_SWIGLU || (K & 7) || K < 8) return false;
+    if (pro == PRO_SWIGLU || (K & 7) || K < 8 || K > XR * NW * 256) return false;
     if (pro == PRO_ATTN && (K & 127)) return false;
     const int NA = epi == EPI_SWIGLU ? 2 : 1;
     const int CPR = (K + 511) / 512;
@@ -509,17 +555,17 @@ static bool gemv_launch_flat(hipStream_t st, int pro, int epi, const WT* W, int 
     if (pro == P && epi == E) {                                                                              \
         static std::atomic<bool> raised{false};                                                              \
         if (!raised.load(std::memory_order_relaxed) && lds > 64 * 1024) {                                                                    \
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemv_flat_kernel<WT, NW, U, P, E>),      \
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemv_flat_kernel<WT, NW, U, XR, P, E>),      \
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGemvFullLds);        \
             raised.store(true, std::memory_order_relaxed);                                                                                 \
         }                                                                                                    \
         if (gemv_timing.start) {                                                                             \
-            hipExtLaunchKernelGGL((gemv_flat_kernel<WT, NW, U, P, E>), dim3(G), dim3(NW * 64), lds, st,      \
+            hipExtLaunchKernelGGL((gemv_flat_kernel<WT, NW, U, XR, P, E>), dim3(G), dim3(NW * 64), lds, st,      \
                                   gemv_timing.start, gemv_timing.stop, 0, W, N, K, X, gain, eps, Y, magic,   \
                                   parts);                                                                    \
             gemv_timing = GemvTiming{};                                                                      \
         } else {                                                                                             \
-            hipLaunchKernelGGL((gemv_flat_kernel<WT, NW, U, P, E>), dim3(G), dim3(NW * 64), lds, st, W, N,   \
+            hipLaunchKernelGGL((gemv_flat_kernel<WT, NW, U, XR, P, E>), dim3(G), dim3(NW * 64), lds, st, W, N,   \
                                K, X, gain, eps, Y, magic, parts);                                            \
         }                                                                                                    \
         return true;                                                                                         \
@@ -575,9 +621,14 @@ static void gemv_launch_mt(hipStream_t st, int pro, int epi, const WT* W, int N,
         // 100 MB and more are cut into more blocks than are resident, which evens out the tail.
         const size_t w_bytes = (size_t)pairs * N * K * sizeof(WT);
         if ((size_t)K * sizeof(float) > 40 * 1024)
-            done = gemv_launch_flat<WT, 16, 4>(st, pro, epi, W, N, K, X, gain, eps, Y, 1, 4);
-        else
-            done = gemv_launch_flat<WT, 8, 4>(st, pro, epi, W, N, K, X, gain, eps, Y, w_bytes >= (100u << 20) ? 3 : 2, 4);
+            done = K <= 20480 ? gemv_launch_flat<WT, 16, 4, 5>(st, pro, epi, W, N, K, X, gain, eps, Y, 1, 4)
+                              : gemv_launch_flat<WT, 16, 4, 8>(st, pro, epi, W, N, K, X, gain, eps, Y, 1, 4);
+        else {
+            const int per_cu = w_bytes >= (100u << 20) ? 3 : 2;
+            done = K <= 2048   ? gemv_launch_flat<WT, 8, 4, 1>(st, pro, epi, W, N, K, X, gain, eps, Y, per_cu, 4)
+                   : K <= 4096 ? gemv_launch_flat<WT, 8, 4, 2>(st, pro, epi, W, N, K, X, gain, eps, Y, per_cu, 4)
+                               : gemv_launch_flat<WT, 8, 4, 5>(st, pro, epi, W, N, K, X, gain, eps, Y, per_cu, 4);
+        }
     }
     if (!done && MT == 1) {
         int R = 8 / pairs;
@@ -609,10 +660,12 @@ static bool gemv_launch_attn(hipStream_t st, const WT* W, int N, int K, AttnPart
     if ((size_t)K * sizeof(float) > 40 * 1024) return false;
     // every block merges the whole row: one block per compute unit keeps that repeated work small
     if (K > 2048)
-        return gemv_launch_flat<WT, 16, 4>(st, PRO_ATTN, EPI_RESID, W, N, K, (const float*)nullptr, (const WT*)nullptr, 0.f,
-                                           Y, 1, 4, parts);
-    return gemv_launch_flat<WT, 8, 4>(st, PRO_ATTN, EPI_RESID, W, N, K, (const float*)nullptr, (const WT*)nullptr, 0.f, Y,
-                                      1, 4, parts);
+        return K <= 4096 ? gemv_launch_flat<WT, 16, 4, 1>(st, PRO_ATTN, EPI_RESID, W, N, K, (const float*)nullptr, (const WT*)nullptr, 0.f,
+                                                          Y, 1, 4, parts)
+                         : gemv_launch_flat<WT, 16, 4, 3>(st, PRO_ATTN, EPI_RESID, W, N, K, (const float*)nullptr, (const WT*)nullptr, 0.f,
+                                                          Y, 1, 4, parts);
+    return gemv_launch_flat<WT, 8, 4, 1>(st, PRO_ATTN, EPI_RESID, W, N, K, (const float*)nullptr, (const WT*)nullptr, 0.f, Y,
+                                         1, 4, parts);
 }
 
 // M <= 8
