@@ -70,6 +70,58 @@ __global__ __launch_bounds__(256) void sgemm_nt_kernel(const float* __restrict__
     }
 }
 
+// The same for products whose 64x64 tiles would leave most of the chip idle (the tiny configuration: 128 rows of 128..1024
+// columns are 4 to 32 of them): 32x32 tiles, 2x2 outputs per thread, K in blocks of 64 with the next block requested while the
+// present one is multiplied.  Those passes are bound by the latency of their K steps: 128 rows x 256 columns, K = 256 and 1024
+// in turn, 42 -> 27 us on average; 128 columns, K = 128 and 512, 23.0 -> 14.9.  Sums run over ascending k in both.
+template <int EPI>
+__global__ __launch_bounds__(256) void sgemm32_nt_kernel(const float* __restrict__ W, int N, int K,
+                                                         const float* __restrict__ X, int ldx,
+                                                         float* __restrict__ Y, int ldy, int M) {
+    constexpr int BK = 64;
+    __shared__ float As[BK][32 + 1];
+    __shared__ float Bs[BK][32 + 1];
+    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+    const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
+    // copies: 16 threads per row of 64 k, rows tid / 16 and tid / 16 + 16
+    const int row = tid >> 4, kq = (tid & 15) * 4;
+    const float* xa[2] = {X + (size_t)min(m0 + row, M - 1) * ldx + kq, X + (size_t)min(m0 + row + 16, M - 1) * ldx + kq};
+    const float* wb[2] = {W + (size_t)min(n0 + row, N - 1) * K + kq, W + (size_t)min(n0 + row + 16, N - 1) * K + kq};
+    float acc[2][2] = {};
+    float4 a[2], b[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) { a[i] = *reinterpret_cast<const float4*>(xa[i]); b[i] = *reinterpret_cast<const float4*>(wb[i]); }
+    for (int k0 = 0; k0 < K; k0 += BK) {                     // (K is a multiple of 64)
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int r = row + 16 * i;
+            As[kq][r] = a[i].x; As[kq + 1][r] = a[i].y; As[kq + 2][r] = a[i].z; As[kq + 3][r] = a[i].w;
+            Bs[kq][r] = b[i].x; Bs[kq + 1][r] = b[i].y; Bs[kq + 2][r] = b[i].z; Bs[kq + 3][r] = b[i].w;
+        }
+        __syncthreads();
+        const int kn = min(k0 + BK, K - BK);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) { a[i] = *reinterpret_cast<const float4*>(xa[i] + kn); b[i] = *reinterpret_cast<const float4*>(wb[i] + kn); }
+#pragma unroll 16
+        for (int k = 0; k < BK; ++k) {
+            const float x0 = As[k][ty * 2], x1 = As[k][ty * 2 + 1], w0 = Bs[k][tx * 2], w1 = Bs[k][tx * 2 + 1];
+            acc[0][0] += x0 * w0; acc[0][1] += x0 * w1;
+            acc[1][0] += x1 * w0; acc[1][1] += x1 * w1;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int m = m0 + ty * 2 + i, n = n0 + tx * 2 + j;
+            if (m < M && n < N) {
+                float* yp = Y + (size_t)m * ldy + n;
+                *yp = (EPI == EPI_RESID) ? (*yp + acc[i][j]) : acc[i][j];
+            }
+        }
+}
+
 // ---------------------------------------------------------------- bf16 MFMA, 2..64 rows, pre-split activations
 // The activations arrive as two bf16 matrices Xh + Xl = x (hi and lo halves, [MT*32][K]; rows beyond M
 // may hold anything: a row of x only ever meets its own row of the result).  A block of eight waves owns
@@ -794,6 +846,12 @@ static void gemm_launch(hipStream_t st, int epi, const float* W, int N, int K, c
     (void)part; (void)part_floats;
     if (M <= 8) { gemv_launch<float>(st, PRO_NONE, epi, W, N, K, X, ldx, nullptr, 0.f, Y, ldy, M); return; }
     const dim3 grid((N + 63) / 64, (M + 63) / 64), block(256);
+    if (grid.x * grid.y < 256) {                             // fewer 64x64 tiles than compute units: see sgemm32_nt_kernel
+        const dim3 grid32((N + 31) / 32, (M + 31) / 32);
+        if (epi == EPI_RESID) hipLaunchKernelGGL((sgemm32_nt_kernel<EPI_RESID>), grid32, block, 0, st, W, N, K, X, ldx, Y, ldy, M);
+        else                  hipLaunchKernelGGL((sgemm32_nt_kernel<EPI_STORE>), grid32, block, 0, st, W, N, K, X, ldx, Y, ldy, M);
+        return;
+    }
     if (epi == EPI_RESID) hipLaunchKernelGGL((sgemm_nt_kernel<EPI_RESID>), grid, block, 0, st, W, N, K, X, ldx, Y, ldy, M);
     else                  hipLaunchKernelGGL((sgemm_nt_kernel<EPI_STORE>), grid, block, 0, st, W, N, K, X, ldx, Y, ldy, M);
 }
