@@ -157,6 +157,26 @@ template <> struct Raw8<float> {
     }
 };
 
+// Sums of V values per lane over the wave: lane l returns sum l * V / 64.  Each step halves the values a lane carries, so V sums
+// take V - 1 + log2(64 / V) exchanges instead of 6 V; the order of the additions is wave_sum's.
+template <int V>
+__device__ __forceinline__ float wave_sums(float (&v)[V]) {
+    static_assert(V >= 1 && V <= 64 && (V & (V - 1)) == 0, "a power of two");
+    const int lane = threadIdx.x & 63;
+    int off = 32;
+#pragma unroll
+    for (int n = V / 2; n >= 1; n >>= 1, off >>= 1) {
+        const bool up = lane & off;
+#pragma unroll
+        for (int j = 0; j < n; ++j) {
+            const float keep = up ? v[j + n] : v[j], send = up ? v[j] : v[j + n];
+            v[j] = keep + __shfl_xor(send, off, RSD_WAVE);
+        }
+    }
+    for (; off >= 1; off >>= 1) v[0] += __shfl_xor(v[0], off, RSD_WAVE);
+    return v[0];
+}
+
 // Variant for activations that fit LDS whole (MT * K floats).  The block stages
 // (and transforms) x once.  Each WAVE then owns row groups (R rows, or R gate/up
 // row pairs) and walks them with its 64 lanes spread along K, 1 KiB per row and
@@ -197,6 +217,16 @@ __global__ __launch_bounds__(256) void gemv_full_kernel(const WT* __restrict__ W
             }
         }
     };
+    // Finished sums: V = MT * R of them per wave, spread over the lanes by wave_sums (one store, and for EPI_RESID one load, for
+    // all of them instead of one after the other); lane q * 64 / V holds sum q = m * R + r.  The old value is requested with
+    // the first weights of its row group.
+    constexpr int V = MT * R, VS = 64 / V;
+    const int out_m = lane / VS / R, out_r = lane / VS % R;
+    const bool out_lane = lane % VS == 0 && out_m < M;
+    auto out_ptr = [&](int g) { return Y + (size_t)out_m * ldy + (rg0 + g * rg_stride) * R + out_r; };
+    auto has_out = [&](int g) { return out_lane && g < my_groups && (rg0 + g * rg_stride) * R + out_r < N; };
+    float old = 0.0f;
+    if (EPI == EPI_RESID && has_out(0)) old = *out_ptr(0);
     Raw8<WT> cur[U][NR], nxt[U][NR];
     if (total > 0) fetch(0, 0, cur);
 
@@ -231,9 +261,6 @@ __global__ __launch_bounds__(256) void gemv_full_kernel(const WT* __restrict__ W
         }
     }
     __syncthreads();
-    float rs[MT];
-#pragma unroll
-    for (int m = 0; m < MT; ++m) rs[m] = PRO == PRO_NORM ? red_rs[m] : 1.0f;
 
     float acc[NA][MT][R];
 #pragma unroll
@@ -268,21 +295,20 @@ __global__ __launch_bounds__(256) void gemv_full_kernel(const WT* __restrict__ W
             }
         }
         if (i == iters - 1) {
-            const int n0 = (rg0 + g * rg_stride) * R;
+            float v[V], u[V];
 #pragma unroll
-            for (int m = 0; m < MT; ++m)
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    float v = wave_sum(acc[0][m][r]) * rs[m];
-                    float u = (EPI == EPI_SWIGLU) ? wave_sum(acc[NA - 1][m][r]) * rs[m] : 0.0f;
-                    acc[0][m][r] = 0.0f;
-                    acc[NA - 1][m][r] = 0.0f;
-                    if (lane == 0 && m < M && n0 + r < N) {
-                        float* yp = Y + (size_t)m * ldy + n0 + r;
-                        if (EPI == EPI_SWIGLU) *yp = v / (1.0f + expf(-v)) * u;
-                        else *yp = (EPI == EPI_RESID) ? (*yp + v) : v;
-                    }
-                }
+            for (int q = 0; q < V; ++q) {
+                v[q] = acc[0][q / R][q % R];
+                u[q] = acc[NA - 1][q / R][q % R];
+                acc[0][q / R][q % R] = acc[NA - 1][q / R][q % R] = 0.0f;
+            }
+            float s0 = wave_sums<V>(v), s1 = (EPI == EPI_SWIGLU) ? wave_sums<V>(u) : 0.0f;
+            if (PRO == PRO_NORM) { const float r1 = red_rs[out_m]; s0 *= r1; s1 *= r1; }
+            if (has_out(g)) {
+                if (EPI == EPI_SWIGLU) *out_ptr(g) = s0 / (1.0f + expf(-s0)) * s1;
+                else *out_ptr(g) = (EPI == EPI_RESID) ? old + s0 : s0;
+            }
+            if (EPI == EPI_RESID && has_out(g + 1)) old = *out_ptr(g + 1);
         }
     };
     // the two register buffers take turns (a copy between them would have to wait for the load)
@@ -652,7 +678,9 @@ static void gemv_launch_mt(hipStream_t st, int pro, int epi, const WT* W, int N,
         else done = U >= 8 ? gemv_launch_full<WT, MT, 1, 8>(st, pro, epi, W, N, K, X, ldx, gain, eps, Y, ldy, M)
                            : gemv_launch_full<WT, MT, 1, 4>(st, pro, epi, W, N, K, X, ldx, gain, eps, Y, ldy, M);
     } else if (!done) {
-        if (pairs == 2) done = gemv_launch_full<WT, MT, 2, 1>(st, pro, epi, W, N, K, X, ldx, gain, eps, Y, ldy, M);
+        // (a product of fewer rows than the chip has waves to spread them over takes one row per wave, with U KiB of it at once)
+        if (N < 4096) done = gemv_launch_full<WT, MT, 1, 4>(st, pro, epi, W, N, K, X, ldx, gain, eps, Y, ldy, M);
+        else if (pairs == 2) done = gemv_launch_full<WT, MT, 2, 1>(st, pro, epi, W, N, K, X, ldx, gain, eps, Y, ldy, M);
         else done = gemv_launch_full<WT, MT, 4, 1>(st, pro, epi, W, N, K, X, ldx, gain, eps, Y, ldy, M);
     }
     if (!done) gemv_launch_chunked<WT, MT, 4>(st, pro, epi, W, N, K, X, ldx, gain, eps, Y, ldy, M);
