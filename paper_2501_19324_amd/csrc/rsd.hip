@@ -482,9 +482,12 @@ template <typename WT>
 bool rows_path(const Model& m, int M) {
     return std::is_same<WT, bf16_t>::value && M >= 2 && m.s.d_model % 64 == 0 && m.q_dim % 64 == 0 && m.s.d_ffn % 64 == 0;
 }
+// threads of a kernel that gives a thread four columns of a row and one block a row
+int row_threads(int K) { return std::min(1024, ceil_div(K / 4, 64) * 64); }
 // x (fp32 rows, optionally through RMSNorm with `gain`) -> the hi / lo halves
 void rows_split(rsd_ctx* c, const float* X, int ldx, int M, int K, const bf16_t* gain, float eps) {
-    hipLaunchKernelGGL((split_rows_kernel<bf16_t>), dim3(M), dim3(256), 0, c->st, X, ldx, K, gain, eps, c->xs_h, c->xs_l);
+    hipLaunchKernelGGL((split_rows_kernel<bf16_t, false>), dim3(M), dim3(row_threads(K)), 0, c->st, const_cast<float*>(X), ldx, K, gain, eps,
+                       c->xs_h, c->xs_l, (const bf16_t*)nullptr, (const int*)nullptr, 0, RowMap{});
 }
 template <int EPI>
 void rows_finish(rsd_ctx* c, int ks, int rows, int M, int N, float* Y, int ldy, const SkGeom& geo) {
@@ -575,17 +578,29 @@ void rows_split(rsd_ctx*, const float*, int, int, int, const float*, float) {}  
 void rows_gemm(rsd_ctx*, const Model&, int, int, const float*, int, int, int, float*, int, const float* = nullptr, float = 0.f,
                QkvParts* = nullptr) {}
 
+template <typename KT, int HD, bool PARTS>
+void launch_rope_kv(rsd_ctx* c, const Model& m, int M, const RowMap& rm, KT* pool_l, const QkvParts& qp) {
+    // a thread per item (four pairs of q or k, four elements of v), in as few rounds as 1024 threads allow
+    const int items = (m.s.n_heads + m.s.n_kv_heads) * (HD / 8) + m.s.n_kv_heads * (HD / 4), rounds = ceil_div(items, 1024);
+    const int threads = ceil_div(ceil_div(items, rounds), 64) * 64;
+    hipLaunchKernelGGL((rope_kv_kernel<KT, HD, PARTS>), dim3(M), dim3(threads), 0, c->st, c->qkv, m.n_qkv, pool_l, m.bt_dev, m.max_pages, rm,
+                       m.rope, m.s.n_heads, m.s.n_kv_heads, qp);
+}
 template <typename WT>
 void run_layers(rsd_ctx* c, Model& m, int M, const RowMap& rm, bool decode) {
     hipStream_t st = c->st;
     const int d = m.s.d_model, F = m.s.d_ffn;
     const float eps = m.s.rms_eps;
     c->xin_h = c->xin_l = nullptr;          // (a redirection is only ever meant for the projection right after its producer)
-    hipLaunchKernelGGL((embed_kernel<WT>), dim3(M), dim3(256), 0, st, wptr<WT>(m, m.off_embed), d, c->ds.tokens,
-                       c->p.max_ctx, rm, c->h);
+    const bool rows = rows_path<WT>(m, M);
+    if (rows)   // the gather also leaves RMSNorm(h) for the first layer
+        hipLaunchKernelGGL((split_rows_kernel<WT, true>), dim3(M), dim3(row_threads(d)), 0, st, c->h, d, d, wptr<WT>(m, m.layers[0].attn_norm),
+                           eps, c->xs_h, c->xs_l, wptr<WT>(m, m.off_embed), c->ds.tokens, c->p.max_ctx, rm);
+    else
+        hipLaunchKernelGGL((embed_kernel<WT>), dim3(M), dim3(256), 0, st, wptr<WT>(m, m.off_embed), d, c->ds.tokens,
+                           c->p.max_ctx, rm, c->h);
     const int S = decode ? m.splits : 1;
     c->cur_phase = decode ? RSD_PROBE_DECODE : RSD_PROBE_PREFILL;
-    const bool rows = rows_path<WT>(m, M);
     const bool fused = M <= 8 && !rows;   // few rows: norm / SwiGLU / residual folded into the weight-streaming kernels
     const bool rows_fuse_norm = rows;                        // the residual GEMMs leave RMSNorm(h) for the next projection
     // the attention kernels over bf16 caches (or their merge kernel) write the output as hi / lo halves themselves
@@ -602,11 +617,11 @@ void run_layers(rsd_ctx* c, Model& m, int M, const RowMap& rm, bool decode) {
             gemv_launch<WT>(st, PRO_NORM, EPI_STORE, wptr<WT>(m, o.wqkv), m.n_qkv, d, c->h, d,
                             wptr<WT>(m, o.attn_norm), eps, c->qkv, m.n_qkv, M);
         } else if (rows) {
-            // (after the first layer the halves of RMSNorm(h) come from the previous layer's last finish)
-            if (l == 0 || !rows_fuse_norm) rows_split(c, c->h, d, M, d, wptr<WT>(m, o.attn_norm), eps);
-            // (the batched decode attention over a bf16 cache adds the projection's K slices itself)
+            // (the halves of RMSNorm(h) come from the gather, after the first layer from the previous layer's last finish)
+            // (the batched decode attention over a bf16 cache and the cache write of a chunked pass add the projection's K
+            // slices themselves)
             rows_gemm(c, m, 0, EPI_STORE, wptr<WT>(m, o.wqkv), m.n_qkv, d, M, c->qkv, m.n_qkv, nullptr, 0.f,
-                      att_halves && decode ? &qkv_parts : nullptr);
+                      att_halves && (decode || M > 128 || !stream_bn(m.n_qkv)) ? &qkv_parts : nullptr);
         } else if constexpr (std::is_same<WT, float>::value) {
             hipLaunchKernelGGL((rmsnorm_kernel<WT>), dim3(M), dim3(256), 0, st, c->h, d, wptr<WT>(m, o.attn_norm), eps, c->xn);
             gemm_launch(st, EPI_STORE, wptr<WT>(m, o.wqkv), m.n_qkv, d, c->xn, d, c->qkv, m.n_qkv, M, c->part_k, c->part_k_floats);
@@ -618,13 +633,12 @@ void run_layers(rsd_ctx* c, Model& m, int M, const RowMap& rm, bool decode) {
             else if (m.hd == 128) launch_attn_decode<WT, 128>(c, m, l, M, which);
             else launch_attn_decode<WT, 32>(c, m, l, M, which);
         } else if (m.hd == 128) {
-            hipLaunchKernelGGL((rope_kv_kernel<WT, 128>), dim3(M), dim3(256), 0, st, c->qkv, m.n_qkv, pool_l, m.bt_dev,
-                               m.max_pages, rm, m.rope, m.s.n_heads, m.s.n_kv_heads);
+            if (qkv_parts.ks > 0) launch_rope_kv<WT, 128, true>(c, m, M, rm, pool_l, qkv_parts);
+            else launch_rope_kv<WT, 128, false>(c, m, M, rm, pool_l, qkv_parts);
             if (m.s.dtype == RSD_BF16) launch_attn_prefill_mfma(c, m, l, rm, att_halves);
             else launch_attn_g<WT, 128>(c, m, l, M, rm, S);
         } else {
-            hipLaunchKernelGGL((rope_kv_kernel<WT, 32>), dim3(M), dim3(256), 0, st, c->qkv, m.n_qkv, pool_l, m.bt_dev,
-                               m.max_pages, rm, m.rope, m.s.n_heads, m.s.n_kv_heads);
+            launch_rope_kv<WT, 32, false>(c, m, M, rm, pool_l, qkv_parts);
             launch_attn_g<WT, 32>(c, m, l, M, rm, S);
         }
         if (fused) {

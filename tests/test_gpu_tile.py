@@ -85,3 +85,16 @@ def test_unsliced_gate_up_and_head(rows, ffn):
     ref = O.lm_logits(m, O.forward_full(m, [int(t) for t in toks[0]], "bf16"))
     assert np.max(np.abs(out - ref)) < TOL / 4           # (logits of rms 0.2)
     R.rsd_destroy(ctx)
+
+
+def test_rows_wider_than_a_block():
+    """d_model above 8192 (the gather with its norm, and the split of attention rows, walk on beyond what a block keeps in
+    registers): two-row passes against single-row ones, which gather and normalise in other kernels."""
+    from rsd_inputs import ModelShape
+    R, ctx = build(ModelShape(1, 8448, 66, 11, 128, 97), 97, 40)
+    toks = np.random.default_rng(3).integers(0, 97, size=(1, 40)).astype(np.int32)
+    lens = np.array([40], np.int32)
+    one = R.rsd_forward(ctx, 0, toks, lens, 1)
+    for chunk in (2, 40):
+        assert float((R.rsd_forward(ctx, 0, toks, lens, chunk) - one).abs().max()) < TOL
+    R.rsd_destroy(ctx)
