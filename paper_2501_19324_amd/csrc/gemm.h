@@ -622,22 +622,24 @@ __device__ __forceinline__ void store_halves(uint16_t* __restrict__ h, uint16_t*
 
 // fp32 rows -> hi + lo bf16 rows, optionally through RMSNorm (gain != nullptr).  One block per row.  EMBED: the rows are token
 // embeddings gathered here and also left in X (one launch instead of two at the start of a pass; rows without a token
-// are skipped).  Bound by latency: a row of up to 8192 is requested once, whole and with its gains, and kept in registers.
-// 7B, 32 rows: gather and split 3.8 + 5.0 us in two launches, 4.6 in one.
+// are skipped).  A row is requested once, whole and with its gains, and kept in registers: few rows are bound by latency (four
+// columns per thread; 7B, 32 rows: gather and split 3.8 + 5.0 us in two launches, 4.6 in one), many by traffic (sixteen columns
+// per thread, small blocks; 6001 rows: split 33.6 -> 28 us, gather and split 67 -> 47).
 template <typename WT, bool EMBED>
 __global__ __launch_bounds__(1024) void split_rows_kernel(float* __restrict__ X, int ldx, int K, const WT* __restrict__ gain, float eps,
                                                           uint16_t* __restrict__ Xh, uint16_t* __restrict__ Xl,
                                                           const WT* __restrict__ E, const int* __restrict__ tokens, int max_ctx,
                                                           RowMap rm) {
     __shared__ float red[16];
-    const int tid = threadIdx.x;
+    constexpr int NI = 4;
+    const int tid = threadIdx.x, step = blockDim.x * 4;
     float* xr = X + (size_t)blockIdx.x * ldx;
     uint16_t* xh = Xh + (size_t)blockIdx.x * K;
     uint16_t* xl = Xl + (size_t)blockIdx.x * K;
-    Raw4<WT> gv[2];
+    Raw4<WT> gv[NI];
     if (gain) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) gv[i].load(gain + min(tid * 4 + i * 4096, K - 4));
+        for (int i = 0; i < NI; ++i) if (i * step < K) gv[i].load(gain + min(tid * 4 + i * step, K - 4));
     }
     const WT* er = nullptr;
     if (EMBED) {
@@ -651,16 +653,16 @@ __global__ __launch_bounds__(1024) void split_rows_kernel(float* __restrict__ X,
         e.load(er + k);
         return e.get();
     };
-    float4 v[2];
+    float4 v[NI];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) v[i] = load(min(tid * 4 + i * 4096, K - 4));
+    for (int i = 0; i < NI; ++i) if (i * step < K) v[i] = load(min(tid * 4 + i * step, K - 4));
     float rs = 1.0f;
     if (gain) {
         float ss = 0.0f;
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-            if (tid * 4 + i * 4096 < K) ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
-        for (int k = tid * 4 + 8192; k < K; k += 4096) {
+        for (int i = 0; i < NI; ++i)
+            if (tid * 4 + i * step < K) ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
+        for (int k = tid * 4 + NI * step; k < K; k += step) {
             const float4 w = load(k);
             ss += w.x * w.x + w.y * w.y + w.z * w.z + w.w * w.w;
         }
@@ -680,11 +682,11 @@ __global__ __launch_bounds__(1024) void split_rows_kernel(float* __restrict__ X,
         store_halves(xh + k, xl + k, x);
     };
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int k = tid * 4 + i * 4096;
+    for (int i = 0; i < NI; ++i) {
+        const int k = tid * 4 + i * step;
         if (k < K) finish(k, v[i], gv[i]);
     }
-    for (int k = tid * 4 + 8192; k < K; k += 4096) {
+    for (int k = tid * 4 + NI * step; k < K; k += step) {
         Raw4<WT> g;
         if (gain) g.load(gain + k);
         finish(k, load(k), g);

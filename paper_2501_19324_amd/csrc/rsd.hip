@@ -482,11 +482,11 @@ template <typename WT>
 bool rows_path(const Model& m, int M) {
     return std::is_same<WT, bf16_t>::value && M >= 2 && m.s.d_model % 64 == 0 && m.q_dim % 64 == 0 && m.s.d_ffn % 64 == 0;
 }
-// threads of a kernel that gives a thread four columns of a row and one block a row
-int row_threads(int K) { return std::min(1024, ceil_div(K / 4, 64) * 64); }
+// threads of split_rows_kernel, one block per row: four columns each, or sixteen when the rows alone fill the chip
+int row_threads(int K, int M) { return std::min(1024, ceil_div(K / (M > 256 ? 16 : 4), 64) * 64); }
 // x (fp32 rows, optionally through RMSNorm with `gain`) -> the hi / lo halves
 void rows_split(rsd_ctx* c, const float* X, int ldx, int M, int K, const bf16_t* gain, float eps) {
-    hipLaunchKernelGGL((split_rows_kernel<bf16_t, false>), dim3(M), dim3(row_threads(K)), 0, c->st, const_cast<float*>(X), ldx, K, gain, eps,
+    hipLaunchKernelGGL((split_rows_kernel<bf16_t, false>), dim3(M), dim3(row_threads(K, M)), 0, c->st, const_cast<float*>(X), ldx, K, gain, eps,
                        c->xs_h, c->xs_l, (const bf16_t*)nullptr, (const int*)nullptr, 0, RowMap{});
 }
 template <int EPI>
@@ -594,7 +594,7 @@ void run_layers(rsd_ctx* c, Model& m, int M, const RowMap& rm, bool decode) {
     c->xin_h = c->xin_l = nullptr;          // (a redirection is only ever meant for the projection right after its producer)
     const bool rows = rows_path<WT>(m, M);
     if (rows)   // the gather also leaves RMSNorm(h) for the first layer
-        hipLaunchKernelGGL((split_rows_kernel<WT, true>), dim3(M), dim3(row_threads(d)), 0, st, c->h, d, d, wptr<WT>(m, m.layers[0].attn_norm),
+        hipLaunchKernelGGL((split_rows_kernel<WT, true>), dim3(M), dim3(row_threads(d, M)), 0, st, c->h, d, d, wptr<WT>(m, m.layers[0].attn_norm),
                            eps, c->xs_h, c->xs_l, wptr<WT>(m, m.off_embed), c->ds.tokens, c->p.max_ctx, rm);
     else
         hipLaunchKernelGGL((embed_kernel<WT>), dim3(M), dim3(256), 0, st, wptr<WT>(m, m.off_embed), d, c->ds.tokens,

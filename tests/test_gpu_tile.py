@@ -88,10 +88,11 @@ def test_unsliced_gate_up_and_head(rows, ffn):
 
 
 def test_rows_wider_than_a_block():
-    """d_model above 8192 (the gather with its norm, and the split of attention rows, walk on beyond what a block keeps in
-    registers): two-row passes against single-row ones, which gather and normalise in other kernels."""
+    """d_model beyond what a block of 1024 threads covers in two rounds (16896 = 4.1 rounds: the gather with its norm and the
+    splits walk on beyond what a block keeps in registers): few-row passes against single-row ones, which gather and normalise
+    in other kernels."""
     from rsd_inputs import ModelShape
-    R, ctx = build(ModelShape(1, 8448, 66, 11, 128, 97), 97, 40)
+    R, ctx = build(ModelShape(1, 16896, 132, 22, 128, 97), 97, 40)
     toks = np.random.default_rng(3).integers(0, 97, size=(1, 40)).astype(np.int32)
     lens = np.array([40], np.int32)
     one = R.rsd_forward(ctx, 0, toks, lens, 1)
