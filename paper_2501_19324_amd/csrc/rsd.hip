@@ -114,7 +114,7 @@ struct rsd_ctx {
     float* part_k = nullptr;         // K-slice partial sums of few-row GEMMs
     uint16_t *xs_h = nullptr, *xs_l = nullptr;   // [rows][widest K]: hi / lo bf16 halves of the activations of the MFMA GEMMs
     size_t part_k_floats = 0;
-    // sampler workspace (per row: block maxima, histograms of the three radix levels, block masses, selections)
+    // sampler workspace (per row: block maxima, histogram and key lists, span masses, selections)
     int smp_rows = 0;
     float* smp_pmax = nullptr; int* smp_pidx = nullptr;
     u64_t *smp_hist = nullptr, *smp_psum = nullptr, *smp_sel = nullptr;
