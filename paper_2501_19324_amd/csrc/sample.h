@@ -411,21 +411,18 @@ __global__ __launch_bounds__(SMP_T) void sample_finish_kernel(SampleArgs a, Appe
         const u64_t pincl = block256_incl_scan_u64(pv, wtot);
         const u64_t zs = wtot[0] + wtot[1] + wtot[2] + wtot[3];
         const u64_t target = (u64_t)floor((double)uu * (double)zs);      // running > u * Z  <=>  running > floor(u * Z)
-        if (tid == 0) { s_blk = -1; s_tok = -1; s_base = 0; sel[5] = tau; sel[6] = target; }
+        if (tid == 0) { s_blk = -1; s_tok = -1; sel[5] = tau; sel[6] = target; }
         __syncthreads();
         if (tid < SMP_NB && pincl > target && pincl - pv <= target) { s_blk = tid; s_base = pincl - pv; }
         __syncthreads();
-        // if rounding of u * Z left no crossing, the draw is the last member: of the last span with a mass
+        // if rounding of u * Z left no crossing, the draw is the last member: of the last span with a mass.  Every thread finds
+        // it for itself (writing it to s_blk / s_base would race with the waves that still read these)
         int blk = s_blk;
         u64_t base = s_base;
         if (blk < 0) {
-            if (tid == 0) {
-                u64_t run = 0; int last = 0;
-                for (int b = 0; b < SMP_NB; ++b) { const u64_t v = s_mass[b]; if (v) { last = b; s_base = run; } run += v; }
-                s_blk = last;
-            }
-            __syncthreads();
-            blk = s_blk; base = s_base;
+            u64_t run = 0;
+            blk = 0; base = 0;
+            for (int b = 0; b < SMP_NB; ++b) { const u64_t v = s_mass[b]; if (v) { blk = b; base = run; } run += v; }
         }
         // every thread takes a run of consecutive tokens of the span; the one whose run holds the crossing walks it
         const int s0 = min(blk * span, a.V), s1 = min(a.V, s0 + span);

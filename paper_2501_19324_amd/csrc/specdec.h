@@ -130,13 +130,9 @@ __global__ __launch_bounds__(SMP_T) void sd_residual_draw_kernel(SdVerifyArgs a,
     int blk = s_blk;
     u64_t base = s_base;
     if (blk < 0) {                                         // u * total rounded up to the total: the last block with mass
-        if (tid == 0) {
-            u64_t run = 0; int last = 0;
-            for (int b = 0; b < SMP_NB; ++b) { const u64_t v = a.rpart[(size_t)s * SMP_NB + b]; if (v) { last = b; s_base = run; } run += v; }
-            s_blk = last;
-        }
-        __syncthreads();
-        blk = s_blk; base = s_base;
+        u64_t run = 0;                                     // (found by every thread: s_blk / s_base may still be read by other waves)
+        blk = 0; base = 0;
+        for (int b = 0; b < SMP_NB; ++b) { const u64_t v = a.rpart[(size_t)s * SMP_NB + b]; if (v) { blk = b; base = run; } run += v; }
     }
     float mp, mq; uint32_t tp, tq; u64_t zp, zq;
     const int rp = r0 + at, rq = s * a.k + at;

@@ -53,3 +53,17 @@ def test_draws_lie_where_the_distribution_puts_them(kind, n, V, T, top_p):
             c = np.cumsum(m)
             ok |= c[t] - m[t] - 1e-6 * c[-1] <= u[i] * c[-1] <= c[t] + 1e-6 * c[-1]
         assert ok, (kind, i, t)
+
+
+@pytest.mark.parametrize("kind", ["normal", "flat", "masked"])
+@pytest.mark.parametrize("n,V", [(1, 151936), (20, 20011), (5, 37)])
+def test_a_uniform_of_one_draws_the_last_member(kind, n, V):
+    """u = 1 leaves no span in which the running mass exceeds u times the total: the draw is the nucleus's last token (top_p 1:
+    the last one with a mass), the same on every call."""
+    import torch
+    from paper_2501_19324_amd import binding as R
+    lg = logits_of(kind, n, V, np.random.default_rng(V + n)).astype(np.float32)
+    want = [np.nonzero(x.astype(np.float64) - x.max() > np.log(2.0 ** -40) + 1e-6)[0][-1] for x in lg]
+    dev, u = torch.from_numpy(lg).cuda(), torch.ones(n, device="cuda")
+    for _ in range(20):
+        assert list(R.rsd_sample_static(dev, u, 1.0, 1.0).cpu().numpy()) == want

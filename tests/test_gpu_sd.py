@@ -286,6 +286,31 @@ def test_sampled_verification_rule_alone(gpu):
     s.close()
 
 
+def test_verification_rule_with_uniforms_of_one(gpu):
+    """u_accept = u_new = 1: a proposal is refused unless p > q there, and the replacement, for which no running mass exceeds
+    u times the total, is the last token of the residual max(p - q, 0)."""
+    from oracle import rsd_oracle as O
+    from rsd_inputs import workload
+    R, torch = gpu["R"], gpu["torch"]
+    w = workload("cfg0", temperature=1.0, top_p=1.0)
+    s = gpu["Session"](w, sd_k=1)
+    V, n = w.draft.vocab, w.batch
+    rng = np.random.default_rng(5)
+    p = rng.normal(size=(n, 2, V)).astype(np.float32)
+    q = rng.normal(size=(n, 1, V)).astype(np.float32)
+    for c in range(n):                                   # the last tokens: clearly more likely under the draft, so outside the residual
+        q[c, 0, V - 3 - c:] = p[c, 0, V - 3 - c:] + 6.0
+    P = [[O.token_distribution(p[c, i].astype(np.float64), 1.0, 1.0) for i in range(2)] for c in range(n)]
+    Q = [O.token_distribution(q[c, 0].astype(np.float64), 1.0, 1.0) for c in range(n)]
+    prop = np.array([[int(np.argmin(P[c][0] - Q[c]))] for c in range(n)], np.int32)
+    want = [int(np.nonzero(P[c][0] - Q[c] > 1e-9)[0][-1]) for c in range(n)]
+    dev = lambda a: torch.from_numpy(a).cuda()
+    for _ in range(20):
+        em, kept = R.rsd_sd_verify(s.ctx, dev(p), dev(q), dev(prop), np.ones(n, np.int32), torch.ones(n, 2, device="cuda"), torch.ones(n, 2, device="cuda"))
+        assert list(kept) == [0] * n and list(em[:, 0]) == want
+    s.close()
+
+
 # ------------------------------------------------------------------ bf16, under a teacher
 def _bf16_setup(gpu, batch, sd_k, check, **kw):
     import test_gpu_bf16 as T
