@@ -461,6 +461,9 @@ __global__ __launch_bounds__(SMP_T) void sample_finish_kernel(SampleArgs a, Appe
         token = s_tok;
     }
     if (tid != 0) return;
+    // a row without any finite logit (or with an infinite one) has no arg max and no member to draw: token 0, never an id outside
+    // the vocabulary, which the next pass would look up in the embedding
+    if (token < 0 || token >= a.V) token = 0;
     if (a.out) a.out[row] = token;
     if (!ap.enabled) return;
     // append the token and decide whether the step of this sequence goes on

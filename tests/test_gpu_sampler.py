@@ -67,3 +67,21 @@ def test_a_uniform_of_one_draws_the_last_member(kind, n, V):
     dev, u = torch.from_numpy(lg).cuda(), torch.ones(n, device="cuda")
     for _ in range(20):
         assert list(R.rsd_sample_static(dev, u, 1.0, 1.0).cpu().numpy()) == want
+
+
+@pytest.mark.parametrize("V", [37, 20011])
+@pytest.mark.parametrize("T,top_p", [(0.0, 1.0), (1.0, 0.9), (1.0, 1.0)])
+def test_rows_without_a_finite_mass_give_ids_of_the_vocabulary(V, T, top_p):
+    """All -inf, all NaN, one +inf (its exponential is NaN, all others are 0), all +inf, NaN beside -inf: there is nothing right to
+    draw, but an engine looks the id up in the embedding.  A row with finite logits in the same call is drawn as usual."""
+    import torch
+    from paper_2501_19324_amd import binding as R
+    lg = np.full((6, V), -np.inf, np.float32)
+    lg[1] = np.nan
+    lg[2] = 0.0; lg[2, V - 1] = np.inf
+    lg[3] = np.inf
+    lg[4, ::2] = np.nan
+    lg[5] = -5.0; lg[5, V // 2] = 40.0
+    u = torch.full((6,), 0.5, device="cuda")
+    out = R.rsd_sample_static(torch.from_numpy(lg).cuda(), u, T, top_p).cpu().numpy()
+    assert out.min() >= 0 and out.max() < V and out[5] == V // 2
