@@ -399,9 +399,9 @@ int rsd_probe_attention(rsd_ctx *c, int32_t model, const int32_t *ctx_len_host, 
 
 /* rsd_sample for callers that cannot allocate device memory: code recording a HIP graph, tight serving
  * loops, harnesses that forbid hipMalloc.  Same choice rule and arguments as rsd_sample (dev logits [n][vocab]
- * fp32, dev uniforms [n], dev out [n]), but no context: the sampler's workspace (block maxima, radix
- * histograms, block masses; about 49 KiB per row) is a device array built into the library, which every GPU
- * the library runs on holds until the process ends (RSD_SAMPLE_STATIC_MAX_ROWS rows, 3.1 MiB).  The call
+ * fp32, dev uniforms [n], dev out [n]), but no context: the sampler's workspace (span maxima, histogram
+ * and key lists, span masses; about 75 KiB per row) is a device array built into the library, which every GPU
+ * the library runs on holds until the process ends (RSD_SAMPLE_STATIC_MAX_ROWS rows, 4.7 MiB).  The call
  * allocates and frees nothing and does not synchronise: the kernels are enqueued on hip_stream (a
  * hipStream_t, NULL: the default stream) and out_dev is valid once that stream has reached them.
  * n > RSD_SAMPLE_STATIC_MAX_ROWS, n < 1, vocab < 1, NULL logits/out, sampling without uniforms or a bad

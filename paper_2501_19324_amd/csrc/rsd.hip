@@ -114,7 +114,7 @@ struct rsd_ctx {
     float* part_k = nullptr;         // K-slice partial sums of few-row GEMMs
     uint16_t *xs_h = nullptr, *xs_l = nullptr;   // [rows][widest K]: hi / lo bf16 halves of the activations of the MFMA GEMMs
     size_t part_k_floats = 0;
-    // sampler workspace (per row: block maxima, histogram and key lists, span masses, selections)
+    // sampler workspace (per row: span maxima, histogram and key lists, span masses, selections)
     int smp_rows = 0;
     float* smp_pmax = nullptr; int* smp_pidx = nullptr;
     u64_t *smp_hist = nullptr, *smp_psum = nullptr, *smp_sel = nullptr;
@@ -1367,10 +1367,10 @@ int rsd_init(rsd_ctx** out, const rsd_model_shape shape[3], const rsd_weights w[
     c->smp_rows = std::max(B, 64);
     HIPCHK(c, dev_alloc(&c->smp_pmax, (size_t)c->smp_rows * SMP_NB));
     HIPCHK(c, dev_alloc(&c->smp_pidx, (size_t)c->smp_rows * SMP_NB));
-    HIPCHK(c, dev_alloc(&c->smp_hist, (size_t)c->smp_rows * 3 * SMP_BINS));
+    HIPCHK(c, dev_alloc(&c->smp_hist, (size_t)c->smp_rows * SMP_WS));
     HIPCHK(c, dev_alloc(&c->smp_psum, (size_t)c->smp_rows * SMP_NB));
     HIPCHK(c, dev_alloc(&c->smp_sel, (size_t)c->smp_rows * 8));
-    HIPCHK(c, hipMemsetAsync(c->smp_hist, 0, (size_t)c->smp_rows * 3 * SMP_BINS * sizeof(u64_t), c->st));
+    HIPCHK(c, hipMemsetAsync(c->smp_hist, 0, (size_t)c->smp_rows * SMP_WS * sizeof(u64_t), c->st));
     HIPCHK(c, hipMemsetAsync(c->smp_sel, 0, (size_t)c->smp_rows * 8 * sizeof(u64_t), c->st));
     HIPCHK(c, dev_alloc(&c->hl, (size_t)B * d));
     HIPCHK(c, dev_alloc(&c->xl, (size_t)B * d));
@@ -1393,10 +1393,10 @@ int rsd_init(rsd_ctx** out, const rsd_model_shape shape[3], const rsd_weights w[
                 auto& ws = c->sd_ws[i];
                 HIPCHK(c, dev_alloc(&ws.pmax, n * SMP_NB));
                 HIPCHK(c, dev_alloc(&ws.pidx, n * SMP_NB));
-                HIPCHK(c, dev_alloc(&ws.hist, n * 3 * SMP_BINS));
+                HIPCHK(c, dev_alloc(&ws.hist, n * SMP_WS));
                 HIPCHK(c, dev_alloc(&ws.psum, n * SMP_NB));
                 HIPCHK(c, dev_alloc(&ws.sel, n * 8));
-                HIPCHK(c, hipMemsetAsync(ws.hist, 0, n * 3 * SMP_BINS * sizeof(u64_t), c->st));
+                HIPCHK(c, hipMemsetAsync(ws.hist, 0, n * SMP_WS * sizeof(u64_t), c->st));
                 HIPCHK(c, hipMemsetAsync(ws.sel, 0, n * 8 * sizeof(u64_t), c->st));
             }
             HIPCHK(c, dev_alloc(&c->sd_aux_dev, rows + 2 * qrows));

@@ -10,18 +10,21 @@
 // No sort: tau is found by selection over the bit patterns of the non-negative floats e_t.  Masses are summed as
 // 64-bit fixed point (e * 2^40), so every sum is exact, order-independent and reproducible from run to run, whatever
 // the path to tau.  A row is cut into SMP_NB spans of the vocabulary; the phases are separate launches:
-//   A  max of every span (or arg max: greedy); clears the histogram
-//   B  histogram of masses over 2048 bins of 1/64 octave (exponent and six mantissa bits, down to 2^-32)
+//   A  max of every span (or arg max: greedy); clears what B and C add to
+//   B  histogram of masses over 1792 bins of 1/32 and 1/64 octave (exponent and five or six mantissa bits, 2^-40 .. 1)
 //   C  every block finds the bin tau lies in, sums what lies above it per span and lists the keys inside it (a bin is
-//      1 % wide: a few keys per span; at most SMP_LIST are kept)
-//   D  one block per row resolves tau among the listed keys (9 + 8 bits), forms the nucleus mass of every span, locates
+//      1 or 2 % wide: mostly a few hundred keys)
+//   D  one block per row resolves tau among the listed keys (10 + 9 bits), forms the nucleus mass of every span, locates
 //      the draw and appends the token to its sequence.
 // So the logits are read three times and everything after C works on a few hundred keys.  (Three radix levels over the
 // whole row and a fifth pass for the masses, with a 2048-bin histogram cleared and flushed for every 2400 tokens, took
-// 115 us on 64 rows of 151936 logits and 35 on one; this takes 62 and 25.  What bounds it: a division and an exponential
-// per token and pass on many rows - about 10 of the 23 and 17 us of B and C -, the chain of block scans in D on few.)
-// Where a span holds more keys of the bin than its list, or tau lies below 2^-32, block D selects over the whole row by
-// itself: slow but rare, it takes thousands of nearly equal logits or a nucleus that leaves less than 4e-5 of the mass out.
+// 109 us on 64 rows of 151936 logits and 36 on one; this takes 52 and 22.  What bounds it: a division and an exponential
+// per token and pass on many rows - about 10 of the 19 and 18 us of B and C -, the chain of block scans in D on few.)
+// A bin that may hold more keys than there is room for (nearly equal logits; the bin's mass tells in advance) makes the row
+// "dense": C then adds up sub-bins of 256 keys instead of listing, and D is SMP_FB blocks, which count the keys of the deciding
+// sub-bin span by span; the last of them to finish resolves tau from these counts and goes on alone.  A call on 64 rows
+// of 151936 equal logits takes 115 us (1055 when the one block of D searched the row by itself, 190 with the three radix levels), on
+// one row 58 (650, 57); 16 rows of a few tied values 71 (668, 67).
 // top_p >= 1 needs no selection: the nucleus is every token whose mass is not zero, e >= 2^-40.
 #pragma once
 #include "common.h"
@@ -29,12 +32,22 @@
 
 typedef unsigned long long u64_t;
 
-constexpr int SMP_NB = 64;      // blocks per row
+constexpr int SMP_NB = 64;      // spans a row is cut into
 constexpr int SMP_T = 256;      // threads per block
-constexpr int SMP_BINS = 2048;  // histogram bins of a row (its workspace: three times as many entries, two thirds hold the lists)
-constexpr int SMP_LIST = 2 * SMP_BINS * 2 / SMP_NB;       // keys of the deciding bin kept per span (128)
-constexpr int SMP_BIN0 = (0x3F800000 >> 17) - (SMP_BINS - 1);   // key >> 17 of bin 0; the last bin holds e = 1
 constexpr uint32_t SMP_UNIT = 0x2B800000u;                // key of 2^-40, the smallest e with a mass
+// histogram bins of a row: 32 per octave (2^18 keys each) from 2^-40 to 2^-16, behind these (from bin SMP_FINE on) 64 per octave to 1;
+// e = 1 itself joins the last one
+constexpr int SMP_FINE = 768, SMP_BINS = 1792, SMP_BIN0 = (int)(SMP_UNIT >> 18);
+static_assert((0x3F800000 >> 17) - 2 * SMP_BIN0 - SMP_FINE == SMP_BINS && (SMP_UNIT & 0x3FFFFu) == 0, "");
+// Workspace of a row, u64 entries: the histogram, behind it the lists of keys (u32: span << 19 | key - first key of the bin), one for
+// every span and one for what these have no room for.  Dense rows: sub-bins of 256 keys at the end, and, when the histogram has
+// been read, counts [span][256] (u32) at the front.
+constexpr int SMP_SUB = 1280;                             // sub-bins: 2^18 / 256, one for e = 1, rounded up to whole threads
+constexpr int SMP_WS = SMP_NB * 256 / 2 + SMP_SUB;
+constexpr int SMP_LIST = 128;                             // words of a span's list
+constexpr int SMP_DENSE = (SMP_WS - SMP_BINS) * 2 - SMP_NB * SMP_LIST;   // of the shared one: a bin that may hold more keys makes the row dense
+static_assert(SMP_DENSE > 0 && SMP_BINS + SMP_SUB <= SMP_WS, "");
+constexpr int SMP_FB = SMP_NB / 4;                        // blocks of phase D of a dense row: a span per wave
 
 __device__ __forceinline__ u64_t shfl_up_u64(u64_t v, int d) {
     const unsigned lo = __shfl_up((unsigned)v, d, RSD_WAVE), hi = __shfl_up((unsigned)(v >> 32), d, RSD_WAVE);
@@ -80,7 +93,8 @@ struct SampleArgs {
     int sep_id; float sep_bias;                          // logit[sep_id] += sep_bias before anything else
     const int* active;                                   // nullable: rows with active[r] == 0 are skipped
     int* out;                                            // nullable when the result is appended
-    // workspace, per row: pmax[SMP_NB], pidx[SMP_NB], hist[3][SMP_BINS], psum[SMP_NB], sel[8]
+    // workspace, per row: pmax[SMP_NB], pidx[SMP_NB], hist[SMP_WS], psum[SMP_NB] and sel[8]: [0] mass the nucleus must reach, [1] mass
+    // above the deciding bin, [2] that bin (-1: none), [3] keys in the shared list, [4] dense, [5] tau, [6] point of the draw, [7] blocks done
     float* pmax; int* pidx; u64_t* hist; u64_t* psum; u64_t* sel;
     // nullable: packed rows.  Row r then stands for sequence row_seq[r] (< 0: unused row); u, u_index, active and
     // the appended state are indexed by the sequence, logits, out and the workspace by the row
@@ -138,7 +152,23 @@ __device__ __forceinline__ int smp_find_bin(const u64_t* hist, u64_t thr, u64_t&
     return *s_bin;
 }
 
-__device__ __forceinline__ int smp_bin(uint32_t key) { return min(max((int)(key >> 17) - SMP_BIN0, 0), SMP_BINS - 1); }
+// bin of the key of an e with a mass
+__device__ __forceinline__ int smp_bin(uint32_t key) {      // (2 i - SMP_FINE overtakes i at i = SMP_FINE)
+    return min(max((int)(key >> 18) - SMP_BIN0, (int)(key >> 17) - 2 * SMP_BIN0 - SMP_FINE), SMP_BINS - 1);
+}
+// keys of a bin: [smp_lo, smp_hi)
+__device__ __forceinline__ uint32_t smp_lo(int bin) {
+    return bin < SMP_FINE ? (uint32_t)(bin + SMP_BIN0) << 18 : (uint32_t)(bin + SMP_FINE + 2 * SMP_BIN0) << 17;
+}
+__device__ __forceinline__ uint32_t smp_hi(int bin) { return bin == SMP_BINS - 1 ? 0x3F800001u : smp_lo(bin + 1); }
+// Adds m to *p for every active lane, where lanes often agree on the key (tied logits): one addition for those that agree with
+// the first
+template <typename M>
+__device__ __forceinline__ void smp_add_tied(M* p, uint32_t key, M m) {
+    const u64_t same = __ballot(key == (uint32_t)__builtin_amdgcn_readfirstlane((int)key));
+    if (!((same >> (threadIdx.x & 63)) & 1)) atomicAdd(p, m);
+    else if ((int)(threadIdx.x & 63) == __builtin_ctzll(same)) atomicAdd(p, m * (M)__popcll(same));
+}
 // span of block blockIdx.x: with WPS = 4 waves per span the block's only one, with WPS = 1 one per wave; thread tid of
 // smp_span_threads() works on it
 template <int WPS> __device__ __forceinline__ int smp_span() { return WPS == 4 ? blockIdx.x : blockIdx.x * 4 + (threadIdx.x >> 6); }
@@ -156,7 +186,12 @@ __global__ __launch_bounds__(SMP_T) void sample_max_kernel(SampleArgs a) {
     const float* lg = a.logits + (size_t)row * a.ld;
     const int span = (a.V + SMP_NB - 1) / SMP_NB, s0 = min(j * span, a.V), s1 = min(a.V, s0 + span);
     constexpr int T = WPS * 64, U = SMP_U<WPS>;
-    if (a.temperature != 0.0f && tid < SMP_BINS / SMP_NB) a.hist[(size_t)row * 3 * SMP_BINS + j * (SMP_BINS / SMP_NB) + tid] = 0;   // for phase B
+    if (a.temperature != 0.0f) {                           // for phases B and C
+        constexpr int NH = SMP_BINS / SMP_NB, NS = SMP_SUB / SMP_NB;
+        u64_t* hist = a.hist + (size_t)row * SMP_WS;
+        if (tid < NH + NS) hist[tid < NH ? j * NH + tid : SMP_WS - SMP_SUB + j * NS + tid - NH] = 0;
+        if (tid == 0 && j == 0) { a.sel[(size_t)row * 8 + 3] = 0; a.sel[(size_t)row * 8 + 7] = 0; }
+    }
     float bv = -INFINITY; int bi = 0x7FFFFFFF;
     for (int i0 = s0 + tid; i0 < s1; i0 += T * U) {
         float v[U];
@@ -199,7 +234,7 @@ __global__ __launch_bounds__(SMP_T) void sample_hist_kernel(SampleArgs a) {
     const int span = (a.V + SMP_NB - 1) / SMP_NB, s0 = min(j * span, a.V), s1 = min(a.V, s0 + span);
     __shared__ u64_t lh[SMP_BINS];
     __shared__ float fred[4];
-    u64_t* hist = a.hist + (size_t)row * 3 * SMP_BINS;
+    u64_t* hist = a.hist + (size_t)row * SMP_WS;
     for (int b = threadIdx.x; b < SMP_BINS; b += SMP_T) lh[b] = 0;
     const float mx = smp_row_max(a, row, fred);           // (holds a barrier)
     constexpr int T = WPS * 64, U = SMP_U<WPS>;
@@ -219,21 +254,23 @@ __global__ __launch_bounds__(SMP_T) void sample_hist_kernel(SampleArgs a) {
         if (lh[b]) atomicAdd(&hist[b], lh[b]);
 }
 
-// ---- phase C: the bin in which the mass reaches top_p of the total; per span the mass above it and the keys inside it
+// ---- phase C: the bin in which the mass reaches top_p of the total; per span the mass above it, and the keys inside it (dense
+// rows: their masses by sub-bin)
 template <int WPS>
 __global__ __launch_bounds__(SMP_T) void sample_select_kernel(SampleArgs a) {
     const int row = blockIdx.y, j = smp_span<WPS>(), tid = smp_lane<WPS>(), wave = threadIdx.x >> 6;
     if (smp_seq(a, row) < 0) return;
     const float* lg = a.logits + (size_t)row * a.ld;
     const int span = (a.V + SMP_NB - 1) / SMP_NB, s0 = min(j * span, a.V), s1 = min(a.V, s0 + span);
+    __shared__ u64_t lds[SMP_SUB];                        // dense rows: the sub-bins
     __shared__ u64_t wtot[4];
     __shared__ float fred[4];
     __shared__ int s_bin, s_cnt[4];
-    __shared__ u64_t s_above;
-    u64_t* hist = a.hist + (size_t)row * 3 * SMP_BINS;
+    __shared__ u64_t s_above, s_mass;
+    u64_t* hist = a.hist + (size_t)row * SMP_WS;
     u64_t* sel = a.sel + (size_t)row * 8;
     const float mx = smp_row_max(a, row, fred);
-    if (threadIdx.x == 0) { s_bin = 0; s_above = 0; }
+    if (threadIdx.x == 0) { s_bin = 0; s_above = 0; s_mass = 0; }
     if (threadIdx.x < 4) s_cnt[threadIdx.x] = 0;
     // (every block repeats the deterministic search)
     constexpr int P = SMP_BINS / SMP_T;
@@ -249,38 +286,57 @@ __global__ __launch_bounds__(SMP_T) void sample_select_kernel(SampleArgs a) {
     u64_t run = incl - loc;
 #pragma unroll
     for (int i = 0; i < P; ++i) {
-        if (run < thr && run + h[i] >= thr) { s_bin = top - i; s_above = run; }
+        if (run < thr && run + h[i] >= thr) { s_bin = top - i; s_above = run; s_mass = h[i]; }
         run += h[i];
     }
     __syncthreads();
     const int bin = thr == z ? -1 : s_bin;                // -1: the nucleus is every token with a mass
     // keys below lo are outside, from hi on inside the nucleus; those between are listed
-    const uint32_t lo = bin < 0 ? SMP_UNIT : bin == 0 ? 0u : (uint32_t)(bin + SMP_BIN0) << 17;
-    const uint32_t hi = bin < 0 ? SMP_UNIT : bin == SMP_BINS - 1 ? 0xFFFFFFFFu : (uint32_t)(bin + 1 + SMP_BIN0) << 17;
-    if (blockIdx.x == 0 && threadIdx.x == 0) { sel[0] = thr; sel[1] = s_above; sel[2] = (u64_t)(long long)bin; }
-    uint32_t* list = reinterpret_cast<uint32_t*>(hist + SMP_BINS) + (size_t)j * SMP_LIST;
+    const uint32_t lo = bin < 0 ? SMP_UNIT : smp_lo(bin), hi = bin < 0 ? SMP_UNIT : smp_hi(bin);
+    // no key of the bin has less than the mass of lo, which bounds their number: those of a row that is not dense fit the shared list
+    const bool dense = bin >= 0 && s_mass > SMP_DENSE * smp_fix(__uint_as_float(lo));
+    if (blockIdx.x == 0 && threadIdx.x == 0) { sel[0] = thr; sel[1] = s_above; sel[2] = (u64_t)(long long)bin; sel[4] = dense; }
+    if (dense) {
+        for (int b = threadIdx.x; b < SMP_SUB; b += SMP_T) lds[b] = 0;
+        __syncthreads();
+    }
+    uint32_t* lists = reinterpret_cast<uint32_t*>(hist + SMP_BINS);
+    uint32_t* list = lists + j * SMP_LIST;
     int* cnt = &s_cnt[WPS == 4 ? 0 : wave];
     u64_t acc = 0;
-    constexpr int T = WPS * 64, U = SMP_U<WPS>;
-    for (int i0 = s0 + tid; i0 < s1; i0 += T * U) {
-        float x[U];
+    constexpr int T = WPS * 64, U = WPS == 4 ? SMP_U<4> : 6;        // (eight spill)
+    auto scan = [&](auto inside) {
+        for (int i0 = s0 + tid; i0 < s1; i0 += T * U) {
+            float x[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) x[u] = smp_x(a, lg, min(i0 + u * T, s1 - 1));
+            for (int u = 0; u < U; ++u) x[u] = smp_x(a, lg, min(i0 + u * T, s1 - 1));
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const float e = expf(x[u] - mx);
-            const uint32_t key = __float_as_uint(e);
-            if (i0 + u * T < s1) {
-                if (key >= hi) acc += smp_fix(e);
-                else if (key >= lo) {
-                    const int at = atomicAdd(cnt, 1);
-                    if (at < SMP_LIST) list[at] = key;
+            for (int u = 0; u < U; ++u) {
+                const float e = expf(x[u] - mx);
+                const uint32_t key = __float_as_uint(e);
+                if (i0 + u * T < s1) {
+                    if (key >= hi) acc += smp_fix(e);
+                    else if (key >= lo) inside(key);
                 }
             }
         }
-    }
+    };
+    if (dense)
+        scan([&](uint32_t key) { smp_add_tied(&lds[(key - lo) >> 8], key, smp_fix(__uint_as_float(key))); });
+    else
+        scan([&](uint32_t key) {
+            const uint32_t w = ((uint32_t)j << 19) | (key - lo);
+            const int at = atomicAdd(cnt, 1);
+            if (at < SMP_LIST) list[at] = w;
+            else lists[SMP_NB * SMP_LIST + atomicAdd(reinterpret_cast<unsigned*>(sel + 3), 1u)] = w;
+        });
     acc = wave_sum_u64(acc);
     __syncthreads();
+    if (dense) {                                          // (the masses of the spans are added up in phase D)
+        for (int b = threadIdx.x; b < SMP_SUB; b += SMP_T)
+            if (lds[b]) atomicAdd(&hist[SMP_WS - SMP_SUB + b], lds[b]);
+        return;
+    }
     if (WPS == 4) {
         if ((tid & 63) == 0) wtot[wave] = acc;
         __syncthreads();
@@ -288,38 +344,96 @@ __global__ __launch_bounds__(SMP_T) void sample_select_kernel(SampleArgs a) {
     }
     if (tid == 0) {
         a.psum[(size_t)row * SMP_NB + j] = acc;
-        a.pidx[(size_t)row * SMP_NB + j] = *cnt;
+        a.pidx[(size_t)row * SMP_NB + j] = min(*cnt, SMP_LIST);
     }
 }
 
-// tau among the keys of [lo, hi) by three radix levels over the whole row, when the lists do not hold them; `need`: the
-// mass the nucleus still takes from this range.  Whole block calls; lh: SMP_BINS entries of LDS
-__device__ uint32_t smp_select_row(const SampleArgs& a, const float* lg, float mx, uint32_t lo, uint32_t hi, u64_t need, u64_t* lh,
-                                   u64_t* wtot, int* s_bin, u64_t* s_above) {
-    const int tid = threadIdx.x;
-    uint32_t prefix = 0;
-    u64_t above = 0;
-    for (int shift = 20; shift >= 0; shift -= 10) {       // keys < 2^31: 11, 10 and 10 bits
-        for (int b = tid; b < SMP_BINS; b += SMP_T) lh[b] = 0;
-        if (tid == 0) { *s_bin = 0; *s_above = above; }
-        __syncthreads();
-        for (int i = tid; i < a.V; i += SMP_T) {
-            const float e = expf(smp_x(a, lg, i) - mx);
+// First part of phase D of a dense row, SMP_FB blocks: every wave counts the keys of the deciding sub-bin in its span and adds up
+// what lies above.  Returns true in the block that is the last to finish, which then holds tau and the mass of every span
+// (s_mass).  Whole block calls; lh: 512 entries of LDS, s_flag: one int
+__device__ bool smp_dense(const SampleArgs& a, int row, float mx, u64_t* lh, u64_t* wtot, int* s_flag, u64_t* s_above, u64_t* s_mass, uint32_t& tau) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const float* lg = a.logits + (size_t)row * a.ld;
+    u64_t* hist = a.hist + (size_t)row * SMP_WS;
+    u64_t* sel = a.sel + (size_t)row * 8;
+    u64_t* counts = hist;                                  // [span][128]: two keys each
+    const u64_t thr = sel[0];
+    u64_t run = sel[1];
+    if (tid == 0) { *s_flag = 0; *s_above = run; }
+    const int sub = smp_find_bin<SMP_SUB / SMP_T>(hist + SMP_WS - SMP_SUB, thr, run, wtot, s_flag, s_above);
+    const uint32_t lo = smp_lo((int)(long long)sel[2]) + ((uint32_t)sub << 8), hi = lo + 256;
+    uint32_t* cnt = reinterpret_cast<uint32_t*>(lh) + wave * 256;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) cnt[lane + 64 * i] = 0;
+    __syncthreads();                                       // (also: s_flag has been read)
+    const int span = (a.V + SMP_NB - 1) / SMP_NB, j = blockIdx.y * 4 + wave, s0 = min(j * span, a.V), s1 = min(a.V, s0 + span);
+    u64_t acc = 0;
+    for (int i0 = s0; i0 < s1; i0 += 64 * 8) {
+        float x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = smp_x(a, lg, min(i0 + lane + u * 64, s1 - 1));
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const float e = expf(x[u] - mx);
             const uint32_t key = __float_as_uint(e);
-            if (key >= lo && key < hi && (shift == 20 || key >> (shift + 10) == prefix)) {
-                const u64_t f = smp_fix(e);
-                if (f) atomicAdd(&lh[shift == 20 ? min(key >> 20, (uint32_t)(SMP_BINS - 1)) : (key >> shift) & 0x3FFu], f);
+            if (i0 + lane + u * 64 < s1) {
+                if (key >= hi) acc += smp_fix(e);
+                else if (key >= lo) smp_add_tied(&cnt[key - lo], key, 1u);
             }
         }
-        __syncthreads();
-        const int bin = smp_find_bin<8>(lh, need, above, wtot, s_bin, s_above);
-        prefix = (shift == 20 ? 0u : prefix << 10) | (uint32_t)bin;
-        __syncthreads();
     }
-    return prefix;
+    acc = wave_sum_u64(acc);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // Counts and masses go past the L2 of this XCD (agent-scope stores), each wave waits until its own have arrived and the
+    // barrier until all have, so the block that then finds itself the last one may read everybody's, past its L2 too.  (Fences
+    // at device scope write back and invalidate the whole L2 of the XCD: 110 us for this kernel on 64 rows.)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int v = lane + 64 * i;
+        __hip_atomic_store(&counts[j * 128 + v], ((u64_t)cnt[v * 2 + 1] << 32) | cnt[v * 2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (lane == 0) __hip_atomic_store(&a.psum[(size_t)row * SMP_NB + j], acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) *s_flag = __hip_atomic_fetch_add(reinterpret_cast<unsigned*>(sel + 7), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == SMP_FB - 1;
+    __syncthreads();
+    if (!*s_flag) return false;
+    auto from_all = [](const u64_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    // key lo + v stands for (number of them) x (its mass); every thread adds up 32 of the 64 spans of two keys
+    lh[tid] = 0;
+    if (tid < SMP_NB) s_mass[tid] = from_all(&a.psum[(size_t)row * SMP_NB + tid]);
+    auto mass = [&](int v, u64_t c) { return c * smp_fix(__uint_as_float(lo + v)); };
+    __syncthreads();
+    const int pair = tid & 127;
+    u64_t c0 = 0, c1 = 0;
+#pragma unroll
+    for (int q = 0; q < SMP_NB / 2; ++q) {
+        const u64_t c = from_all(&counts[(2 * q + (tid >> 7)) * 128 + pair]);
+        c0 += (uint32_t)c; c1 += c >> 32;
+    }
+    if (c0) atomicAdd(&lh[pair * 2], mass(pair * 2, c0));
+    if (c1) atomicAdd(&lh[pair * 2 + 1], mass(pair * 2 + 1, c1));
+    if (tid == 0) { *s_flag = 0; *s_above = run; }
+    __syncthreads();
+    const int low = smp_find_bin<1>(lh, thr, run, wtot, s_flag, s_above);
+    tau = lo + low;
+    u64_t m = 0;                                           // four threads per span
+#pragma unroll
+    for (int q = 0; q < 32; ++q) {
+        const int v = 2 * (4 * q + (tid & 3));
+        const u64_t c = from_all(&counts[(tid >> 2) * 128 + v / 2]);
+        if (v >= low) m += mass(v, (uint32_t)c);
+        if (v + 1 >= low) m += mass(v + 1, c >> 32);
+    }
+    m += shfl_xor_u64(m, 1);
+    m += shfl_xor_u64(m, 2);
+    if ((tid & 3) == 0) s_mass[tid >> 2] += m;
+    return true;
 }
 
-// ---- phase D: one block per row: tau, the nucleus mass of every span, the token; appends it
+// ---- phase D: one block per row (dense rows: SMP_FB of which one goes on): tau, the nucleus mass of every span, the token;
+// appends it
 __global__ __launch_bounds__(SMP_T) void sample_finish_kernel(SampleArgs a, AppendArgs ap) {
     const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int seq = smp_seq(a, row);
@@ -344,65 +458,71 @@ __global__ __launch_bounds__(SMP_T) void sample_finish_kernel(SampleArgs a, Appe
         __syncthreads();
         token = s_tok;
     } else {
-        const float* lg = a.logits + (size_t)row * a.ld;
-        u64_t* hist = a.hist + (size_t)row * 3 * SMP_BINS;
         u64_t* sel = a.sel + (size_t)row * 8;
-        __shared__ u64_t lh[SMP_BINS];
+        const float* lg = a.logits + (size_t)row * a.ld;
+        const u64_t* hist = a.hist + (size_t)row * SMP_WS;
+        __shared__ u64_t lh[768 + 512];
         __shared__ u64_t s_mass[SMP_NB];
-        const float uu = a.u[(size_t)seq * a.u_stride + (a.u_index ? a.u_index[seq] : 0)];
-        const u64_t thr = sel[0], above = sel[1];
-        const int bin = (int)(long long)sel[2];
-        const int span = (a.V + SMP_NB - 1) / SMP_NB;
-        // four threads per span hold its keys of the bin
-        const int my_span = tid >> 2, n_list = a.pidx[(size_t)row * SMP_NB + my_span];
-        const uint32_t* list = reinterpret_cast<const uint32_t*>(hist + SMP_BINS) + (size_t)my_span * SMP_LIST;
-        constexpr int NK = 4;                                  // the first 16 keys of a span (mostly all) are requested at once and kept
+        // what a row that is not dense needs is requested together with the word that says so: four threads per span hold the keys
+        // of its list; the first 16 (mostly all) are kept
+        constexpr int NK = 4;
+        const uint32_t* lists = reinterpret_cast<const uint32_t*>(hist + SMP_BINS);
+        const uint32_t* list = lists + (tid >> 2) * SMP_LIST;
+        int n_list = 0;
         uint32_t kept[NK];
+        u64_t mass_above = 0;
+        if (blockIdx.y == 0) {
+            n_list = a.pidx[(size_t)row * SMP_NB + (tid >> 2)];
 #pragma unroll
-        for (int i = 0; i < NK; ++i) kept[i] = list[(tid & 3) + 4 * i];
-        auto each_key = [&](auto f) {
-#pragma unroll
-            for (int i = 0; i < NK; ++i) if ((tid & 3) + 4 * i < n_list) f(kept[i]);
-            for (int i = (tid & 3) + 4 * NK; i < n_list; i += 4) f(list[i]);
-        };
-        if (tid < SMP_NB) s_mass[tid] = a.psum[(size_t)row * SMP_NB + tid];
-        const float mx = smp_row_max(a, row, fred);
+            for (int i = 0; i < NK; ++i) kept[i] = list[(tid & 3) + 4 * i];
+            mass_above = a.psum[(size_t)row * SMP_NB + (tid & (SMP_NB - 1))];
+        }
+        const u64_t thr = sel[0], above = sel[1];
+        const int bin = (int)(long long)sel[2], n_over = (int)sel[3];
+        const bool dense = sel[4] != 0;
+        if (!dense && blockIdx.y > 0) return;
+        const float uu = a.u[(size_t)seq * a.u_stride + (a.u_index ? a.u_index[seq] : 0)];
+        const int span = (a.V + SMP_NB - 1) / SMP_NB;
         uint32_t tau = SMP_UNIT;
-        if (bin >= 0) {
-            const bool whole = __syncthreads_or(n_list > SMP_LIST) || bin == 0;
-            if (!whole) {
-                u64_t run = above;
-                // bits 8..16, then 0..7 of the keys; their upper bits are the bin
-                for (int b = tid; b < 512 + 256; b += SMP_T) lh[b] = 0;
-                if (tid == 0) { s_bin = 0; s_above = run; }
-                __syncthreads();
-                each_key([&](uint32_t k) { atomicAdd(&lh[(k >> 8) & 0x1FFu], smp_fix(__uint_as_float(k))); });
-                __syncthreads();
-                const uint32_t up = (uint32_t)smp_find_bin<2>(lh, thr, run, wtot, &s_bin, &s_above);
-                __syncthreads();
-                each_key([&](uint32_t k) { if (((k >> 8) & 0x1FFu) == up) atomicAdd(&lh[512 + (k & 0xFFu)], smp_fix(__uint_as_float(k))); });
-                __syncthreads();
-                const uint32_t low = (uint32_t)smp_find_bin<1>(lh + 512, thr, run, wtot, &s_bin, &s_above);
-                tau = ((uint32_t)(bin + SMP_BIN0) << 17) | (up << 8) | low;
-                u64_t m = 0;
-                each_key([&](uint32_t k) { if (k >= tau) m += smp_fix(__uint_as_float(k)); });
-                m += shfl_xor_u64(m, 1);
-                m += shfl_xor_u64(m, 2);
-                if ((tid & 3) == 0) s_mass[my_span] += m;
-            } else {
-                const uint32_t lo = bin == 0 ? 0u : (uint32_t)(bin + SMP_BIN0) << 17;
-                const uint32_t hi = bin == SMP_BINS - 1 ? 0xFFFFFFFFu : (uint32_t)(bin + 1 + SMP_BIN0) << 17;
-                tau = smp_select_row(a, lg, mx, lo, hi, thr - above, lh, wtot, &s_bin, &s_above);
-                for (int j = wave; j < SMP_NB; j += 4) {
-                    const int s0 = min(j * span, a.V), s1 = min(a.V, s0 + span);
-                    u64_t m = 0;
-                    for (int i = s0 + lane; i < s1; i += 64) {
-                        const float e = expf(smp_x(a, lg, i) - mx);
-                        if (__float_as_uint(e) >= tau) m += smp_fix(e);
-                    }
-                    m = wave_sum_u64(m);
-                    if (lane == 0) s_mass[j] = m;
+        float mx;
+        if (dense) {
+            mx = smp_row_max(a, row, fred);
+            if (!smp_dense(a, row, mx, lh, wtot, &s_bin, &s_above, s_mass, tau)) return;
+        } else {
+            auto rest = [&](const uint32_t* p, int i0, int step, int n, auto f) {
+                for (; i0 < n; i0 += step * NK) {
+                    uint32_t w[NK];
+#pragma unroll
+                    for (int i = 0; i < NK; ++i) w[i] = p[min(i0 + step * i, n - 1)];
+#pragma unroll
+                    for (int i = 0; i < NK; ++i) if (i0 + step * i < n) f(w[i]);
                 }
+            };
+            auto each_key = [&](auto f) {
+#pragma unroll
+                for (int i = 0; i < NK; ++i) if ((tid & 3) + 4 * i < n_list) f(kept[i]);
+                rest(list, (tid & 3) + 4 * NK, 4, n_list, f);
+                rest(lists + SMP_NB * SMP_LIST, tid, SMP_T, n_over, f);
+            };
+            if (tid < SMP_NB) s_mass[tid] = mass_above;
+            for (int b = tid; b < 768 + 512; b += SMP_T) lh[b] = 0;
+            if (tid == 0) { s_bin = 0; s_above = above; }
+            mx = smp_row_max(a, row, fred);                // (holds a barrier)
+            if (bin >= 0) {
+                const uint32_t lo = smp_lo(bin);
+                auto off = [](uint32_t w) { return w & 0x7FFFFu; };
+                auto mass = [&](uint32_t w) { return smp_fix(__uint_as_float(lo + off(w))); };
+                u64_t run = above;
+                // bits 9..18, then 0..8 of the keys' distance from the bin's first
+                each_key([&](uint32_t w) { atomicAdd(&lh[off(w) >> 9], mass(w)); });
+                __syncthreads();
+                const uint32_t up = (uint32_t)smp_find_bin<3>(lh, thr, run, wtot, &s_bin, &s_above);
+                __syncthreads();
+                each_key([&](uint32_t w) { if (off(w) >> 9 == up) atomicAdd(&lh[768 + (off(w) & 0x1FFu)], mass(w)); });
+                __syncthreads();
+                const uint32_t rel = (up << 9) | (uint32_t)smp_find_bin<2>(lh + 768, thr, run, wtot, &s_bin, &s_above);
+                tau = lo + rel;
+                each_key([&](uint32_t w) { if (off(w) >= rel) atomicAdd(&s_mass[w >> 19], mass(w)); });
             }
         }
         __syncthreads();
@@ -515,5 +635,5 @@ static void sample_launch_spans(hipStream_t st, const SampleArgs& a, int rows) {
 static void sample_launch(hipStream_t st, const SampleArgs& a, const AppendArgs& ap, int rows) {
     if (rows < 16) sample_launch_spans<4>(st, a, rows);
     else sample_launch_spans<1>(st, a, rows);
-    hipLaunchKernelGGL(sample_finish_kernel, dim3(rows), dim3(SMP_T), 0, st, a, ap);
+    hipLaunchKernelGGL(sample_finish_kernel, dim3(rows, a.temperature == 0.0f ? 1 : SMP_FB), dim3(SMP_T), 0, st, a, ap);
 }

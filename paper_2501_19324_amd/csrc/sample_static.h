@@ -10,7 +10,7 @@
 // never uses the array's name as a pointer, only the address looked up once per device.
 namespace {
 
-constexpr size_t kSmpHist = (size_t)RSD_SAMPLE_STATIC_MAX_ROWS * 3 * SMP_BINS;      // u64 each
+constexpr size_t kSmpHist = (size_t)RSD_SAMPLE_STATIC_MAX_ROWS * SMP_WS;      // u64 each
 constexpr size_t kSmpPsum = (size_t)RSD_SAMPLE_STATIC_MAX_ROWS * SMP_NB;            // u64
 constexpr size_t kSmpSel = (size_t)RSD_SAMPLE_STATIC_MAX_ROWS * 8;                  // u64
 constexpr size_t kSmpPmax = (size_t)RSD_SAMPLE_STATIC_MAX_ROWS * SMP_NB;            // float
