@@ -622,8 +622,11 @@ __global__ __launch_bounds__(SMP_T) void sample_finish_kernel(SampleArgs a, Appe
     }
 }
 
-// Few rows: a span per block of four waves, to have many blocks.  From 16 rows on a span per wave: a block then works on
-// four spans, which spreads the cost of its histogram (clearing and flushing 2048 bins) over 9500 tokens instead of 2400.
+// Few rows of a large vocabulary: a span per block of four waves, to have many blocks.  Otherwise a span per wave: a block then works
+// on four spans, which spreads the cost of its histogram (clearing and flushing 1792 bins) over four times as many tokens.  The
+// line: us of the four launches, span per block / per wave: 151936 tokens, 16 rows 32.7 / 33.8, 24 rows 38.1 / 36.8; 100000, 8 rows 25.5 /
+// 28.2, 15 rows 31.2 / 29.4; 50257, 4 rows 20.9 / 21.9, 8 rows 22.9 / 22.6; 32000, 1 row 19.0 / 19.4, 4 rows 20.4 / 19.6; 16384, 1 row
+// 18.5 / 18.3, 15 rows 24.9 / 20.1.
 template <int WPS>
 static void sample_launch_spans(hipStream_t st, const SampleArgs& a, int rows) {
     const dim3 grid(SMP_NB * WPS / 4, rows), block(SMP_T);
@@ -633,7 +636,7 @@ static void sample_launch_spans(hipStream_t st, const SampleArgs& a, int rows) {
     hipLaunchKernelGGL((sample_select_kernel<WPS>), grid, block, 0, st, a);
 }
 static void sample_launch(hipStream_t st, const SampleArgs& a, const AppendArgs& ap, int rows) {
-    if (rows < 16) sample_launch_spans<4>(st, a, rows);
+    if (rows * 8192LL < a.V) sample_launch_spans<4>(st, a, rows);
     else sample_launch_spans<1>(st, a, rows);
     hipLaunchKernelGGL(sample_finish_kernel, dim3(rows, a.temperature == 0.0f ? 1 : SMP_FB), dim3(SMP_T), 0, st, a, ap);
 }

@@ -1,4 +1,5 @@
-"""The sampler at the places where its selection changes path: a few and many rows (span per block / per wave), vocabularies
+"""The sampler at the places where its selection changes path: a few and many rows for the vocabulary (span per block / per
+wave), vocabularies
 smaller than, and no multiple of, its 64 spans, a deciding bin that overflows the lists of some spans (logits that fall with the
 id) or holds too many keys to be listed at all (equal and nearly equal logits), a threshold near the histogram's lower end,
 top_p 0 and 1, masked tokens.
@@ -36,7 +37,7 @@ def logits_of(kind, n, V, rng):
 
 
 @pytest.mark.parametrize("kind", ["normal", "flat", "steps", "near", "ramp", "low", "wide", "masked"])
-@pytest.mark.parametrize("n,V", [(1, 151936), (20, 20011), (5, 37), (17, 65)])
+@pytest.mark.parametrize("n,V", [(1, 151936), (3, 32011), (4, 32011), (20, 20011), (5, 37), (17, 65)])
 @pytest.mark.parametrize("T,top_p", [(0.7, 0.95), (1.0, 1.0), (1.0, 0.0), (0.5, 0.9999999)])
 def test_draws_lie_where_the_distribution_puts_them(kind, n, V, T, top_p):
     import torch
