@@ -905,10 +905,19 @@ static void gemm_launch(hipStream_t st, int epi, const float* W, int N, int K, c
     else                  hipLaunchKernelGGL((sgemm_nt_kernel<EPI_STORE>), grid, block, 0, st, W, N, K, X, ldx, Y, ldy, M);
 }
 
-// silu(g) * u with the hardware's exponential and reciprocal (a few 1e-7 relative; the result is stored with 16 bits).  The
-// library forms (expf, a full division) cost the tile kernel's epilogue about 45 instructions per value, 10 us per round of tiles.
+// silu(g) * u as accurate as g / (1 + expf(-g)) * u (largest relative error against 64 bits 1.8e-7 in both, rms 4e-8), in 16 vector
+// instructions instead of 27.  e = exp(-g) is 2^n times the hardware's exponential of an exactly reduced argument (n an integer,
+// |t| <= 1/2 with the low part of log2 e); the quotient is a reciprocal with one correction.  Both are kept a factor of 4 smaller than
+// they are: the reciprocal of (1 + e) / 4 is a normal number as long as e is finite, and beyond that (g < -88.72) zero.
+// (exp2(-g log2 e) unreduced with the bare reciprocal, six instructions, has an error that grows with |g|: 1e-6 at -20, 3.9e-6 at -87.
+// 7B gate/up of 2048 rows 878 us, 868 with that; scoring of 16 x 128 tokens 1.0 % and a Best-of-N step 1.1 % slower than with it, 1.5 %
+// and 2 % with the library forms.)
 __device__ __forceinline__ float silu_mul(float g, float u) {
-    return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g)) * u;
+    const float c = __builtin_amdgcn_fmed3f(g, -89.0f, 100.0f), n = __builtin_rintf(-1.4426950408889634f * c);
+    const float t = fmaf(-1.9259629911e-8f, c, fmaf(-1.4426950408889634f, c, -n));
+    const float s = 0.25f + __builtin_ldexpf(__builtin_amdgcn_exp2f(t), (int)n - 2), r = __builtin_amdgcn_rcpf(s);
+    const float h = 0.25f * g, q = h * r;
+    return fmaf(fmaf(-s, q, h), r, q) * u;
 }
 
 // ---------------------------------------------------------------- bf16 MFMA, many rows, pre-split activations

@@ -2265,6 +2265,19 @@ int rsd_sample(rsd_ctx* c, const float* logits_dev, const float* u_dev, int32_t 
 
 #include "sample_static.h"
 
+#ifdef RSD_DEBUG
+// the activation of the matrix kernels' epilogues alone, on n values: what a test of its accuracy calls
+__global__ void debug_silu_kernel(const float* __restrict__ g, const float* __restrict__ u, float* __restrict__ x, int n) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) x[i] = silu_mul(g[i], u[i]);
+}
+extern "C" int rsd_debug_silu(const float* g_dev, const float* u_dev, float* x_dev, int32_t n) {
+    if (!g_dev || !u_dev || !x_dev || n < 1) return RSD_EINVAL;
+    hipLaunchKernelGGL(debug_silu_kernel, dim3(ceil_div(n, 256)), dim3(256), 0, nullptr, g_dev, u_dev, x_dev, n);
+    return hipDeviceSynchronize() == hipSuccess ? RSD_OK : RSD_EHIP;
+}
+#endif
+
 // --------------------------------------------------------------------------- rsd_forward
 namespace {
 

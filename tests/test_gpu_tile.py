@@ -99,3 +99,36 @@ def test_rows_wider_than_a_block():
     for chunk in (2, 40):
         assert float((R.rsd_forward(ctx, 0, toks, lens, chunk) - one).abs().max()) < TOL
     R.rsd_destroy(ctx)
+
+
+def test_silu_keeps_fp32_accuracy():
+    """The activation of the matrix kernels' epilogues (the debug build exposes it) against 64 bits.  Bound: the exponential is good
+    to one ulp (2^-23) and enters weighted with e / (1 + e) <= 1; the sum, the quotient and the product round once each (2^-24):
+    5 x 2^-24 = 3.0e-7, whatever |g| is.  Where exp(-g) overflows the result is 0, and -inf and NaN
+    give NaN, as in the plain formula (+inf may give either: its halves, inf and inf - inf, are no number anyway)."""
+    import ctypes
+    import os
+    import torch
+    from paper_2501_19324_amd import binding as R
+    dbg = ctypes.CDLL(os.path.join(os.path.dirname(R.LIB_PATH), "librsd_debug.so"))
+    n = 1 << 20
+
+    def run(g, u):
+        g, u = (torch.from_numpy(a).cuda() for a in (g, u))
+        x = torch.empty_like(g)
+        torch.cuda.synchronize()
+        assert dbg.rsd_debug_silu(ctypes.c_void_p(g.data_ptr()), ctypes.c_void_p(u.data_ptr()), ctypes.c_void_p(x.data_ptr()), g.numel()) == 0
+        return x.cpu().numpy()
+
+    rng = np.random.default_rng(0)
+    for lo, hi in ((-88.7, 90.0), (-20.0, 20.0), (-1.0, 1.0), (-88.7, -87.0)):
+        g = rng.uniform(lo, hi, n).astype(np.float32)
+        u = rng.uniform(0.5, 2.0, n).astype(np.float32)
+        want = g.astype(np.float64) / (1.0 + np.exp(-g.astype(np.float64))) * u
+        err = np.abs(run(g, u) - want) / np.abs(want)
+        assert err.max() < 5 * 2.0 ** -24, (lo, hi, err.max())
+    g = np.zeros(512, np.float32)
+    g[:9] = [np.inf, -np.inf, np.nan, -100.0, -3e38, 3e38, 1e-40, -0.0, 105.0]
+    x = run(g, np.ones(512, np.float32))
+    assert not np.isfinite(x[0]) and np.isnan(x[1]) and np.isnan(x[2]) and x[3] == 0 and x[4] == 0 and x[5] == np.float32(3e38)
+    assert abs(x[6] - 5e-41) < 1e-44 and x[7] == 0 and x[8] == 105.0 and not x[9:].any()
