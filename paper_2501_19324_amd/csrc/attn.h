@@ -188,8 +188,9 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(const float* __restrict_
     }
 }
 
-// Merge the S partial results of every (row, head).
-template <int HD>
+// Merge the S partial results of every (row, head).  LOG2: their maxima are in units of log2 (chunked prefill) - merged as they
+// are, since a conversion would round them and with that move a split's weight by up to 2^-24 of its maximum.
+template <int HD, bool LOG2 = false>
 __global__ void attn_combine_kernel(const float* __restrict__ part_acc, const float* __restrict__ part_ml,
                                     RowMap rm, int H, int S, float* __restrict__ out, int ldo,
                                     uint16_t* __restrict__ out_h = nullptr, uint16_t* __restrict__ out_l = nullptr) {
@@ -202,7 +203,7 @@ __global__ void attn_combine_kernel(const float* __restrict__ part_acc, const fl
     float a = 0.0f, ll = 0.0f;
     for (int s = 0; s < S; ++s) {
         const float m = part_ml[(base + s) * 2];
-        const float c = (m == -INFINITY) ? 0.0f : __expf(m - mn);
+        const float c = (m == -INFINITY) ? 0.0f : (LOG2 ? __builtin_amdgcn_exp2f(m - mn) : __expf(m - mn));
         a += part_acc[(base + s) * HD + e] * c;
         ll += part_ml[(base + s) * 2 + 1] * c;
     }
@@ -874,8 +875,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_decode_mfma_ker
 // through L2 once per four rows.
 // Measured per layer: 8192 rows of 1024-token prompts 7B 382 -> 187 us, 1.5B 215 -> 107 us; 6001 rows of one context 7B
 // 1315 -> 582 us.
-// gridDim.z = S > 1 (few rows over a long context): split sp walks its share of the steps and leaves a partial (max, sum,
-// accumulator) per (row, head) for attn_combine_kernel, in the layout of the decode kernels.
+// gridDim.z = S > 1 (few rows over a long context): split sp walks its share of the steps and leaves a partial (max in units of
+// log2, sum, accumulator) per (row, head) for attn_combine_kernel, in the layout of the decode kernels.
 // The result is written as hi + lo bf16 halves, the input of the output projection (out: as fp32, a pass of a single row).
 constexpr int kPfItemRows = 16;
 template <int G>
@@ -1098,7 +1099,6 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(const float* 
             for (int q = 0; q < 4; ++q)
                 *reinterpret_cast<float4*>(part_acc + pi * HD + 32 * m + 8 * q + 4 * h) =
                     make_float4(o[m][4 * q], o[m][4 * q + 1], o[m][4 * q + 2], o[m][4 * q + 3]);
-        // (the merge works with natural exponentials)
-        if (h == 0) { part_ml[pi * 2] = m_run * 0.6931471805599453f; part_ml[pi * 2 + 1] = l_run; }
+        if (h == 0) { part_ml[pi * 2] = m_run; part_ml[pi * 2 + 1] = l_run; }
     }
 }

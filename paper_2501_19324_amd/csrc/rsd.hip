@@ -470,7 +470,7 @@ void launch_attn_prefill_mfma(rsd_ctx* c, const Model& m, int l, const RowMap& r
     }
 #undef RSD_ATTN_CASE
     if (S > 1)
-        hipLaunchKernelGGL((attn_combine_kernel<128>), dim3(c->pf_rows, m.s.n_heads), dim3(128), 0, c->st, c->part_acc,
+        hipLaunchKernelGGL((attn_combine_kernel<128, true>), dim3(c->pf_rows, m.s.n_heads), dim3(128), 0, c->st, c->part_acc,
                            c->part_ml, rm, m.s.n_heads, S, c->att, m.q_dim, halves ? c->xs_h : nullptr, halves ? c->xs_l : nullptr);
 }
 

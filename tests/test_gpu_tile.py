@@ -70,6 +70,48 @@ def test_chunked_attention_at_the_edges_of_its_work_items(chunk):
     R.rsd_destroy(ctx)
 
 
+def test_large_scores_survive_the_merge_of_splits():
+    """Scores of 33400 (in units of log2) that differ little, so that every split of the context has weight: 16 rows over 400 tokens
+    in eight splits against the same rows in one (nine copies of the sequence: more rows than are split).  All weights are
+    zero but for one column per output, so both sides compute the same q, k, v and scores bit for bit, whatever their
+    kernels' order of summation; what differs is the merge.  The output is 64 x the weighted mean of values +1 and -1:
+    probabilities and output are kept as two bf16 halves (2^-17 each, on either side), 4 x 64 x 2^-17 = 2e-3.  Maxima rounded on their
+    way to the merge move a split's weight by up to 2^-24 x 33400 = 2e-3 each way and the output by up to 0.1 (0.033 here)."""
+    import torch
+    from dataclasses import replace
+    from rsd_inputs import ModelShape, blob_layout, model_blob_torch
+    from paper_2501_19324_amd import binding as R
+    n, vocab = 400, 16
+    shape = ModelShape(1, 1024, 8, 1, 64, vocab)
+    layout, total = blob_layout(shape)
+    blob = torch.zeros(total, dtype=torch.bfloat16, device="cuda")
+    t = {name: blob[off:off + r * c].view(r, c) for name, r, c, off in layout}
+    for name in t:
+        if "norm" in name:
+            t[name].fill_(1.0)
+    t["embed"].fill_(1.0)
+    t["embed"][1::2, 1] = -1.0                              # odd tokens: value -1
+    for h in range(8):
+        t["l0.wq"][h * 128 + 63, 0] = 512.0                 # the slowest rotary pair: cos(1.15e-4 x distance)
+    t["l0.wk"][63, 0] = 512.0
+    t["l0.wv"][0, 1] = 1.0
+    t["l0.wo"][2, 0] = 64.0
+    t["lm_head"][0, 2] = 1.0
+    stub = ModelShape(1, 128, 1, 1, 64, vocab)
+    shapes = [shape, stub, replace(stub, head_kind="reward")]
+    stubs = [model_blob_torch(7, i, shapes[i], torch.device("cuda")) for i in (1, 2)]
+    torch.cuda.synchronize()
+    toks = np.repeat(np.random.default_rng(1).integers(0, vocab, 25), 16)[None, :].astype(np.int32)      # runs of equal values
+    out = []
+    for batch in (1, 9):
+        ctx = R.rsd_init(shapes, [blob] + stubs, batch=batch, delta=0.5, sep_id=vocab - 1, step_cap=1, max_steps=1, max_ctx=n + 1)
+        out.append(R.rsd_forward(ctx, 0, np.repeat(toks, batch, 0), np.full(batch, n, np.int32), 16)[0, :, 0])
+        R.rsd_destroy(ctx)
+    assert float(out[1].abs().max()) > 5.0                   # (the values are there)
+    err = float((out[0] - out[1]).abs().max())
+    assert err < 2e-3, err
+
+
 @pytest.mark.parametrize("rows", [2, 31, 33, 64, 65, 127, 128])
 @pytest.mark.parametrize("ffn", [5248, 8320, 12864])
 def test_unsliced_gate_up_and_head(rows, ffn):
