@@ -946,6 +946,8 @@ __device__ __forceinline__ float silu_mul(float g, float u) {
 // gridDim.z > 1 cuts K into slices whose partial tiles go to part[z][M][N] (finished by rows_finish_kernel).
 __device__ __forceinline__ void copy16_to_lds(uint32_t lds_off, uint32_t voff, const char* base) {
     // lane l: 16 bytes at base + voff -> LDS byte lds_off + 16 l  (M0 holds the wave's LDS address; one wait state behind its write)
+    // (M0 is not named as clobbered: it is a reserved register, in which the compiler keeps no value from one statement to the next -
+    // naming it draws a warning - and in these kernels no instruction of the compiler's own reads it)
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_off), "v"(voff), "s"(base) : "memory");
 }
 template <int BM, int BN>

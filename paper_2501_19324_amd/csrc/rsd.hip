@@ -602,9 +602,8 @@ void run_layers(rsd_ctx* c, Model& m, int M, const RowMap& rm, bool decode) {
     const int S = decode ? m.splits : 1;
     c->cur_phase = decode ? RSD_PROBE_DECODE : RSD_PROBE_PREFILL;
     const bool fused = M <= 8 && !rows;   // few rows: norm / SwiGLU / residual folded into the weight-streaming kernels
-    const bool rows_fuse_norm = rows;                        // the residual GEMMs leave RMSNorm(h) for the next projection
-    // the attention kernels over bf16 caches (or their merge kernel) write the output as hi / lo halves themselves
-    const bool att_halves = rows && m.s.dtype == RSD_BF16 && m.hd == 128;
+    // (rows: the residual GEMMs leave RMSNorm(h) for the next projection, and the attention kernels over bf16 caches, or their
+    // merge kernel, write the output as hi / lo halves themselves)
     // single-row decode over a bf16 cache: the output projection merges the attention splits itself
     const bool parts_to_o = decode && M == 1 && S > 1 && m.s.dtype == RSD_BF16 && m.hd == 128 &&
                             (size_t)m.q_dim * sizeof(float) <= 40 * 1024;
@@ -621,7 +620,7 @@ void run_layers(rsd_ctx* c, Model& m, int M, const RowMap& rm, bool decode) {
             // (the batched decode attention over a bf16 cache and the cache write of a chunked pass add the projection's K
             // slices themselves)
             rows_gemm(c, m, 0, EPI_STORE, wptr<WT>(m, o.wqkv), m.n_qkv, d, M, c->qkv, m.n_qkv, nullptr, 0.f,
-                      att_halves && (decode || M > 128 || !stream_bn(m.n_qkv)) ? &qkv_parts : nullptr);
+                      rows && (decode || M > 128 || !stream_bn(m.n_qkv)) ? &qkv_parts : nullptr);
         } else if constexpr (std::is_same<WT, float>::value) {
             hipLaunchKernelGGL((rmsnorm_kernel<WT>), dim3(M), dim3(256), 0, st, c->h, d, wptr<WT>(m, o.attn_norm), eps, c->xn);
             gemm_launch(st, EPI_STORE, wptr<WT>(m, o.wqkv), m.n_qkv, d, c->xn, d, c->qkv, m.n_qkv, M, c->part_k, c->part_k_floats);
@@ -629,13 +628,13 @@ void run_layers(rsd_ctx* c, Model& m, int M, const RowMap& rm, bool decode) {
         WT* pool_l = reinterpret_cast<WT*>(m.pool) + (size_t)l * m.pool_pages * m.page_elts;
         if (decode) {
             const int which = (int)(&m - &c->m[0]);
-            if (m.s.dtype == RSD_BF16) launch_attn_decode_mfma(c, m, l, M, which, !parts_to_o, att_halves, qkv_parts);
+            if (m.s.dtype == RSD_BF16) launch_attn_decode_mfma(c, m, l, M, which, !parts_to_o, rows, qkv_parts);
             else if (m.hd == 128) launch_attn_decode<WT, 128>(c, m, l, M, which);
             else launch_attn_decode<WT, 32>(c, m, l, M, which);
         } else if (m.hd == 128) {
             if (qkv_parts.ks > 0) launch_rope_kv<WT, 128, true>(c, m, M, rm, pool_l, qkv_parts);
             else launch_rope_kv<WT, 128, false>(c, m, M, rm, pool_l, qkv_parts);
-            if (m.s.dtype == RSD_BF16) launch_attn_prefill_mfma(c, m, l, rm, att_halves);
+            if (m.s.dtype == RSD_BF16) launch_attn_prefill_mfma(c, m, l, rm, rows);
             else launch_attn_g<WT, 128>(c, m, l, M, rm, S);
         } else {
             launch_rope_kv<WT, 32, false>(c, m, M, rm, pool_l, qkv_parts);
@@ -674,15 +673,9 @@ void run_layers(rsd_ctx* c, Model& m, int M, const RowMap& rm, bool decode) {
                 }
             }
         } else if (rows) {
-            if (!att_halves) rows_split(c, c->att, m.q_dim, M, m.q_dim, (const WT*)nullptr, 0.f);
-            if (rows_fuse_norm) {
-                rows_gemm(c, m, 1, EPI_RESID, wptr<WT>(m, o.wo), d, m.q_dim, M, c->h, d, wptr<WT>(m, o.ffn_norm), eps);
-            } else {
-                rows_gemm(c, m, 1, EPI_RESID, wptr<WT>(m, o.wo), d, m.q_dim, M, c->h, d);
-                rows_split(c, c->h, d, M, d, wptr<WT>(m, o.ffn_norm), eps);
-            }
+            rows_gemm(c, m, 1, EPI_RESID, wptr<WT>(m, o.wo), d, m.q_dim, M, c->h, d, wptr<WT>(m, o.ffn_norm), eps);
             rows_gemm(c, m, 2, EPI_SWIGLU, wptr<WT>(m, o.wgu), 2 * F, d, M, nullptr, 0);     // activated values stay as halves
-            if (rows_fuse_norm && l + 1 < m.s.n_layers)
+            if (l + 1 < m.s.n_layers)
                 rows_gemm(c, m, 3, EPI_RESID, wptr<WT>(m, o.wdown), d, F, M, c->h, d, wptr<WT>(m, m.layers[l + 1].attn_norm), eps);
             else
                 rows_gemm(c, m, 3, EPI_RESID, wptr<WT>(m, o.wdown), d, F, M, c->h, d);
@@ -1370,8 +1363,6 @@ int rsd_init(rsd_ctx** out, const rsd_model_shape shape[3], const rsd_weights w[
     HIPCHK(c, dev_alloc(&c->smp_hist, (size_t)c->smp_rows * SMP_WS));
     HIPCHK(c, dev_alloc(&c->smp_psum, (size_t)c->smp_rows * SMP_NB));
     HIPCHK(c, dev_alloc(&c->smp_sel, (size_t)c->smp_rows * 8));
-    HIPCHK(c, hipMemsetAsync(c->smp_hist, 0, (size_t)c->smp_rows * SMP_WS * sizeof(u64_t), c->st));
-    HIPCHK(c, hipMemsetAsync(c->smp_sel, 0, (size_t)c->smp_rows * 8 * sizeof(u64_t), c->st));
     HIPCHK(c, dev_alloc(&c->hl, (size_t)B * d));
     HIPCHK(c, dev_alloc(&c->xl, (size_t)B * d));
     HIPCHK(c, dev_alloc(&c->logits, (size_t)B * V));
@@ -1396,8 +1387,6 @@ int rsd_init(rsd_ctx** out, const rsd_model_shape shape[3], const rsd_weights w[
                 HIPCHK(c, dev_alloc(&ws.hist, n * SMP_WS));
                 HIPCHK(c, dev_alloc(&ws.psum, n * SMP_NB));
                 HIPCHK(c, dev_alloc(&ws.sel, n * 8));
-                HIPCHK(c, hipMemsetAsync(ws.hist, 0, n * SMP_WS * sizeof(u64_t), c->st));
-                HIPCHK(c, hipMemsetAsync(ws.sel, 0, n * 8 * sizeof(u64_t), c->st));
             }
             HIPCHK(c, dev_alloc(&c->sd_aux_dev, rows + 2 * qrows));
             HIPCHK(c, pin_alloc(&c->sd_aux_h, rows + 2 * qrows));

@@ -57,10 +57,6 @@ __device__ __forceinline__ u64_t shfl_xor_u64(u64_t v, int d) {
     const unsigned lo = __shfl_xor((unsigned)v, d, RSD_WAVE), hi = __shfl_xor((unsigned)(v >> 32), d, RSD_WAVE);
     return ((u64_t)hi << 32) | lo;
 }
-__device__ __forceinline__ u64_t shfl_u64(u64_t v, int src) {
-    const unsigned lo = __shfl((unsigned)v, src, RSD_WAVE), hi = __shfl((unsigned)(v >> 32), src, RSD_WAVE);
-    return ((u64_t)hi << 32) | lo;
-}
 __device__ __forceinline__ u64_t wave_sum_u64(u64_t v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v += shfl_xor_u64(v, off);
@@ -169,8 +165,8 @@ __device__ __forceinline__ void smp_add_tied(M* p, uint32_t key, M m) {
     if (!((same >> (threadIdx.x & 63)) & 1)) atomicAdd(p, m);
     else if ((int)(threadIdx.x & 63) == __builtin_ctzll(same)) atomicAdd(p, m * (M)__popcll(same));
 }
-// span of block blockIdx.x: with WPS = 4 waves per span the block's only one, with WPS = 1 one per wave; thread tid of
-// smp_span_threads() works on it
+// span of block blockIdx.x: with WPS = 4 waves per span the block's only one, with WPS = 1 one per wave; lane smp_lane() of
+// its threads works on it
 template <int WPS> __device__ __forceinline__ int smp_span() { return WPS == 4 ? blockIdx.x : blockIdx.x * 4 + (threadIdx.x >> 6); }
 template <int WPS> __device__ __forceinline__ int smp_lane() { return WPS == 4 ? threadIdx.x : threadIdx.x & 63; }
 
