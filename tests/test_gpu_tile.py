@@ -5,6 +5,8 @@ Small model: against the fp64 checker.  Full widths: against the same model eval
 kernels serve.  Both sides keep 16 bits of every activation, so they differ by the flips of single bf16 cache entries only:
 a flip moves one key or value by 2^-8 of itself, which the softmax average and the projections spread to less than the
 2e-2 the bf16 tests allow; a wrong row or column of a tile is off by the logits' own size (0.5 rms and more)."""
+import functools
+
 import numpy as np
 import pytest
 
@@ -126,6 +128,30 @@ def test_unsliced_gate_up_and_head(rows, ffn):
     m = O.OracleModel(shape, model_weights_np(7, 0, shape))
     ref = O.lm_logits(m, O.forward_full(m, [int(t) for t in toks[0]], "bf16"))
     assert np.max(np.abs(out - ref)) < TOL / 4           # (logits of rms 0.2)
+    R.rsd_destroy(ctx)
+
+
+@functools.lru_cache(maxsize=1)
+def stream_model(ffn, vocab):
+    from oracle import rsd_oracle as O
+    from rsd_inputs import ModelShape, model_weights_np
+    shape = ModelShape(1, 896, 7, 7, ffn, vocab)
+    return shape, O.OracleModel(shape, model_weights_np(7, 0, shape, threads=8))
+
+
+@pytest.mark.parametrize("ffn,vocab", [(5248, 10241), (8320, 16449), (12864, 25601)])
+@pytest.mark.parametrize("rows", [17, 33, 65, 128])
+def test_unsliced_kernel_around_its_ring(ffn, vocab, rows):
+    """The same kernel with K = 896, 14 K blocks: its ring of three to six stages wraps several times and ends in another stage
+    than it began; gate/up pair and head of every block width (64, 96, 160), one, two and four row tiles.  (With K = 128, as
+    above, no stage is ever used twice.)"""
+    from oracle import rsd_oracle as O
+    shape, m = stream_model(ffn, vocab)
+    R, ctx = build(shape, vocab, 129)
+    toks = np.random.default_rng(rows).integers(0, vocab, size=(1, rows)).astype(np.int32)
+    out = R.rsd_forward(ctx, 0, toks, np.array([rows], np.int32), 128).cpu().numpy()[0]
+    ref = O.lm_logits(m, O.forward_full(m, [int(t) for t in toks[0]], "bf16"))
+    assert np.max(np.abs(out - ref)) < TOL / 4           # (logits of rms 0.6; a stage read too early or late is off by that)
     R.rsd_destroy(ctx)
 
 
