@@ -7,9 +7,11 @@
 //     writes the halves itself), and every weight tile is multiplied with both
 //     (W.hi + W.lo, fp32 accumulation): the activations keep 16 mantissa bits, which
 //     the bit-for-bit agreement of the bf16 KV-cache entries with an exact evaluation
-//     needs; one bf16 pass would leave 8.  2..64 rows: weight-streaming
-//     gemm_rows_kernel (gemm_rows64_kernel for small matrices); more rows: 256 x 256
-//     or 128 x 256 tiles, gemm_tile_kernel.
+//     needs; one bf16 pass would leave 8.
+//       2..128 rows, gate/up with SwiGLU and heads of 160..256 row blocks: gemm_stream_kernel
+//       2..64 rows, the rest: gemm_rows_kernel with K slices (gemm_rows64_kernel for small matrices,
+//         gemm_rows_sk_kernel, work dealt evenly, for those of 200 row blocks and more)
+//       more rows: gemm_tile_kernel, five block tiles from 128 x 128 to 256 x 256
 // Requirements checked by the caller: K % 64 == 0; N, M arbitrary.
 #pragma once
 #include <algorithm>
@@ -810,7 +812,8 @@ __global__ __launch_bounds__(1024) void rows_finish_norm_kernel(const float* __r
 // K slices for gemm_rows_kernel.  Measured (K-slice sweeps over the 1.5B / 7B / 72B shapes at 16 and 64 rows):
 // the kernel is fastest when the grid has at most one block per compute unit and covers most of them
 // (7B down: 252 or 224 blocks 32 us, 280 blocks 45 us, 462 blocks 35 us); two co-resident blocks only
-// pay when one per unit would leave the chip half empty (7B gate/up: 148 x 3 blocks 59 us, 148 x 1 86 us).
+// pay when one per unit would leave the chip half empty (148 row blocks of K = 3584: x 3 slices 59 us, x 1 86 us; the 7B gate/up pair
+// has that shape, but goes to gemm_stream_kernel).
 // So: the largest count with rows-of-blocks x slices <= 256 if that fills 200 units or more; otherwise the
 // count that minimises (rounds of 512 resident blocks) x (K blocks per slice) plus the traffic of the
 // partial results, in units of one K block over 256 rows of W.
@@ -939,7 +942,9 @@ __device__ __forceinline__ float silu_mul(float g, float u) {
 // otherwise drain them (vmcnt(0)) in front of every LDS read.  They write no registers.
 // Measured at 8192 x 37888 x 3584 (256 x 256 tile): 2130 shader cycles per K block against 2048 of MFMA issue; the chip
 // then holds 1.50 GHz (the register-staged, two-stage predecessor: 2610 cycles at 1.71 GHz), 3.95 -> 3.23 ms = 1.38 PFLOP/s
-// executed, what a library bf16 product of this shape reaches on this part.  Fewer, larger waves (four of 128 x 128,
+// executed, what a library bf16 product of this shape reaches on this part (1.36..1.38).  Over whole launches with their SwiGLU
+// epilogue, the filling of the ring and the last partial round of tiles (7B gate/up): matrix cores busy 75 % of the time at 6001 rows
+// and 68 % at 2048, 1.31 and 1.26 PFLOP/s executed at 1.6 GHz; no LDS bank conflicts.  Fewer, larger waves (four of 128 x 128,
 // a quarter less LDS traffic) leave the barrier exposed: 2610 cycles, 3.44 ms.
 // Thread blocks go to the XCDs round-robin by index; they are renumbered so that an XCD works on consecutive tiles in
 // groups of four row tiles (32 resident blocks = 4 x 8 tiles share their operands in that XCD's L2): 3.50 -> 3.23 ms.

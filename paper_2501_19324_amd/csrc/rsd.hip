@@ -475,7 +475,7 @@ void launch_attn_prefill_mfma(rsd_ctx* c, const Model& m, int l, const RowMap& r
 }
 
 // Two or more rows over bf16 weights: MFMA kernels on activations split into hi + lo bf16 halves, which
-// live in c->xs_h / c->xs_l between the launches (2..64 rows: weight-streaming kernel; more: tile kernel).
+// live in c->xs_h / c->xs_l between the launches (which kernel serves which row count and matrix: gemm.h).
 // (Measured on the 7B shape: a pass over 2 / 4 / 8 rows takes 6.5 / 6.3 / 5.7 ms this way and
 // 6.8 / 8.5 / 16.1 ms through the multi-row vector kernel, which fp32 weights still use.)
 template <typename WT>
