@@ -21,6 +21,7 @@
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
 // ---------------------------------------------------------------- fp32 tiles
 // 64x64 output tile, 16x16 threads, 4x4 outputs per thread, BK = 16.
@@ -925,27 +926,31 @@ __device__ __forceinline__ float silu_mul(float g, float u) {
 
 // ---------------------------------------------------------------- bf16 MFMA, many rows, pre-split activations
 // Y[m][n] (+)= sum_k (Xh + Xl)[m][k] * W[n][k] for more than 64 rows (prefill chunks, large decode batches).
-// Block tile BM rows of X x BN rows of W on eight waves, MFMA tiles of 32x32x16, lo pass then hi pass on each.
+// Block tile BM rows of X x BN rows of W on eight waves, MFMA tiles of 16x16x32, lo half of X first, then hi.
 //
-// What bounds it: MFMA issue, and behind that the power the chip may draw.  The K loop is built so that the matrix
-// cores never wait for operands:
-//   * LDS holds a ring of three stages of 32 k ([rows][32 k] tiles of Xh, Xl and W; chunks of 16 bytes permuted by
-//     (row / 4) % 4, which makes the operand reads conflict-free without padding).  The copies go straight from
-//     global memory into LDS (global_load_lds, 1 KB per wave request, the permutation applied to the source address)
-//     and are requested more than two K blocks before they are used;
-//   * the operands of the next half K block (16 k) are read from LDS into a second register set between the MFMAs of
-//     the half being multiplied, so neither a barrier nor an LDS round trip stands between two MFMAs;
-//   * one barrier per K block, in its middle: before it every wave has its own copies of the next block landed
-//     (vmcnt) and has read the rest of this block (lgkmcnt), so behind it the next block may be read and the ring's
-//     oldest stage overwritten.
-// The order inside the loop is pinned with sched_barrier; the requests are inline assembly because the compiler would
-// otherwise drain them (vmcnt(0)) in front of every LDS read.  They write no registers.
-// Measured at 8192 x 37888 x 3584 (256 x 256 tile): 2130 shader cycles per K block against 2048 of MFMA issue; the chip
-// then holds 1.50 GHz (the register-staged, two-stage predecessor: 2610 cycles at 1.71 GHz), 3.95 -> 3.23 ms = 1.38 PFLOP/s
-// executed, what a library bf16 product of this shape reaches on this part (1.36..1.38).  Over whole launches with their SwiGLU
-// epilogue, the filling of the ring and the last partial round of tiles (7B gate/up): matrix cores busy 75 % of the time at 6001 rows
-// and 68 % at 2048, 1.31 and 1.26 PFLOP/s executed at 1.6 GHz; no LDS bank conflicts.  Fewer, larger waves (four of 128 x 128,
-// a quarter less LDS traffic) leave the barrier exposed: 2610 cycles, 3.44 ms.
+// What bounds it: the power the chip may draw, and with it the energy of a product.  Three choices follow from that:
+//   * 16x16x32 MFMAs instead of 32x32x16: the same products with half as much accumulator traffic.  A register-only loop on
+//     normally distributed operands sustains 2.04 PFLOP/s at 2.0 GHz with them, 1.81 at 1.77 GHz with 32x32x16; in this
+//     kernel 8192 x 37888 x 3584 3340 -> 3178 us, 8192 x 4608 x 3584 424 -> 393.  W is the first operand: a lane then holds
+//     four consecutive columns of a row and stores them at once;
+//   * K blocks of 64, so that every request of the copies covers whole 128-byte lines: with blocks of 32 each line was asked
+//     for in two halves, twice the requests at L2 (8192 x 3584 x 18944: 2.08e8 -> 1.06e8).  With the copies taken
+//     out altogether the loop runs 14-24 % faster: what moves through L2 costs both issue slots and power.
+//     8192 x 37888 x 3584 3178 -> 3118 us, 8192 x 3584 x 18944 1642 -> 1557, 8192 x 1536 x 8960 367 -> 331;
+//   * operands stay in registers as long as they are used: a tile of W is overwritten by its successor right behind its
+//     last product, the X operands of the next pass are read while this one multiplies.
+// A K block is four passes of 32 k: lo half of X first and second 32 k, hi half first and second.  LDS holds a ring of three
+// X units (the lo and the hi half of a block in turn) and two W units, [rows][64 k] with chunks of 16 bytes permuted by
+// (row / 2) % 8, which makes the operand reads conflict-free without padding.  The copies go straight from global memory
+// into LDS (global_load_lds, 1 KB per wave request, the permutation applied to the source address), a whole K block before
+// they are used.  One barrier in the second pass of either half, two tiles of W into it, while the products have all their
+// operands: before it every wave has the unit that is read next landed (vmcnt) and has read the one that becomes free
+// (lgkmcnt).  The order inside a pass is pinned with sched_barrier; the requests are inline assembly because the compiler
+// would otherwise drain them (vmcnt(0)) in front of every LDS read.  They write no registers.
+// Measured against the kernel of 32x32x16 MFMAs and blocks of 32 k (one card): 8192 x 37888 x 3584 3340 -> 3118 us (1.33 -> 1.43
+// PFLOP/s executed), 2048 rows of it 843 -> 788, 8192 x 3584 x 18944 1705 -> 1557, 8192 x 4608 x 3584 424 -> 373, 8192 x 17920 x
+// 1536 735 -> 704, 8192 x 1536 x 8960 384 -> 331; 2400 shader cycles per 32 k (2048 of MFMA issue) at 1.82 GHz, 2270 at 1.60
+// before; no LDS bank conflicts.  Fewer, larger waves (four of 128 x 128) leave the barrier exposed.
 // Thread blocks go to the XCDs round-robin by index; they are renumbered so that an XCD works on consecutive tiles in
 // groups of four row tiles (32 resident blocks = 4 x 8 tiles share their operands in that XCD's L2): 3.50 -> 3.23 ms.
 // gridDim.z > 1 cuts K into slices whose partial tiles go to part[z][M][N] (finished by rows_finish_kernel).
@@ -957,13 +962,12 @@ __device__ __forceinline__ void copy16_to_lds(uint32_t lds_off, uint32_t voff, c
 }
 template <int BM, int BN>
 struct TileCfg {
-    static constexpr int BK = 32, NS = 3;
+    static constexpr int BK = 64;
     static constexpr int WN = 2, WM = 4;                                 // waves along the columns / rows of the tile
-    static constexpr int TM = BM / 32 / WM, TN = BN / 32 / WN;           // MFMA tiles of a wave
-    static constexpr int STAGE = (2 * BM + BN) * BK;                     // bf16 elements of a stage
-    static constexpr int LDS = NS * STAGE * 2;
-    static constexpr int NA = BM / 128;                                  // 16-row requests of a wave per X half
-    static constexpr int NB = BN / 128, NBX = (BN / 16) % 8;             // ... of W: NB, one more for the first NBX waves
+    static constexpr int TM = BM / 16 / WM, TN = BN / 16 / WN;           // MFMA tiles of a wave
+    static constexpr int XU = BM * BK, WU = BN * BK;                     // bf16 elements of a ring unit
+    static constexpr int LDS = (3 * XU + 2 * WU) * 2;
+    static constexpr int NA = BM / 64, NB = BN / 64;                     // requests of a wave per X half / per W unit
 };
 template <int EPI, int BM, int BN>
 __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(const bf16_t* __restrict__ W, int N, int K,
@@ -979,8 +983,7 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(const bf16_t* __restr
     long long clk_c0 = 0, clk_w0 = 0;
     if (clk) { clk_c0 = clock64(); clk_w0 = wall_clock64(); }
     using C = TileCfg<BM, BN>;
-    constexpr int BK = C::BK, TM = C::TM, TN = C::TN, STAGE = C::STAGE, NA = C::NA, NB = C::NB, NBX = C::NBX;
-    constexpr int ND = 2 * NA + NB;                          // requests of a wave per K block (waves below NBX: one more)
+    constexpr int BK = C::BK, TM = C::TM, TN = C::TN, XU = C::XU, WU = C::WU, NA = C::NA, NB = C::NB;
     extern __shared__ __attribute__((aligned(16))) uint16_t tile_sm[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / C::WN, wn = wave % C::WN;
@@ -1003,105 +1006,114 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(const bf16_t* __restr
     const int per = __builtin_amdgcn_readfirstlane((nkb_all + gridDim.z - 1) / gridDim.z);
     const int nk = min(nkb_all, bz * per + per) - bz * per, kb0 = min(bz * per, nkb_all - 1);     // K blocks of this slice (an empty one: nk <= 0, zeros)
 
-    // copies: lane -> row lane / 4 of a 16-row group, LDS chunk lane % 4, which holds source chunk (lane % 4) ^ ((row / 4) % 4)
-    const int lrow = lane >> 2, lch = (lane & 3) ^ ((lane >> 4) & 3);
+    // copies: a request covers eight rows of 128 bytes; lane -> row lane / 8, LDS chunk lane % 8, which holds source chunk
+    // (lane % 8) ^ ((row / 2) % 8); request i of a wave: rows 8 (wave + 8 i) .. + 7 of a unit
+    const int lrow = lane >> 3, lch = (lane & 7) ^ ((((wave & 1) * 4 + (lane >> 4))) & 7);
     // W row behind tile row r.  EPI_SWIGLU (W = [gate | up], N = 2F, never K-sliced): a 32-row group is 16 gate rows and the
     // 16 up rows of the same units
     const int F = N / 2;
     auto wrow = [&](int r) { return EPI == EPI_SWIGLU ? ((r >> 4) & 1) * F + min(bx * (BN / 2) + (r >> 5) * 16 + (r & 15), F - 1) : min(n0 + r, N - 1); };
-    const char *pa_h[NA], *pa_l[NA], *pb[NB + 1];
-    uint32_t va[NA], vb[NB + 1];
+    const char *pa_h[NA], *pa_l[NA], *pb[NB];
+    uint32_t va[NA], vb[NB];
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
-        const int r = m0 + (i * 8 + wave) * 16, b = min(r, M - 1);
+        const int r = m0 + (i * 8 + wave) * 8, b = min(r, M - 1);
         va[i] = (uint32_t)(min(r + lrow, M - 1) - b) * (uint32_t)K * 2u + lch * 16u;
         pa_h[i] = reinterpret_cast<const char*>(Xh + (size_t)b * K + (size_t)kb0 * BK);
         pa_l[i] = reinterpret_cast<const char*>(Xl + (size_t)b * K + (size_t)kb0 * BK);
     }
 #pragma unroll
-    for (int i = 0; i < NB + 1; ++i) {                       // (the last one is used by the waves below NBX only)
-        const int r = min((i * 8 + wave) * 16, BN - 16), b = wrow(r);
+    for (int i = 0; i < NB; ++i) {
+        const int r = (i * 8 + wave) * 8, b = wrow(r);
         vb[i] = (uint32_t)(wrow(r + lrow) - b) * (uint32_t)K * 2u + lch * 16u;
         pb[i] = reinterpret_cast<const char*>(W + (size_t)b * K + (size_t)kb0 * BK);
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)tile_sm + wave * 1024;
-    // request d of a wave for K block kb into stage s; past the end the last block is requested again (never used)
-    auto request = [&](int kb, int s, int d) {
-        const size_t ko = (size_t)max(min(kb, nk - 1), 0) * (BK * 2);
-        const uint32_t l = lds0 + s * (STAGE * 2);
-        if (d < NA) copy16_to_lds(l + d * 8192, va[d], pa_h[d] + ko);
-        else if (d < 2 * NA) copy16_to_lds(l + BM * 64 + (d - NA) * 8192, va[d - NA], pa_l[d - NA] + ko);
-        else copy16_to_lds(l + 2 * BM * 64 + (d - 2 * NA) * 8192, vb[d - 2 * NA], pb[d - 2 * NA] + ko);
-    };
-    const bool extra = NBX > 0 && wave < NBX;
+    auto request_x = [&](const char* const* p, int kb, int s, int d) { copy16_to_lds(lds0 + s * (XU * 2) + d * 8192, va[d], p[d] + (size_t)kb * (BK * 2)); };
+    auto request_w = [&](int kb, int s, int d) { copy16_to_lds(lds0 + 3 * XU * 2 + s * (WU * 2) + d * 8192, vb[d], pb[d] + (size_t)kb * (BK * 2)); };
 
-    f32x16_t acc[TM][TN];
+    f32x4_t acc[TN][TM];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-    const int l32 = lane & 31, kg = lane >> 5;
-    // operand reads: rows of a wave's tiles start at multiples of 32, so the permutation depends on the lane alone
-    const int swz = (l32 >> 2) & 3;
-    const int o0 = l32 * BK + ((kg ^ swz) << 3), o1 = l32 * BK + (((2 + kg) ^ swz) << 3);      // first / second 16 k of a block
-    const uint16_t* A = tile_sm + wm * TM * 32 * BK;
-    const uint16_t* B = tile_sm + 2 * BM * BK + wn * TN * 32 * BK;
-    struct Ops { u32x4_t h[TM], l[TM], b[TN]; };
-    Ops P, Q;
-    constexpr int NR = 2 * TM + TN, NM = 2 * TM * TN;        // operand reads and MFMAs of a half block
-    // read number r of a half block, in the order in which the MFMAs need them: lo row 0, W, lo rows, hi rows
-    auto read = [&](Ops& d, const uint16_t* a, const uint16_t* b, int r) {
-        if (r == 0) d.l[0] = *reinterpret_cast<const u32x4_t*>(a + BM * BK);
-        else if (r <= TN) d.b[r - 1] = *reinterpret_cast<const u32x4_t*>(b + (r - 1) * 32 * BK);
-        else if (r < TN + TM) d.l[r - TN] = *reinterpret_cast<const u32x4_t*>(a + BM * BK + (r - TN) * 32 * BK);
-        else d.h[r - TN - TM] = *reinterpret_cast<const u32x4_t*>(a + (r - TN - TM) * 32 * BK);
+            for (int v = 0; v < 4; ++v) acc[j][i][v] = 0.0f;
+    const int l16 = lane & 15, kg = lane >> 4;
+    // operand reads: rows of a wave's tiles start at multiples of 16, so the permutation depends on the lane alone
+    const int o0 = l16 * BK + ((kg ^ (l16 >> 1)) << 3), o1 = l16 * BK + (((4 + kg) ^ (l16 >> 1)) << 3);      // first / second 32 k of a block
+    const uint16_t* A = tile_sm + wm * TM * 16 * BK;
+    const uint16_t* B = tile_sm + 3 * XU + wn * TN * 16 * BK;
+    u32x4_t w[TN], x[2][TM];
+    auto lds16 = [](const uint16_t* p) { return *reinterpret_cast<const u32x4_t*>(p); };
+    constexpr int T = TM * TN, TB = 2 * TM;
+    // product t of a pass: tiles of W in ascending order, the rows of X up and down in turn (one operand is always the one before)
+    auto mfma = [&](const u32x4_t* xs, int t) {
+        const int j = t / TM, i = j & 1 ? TM - 1 - t % TM : t % TM;
+        acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w[j]), __builtin_bit_cast(bf16x8_t, xs[i]), acc[j][i], 0, 0, 0);
     };
-    auto mfma = [&](const Ops& o, int t) {
-        const int u = t % (TM * TN), i = u / TN, j = u % TN;
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, t < TM * TN ? o.l[i] : o.h[i]),
-                                                            __builtin_bit_cast(bf16x8_t, o.b[j]), acc[i][j], 0, 0, 0);
+    // a pass: the products of 32 k of one half; the X operands of the next pass are read from a, and W tile by tile, behind its last use, from b
+    auto pass = [&](const u32x4_t* xs, u32x4_t* xn, const uint16_t* a, const uint16_t* b) {
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            mfma(xs, t);
+            if (t < TM) xn[t] = lds16(a + t * 16 * BK);
+            if (t % TM == TM - 1) w[t / TM] = lds16(b + t / TM * 16 * BK);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     };
+    // the same with the barrier behind its first two tiles of W: only behind it may a and b be read
+    auto pass_bar = [&](const u32x4_t* xs, u32x4_t* xn, const uint16_t* a, const uint16_t* b, auto wait, auto req, int nreq) {
 #pragma unroll
-    for (int s = 0; s < 3; ++s) {
+        for (int t = 0; t < T; ++t) {
+            if (t == TB) { wait(); __builtin_amdgcn_sched_barrier(0); }
+            mfma(xs, t);
+            if (t >= TB && t < TB + TM) xn[t - TB] = lds16(a + (t - TB) * 16 * BK);
+            if (t == TB) w[0] = lds16(b);
+            if (t == TB + 1) w[1] = lds16(b + 16 * BK);
+            if (t >= TB && t % TM == TM - 1) w[t / TM] = lds16(b + t / TM * 16 * BK);
 #pragma unroll
-        for (int d = 0; d < ND; ++d) request(s, s, d);
-        if (extra) request(s, s, ND);
+            for (int d = 0; d < nreq; ++d) if (t == TB + 1 + d * (T - TB - 1) / nreq) req(d);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    {
+        const int last = max(nk - 1, 0), k1 = min(1, last);
+#pragma unroll
+        for (int d = 0; d < NA; ++d) request_x(pa_l, 0, 0, d);
+#pragma unroll
+        for (int d = 0; d < NB; ++d) request_w(0, 0, d);
+#pragma unroll
+        for (int d = 0; d < NA; ++d) request_x(pa_h, 0, 1, d);
+#pragma unroll
+        for (int d = 0; d < NA; ++d) request_x(pa_l, k1, 2, d);
+#pragma unroll
+        for (int d = 0; d < NB; ++d) request_w(k1, 1, d);
     }
-    // the first stage has landed when at most the requests of the two others are outstanding
-    if (extra) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * ND + 2) : "memory");
-    else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * ND) : "memory");
+    // the lo half and W of the first block have landed when at most the requests behind them are outstanding
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * NA + NB) : "memory");
 #pragma unroll
-    for (int r = 0; r < NR; ++r) read(P, A + o0, B + o0, r);
-    int stg = 0;
-    for (int kb = 0; kb < nk; ++kb) {
-        const uint16_t *a = A + stg * STAGE + o1, *b = B + stg * STAGE + o1;
+    for (int i = 0; i < TM; ++i) x[0][i] = lds16(A + o0 + i * 16 * BK);
 #pragma unroll
-        for (int t = 0; t < NM; ++t) {                       // first half: multiply P, read the second half into Q
-            mfma(P, t);
-            if (t < NR) read(Q, a, b, t);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        // the next block's copies have landed (only the block after it may be outstanding) and this block is read
-        if (extra) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(ND + 1) : "memory");
-        else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(ND) : "memory");
+    for (int j = 0; j < TN; ++j) {                           // (in the order of the loop, so that the first product need not wait for the last of them)
         __builtin_amdgcn_sched_barrier(0);
-        const int nst = stg == 2 ? 0 : stg + 1;
-        a = A + nst * STAGE + o0; b = B + nst * STAGE + o0;
-#pragma unroll
-        for (int t = 0; t < NM; ++t) {                       // second half: multiply Q, read the next block's first half, request block kb + 3
-            mfma(Q, t);
-            constexpr int IT = NR + ND;
-#pragma unroll
-            for (int k = t * IT / NM; k < (t + 1) * IT / NM; ++k) {
-                if (k < NR) read(P, a, b, k);
-                else request(kb + 3, stg, k - NR);
-            }
-            if (t == NM - 1 && extra) request(kb + 3, stg, ND);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        stg = nst;
+        w[j] = lds16(B + o0 + j * 16 * BK);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    int sl = 0, sh = 1, sn = 2;                              // ring units of this block's lo half, its hi half and the next block's lo half
+    for (int kb = 0; kb < nk; ++kb) {
+        const uint16_t *b = B + (kb & 1) * WU, *bn = B + ((kb & 1) ^ 1) * WU;
+        const int k1 = min(kb + 1, nk - 1), k2 = min(kb + 2, nk - 1);
+        pass(x[0], x[1], A + sl * XU + o1, b + o1);                                     // lo half, first 32 k
+        pass_bar(x[1], x[0], A + sh * XU + o0, b + o0,                                  // lo half, second 32 k; behind the barrier the lo half's unit is free and the hi half has landed
+                 [&] { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NA + NB) : "memory"); },
+                 [&](int d) { request_x(pa_h, k1, sl, d); }, NA);
+        pass(x[0], x[1], A + sh * XU + o1, b + o1);                                     // hi half, first 32 k
+        pass_bar(x[1], x[0], A + sn * XU + o0, bn + o0,                                 // hi half, second 32 k; behind the barrier its unit and W's are free and the next block's lo half and W have landed
+                 [&] { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NA) : "memory"); },
+                 [&](int d) { if (d < NA) request_x(pa_l, k2, sh, d); else request_w(k2, kb & 1, d - NA); }, NA + NB);
+        const int f = sl;
+        sl = sn; sn = sh; sh = f;
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");      // nothing is in flight into LDS when the block ends
     if (clk && tid == 0 && blockIdx.x == gridDim.x / 2 && blockIdx.y == gridDim.y / 2 && blockIdx.z == 0) {
@@ -1110,51 +1122,61 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(const bf16_t* __restr
         atomicAdd(&clk[2], 1ull);
     }
 
+    // a lane's accumulator of tile (j, i): columns (wn TN + j) 16 + 4 (lane / 16) .. + 3 of row (wm TM + i) 16 + lane % 16
     if (EPI == EPI_SWIGLU) {
-        // silu(gate) * up straight into the hi / lo halves the down projection reads.  Lanes 0..15 of a 32-lane half hold
-        // gate, 16..31 up of the same 16 units; a row swap of two accumulator registers gives every lane both of one row
+        // silu(gate) * up straight into the hi / lo halves the down projection reads; tiles 2 p and 2 p + 1 are gate and up of the same units
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int p = 0; p < TN / 2; ++p)
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int col = bx * (BN / 2) + (wn * TN + j) * 16 + (lane & 15);
-#pragma unroll
-                for (int v = 0; v < 8; ++v) {
-                    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[i][j][v]), __float_as_uint(acc[i][j][v + 8]), false, false);
-                    const float g = __uint_as_float(s[0]), u = __uint_as_float(s[1]);
-                    const int m = m0 + (wm * TM + i) * 32 + 8 * (v >> 2) + 4 * kg + (v & 3) + ((lane & 16) ? 16 : 0);
-                    if (m < M && col < F) {
-                        const float x = silu_mul(g, u);
-                        const uint16_t hi = f2bf(x);
-                        Oh[(size_t)m * F + col] = hi;
-                        Ol[(size_t)m * F + col] = f2bf(x - bf2f(hi));
-                    }
+            for (int i = 0; i < TM; ++i) {
+                const int col = bx * (BN / 2) + (wn * (TN / 2) + p) * 16 + 4 * kg, m = m0 + (wm * TM + i) * 16 + l16;
+                if (m < M && col < F) {                      // (F is a multiple of 64: it is the K of the down projection)
+                    const f32x4_t g = acc[2 * p][i], u = acc[2 * p + 1][i];
+                    store_halves(Oh + (size_t)m * F + col, Ol + (size_t)m * F + col,
+                                 make_float4(silu_mul(g[0], u[0]), silu_mul(g[1], u[1]), silu_mul(g[2], u[2]), silu_mul(g[3], u[3])));
                 }
             }
         return;
     }
     const bool sliced = gridDim.z > 1;
-    float res[2][16];        // EPI_RESID: the residual values of a tile are requested while the tile before it is stored
-    auto fetch_res = [&](int t, float* r) {
-        const int i = t / TN, j = t % TN, n = min(n0 + (wn * TN + j) * 32 + l32, N - 1);
+    float* out = sliced ? part + (size_t)bz * M * N : Y;
+    const size_t ldo = sliced ? N : ldy;
+    const bool add = EPI == EPI_RESID && !sliced;
+    if (((N | (int)ldo) & 3) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
+        float4 res[2][TM];   // EPI_RESID: the residual values of a column of tiles are requested while the one before it is stored
+        auto at = [&](int j, int i) { return out + (size_t)min(m0 + (wm * TM + i) * 16 + l16, M - 1) * ldo + min(n0 + (wn * TN + j) * 16 + 4 * kg, N - 4); };
+        if (add) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
-            r[v] = Y[(size_t)min(m0 + (wm * TM + i) * 32 + 8 * (v >> 2) + 4 * kg + (v & 3), M - 1) * ldy + n];
-    };
-    if (EPI == EPI_RESID && !sliced) fetch_res(0, res[0]);
+            for (int i = 0; i < TM; ++i) res[0][i] = *reinterpret_cast<const float4*>(at(0, i));
+        }
 #pragma unroll
-    for (int t = 0; t < TM * TN; ++t) {
-        if (EPI == EPI_RESID && !sliced && t + 1 < TM * TN) fetch_res(t + 1, res[(t + 1) & 1]);
-        const int i = t / TN, j = t % TN, n = n0 + (wn * TN + j) * 32 + l32;
+        for (int j = 0; j < TN; ++j) {
+            if (add && j + 1 < TN) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int m = m0 + (wm * TM + i) * 32 + 8 * (v >> 2) + 4 * kg + (v & 3);
-            if (m < M && n < N) {
-                if (sliced) part[((size_t)bz * M + m) * N + n] = acc[i][j][v];
-                else Y[(size_t)m * ldy + n] = EPI == EPI_RESID ? res[t & 1][v] + acc[i][j][v] : acc[i][j][v];
+                for (int i = 0; i < TM; ++i) res[(j + 1) & 1][i] = *reinterpret_cast<const float4*>(at(j + 1, i));
+            }
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                if (m0 + (wm * TM + i) * 16 + l16 >= M || n0 + (wn * TN + j) * 16 + 4 * kg >= N) continue;
+                float4 y = make_float4(acc[j][i][0], acc[j][i][1], acc[j][i][2], acc[j][i][3]);
+                if (add) { const float4 r = res[j & 1][i]; y.x += r.x; y.y += r.y; y.z += r.z; y.w += r.w; }
+                *reinterpret_cast<float4*>(at(j, i)) = y;
             }
         }
+        return;
     }
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int m = m0 + (wm * TM + i) * 16 + l16, n = n0 + (wn * TN + j) * 16 + 4 * kg + v;
+                if (m < M && n < N) {
+                    float* y = out + (size_t)m * ldo + n;
+                    *y = add ? *y + acc[j][i][v] : acc[j][i][v];
+                }
+            }
 }
 
 // Block tile and K slices of a many-row product: the plan for which a cost model is smallest.  The model was fitted to
@@ -1170,15 +1192,15 @@ static constexpr TileCost kTileCosts[] = {
     {256, 256, 1, 1.596f, 0.856f, 8.7f}, {256, 192, 1, 1.279f, 0.690f, 6.7f}, {128, 256, 1, 0.903f, 0.435f, 5.0f},
     {128, 192, 1, 0.718f, 0.382f, 4.3f}, {128, 128, 2, 1.106f, 0.194f, 3.3f}};
 static TilePlan gemm_tile_plan(int epi, int N, int K, int M, size_t part_floats) {
-    const int nkb = K / 32;
+    const int nkb = K / 64;
     const float mn = 1e-6f * (float)M * (float)N;
     TilePlan best{256, 256, 1};
     float best_us = 1e30f;
     for (const TileCost& c : kTileCosts)
         for (int ks : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
-            const int kb = (nkb + ks - 1) / ks;
-            // slices: whole columns of four (finish kernels), at least six K blocks each, none empty, room for the partial sums
-            if (ks > 1 && (N % 4 || kb < 6 || (ks - 1) * kb >= nkb || (size_t)ks * M * N > part_floats)) continue;
+            const int per = (nkb + ks - 1) / ks, kb = 2 * per;
+            // slices: whole columns of four (finish kernels), at least three K blocks each, none empty, room for the partial sums
+            if (ks > 1 && (N % 4 || per < 3 || (ks - 1) * per >= nkb || (size_t)ks * M * N > part_floats)) continue;
             const long long blocks = (long long)((N + c.bn - 1) / c.bn) * ((M + c.bm - 1) / c.bm) * ks, cap = 256 * c.per_cu;
             const float part = (float)(blocks % cap) / (float)cap;
             float us = (float)(blocks / cap) * (kb * c.full + c.over);
