@@ -223,7 +223,7 @@ struct QkvParts { const float* part; int ks; size_t stride; };
 
 __device__ __forceinline__ void store4(float* p, const float4& v) { *reinterpret_cast<float4*>(p) = v; }
 __device__ __forceinline__ void store4(bf16_t* p, const float4& v) {
-    *reinterpret_cast<uint2*>(p) = make_uint2((uint32_t)f2bf(v.x) | ((uint32_t)f2bf(v.y) << 16), (uint32_t)f2bf(v.z) | ((uint32_t)f2bf(v.w) << 16));
+    *reinterpret_cast<uint2*>(p) = make_uint2(f2bf2(v.x, v.y), f2bf2(v.z, v.w));
 }
 
 // Rotate q (in place, fp32) and k with the precomputed table rope[pos][i] =
@@ -311,10 +311,10 @@ __device__ __forceinline__ void store8(float* p, const float v[8]) {
 }
 __device__ __forceinline__ void store8(bf16_t* p, const float v[8]) {
     uint4 r;
-    r.x = (uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16);
-    r.y = (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16);
-    r.z = (uint32_t)f2bf(v[4]) | ((uint32_t)f2bf(v[5]) << 16);
-    r.w = (uint32_t)f2bf(v[6]) | ((uint32_t)f2bf(v[7]) << 16);
+    r.x = f2bf2(v[0], v[1]);
+    r.y = f2bf2(v[2], v[3]);
+    r.z = f2bf2(v[4], v[5]);
+    r.w = f2bf2(v[6], v[7]);
     *reinterpret_cast<uint4*>(p) = r;
 }
 
@@ -526,16 +526,13 @@ typedef __attribute__((ext_vector_type(4))) short as16x4_t;
 typedef __attribute__((ext_vector_type(4))) float af32x4_t;
 
 __device__ __forceinline__ void split_hi_lo8(const float x[8], abf16x8_t& hi, abf16x8_t& lo) {
-    uint32_t h[4], l[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const uint16_t h0 = f2bf(x[2 * e]), h1 = f2bf(x[2 * e + 1]);
-        const uint16_t l0 = f2bf(x[2 * e] - bf2f(h0)), l1 = f2bf(x[2 * e + 1] - bf2f(h1));
-        h[e] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-        l[e] = (uint32_t)l0 | ((uint32_t)l1 << 16);
-    }
-    hi = __builtin_bit_cast(abf16x8_t, make_uint4(h[0], h[1], h[2], h[3]));
-    lo = __builtin_bit_cast(abf16x8_t, make_uint4(l[0], l[1], l[2], l[3]));
+    uint4 h, l;
+    split2(x[0], x[1], h.x, l.x);
+    split2(x[2], x[3], h.y, l.y);
+    split2(x[4], x[5], h.z, l.z);
+    split2(x[6], x[7], h.w, l.w);
+    hi = __builtin_bit_cast(abf16x8_t, h);
+    lo = __builtin_bit_cast(abf16x8_t, l);
 }
 
 // PARTS: the kernel adds the K slices of the QKV projection itself (ascending, like the finish kernels) while
@@ -718,7 +715,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_decode_mfma_ker
                     const float2 t = cn[j & 1][e];
                     k2[u] = j < 2 ? kx[j][e] * t.x - kx[j + 2 < 4 ? j + 2 : 0][e] * t.y : kx[j][e] * t.x + kx[j >= 2 ? j - 2 : 0][e] * t.y;
                 }
-                w[i] = (uint32_t)f2bf(k2[0]) | ((uint32_t)f2bf(k2[1]) << 16);
+                w[i] = f2bf2(k2[0], k2[1]);
             }
             const uint4 pk = make_uint4(w[0], w[1], w[2], w[3]);
             if (l16 == 0) *reinterpret_cast<uint4*>(kb + kv_tiled_k(slot, j * 32 + c * 8)) = pk;
@@ -772,11 +769,10 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_decode_mfma_ker
         lsum = rows4_sum(lsum);
         l_run = l_run * corr + lsum;
         m_run = m_new;
-        uint16_t ph[4], pl[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { ph[i] = f2bf(p[i]); pl[i] = f2bf(p[i] - bf2f(ph[i])); }
-        const as16x4_t pa = __builtin_bit_cast(as16x4_t, make_uint2((uint32_t)ph[0] | ((uint32_t)ph[1] << 16), (uint32_t)ph[2] | ((uint32_t)ph[3] << 16)));
-        const as16x4_t pb = __builtin_bit_cast(as16x4_t, make_uint2((uint32_t)pl[0] | ((uint32_t)pl[1] << 16), (uint32_t)pl[2] | ((uint32_t)pl[3] << 16)));
+        uint2 ph, pl;
+        split2(p[0], p[1], ph.x, pl.x);
+        split2(p[2], p[3], ph.y, pl.y);
+        const as16x4_t pa = __builtin_bit_cast(as16x4_t, ph), pb = __builtin_bit_cast(as16x4_t, pl);
         // slots past the sequence hold whatever the pool held: zero them (0 * NaN would poison the sum)
         const uint32_t mk0 = ((vmask & 1) ? 0xFFFFu : 0u) | ((vmask & 2) ? 0xFFFF0000u : 0u);
         const uint32_t mk1 = ((vmask & 4) ? 0xFFFFu : 0u) | ((vmask & 8) ? 0xFFFF0000u : 0u);
@@ -960,8 +956,6 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(const float* 
     const int k_addr = (col >> 4) * (RSD_PAGE * HD) + (h * 16 + (col & 15)) * 8;              // + j * 256
     // V: dim 32 m + col, tokens 4 h .. + 3 and 8 + 4 h .. + 3 of page a: 8 bytes each
     const int v_addr_ = 2 * RSD_PAGE * HD + h * 128 + (col & 15) * 8 + (col >> 4) * 4;        // + a * 2048 + m * 512 (+ 256)
-    typedef __attribute__((ext_vector_type(2))) float f2_t;
-    typedef __attribute__((ext_vector_type(2))) __bf16 b2_t;
     uint4 kf[8], vf[8];                                      // operands: K chunk j; V of page a, dims 32 m (vf[4 a + m])
     auto read_k = [&](const uint16_t* kv, int j) { kf[j] = *reinterpret_cast<const uint4*>(kv + k_addr + j * 256); };
     auto read_v = [&](const uint16_t* kv, int i) {
@@ -1029,8 +1023,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(const float* 
         for (int i = 0; i < 8; ++i) {
             const float a = __builtin_amdgcn_exp2f(sc[2 * i] - m_use), b = __builtin_amdgcn_exp2f(sc[2 * i + 1] - m_use);
             lsum += a + b;
-            ph[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2_t{a, b}, b2_t));
-            pl[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2_t{a - __uint_as_float(ph[i] << 16), b - __uint_as_float(ph[i] & 0xFFFF0000u)}, b2_t));
+            split2(a, b, ph[i], pl[i]);
         }
         l_run += lsum;                                       // (each half of the wave sums its own tokens; added up at the end)
         if (s * STEP + STEP - 1 > p_last) {                  // slots behind the last row hold whatever the pool held: zero those values
@@ -1080,17 +1073,11 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(const float* 
                         make_float4(o[m][4 * q] * inv, o[m][4 * q + 1] * inv, o[m][4 * q + 2] * inv, o[m][4 * q + 3] * inv);
                     continue;
                 }
-                uint16_t hi[4], lo[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float y = o[m][4 * q + e] * inv;
-                    hi[e] = f2bf(y);
-                    lo[e] = f2bf(y - bf2f(hi[e]));
-                }
-                *reinterpret_cast<uint2*>(out_h + at + 32 * m + 8 * q) =
-                    make_uint2((uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16));
-                *reinterpret_cast<uint2*>(out_l + at + 32 * m + 8 * q) =
-                    make_uint2((uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16));
+                uint2 hi, lo;
+                split2(o[m][4 * q] * inv, o[m][4 * q + 1] * inv, hi.x, lo.x);
+                split2(o[m][4 * q + 2] * inv, o[m][4 * q + 3] * inv, hi.y, lo.y);
+                *reinterpret_cast<uint2*>(out_h + at + 32 * m + 8 * q) = hi;
+                *reinterpret_cast<uint2*>(out_l + at + 32 * m + 8 * q) = lo;
             }
     } else {
         const size_t pi = ((size_t)row * H + hk * G + g) * S + sp;

@@ -614,13 +614,12 @@ __global__ __launch_bounds__(512, 2) void gemm_rows64_kernel(const bf16_t* __res
 }
 
 // x[4] as hi + lo bf16 halves
-__device__ __forceinline__ void store_halves(uint16_t* __restrict__ h, uint16_t* __restrict__ l, const float4& v) {
-    const float x[4] = {v.x, v.y, v.z, v.w};
-    uint16_t hi[4], lo[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { hi[e] = f2bf(x[e]); lo[e] = f2bf(x[e] - bf2f(hi[e])); }
-    *reinterpret_cast<uint2*>(h) = make_uint2((uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16));
-    *reinterpret_cast<uint2*>(l) = make_uint2((uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16));
+__device__ __forceinline__ void store_halves(uint16_t* __restrict__ h, uint16_t* __restrict__ l, const float4& x) {
+    uint2 hi, lo;
+    split2(x.x, x.y, hi.x, lo.x);
+    split2(x.z, x.w, hi.y, lo.y);
+    *reinterpret_cast<uint2*>(h) = hi;
+    *reinterpret_cast<uint2*>(l) = lo;
 }
 
 // fp32 rows -> hi + lo bf16 rows, optionally through RMSNorm (gain != nullptr).  One block per row.  EMBED: the rows are token
@@ -741,15 +740,9 @@ __global__ void rows_finish_kernel(const float* __restrict__ part, int KS, int R
     float4 a = sum(n);
     if (EPI == EPI_SWIGLU) {
         const float4 u = sum(NO + n);
-        const float x[4] = {a.x / (1.0f + expf(-a.x)) * u.x, a.y / (1.0f + expf(-a.y)) * u.y,
-                            a.z / (1.0f + expf(-a.z)) * u.z, a.w / (1.0f + expf(-a.w)) * u.w};
-        uint16_t hi[4], lo[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { hi[e] = f2bf(x[e]); lo[e] = f2bf(x[e] - bf2f(hi[e])); }
-        *reinterpret_cast<uint2*>(Oh + m * NO + n) =
-            make_uint2((uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16));
-        *reinterpret_cast<uint2*>(Ol + m * NO + n) =
-            make_uint2((uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16));
+        store_halves(Oh + m * NO + n, Ol + m * NO + n,
+                     make_float4(a.x / (1.0f + expf(-a.x)) * u.x, a.y / (1.0f + expf(-a.y)) * u.y,
+                                 a.z / (1.0f + expf(-a.z)) * u.z, a.w / (1.0f + expf(-a.w)) * u.w));
     } else {
         float4* yp = reinterpret_cast<float4*>(Y + m * ldy + n);
         if (EPI == EPI_RESID) { const float4 y = *yp; a.x += y.x; a.y += y.y; a.z += y.z; a.w += y.w; }
@@ -797,15 +790,9 @@ __global__ __launch_bounds__(1024) void rows_finish_norm_kernel(const float* __r
     for (int i = 0; i < 2; ++i) {
         const int n = tid * 4 + i * 4096;
         if (n < N) {
-            const float x[4] = {v[i].x * (rs * ld1(gain + n)), v[i].y * (rs * ld1(gain + n + 1)),
-                                v[i].z * (rs * ld1(gain + n + 2)), v[i].w * (rs * ld1(gain + n + 3))};
-            uint16_t hi[4], lo[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { hi[e] = f2bf(x[e]); lo[e] = f2bf(x[e] - bf2f(hi[e])); }
-            *reinterpret_cast<uint2*>(Xh + (size_t)m * N + n) =
-                make_uint2((uint32_t)hi[0] | ((uint32_t)hi[1] << 16), (uint32_t)hi[2] | ((uint32_t)hi[3] << 16));
-            *reinterpret_cast<uint2*>(Xl + (size_t)m * N + n) =
-                make_uint2((uint32_t)lo[0] | ((uint32_t)lo[1] << 16), (uint32_t)lo[2] | ((uint32_t)lo[3] << 16));
+            store_halves(Xh + (size_t)m * N + n, Xl + (size_t)m * N + n,
+                         make_float4(v[i].x * (rs * ld1(gain + n)), v[i].y * (rs * ld1(gain + n + 1)),
+                                     v[i].z * (rs * ld1(gain + n + 2)), v[i].w * (rs * ld1(gain + n + 3))));
         }
     }
 }
@@ -909,17 +896,21 @@ static void gemm_launch(hipStream_t st, int epi, const float* W, int N, int K, c
     else                  hipLaunchKernelGGL((sgemm_nt_kernel<EPI_STORE>), grid, block, 0, st, W, N, K, X, ldx, Y, ldy, M);
 }
 
-// silu(g) * u as accurate as g / (1 + expf(-g)) * u (largest relative error against 64 bits 1.8e-7 in both, rms 4e-8), in 16 vector
+// silu(g) * u as accurate as g / (1 + expf(-g)) * u (largest relative error against 64 bits 1.8e-7 in both, rms 4e-8), in 14 vector
 // instructions instead of 27.  e = exp(-g) is 2^n times the hardware's exponential of an exactly reduced argument (n an integer,
-// |t| <= 1/2 with the low part of log2 e); the quotient is a reciprocal with one correction.  Both are kept a factor of 4 smaller than
-// they are: the reciprocal of (1 + e) / 4 is a normal number as long as e is finite, and beyond that (g < -88.72) zero.
-// (exp2(-g log2 e) unreduced with the bare reciprocal, six instructions, has an error that grows with |g|: 1e-6 at -20, 3.9e-6 at -87.
-// 7B gate/up of 2048 rows 878 us, 868 with that; scoring of 16 x 128 tokens 1.0 % and a Best-of-N step 1.1 % slower than with it, 1.5 %
-// and 2 % with the library forms.)
+// |t| <= 1/2 with the low part of log2 e); n is rounded and shifted into the exponent by one addition each (as long as e / 4 is a
+// normal number, hence the upper limit: beyond 60 it vanishes in the sum); the quotient is a reciprocal with one correction.  Sum and
+// numerator are kept a factor of 4 smaller than they are: the reciprocal of (1 + e) / 4 is a normal number as long as e is finite, and
+// beyond that (g < -88.72) zero.
+// Together with the conversions of common.h (30 -> 18 vector instructions per value in the epilogue, which no product overlaps):
+// 8192 x 17920 x 1536 683 -> 674 us, 2048 x 37888 x 3584 763 -> 759.
+// (exp2(-g log2 e) unreduced with the bare reciprocal, six instructions, has an error that grows with |g|: 1e-6 at -20, 3.9e-6 at -87.)
 __device__ __forceinline__ float silu_mul(float g, float u) {
-    const float c = __builtin_amdgcn_fmed3f(g, -89.0f, 100.0f), n = __builtin_rintf(-1.4426950408889634f * c);
+    constexpr float R = 12582910.0f;                         // 1.5 x 2^23 - 2: the sum's low bits are n - 2
+    const float c = __builtin_amdgcn_fmed3f(g, -89.0f, 60.0f), m = fmaf(-1.4426950408889634f, c, R), n = m - R;
     const float t = fmaf(-1.9259629911e-8f, c, fmaf(-1.4426950408889634f, c, -n));
-    const float s = 0.25f + __builtin_ldexpf(__builtin_amdgcn_exp2f(t), (int)n - 2), r = __builtin_amdgcn_rcpf(s);
+    const float e = __uint_as_float((__float_as_uint(m) << 23) + __float_as_uint(__builtin_amdgcn_exp2f(t)));
+    const float s = 0.25f + e, r = __builtin_amdgcn_rcpf(s);
     const float h = 0.25f * g, q = h * r;
     return fmaf(fmaf(-s, q, h), r, q) * u;
 }
