@@ -1171,17 +1171,19 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(const bf16_t* __restr
 }
 
 // Block tile and K slices of a many-row product: the plan for which a cost model is smallest.  The model was fitted to
-// 4456 timings (12 projection shapes of the 1.5B / 7B / 72B models x 14 row counts from 70 to 8192 x all tiles and slice
-// counts; rms error 9 %, the plans it picks are 1.4 % slower than the best measured ones on average): a round of thread
-// blocks that fills the chip costs `full` per K block of 32, one that occupies the share x of it `light` + x (`full` -
-// `light`) (fewer busy units clock higher), and every round `over` for filling the ring and storing the tile.  K slices
+// 3385 timings (12 projection shapes of the 1.5B / 7B / 72B models x 14 row counts from 70 to 8192 x all tiles and slice
+// counts; rms error 8 %, the plans it picks are 1.0 % slower than the best measured ones on average and 16 % at worst; with the
+// constants fitted to the kernel's predecessor 2.2 % and 46 %): a round of thread
+// blocks that fills the chip costs `full` per 32 k, one that occupies the share x of it `light` + x (`full` -
+// `light`) (fewer busy units clock higher) but not less than `least` (the latency of a block's own loop), and every round `over` for
+// filling the ring and storing the tile.  K slices
 // pay a finish kernel that reads their partial sums back; a residual product without slices pays the separate kernel
 // that leaves the normalised halves for the next projection.
 struct TilePlan { int bm, bn, ks; };
-struct TileCost { int bm, bn, per_cu; float full, light, over; };        // microseconds
+struct TileCost { int bm, bn, per_cu; float full, light, least, over; };        // microseconds
 static constexpr TileCost kTileCosts[] = {
-    {256, 256, 1, 1.596f, 0.856f, 8.7f}, {256, 192, 1, 1.279f, 0.690f, 6.7f}, {128, 256, 1, 0.903f, 0.435f, 5.0f},
-    {128, 192, 1, 0.718f, 0.382f, 4.3f}, {128, 128, 2, 1.106f, 0.194f, 3.3f}};
+    {256, 256, 1, 1.399f, 0.921f, 0.979f, 8.8f}, {256, 192, 1, 1.108f, 0.740f, 0.667f, 5.6f}, {128, 256, 1, 0.809f, 0.537f, 0.483f, 4.0f},
+    {128, 192, 1, 0.619f, 0.386f, 0.488f, 4.0f}, {128, 128, 2, 0.951f, 0.148f, 0.305f, 3.4f}};
 static TilePlan gemm_tile_plan(int epi, int N, int K, int M, size_t part_floats) {
     const int nkb = K / 64;
     const float mn = 1e-6f * (float)M * (float)N;
@@ -1195,9 +1197,9 @@ static TilePlan gemm_tile_plan(int epi, int N, int K, int M, size_t part_floats)
             const long long blocks = (long long)((N + c.bn - 1) / c.bn) * ((M + c.bm - 1) / c.bm) * ks, cap = 256 * c.per_cu;
             const float part = (float)(blocks % cap) / (float)cap;
             float us = (float)(blocks / cap) * (kb * c.full + c.over);
-            if (part > 0.0f) us += kb * (c.light + part * (c.full - c.light)) + c.over;
-            if (ks > 1) us += 5.4f + 1.03f * ks * mn;
-            else if (epi == EPI_RESID) us += 8.7f + 0.69f * mn;
+            if (part > 0.0f) us += kb * std::max(c.least, c.light + part * (c.full - c.light)) + c.over;
+            if (ks > 1) us += 5.7f + 1.10f * ks * mn;
+            else if (epi == EPI_RESID) us += 7.2f + 0.82f * mn;
             if (us < best_us) { best_us = us; best = TilePlan{c.bm, c.bn, ks}; }
         }
     return best;
