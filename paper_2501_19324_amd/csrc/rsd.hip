@@ -1362,7 +1362,8 @@ int rsd_init(rsd_ctx** out, const rsd_model_shape shape[3], const rsd_weights w[
     HIPCHK(c, dev_alloc(&c->smp_pidx, (size_t)c->smp_rows * SMP_NB));
     HIPCHK(c, dev_alloc(&c->smp_hist, (size_t)c->smp_rows * SMP_WS));
     HIPCHK(c, dev_alloc(&c->smp_psum, (size_t)c->smp_rows * SMP_NB));
-    HIPCHK(c, dev_alloc(&c->smp_sel, (size_t)c->smp_rows * 8));
+    HIPCHK(c, dev_alloc(&c->smp_sel, (size_t)c->smp_rows * SMP_SEL));
+    HIPCHK(c, hipMemsetAsync(c->smp_sel, 0, (size_t)c->smp_rows * SMP_SEL * sizeof(u64_t), c->st));
     HIPCHK(c, dev_alloc(&c->hl, (size_t)B * d));
     HIPCHK(c, dev_alloc(&c->xl, (size_t)B * d));
     HIPCHK(c, dev_alloc(&c->logits, (size_t)B * V));
@@ -1386,7 +1387,8 @@ int rsd_init(rsd_ctx** out, const rsd_model_shape shape[3], const rsd_weights w[
                 HIPCHK(c, dev_alloc(&ws.pidx, n * SMP_NB));
                 HIPCHK(c, dev_alloc(&ws.hist, n * SMP_WS));
                 HIPCHK(c, dev_alloc(&ws.psum, n * SMP_NB));
-                HIPCHK(c, dev_alloc(&ws.sel, n * 8));
+                HIPCHK(c, dev_alloc(&ws.sel, n * SMP_SEL));
+                HIPCHK(c, hipMemsetAsync(ws.sel, 0, n * SMP_SEL * sizeof(u64_t), c->st));
             }
             HIPCHK(c, dev_alloc(&c->sd_aux_dev, rows + 2 * qrows));
             HIPCHK(c, pin_alloc(&c->sd_aux_h, rows + 2 * qrows));

@@ -10,7 +10,8 @@
 // No sort: tau is found by selection over the bit patterns of the non-negative floats e_t.  Masses are summed as
 // 64-bit fixed point (e * 2^40), so every sum is exact, order-independent and reproducible from run to run, whatever
 // the path to tau.  A row is cut into SMP_NB spans of the vocabulary; the phases are separate launches:
-//   A  max of every span (or arg max: greedy); clears what B and C add to
+//   A  max of every span; clears what B and C add to.  Greedy: arg max of every span, and the block that finishes a row's last
+//      span chooses among them and appends the token
 //   B  histogram of masses over 1792 bins of 1/32 and 1/64 octave (exponent and five or six mantissa bits, 2^-40 .. 1)
 //   C  every block finds the bin tau lies in, sums what lies above it per span and lists the keys inside it (a bin is
 //      1 or 2 % wide: mostly a few hundred keys)
@@ -47,6 +48,7 @@ constexpr int SMP_WS = SMP_NB * 256 / 2 + SMP_SUB;
 constexpr int SMP_LIST = 128;                             // words of a span's list
 constexpr int SMP_DENSE = (SMP_WS - SMP_BINS) * 2 - SMP_NB * SMP_LIST;   // of the shared one: a bin that may hold more keys makes the row dense
 static_assert(SMP_DENSE > 0 && SMP_BINS + SMP_SUB <= SMP_WS, "");
+constexpr int SMP_SEL = 9;                                // words of a row's `sel`
 constexpr int SMP_FB = SMP_NB / 4;                        // blocks of phase D of a dense row: a span per wave
 
 __device__ __forceinline__ u64_t shfl_up_u64(u64_t v, int d) {
@@ -89,8 +91,9 @@ struct SampleArgs {
     int sep_id; float sep_bias;                          // logit[sep_id] += sep_bias before anything else
     const int* active;                                   // nullable: rows with active[r] == 0 are skipped
     int* out;                                            // nullable when the result is appended
-    // workspace, per row: pmax[SMP_NB], pidx[SMP_NB], hist[SMP_WS], psum[SMP_NB] and sel[8]: [0] mass the nucleus must reach, [1] mass
-    // above the deciding bin, [2] that bin (-1: none), [3] keys in the shared list, [4] dense, [5] tau, [6] point of the draw, [7] blocks done
+    // workspace, per row: pmax[SMP_NB], pidx[SMP_NB], hist[SMP_WS], psum[SMP_NB] and sel[SMP_SEL]: [0] mass the nucleus must reach, [1] mass
+    // above the deciding bin, [2] that bin (-1: none), [3] keys in the shared list, [4] dense, [5] tau, [6] point of the draw, [7] blocks done,
+    // [8] spans whose arg max is known: 64 more with every greedy call, zero at first
     float* pmax; int* pidx; u64_t* hist; u64_t* psum; u64_t* sel;
     // nullable: packed rows.  Row r then stands for sequence row_seq[r] (< 0: unused row); u, u_index, active and
     // the appended state are indexed by the sequence, logits, out and the workspace by the row
@@ -173,20 +176,64 @@ template <int WPS> __device__ __forceinline__ int smp_lane() { return WPS == 4 ?
 // tokens a thread requests together: two batches cover a span of 2374 with 256 threads, five with 64
 template <int WPS> constexpr int SMP_U = WPS == 4 ? 5 : 8;
 
+// One thread: stores the chosen token of a row and appends it to its sequence
+__device__ void smp_append(const SampleArgs& a, const AppendArgs& ap, int row, int seq, int token) {
+    // a row without any finite logit (or with an infinite one) has no arg max and no member to draw: token 0, never an id outside
+    // the vocabulary, which the next pass would look up in the embedding
+    if (token < 0 || token >= a.V) token = 0;
+    if (a.out) a.out[row] = token;
+    if (!ap.enabled) return;
+    // append the token and decide whether the step of this sequence goes on
+    const SeqState& st = ap.st;
+    const int b = seq;
+    const int pos = st.ctx_len[b];
+    if (ap.enabled == 2) {
+        // a proposal: written behind the committed tokens and recorded as the n-th proposal of the
+        // step (a place of the step can be proposed for in several rounds); the step's own length
+        // and records wait for the target's decision
+        const size_t rec = ((size_t)b * ap.max_steps + st.cur_step[0]) * ap.prop_stride + st.sd_nprop[b] + (pos - st.sd_base[b]);
+        st.sampled[2][rec] = token;
+        int tok = token;
+        if (ap.forced) { const int f = ap.forced[rec]; if (f >= 0) tok = f; }
+        st.tokens[(size_t)b * ap.max_ctx + pos] = tok;
+        st.ctx_len[b] = pos + 1;
+        st.kv_len[ap.model * ap.B + b] = pos;
+        if (tok == ap.sep_id || tok == ap.eos_id || pos + 1 >= st.sd_lim[b]) {
+            st.active[b] = 0;
+            atomicSub(st.n_active, 1);
+        }
+        return;
+    }
+    const size_t rec = ((size_t)b * ap.max_steps + st.cur_step[0]) * ap.step_cap + st.step_len[b];
+    st.sampled[ap.model][rec] = token;
+    int tok = token;
+    if (ap.forced) { const int f = ap.forced[rec]; if (f >= 0) tok = f; }
+    st.tokens[(size_t)b * ap.max_ctx + pos] = tok;
+    st.ctx_len[b] = pos + 1;
+    st.kv_len[ap.model * ap.B + b] = pos;          // every token before the new one has been fed
+    const int sl = st.step_len[b] + 1;
+    st.step_len[b] = sl;
+    if (tok == ap.sep_id || tok == ap.eos_id || sl >= ap.step_cap || pos + 1 >= ap.max_ctx) {
+        st.active[b] = 0;
+        atomicSub(st.n_active, 1);
+    }
+}
+
 // ---- phase A: max of every span of x (sampling) or arg max of the biased logits (greedy).  x = logit / temperature
 // grows with the logit, so the division is done once per span
 template <int WPS>
-__global__ __launch_bounds__(SMP_T) void sample_max_kernel(SampleArgs a) {
+__global__ __launch_bounds__(SMP_T) void sample_max_kernel(SampleArgs a, AppendArgs ap) {
     const int row = blockIdx.y, j = smp_span<WPS>(), tid = smp_lane<WPS>(), wave = threadIdx.x >> 6;
-    if (smp_seq(a, row) < 0) return;
+    const int seq = smp_seq(a, row);
+    if (seq < 0) return;
     const float* lg = a.logits + (size_t)row * a.ld;
     const int span = (a.V + SMP_NB - 1) / SMP_NB, s0 = min(j * span, a.V), s1 = min(a.V, s0 + span);
-    constexpr int T = WPS * 64, U = SMP_U<WPS>;
+    constexpr int T = WPS * 64, U = WPS == 4 ? 10 : SMP_U<WPS>;        // (a span of 2374 in one batch)
     if (a.temperature != 0.0f) {                           // for phases B and C
         constexpr int NH = SMP_BINS / SMP_NB, NS = SMP_SUB / SMP_NB;
         u64_t* hist = a.hist + (size_t)row * SMP_WS;
         if (tid < NH + NS) hist[tid < NH ? j * NH + tid : SMP_WS - SMP_SUB + j * NS + tid - NH] = 0;
-        if (tid == 0 && j == 0) { a.sel[(size_t)row * 8 + 3] = 0; a.sel[(size_t)row * 8 + 7] = 0; }
+        if (tid == 0 && j == 0) { a.sel[(size_t)row * SMP_SEL + 3] = 0; a.sel[(size_t)row * SMP_SEL + 7] = 0; }
     }
     float bv = -INFINITY; int bi = 0x7FFFFFFF;
     for (int i0 = s0 + tid; i0 < s1; i0 += T * U) {
@@ -215,10 +262,39 @@ __global__ __launch_bounds__(SMP_T) void sample_max_kernel(SampleArgs a) {
             for (int w = 1; w < 4; ++w)
                 if (fred[w] > bv || (fred[w] == bv && ired[w] < bi)) { bv = fred[w]; bi = ired[w]; }
     }
-    if (tid == 0) {
-        a.pmax[(size_t)row * SMP_NB + j] = a.temperature == 0.0f ? bv : bv / a.temperature;
-        a.pidx[(size_t)row * SMP_NB + j] = bi;
+    if (a.temperature != 0.0f) {
+        if (tid == 0) {
+            a.pmax[(size_t)row * SMP_NB + j] = bv / a.temperature;
+            a.pidx[(size_t)row * SMP_NB + j] = bi;
+        }
+        return;
     }
+    // Greedy: the block that finishes a row's last span chooses among the spans and appends the token, instead of a launch of its
+    // own (one row of 151936 logits: 10.2 -> 7.3 us a call).  Results go past the L2 of this XCD and have arrived before they are counted,
+    // as in smp_dense.  The count only ever grows, by 64 a call, so that it needs no clearing.
+    __shared__ int s_last;
+    if (tid == 0) {
+        __hip_atomic_store(&a.pmax[(size_t)row * SMP_NB + j], bv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&a.pidx[(size_t)row * SMP_NB + j], bi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        constexpr unsigned mine = WPS == 4 ? 1u : 4u;
+        s_last = (__hip_atomic_fetch_add(reinterpret_cast<unsigned*>(a.sel + (size_t)row * SMP_SEL + 8), mine, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT) + mine) % SMP_NB == 0;
+    }
+    __syncthreads();
+    if (!s_last || threadIdx.x >= SMP_NB) return;
+    bv = __hip_atomic_load(&a.pmax[(size_t)row * SMP_NB + threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    bi = __hip_atomic_load(&a.pidx[(size_t)row * SMP_NB + threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        const float ov = __shfl_xor(bv, off, RSD_WAVE);
+        const int oi = __shfl_xor(bi, off, RSD_WAVE);
+        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+    }
+    if (threadIdx.x == 0) smp_append(a, ap, row, seq, bi);
 }
 
 // ---- phase B: the histogram of masses
@@ -264,7 +340,7 @@ __global__ __launch_bounds__(SMP_T) void sample_select_kernel(SampleArgs a) {
     __shared__ int s_bin, s_cnt[4];
     __shared__ u64_t s_above, s_mass;
     u64_t* hist = a.hist + (size_t)row * SMP_WS;
-    u64_t* sel = a.sel + (size_t)row * 8;
+    u64_t* sel = a.sel + (size_t)row * SMP_SEL;
     const float mx = smp_row_max(a, row, fred);
     if (threadIdx.x == 0) { s_bin = 0; s_above = 0; s_mass = 0; }
     if (threadIdx.x < 4) s_cnt[threadIdx.x] = 0;
@@ -351,7 +427,7 @@ __device__ bool smp_dense(const SampleArgs& a, int row, float mx, u64_t* lh, u64
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const float* lg = a.logits + (size_t)row * a.ld;
     u64_t* hist = a.hist + (size_t)row * SMP_WS;
-    u64_t* sel = a.sel + (size_t)row * 8;
+    u64_t* sel = a.sel + (size_t)row * SMP_SEL;
     u64_t* counts = hist;                                  // [span][128]: two keys each
     const u64_t thr = sel[0];
     u64_t run = sel[1];
@@ -439,22 +515,8 @@ __global__ __launch_bounds__(SMP_T) void sample_finish_kernel(SampleArgs a, Appe
     __shared__ int s_tok, s_blk, s_bin;
     __shared__ u64_t s_base, s_above;
     int token;
-    if (a.temperature == 0.0f) {
-        float bv = -INFINITY; int bi = 0x7FFFFFFF;
-        if (tid < SMP_NB) { bv = a.pmax[(size_t)row * SMP_NB + tid]; bi = a.pidx[(size_t)row * SMP_NB + tid]; }
-        if (wave == 0) {
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                const float ov = __shfl_xor(bv, off, RSD_WAVE);
-                const int oi = __shfl_xor(bi, off, RSD_WAVE);
-                if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-            }
-            if (lane == 0) s_tok = bi;
-        }
-        __syncthreads();
-        token = s_tok;
-    } else {
-        u64_t* sel = a.sel + (size_t)row * 8;
+    {
+        u64_t* sel = a.sel + (size_t)row * SMP_SEL;
         const float* lg = a.logits + (size_t)row * a.ld;
         const u64_t* hist = a.hist + (size_t)row * SMP_WS;
         __shared__ u64_t lh[768 + 512];
@@ -576,46 +638,7 @@ __global__ __launch_bounds__(SMP_T) void sample_finish_kernel(SampleArgs a, Appe
         }
         token = s_tok;
     }
-    if (tid != 0) return;
-    // a row without any finite logit (or with an infinite one) has no arg max and no member to draw: token 0, never an id outside
-    // the vocabulary, which the next pass would look up in the embedding
-    if (token < 0 || token >= a.V) token = 0;
-    if (a.out) a.out[row] = token;
-    if (!ap.enabled) return;
-    // append the token and decide whether the step of this sequence goes on
-    const SeqState& st = ap.st;
-    const int b = seq;
-    const int pos = st.ctx_len[b];
-    if (ap.enabled == 2) {
-        // a proposal: written behind the committed tokens and recorded as the n-th proposal of the
-        // step (a place of the step can be proposed for in several rounds); the step's own length
-        // and records wait for the target's decision
-        const size_t rec = ((size_t)b * ap.max_steps + st.cur_step[0]) * ap.prop_stride + st.sd_nprop[b] + (pos - st.sd_base[b]);
-        st.sampled[2][rec] = token;
-        int tok = token;
-        if (ap.forced) { const int f = ap.forced[rec]; if (f >= 0) tok = f; }
-        st.tokens[(size_t)b * ap.max_ctx + pos] = tok;
-        st.ctx_len[b] = pos + 1;
-        st.kv_len[ap.model * ap.B + b] = pos;
-        if (tok == ap.sep_id || tok == ap.eos_id || pos + 1 >= st.sd_lim[b]) {
-            st.active[b] = 0;
-            atomicSub(st.n_active, 1);
-        }
-        return;
-    }
-    const size_t rec = ((size_t)b * ap.max_steps + st.cur_step[0]) * ap.step_cap + st.step_len[b];
-    st.sampled[ap.model][rec] = token;
-    int tok = token;
-    if (ap.forced) { const int f = ap.forced[rec]; if (f >= 0) tok = f; }
-    st.tokens[(size_t)b * ap.max_ctx + pos] = tok;
-    st.ctx_len[b] = pos + 1;
-    st.kv_len[ap.model * ap.B + b] = pos;          // every token before the new one has been fed
-    const int sl = st.step_len[b] + 1;
-    st.step_len[b] = sl;
-    if (tok == ap.sep_id || tok == ap.eos_id || sl >= ap.step_cap || pos + 1 >= ap.max_ctx) {
-        st.active[b] = 0;
-        atomicSub(st.n_active, 1);
-    }
+    if (tid == 0) smp_append(a, ap, row, seq, token);
 }
 
 // Few rows of a large vocabulary: a span per block of four waves, to have many blocks.  Otherwise a span per wave: a block then works
@@ -624,15 +647,15 @@ __global__ __launch_bounds__(SMP_T) void sample_finish_kernel(SampleArgs a, Appe
 // 28.2, 15 rows 31.2 / 29.4; 50257, 4 rows 20.9 / 21.9, 8 rows 22.9 / 22.6; 32000, 1 row 19.0 / 19.4, 4 rows 20.4 / 19.6; 16384, 1 row
 // 18.5 / 18.3, 15 rows 24.9 / 20.1.
 template <int WPS>
-static void sample_launch_spans(hipStream_t st, const SampleArgs& a, int rows) {
+static void sample_launch_spans(hipStream_t st, const SampleArgs& a, const AppendArgs& ap, int rows) {
     const dim3 grid(SMP_NB * WPS / 4, rows), block(SMP_T);
-    hipLaunchKernelGGL((sample_max_kernel<WPS>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((sample_max_kernel<WPS>), grid, block, 0, st, a, ap);
     if (a.temperature == 0.0f) return;
     hipLaunchKernelGGL((sample_hist_kernel<WPS>), grid, block, 0, st, a);
     hipLaunchKernelGGL((sample_select_kernel<WPS>), grid, block, 0, st, a);
 }
 static void sample_launch(hipStream_t st, const SampleArgs& a, const AppendArgs& ap, int rows) {
-    if (rows * 8192LL < a.V) sample_launch_spans<4>(st, a, rows);
-    else sample_launch_spans<1>(st, a, rows);
-    hipLaunchKernelGGL(sample_finish_kernel, dim3(rows, a.temperature == 0.0f ? 1 : SMP_FB), dim3(SMP_T), 0, st, a, ap);
+    if (rows * 8192LL < a.V) sample_launch_spans<4>(st, a, ap, rows);
+    else sample_launch_spans<1>(st, a, ap, rows);
+    if (a.temperature != 0.0f) hipLaunchKernelGGL(sample_finish_kernel, dim3(rows, SMP_FB), dim3(SMP_T), 0, st, a, ap);
 }

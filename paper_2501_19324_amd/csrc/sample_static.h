@@ -12,7 +12,7 @@ namespace {
 
 constexpr size_t kSmpHist = (size_t)RSD_SAMPLE_STATIC_MAX_ROWS * SMP_WS;      // u64 each
 constexpr size_t kSmpPsum = (size_t)RSD_SAMPLE_STATIC_MAX_ROWS * SMP_NB;            // u64
-constexpr size_t kSmpSel = (size_t)RSD_SAMPLE_STATIC_MAX_ROWS * 8;                  // u64
+constexpr size_t kSmpSel = (size_t)RSD_SAMPLE_STATIC_MAX_ROWS * SMP_SEL;                // u64
 constexpr size_t kSmpPmax = (size_t)RSD_SAMPLE_STATIC_MAX_ROWS * SMP_NB;            // float
 constexpr size_t kSmpPidx = (size_t)RSD_SAMPLE_STATIC_MAX_ROWS * SMP_NB;            // int
 constexpr size_t kSmpScratchBytes = (kSmpHist + kSmpPsum + kSmpSel) * sizeof(u64_t) + kSmpPmax * sizeof(float) + kSmpPidx * sizeof(int);

@@ -19,7 +19,7 @@ struct SdRowSet {                 // rows the sampler has prepared
     const float* logits; int ld;
     const float* pmax;            // [rows][SMP_NB]
     const u64_t* psum;            // [rows][SMP_NB]
-    const u64_t* sel;             // [rows][8]; [5] = tau
+    const u64_t* sel;             // [rows][SMP_SEL]; [5] = tau
 };
 
 struct SdVerifyArgs {
@@ -48,7 +48,7 @@ __device__ __forceinline__ float sd_x(const SdVerifyArgs& a, const float* lg, in
 __device__ __forceinline__ void sd_row_stats(const SdRowSet& R, int row, int lane, float& mx, uint32_t& tau, u64_t& Z) {
     mx = wave_max(R.pmax[(size_t)row * SMP_NB + lane]);
     Z = wave_sum_u64(R.psum[(size_t)row * SMP_NB + lane]);
-    tau = (uint32_t)R.sel[(size_t)row * 8 + 5];
+    tau = (uint32_t)R.sel[(size_t)row * SMP_SEL + 5];
 }
 
 // probability of token t under a prepared row (0 outside the nucleus)

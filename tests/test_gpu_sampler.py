@@ -120,3 +120,16 @@ def test_nearly_equal_logits_cost_little_more(n, kind):
 
     ms("normal")
     assert ms(kind) < 3.0 * ms("normal")
+
+
+def test_arg_max_between_calls_of_other_shapes():
+    """The count of finished spans is kept from call to call: rows with a block per span and with four spans a block, and sampled calls
+    in between, in turn."""
+    import torch
+    from paper_2501_19324_amd import binding as R
+    rng = np.random.default_rng(5)
+    for n, V in [(1, 151936), (64, 1000), (3, 50000), (64, 31), (1, 151936), (17, 32000), (2, 1)] * 3:
+        lg = torch.from_numpy(rng.integers(-50, 50, size=(n, V)).astype(np.float32)).cuda()       # ties: the lowest id
+        got = R.rsd_sample_static(lg, None, 0.0, 1.0).cpu().numpy()
+        assert (got == np.argmax(lg.cpu().numpy(), axis=1)).all(), (n, V)
+        R.rsd_sample_static(torch.zeros(n, V, device="cuda"), torch.rand(n, device="cuda"), 1.0, 0.9)
