@@ -12,15 +12,17 @@
 // the path to tau.  A row is cut into SMP_NB spans of the vocabulary; the phases are separate launches:
 //   A  max of every span; clears what B and C add to.  Greedy: arg max of every span, and the block that finishes a row's last
 //      span chooses among them and appends the token
-//   B  histogram of masses over 1792 bins of 1/32 and 1/64 octave (exponent and five or six mantissa bits, 2^-40 .. 1)
+//   B  histogram of masses over 1792 bins of 1/32 and 1/64 octave (exponent and five or six mantissa bits, 2^-40 .. 1); tokens so
+//      light that the threshold cannot lie among them are only added up
 //   C  every block finds the bin tau lies in, sums what lies above it per span and lists the keys inside it (a bin is
 //      1 or 2 % wide: mostly a few hundred keys)
 //   D  one block per row resolves tau among the listed keys (10 + 9 bits), forms the nucleus mass of every span, locates
 //      the draw and appends the token to its sequence.
 // So the logits are read three times and everything after C works on a few hundred keys.  (Three radix levels over the
 // whole row and a fifth pass for the masses, with a 2048-bin histogram cleared and flushed for every 2400 tokens, took
-// 109 us on 64 rows of 151936 logits and 36 on one; this takes 52 and 22.  What bounds it: a division and an exponential
-// per token and pass on many rows - about 10 of the 19 and 18 us of B and C -, the chain of block scans in D on few.)
+// 109 us on 64 rows of 151936 logits and 36 on one.)  What bounds it on many rows: vector instructions of B (9 of 10 cycles) and the
+// reading of the logits, on few rows the chain of block scans in D.  Launches of 64 rows, A to D: 9.5 / 14.8 / 10.6 / 9.3 us; with a
+// bin for every token, a full division and expf for each in B and C 9.5 / 18.2 / 17.2 / 9.3.
 // A bin that may hold more keys than there is room for (nearly equal logits; the bin's mass tells in advance) makes the row
 // "dense": C then adds up sub-bins of 256 keys instead of listing, and D is SMP_FB blocks, which count the keys of the deciding
 // sub-bin span by span; the last of them to finish resolves tau from these counts and goes on alone.  A call on 64 rows
@@ -116,6 +118,82 @@ struct AppendArgs {
 
 __device__ __forceinline__ float smp_x(const SampleArgs& a, const float* lg, int i) {
     return (lg[i] + (i == a.sep_id ? a.sep_bias : 0.0f)) / a.temperature;
+}
+// x of U biased logits.  The division is by the same number for every token: a product with its reciprocal r (rounded to nearest) and two
+// corrections give the correctly rounded quotient in five instructions instead of twelve - the first leaves an error below
+// an ulp, from which the second, by Markstein's theorem, gets the rounded quotient - where nothing in between leaves the normal
+// range: T within 2^-20 .. 2^20 and no |v| above 2^60 (a tiny |v| may come out a tiny bit off, which the difference to
+// the maximum does not show).  Otherwise, infinities among them, it is the plain division.  (NaN, also what an infinity would
+// become, has no mass.)
+template <int U>
+__device__ __forceinline__ void smp_divide(const float (&v)[U], float (&x)[U], float T, float r) {
+    float m = 0.0f;
+#pragma unroll
+    for (int u = 0; u < U; ++u) m = fmaxf(m, fabsf(v[u]));
+    if (T >= 0x1p-20f && T <= 0x1p20f && !__any(m > 0x1p60f)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            float q = v[u] * r;
+            q = fmaf(fmaf(-q, T, v[u]), r, q);
+            x[u] = fmaf(fmaf(-q, T, v[u]), r, q);
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = v[u] / T;
+    }
+}
+// f(i, v) for the biased logits v[u] of tokens i + u * step of [s0, s1), `fill` past the end, i = s0 + lane + multiples of U * step.
+// AHEAD: the next batch is requested before the present one is worked on (two register sets in turn: a copy would wait for the load)
+template <int U, bool AHEAD, typename F>
+__device__ __forceinline__ void smp_scan(const SampleArgs& a, const float* lg, int s0, int s1, int lane, int step, float fill, F f) {
+    auto load = [&](float (&v)[U], int base) {
+        const float* p = lg + base + lane;
+        if (base + U * step <= s1) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = p[u * step];
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = lg[min(base + lane + u * step, s1 - 1)];
+        }
+    };
+    auto use = [&](float (&v)[U], int base) {
+        if (a.sep_id >= base && a.sep_id < base + U * step) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] += base + lane + u * step == a.sep_id ? a.sep_bias : 0.0f;
+        }
+        if (base + U * step > s1) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = base + lane + u * step < s1 ? v[u] : fill;
+        }
+        f(base + lane, v);
+    };
+    if (!AHEAD || s1 - s0 <= U * step) {
+        for (int base = s0; base < s1; base += U * step) {
+            float v[U];
+            load(v, base);
+            use(v, base);
+        }
+    } else {
+        float p[U], q[U];
+        load(p, s0);
+        for (int base = s0;;) {
+            load(q, base + U * step);
+            use(p, base);
+            if ((base += U * step) >= s1) break;
+            load(p, base + U * step);
+            use(q, base);
+            if ((base += U * step) >= s1) break;
+        }
+    }
+}
+// exp(d) of a difference to the maximum, d <= 0: 2^n times the hardware's exponential of the rest of d log2 e, which is known to more than
+// a float's digits (product, its rounding error and the low part of log2 e); n is rounded and shifted into the exponent by one
+// addition each.  Below -80 (no mass; NaN as well) 2^-115.  Three instructions fewer than expf, which also looks after the ends of its range;
+// as accurate (largest relative error 8.32e-8, rms 2.10e-8 over all floats of -28 .. -1e-6 for both).
+__device__ __forceinline__ float smp_exp(float d) {
+    const float c = fmaxf(d, -80.0f), y = 1.44269502f * c, m = y + 12582912.0f, n = m - 12582912.0f;
+    const float t = (y - n) + fmaf(1.92596303e-8f, c, fmaf(1.44269502f, c, -y));
+    return __uint_as_float((__float_as_uint(m) << 23) + __float_as_uint(__builtin_amdgcn_exp2f(t)));
 }
 __device__ __forceinline__ u64_t smp_fix(float e) { return (u64_t)(e * 1099511627776.0f); }   // e * 2^40, e in [0, 1]
 
@@ -228,7 +306,7 @@ __global__ __launch_bounds__(SMP_T) void sample_max_kernel(SampleArgs a, AppendA
     if (seq < 0) return;
     const float* lg = a.logits + (size_t)row * a.ld;
     const int span = (a.V + SMP_NB - 1) / SMP_NB, s0 = min(j * span, a.V), s1 = min(a.V, s0 + span);
-    constexpr int T = WPS * 64, U = WPS == 4 ? 10 : SMP_U<WPS>;        // (a span of 2374 in one batch)
+    constexpr int T = WPS * 64, U = SMP_U<WPS>;
     if (a.temperature != 0.0f) {                           // for phases B and C
         constexpr int NH = SMP_BINS / SMP_NB, NS = SMP_SUB / SMP_NB;
         u64_t* hist = a.hist + (size_t)row * SMP_WS;
@@ -236,17 +314,11 @@ __global__ __launch_bounds__(SMP_T) void sample_max_kernel(SampleArgs a, AppendA
         if (tid == 0 && j == 0) { a.sel[(size_t)row * SMP_SEL + 3] = 0; a.sel[(size_t)row * SMP_SEL + 7] = 0; }
     }
     float bv = -INFINITY; int bi = 0x7FFFFFFF;
-    for (int i0 = s0 + tid; i0 < s1; i0 += T * U) {
-        float v[U];
+    smp_scan<U, false>(a, lg, s0, s1, tid, T, -INFINITY, [&](int i, const float (&v)[U]) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = lg[min(i0 + u * T, s1 - 1)];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = min(i0 + u * T, s1 - 1);
-            if (i == a.sep_id) v[u] += a.sep_bias;
-            if (v[u] > bv) { bv = v[u]; bi = i; }
-        }
-    }
+        for (int u = 0; u < U; ++u)
+            if (v[u] > bv) { bv = v[u]; bi = i + u * T; }
+    });
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
         const float ov = __shfl_xor(bv, off, RSD_WAVE);
@@ -310,17 +382,84 @@ __global__ __launch_bounds__(SMP_T) void sample_hist_kernel(SampleArgs a) {
     for (int b = threadIdx.x; b < SMP_BINS; b += SMP_T) lh[b] = 0;
     const float mx = smp_row_max(a, row, fred);           // (holds a barrier)
     constexpr int T = WPS * 64, U = SMP_U<WPS>;
-    for (int i0 = s0 + tid; i0 < s1; i0 += T * U) {
-        float x[U];
+    const float rT = 1.0f / a.temperature;
+    // The mass reached from the top is at least top_p of a total of at least 1 (the maximum's own e), so tokens that even all together
+    // have less than 1 - top_p need no bin of their own: those below `tail` are only added up, in registers (exactly: less than
+    // 2^28 + 2^26 units a lane) and at the end in the lowest bin.  For 151936 tokens and 0.95 that is e < 2^-22: nearly all of them
+    const float rest = 0.99f * (1.0f - a.top_p) / (float)a.V;
+    const uint32_t tail = min(max(__float_as_uint(rest) & 0x7F800000u, SMP_UNIT), 0x38800000u);      // (2^-14)
+    uint32_t low = 0;
+    // the others are few, then, in most waves: a batch's are listed, without a branch (lanes with nothing to list write to a slot
+    // nobody reads), and added to the histogram 64 at a time; where half of a batch is above the tail, at once
+    // (few rows and short spans are bound by latency, which the sum over the lanes adds to: there, and where there is no tail, all are
+    // added at once)
+    constexpr int LIST = WPS == 1 ? 64 + 32 * U : 0;
+    const bool lists = WPS == 1 && tail > SMP_UNIT && span > U * T;
+    __shared__ uint32_t s_list[4][LIST + 64];
+    uint32_t* list = s_list[threadIdx.x >> 6];
+    const int lane = threadIdx.x & 63;
+    int n = 0;
+    auto add = [&](uint32_t key) { atomicAdd(&lh[smp_bin(key)], smp_fix(__uint_as_float(key))); };
+    smp_scan<U, false>(a, lg, s0, s1, tid, T, __builtin_nanf(""), [&](int i, const float (&v)[U]) {
+        if (s1 - (i - tid) <= U / 2 * T) {                  // (a short end: only what is there, as it comes)
 #pragma unroll
-        for (int u = 0; u < U; ++u) x[u] = smp_x(a, lg, min(i0 + u * T, s1 - 1));
+            for (int u = 0; u < U / 2; ++u) {
+                if (s1 - (i - tid) <= u * T) break;
+                const uint32_t key = __float_as_uint(smp_exp(v[u] / a.temperature - mx));
+                low += key >= tail ? 0u : (uint32_t)(__uint_as_float(key) * 1099511627776.0f);
+                if (key >= tail) add(key);
+            }
+            return;
+        }
+        float x[U];
+        uint32_t key[U];
+        int above = 0;
+        smp_divide<U>(v, x, a.temperature, rT);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const float e = expf(x[u] - mx);
-            const u64_t f = smp_fix(e);
-            if (f && i0 + u * T < s1) atomicAdd(&lh[smp_bin(__float_as_uint(e))], f);
+            const float e = smp_exp(x[u] - mx);
+            key[u] = __float_as_uint(e);
+            above += key[u] >= tail;
+            low += key[u] >= tail ? 0u : (uint32_t)(e * 1099511627776.0f);
         }
-    }
+        if (!lists) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) if (key[u] >= tail) add(key[u]);
+            return;
+        }
+        int at = above;                                    // inclusive sum over the lanes
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int o = __shfl_up(at, d, RSD_WAVE);
+            if (lane >= d) at += o;
+        }
+        const int k = __builtin_amdgcn_readlane(at, 63);
+        if (k == 0) return;
+        if (k > 32 * U) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) if (key[u] >= tail) add(key[u]);
+            return;
+        }
+        at += n - above;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool in = key[u] >= tail;
+            list[in ? at : LIST + lane] = key[u];
+            at += in;
+        }
+        n += k;
+        while (n >= 64) {
+            n -= 64;
+            add(list[n + lane]);
+        }
+    });
+    if (lists && lane < n) add(list[lane]);
+    // (eight lanes at a time: less than 2^32)
+    auto dpp = [](uint32_t x, auto ctrl) { return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, 0xF, 0xF, true); };
+    low = dpp(low, std::integral_constant<int, 0xB1>{});       // quad_perm [1,0,3,2]
+    low = dpp(low, std::integral_constant<int, 0x4E>{});       // quad_perm [2,3,0,1]
+    low = dpp(low, std::integral_constant<int, 0x141>{});      // row_half_mirror
+    if ((threadIdx.x & 7) == 0 && low) atomicAdd(&lh[0], (u64_t)low);
     __syncthreads();
     for (int b = threadIdx.x; b < SMP_BINS; b += SMP_T)
         if (lh[b]) atomicAdd(&hist[b], lh[b]);
@@ -372,26 +511,26 @@ __global__ __launch_bounds__(SMP_T) void sample_select_kernel(SampleArgs a) {
         for (int b = threadIdx.x; b < SMP_SUB; b += SMP_T) lds[b] = 0;
         __syncthreads();
     }
+    // A logit below cut is outside for certain: the margin is far above the rounding of quotient, difference, exponential and of cut
+    // itself.  Most tokens are (a nucleus of top_p 0.95 is some hundred of 151936), so that a wave seldom has to form one's key.
+    // (Not a number, from an infinite maximum: nothing is below it.)
+    const float x_lo = mx + __logf(__uint_as_float(lo)), cut = (x_lo - (1e-3f + 1e-5f * (fabsf(mx) + fabsf(x_lo)))) * a.temperature;
     uint32_t* lists = reinterpret_cast<uint32_t*>(hist + SMP_BINS);
     uint32_t* list = lists + j * SMP_LIST;
     int* cnt = &s_cnt[WPS == 4 ? 0 : wave];
     u64_t acc = 0;
     constexpr int T = WPS * 64, U = WPS == 4 ? SMP_U<4> : 6;        // (eight spill)
     auto scan = [&](auto inside) {
-        for (int i0 = s0 + tid; i0 < s1; i0 += T * U) {
-            float x[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) x[u] = smp_x(a, lg, min(i0 + u * T, s1 - 1));
+        smp_scan<U, true>(a, lg, s0, s1, tid, T, -INFINITY, [&](int, const float (&v)[U]) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const float e = expf(x[u] - mx);
+                if (!__any(!(v[u] < cut))) continue;
+                const float e = smp_exp(v[u] / a.temperature - mx);
                 const uint32_t key = __float_as_uint(e);
-                if (i0 + u * T < s1) {
-                    if (key >= hi) acc += smp_fix(e);
-                    else if (key >= lo) inside(key);
-                }
+                if (key >= hi) acc += smp_fix(e);
+                else if (key >= lo) inside(key);
             }
-        }
+        });
     };
     if (dense)
         scan([&](uint32_t key) { smp_add_tied(&lds[(key - lo) >> 8], key, smp_fix(__uint_as_float(key))); });
@@ -446,7 +585,7 @@ __device__ bool smp_dense(const SampleArgs& a, int row, float mx, u64_t* lh, u64
         for (int u = 0; u < 8; ++u) x[u] = smp_x(a, lg, min(i0 + lane + u * 64, s1 - 1));
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const float e = expf(x[u] - mx);
+            const float e = smp_exp(x[u] - mx);
             const uint32_t key = __float_as_uint(e);
             if (i0 + lane + u * 64 < s1) {
                 if (key >= hi) acc += smp_fix(e);
@@ -613,7 +752,7 @@ __global__ __launch_bounds__(SMP_T) void sample_finish_kernel(SampleArgs a, Appe
             for (int u = 0; u < 10; ++u) x[u] = smp_x(a, lg, min(i0 + u, t1 - 1));
 #pragma unroll
             for (int u = 0; u < 10; ++u) {
-                const float e = expf(x[u] - mx);
+                const float e = smp_exp(x[u] - mx);
                 if (i0 + u < t1 && __float_as_uint(e) >= tau) { mine += smp_fix(e); last_member = i0 + u; }
             }
         }
@@ -621,7 +760,7 @@ __global__ __launch_bounds__(SMP_T) void sample_finish_kernel(SampleArgs a, Appe
         if (mine && incl > target && incl - mine <= target) {
             u64_t run = incl - mine;
             for (int i = t0; i < t1; ++i) {
-                const float e = expf(smp_x(a, lg, i) - mx);
+                const float e = smp_exp(smp_x(a, lg, i) - mx);
                 if (__float_as_uint(e) >= tau) { run += smp_fix(e); if (run > target) { s_tok = i; break; } }
             }
         }

@@ -53,7 +53,7 @@ __device__ __forceinline__ void sd_row_stats(const SdRowSet& R, int row, int lan
 
 // probability of token t under a prepared row (0 outside the nucleus)
 __device__ __forceinline__ double sd_prob(const SdVerifyArgs& a, const SdRowSet& R, int row, int t, float mx, uint32_t tau, u64_t Z) {
-    const float e = expf(sd_x(a, R.logits + (size_t)row * R.ld, t) - mx);
+    const float e = smp_exp(sd_x(a, R.logits + (size_t)row * R.ld, t) - mx);
     return __float_as_uint(e) >= tau ? (double)smp_fix(e) / (double)Z : 0.0;
 }
 

@@ -122,6 +122,33 @@ def test_nearly_equal_logits_cost_little_more(n, kind):
     assert ms(kind) < 3.0 * ms("normal")
 
 
+@pytest.mark.parametrize("kind", ["normal", "low", "wide", "masked"])
+@pytest.mark.parametrize("n,V", [(19, 151936), (10, 70001)])
+@pytest.mark.parametrize("T,top_p", [(0.7, 0.95), (1.0, 0.3), (0.6, 0.999)])
+def test_tokens_too_light_for_a_bin(kind, n, V, T, top_p):
+    """Spans of more than one batch on many rows, where tokens below the tail are only added up and those above it listed.
+    (Not of 151936 nearly equal logits: with top_p 0.3 several of their distinct fp64 masses at the edge are one fp32 key, where the
+    check accepts the edge's neighbours only.)"""
+    test_draws_lie_where_the_distribution_puts_them(kind, n, V, T, top_p)
+
+
+@pytest.mark.parametrize("n,V", [(2, 151936), (20, 151936), (33, 1027)])
+def test_quotients_do_not_depend_on_the_way_they_are_formed(n, V):
+    """Logits and temperature times 2^61 have the same quotients, but leave the range of the division by reciprocal."""
+    import torch
+    from paper_2501_19324_amd import binding as R
+    rng = np.random.default_rng(n)
+    lg = torch.from_numpy((rng.normal(size=(n, V)) * 3).astype(np.float32)).cuda()
+    lg[:, V // 3] = -torch.inf
+    for T in (0.7, 1.3):
+        T = float(np.float32(T))
+        for i in range(4):
+            u = torch.from_numpy(rng.random(n).astype(np.float32)).cuda()
+            a = R.rsd_sample_static(lg, u, T, 0.9).cpu().numpy()
+            b = R.rsd_sample_static(lg * 2.0 ** 61, u, T * 2.0 ** 61, 0.9).cpu().numpy()
+            assert (a == b).all(), (T, i)
+
+
 def test_arg_max_between_calls_of_other_shapes():
     """The count of finished spans is kept from call to call: rows with a block per span and with four spans a block, and sampled calls
     in between, in turn."""
