@@ -68,6 +68,20 @@ __global__ void gather_rows_kernel(const float* __restrict__ src, const int* __r
         *reinterpret_cast<float4*>(dst + (size_t)i * d + k) = *reinterpret_cast<const float4*>(src + (size_t)r * d + k);
 }
 
+// Rows of V values, row r to place row_seq[r] * T + row_pos[r] of dst: the logits of a pass over several sequences, multiplied together,
+// at the places of their tokens.  Grid (rows, parts of a row).
+__global__ __launch_bounds__(256) void scatter_rows_kernel(const float* __restrict__ src, int V, const int* __restrict__ row_seq,
+                                                           const int* __restrict__ row_pos, int T, float* __restrict__ dst) {
+    const int r = blockIdx.x, step = blockDim.x * gridDim.y, i0 = blockIdx.y * blockDim.x + threadIdx.x;
+    const float* s = src + (size_t)r * V;
+    float* d = dst + ((size_t)row_seq[r] * T + row_pos[r]) * V;
+    if (V % 4 == 0 && (reinterpret_cast<uintptr_t>(dst) & 15) == 0) {
+        for (int i = i0 * 4; i < V; i += step * 4) *reinterpret_cast<float4*>(d + i) = *reinterpret_cast<const float4*>(s + i);
+    } else {
+        for (int i = i0; i < V; i += step) d[i] = s[i];
+    }
+}
+
 // Diagnostic: do the page tables on the device cover what a pass over these rows will touch?  A row in use at
 // (seq, pos) reads the pages 0 .. pos / RSD_PAGE of its sequence and writes into the last of them, so the
 // sequence must own that many pages and every entry up to there must name a page of the pool.  The first

@@ -2313,6 +2313,17 @@ int forward_impl(rsd_ctx* c, int which, const int32_t* tokens_host, const int32_
                 if (s0 < lens[b]) pieces.push_back(Piece{b, s0, std::min(lens[b], s0 + chunk)});
             auto after = [&](const std::vector<Piece>& pass, const std::vector<int>& first, int M) {
                 if (!lm) reward_rows<WT>(c, m, c->h, M, nullptr, c->tmp_reward);
+                // Short pieces of several sequences go through the head together, by way of the gate/up workspace, instead of
+                // reading its weights once per piece (four pieces of 8 rows, a head of 16384 x 3584: 96 -> 32 us); the copy costs more than that from
+                // about 64 rows a piece.  Single rows keep the kernel that takes their activations in fp32.
+                size_t shortest = M;
+                for (const Piece& pc : pass) shortest = std::min<size_t>(shortest, pc.end - pc.start);
+                if (lm && pass.size() > 1 && shortest > 1 && (size_t)M < 64 * pass.size() && (size_t)M * V <= (size_t)c->ws_rows * 2 * m.s.d_ffn) {
+                    lm_head<WT>(c, m, c->h, M, c->gu, V);
+                    hipLaunchKernelGGL(scatter_rows_kernel, dim3(M, std::max(1, std::min(16, V / 4096))), dim3(256), 0, c->st, c->gu, V, c->row_seq_dev,
+                                       c->row_pos_dev, T, out);
+                    return RSD_OK;
+                }
                 for (size_t i = 0; i < pass.size(); ++i) {
                     const Piece& pc = pass[i];
                     const int n = pc.end - pc.start;

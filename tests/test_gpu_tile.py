@@ -200,3 +200,23 @@ def test_silu_keeps_fp32_accuracy():
     x = run(g, np.ones(512, np.float32))
     assert not np.isfinite(x[0]) and np.isnan(x[1]) and np.isnan(x[2]) and x[3] == 0 and x[4] == 0 and x[5] == np.float32(3e38)
     assert abs(x[6] - 5e-41) < 1e-44 and x[7] == 0 and x[8] == 105.0 and not x[9:].any()
+
+
+@pytest.mark.parametrize("vocab", [1001, 4096])
+@pytest.mark.parametrize("chunk", [2, 7, 40])
+def test_short_pieces_share_the_head(vocab, chunk):
+    """Chunked evaluation of several ragged sequences, whose pieces go through the output head together, against the same
+    sequences one at a time; with and without pieces of a single row; nothing is written behind the end of a sequence."""
+    from rsd_inputs import ModelShape
+    shape = ModelShape(2, 640, 5, 5, 448, vocab)
+    toks = np.random.default_rng(vocab + chunk).integers(0, vocab, (3, 41)).astype(np.int32)
+    R, ctx = build(shape, vocab, 64, batch=3)
+    R1, one = build(shape, vocab, 64)
+    for lens in ([41, 40, 41], [41, 22, 9], [36, 1, 29]):
+        out = R.rsd_forward(ctx, 0, toks, np.array(lens, np.int32), chunk).cpu().numpy()
+        for b, n in enumerate(lens):
+            ref = R1.rsd_forward(one, 0, toks[b:b + 1], np.array([n], np.int32), chunk).cpu().numpy()[0]
+            assert np.max(np.abs(out[b, :n] - ref[:n])) < TOL / 4, (lens, b)       # (logits of rms 0.5)
+            assert np.isnan(out[b, n:]).all()
+    R.rsd_destroy(ctx)
+    R1.rsd_destroy(one)
