@@ -2267,6 +2267,16 @@ extern "C" int rsd_debug_silu(const float* g_dev, const float* u_dev, float* x_d
     hipLaunchKernelGGL(debug_silu_kernel, dim3(ceil_div(n, 256)), dim3(256), 0, nullptr, g_dev, u_dev, x_dev, n);
     return hipDeviceSynchronize() == hipSuccess ? RSD_OK : RSD_EHIP;
 }
+// the sampler's exponential alone, beside the library's
+__global__ void debug_smp_exp_kernel(const float* __restrict__ d, float* __restrict__ e, float* __restrict__ lib, int n) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) { e[i] = smp_exp(d[i]); lib[i] = expf(d[i]); }
+}
+extern "C" int rsd_debug_smp_exp(const float* d_dev, float* e_dev, float* lib_dev, int32_t n) {
+    if (!d_dev || !e_dev || !lib_dev || n < 1) return RSD_EINVAL;
+    hipLaunchKernelGGL(debug_smp_exp_kernel, dim3(ceil_div(n, 256)), dim3(256), 0, nullptr, d_dev, e_dev, lib_dev, n);
+    return hipDeviceSynchronize() == hipSuccess ? RSD_OK : RSD_EHIP;
+}
 #endif
 
 // --------------------------------------------------------------------------- rsd_forward

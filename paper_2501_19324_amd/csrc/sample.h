@@ -188,9 +188,11 @@ __device__ __forceinline__ void smp_scan(const SampleArgs& a, const float* lg, i
 }
 // exp(d) of a difference to the maximum, d <= 0: 2^n times the hardware's exponential of the rest of d log2 e, which is known to more than
 // a float's digits (product, its rounding error and the low part of log2 e); n is rounded and shifted into the exponent by one
-// addition each.  Below -80 (no mass; NaN as well) 2^-115.  Three instructions fewer than expf, which also looks after the ends of its range;
-// as accurate (largest relative error 8.32e-8, rms 2.10e-8 over all floats of -28 .. -1e-6 for both).
+// addition each.  Below -80 (no mass; NaN as well) 2^-115.  Three instructions fewer than expf, which also looks after the ends of its range.
+// No contraction: y stands for the rounded product in both of its places.  (Fused into y - n, the product would bring in there the
+// rounding error that the other term adds: 1.4e-6 off at -28, 7e-7 at -15.)
 __device__ __forceinline__ float smp_exp(float d) {
+#pragma clang fp contract(off)
     const float c = fmaxf(d, -80.0f), y = 1.44269502f * c, m = y + 12582912.0f, n = m - 12582912.0f;
     const float t = (y - n) + fmaf(1.92596303e-8f, c, fmaf(1.44269502f, c, -y));
     return __uint_as_float((__float_as_uint(m) << 23) + __float_as_uint(__builtin_amdgcn_exp2f(t)));

@@ -160,3 +160,42 @@ def test_arg_max_between_calls_of_other_shapes():
         got = R.rsd_sample_static(lg, None, 0.0, 1.0).cpu().numpy()
         assert (got == np.argmax(lg.cpu().numpy(), axis=1)).all(), (n, V)
         R.rsd_sample_static(torch.zeros(n, V, device="cuda"), torch.rand(n, device="cuda"), 1.0, 0.9)
+
+
+def debug_library():
+    import ctypes
+    import os
+    from paper_2501_19324_amd import binding as R
+    return ctypes.CDLL(os.path.join(os.path.dirname(R.LIB_PATH), "librsd_debug.so"))
+
+
+def test_exponential_is_as_accurate_as_the_library_s():
+    """The sampler's exponential (the debug build exposes it) over the differences that carry mass, -28 .. 0, against 64 bits, and
+    expf on the same values.  Bound: the argument is exact to 2^-25 of an octave (n is an integer, the rest is at most 1/2 and known to
+    2^-26, its sum rounds once more), which is 0.7 x 2^-25 = 2.1e-8 of the value, and the hardware's exponential is good to one ulp of
+    a number in [0.7, 1.42), 2^-24 / 0.7 = 8.5e-8 at the worst: 1.1e-7.  An argument with the product's rounding error counted twice
+    is up to 1.4e-6 off.  What is below -80, and what is no number, has no mass."""
+    import ctypes
+    import torch
+    dbg = debug_library()
+
+    def run(d):
+        d = torch.from_numpy(d).cuda()
+        e, lib = torch.empty_like(d), torch.empty_like(d)
+        torch.cuda.synchronize()
+        assert dbg.rsd_debug_smp_exp(*(ctypes.c_void_p(t.data_ptr()) for t in (d, e, lib)), d.numel()) == 0
+        return e.cpu().numpy(), lib.cpu().numpy()
+
+    rng = np.random.default_rng(0)
+    for lo, hi in ((-28.0, -16.0), (-16.0, -8.0), (-8.0, -4.0), (-4.0, -1.0), (-1.0, 0.0), (-1e-3, 0.0)):
+        d = rng.uniform(lo, hi, 1 << 21).astype(np.float32)
+        e, lib = run(d)
+        want = np.exp(d.astype(np.float64))
+        err, ref = (np.abs(x - want) / want for x in (e, lib))
+        assert err.max() < 1.1e-7, (lo, hi, err.max())
+        assert err.max() < 1.05 * ref.max() and np.sqrt(np.mean(err ** 2)) < 1.01 * np.sqrt(np.mean(ref ** 2)), (lo, hi)
+        assert e.max() <= 1.0
+    d = np.float32([0.0, -0.0, -27.0, -81.0, -1e30, -np.inf, np.nan, np.inf - np.inf])
+    e, _ = run(d)
+    assert e[0] == 1.0 and e[1] == 1.0 and abs(e[2] / np.exp(-27.0) - 1.0) < 1.1e-7
+    assert (e[3:] < 2.0 ** -40).all() and (e[3:] > 0.0).all()
