@@ -2325,18 +2325,21 @@ int forward_impl(rsd_ctx* c, int which, const int32_t* tokens_host, const int32_
                 if (!lm) reward_rows<WT>(c, m, c->h, M, nullptr, c->tmp_reward);
                 // Short pieces of several sequences go through the head together, by way of the gate/up workspace, instead of
                 // reading its weights once per piece (four pieces of 8 rows, a head of 16384 x 3584: 96 -> 32 us); the copy costs more than that from
-                // about 64 rows a piece.  Single rows keep the kernel that takes their activations in fp32.
-                size_t shortest = M;
-                for (const Piece& pc : pass) shortest = std::min<size_t>(shortest, pc.end - pc.start);
-                if (lm && pass.size() > 1 && shortest > 1 && (size_t)M < 64 * pass.size() && (size_t)M * V <= (size_t)c->ws_rows * 2 * m.s.d_ffn) {
+                // about 64 rows a piece.  Single rows keep the kernel that takes their activations in fp32: it writes over the place that
+                // the common product has filled.
+                size_t n_many = 0, many = 0;         // pieces of two or more rows, and their rows
+                for (const Piece& pc : pass)
+                    if (pc.end - pc.start > 1) { ++n_many; many += pc.end - pc.start; }
+                const bool shared = lm && n_many > 1 && many < 64 * n_many && (size_t)M * V <= (size_t)c->ws_rows * 2 * m.s.d_ffn;
+                if (shared) {
                     lm_head<WT>(c, m, c->h, M, c->gu, V);
                     hipLaunchKernelGGL(scatter_rows_kernel, dim3(M, std::max(1, std::min(16, V / 4096))), dim3(256), 0, c->st, c->gu, V, c->row_seq_dev,
                                        c->row_pos_dev, T, out);
-                    return RSD_OK;
                 }
                 for (size_t i = 0; i < pass.size(); ++i) {
                     const Piece& pc = pass[i];
                     const int n = pc.end - pc.start;
+                    if (shared && n > 1) continue;
                     if (lm) lm_head<WT>(c, m, c->h + (size_t)first[i] * m.s.d_model, n, out + ((size_t)pc.b * T + pc.start) * V, V);
                     else HIPCHK(c, hipMemcpyAsync(out + (size_t)pc.b * T + pc.start, c->tmp_reward + first[i], n * sizeof(float), hipMemcpyDeviceToDevice, c->st));
                 }

@@ -220,3 +220,26 @@ def test_short_pieces_share_the_head(vocab, chunk):
             assert np.isnan(out[b, n:]).all()
     R.rsd_destroy(ctx)
     R1.rsd_destroy(one)
+
+
+def test_a_piece_of_one_row_leaves_the_others_their_shared_head():
+    """32 sequences in chunks of 5, a head of 65536 x 1536 (200 MB): where one of them ends on a single row the others still share
+    the head.  That row costs the head's weights once more (by bytes 35 us; a pass over 160 rows takes several times as
+    long); one product per sequence made the pass four times as long.  Shortest of ten calls each."""
+    import time
+    from rsd_inputs import ModelShape
+    R, ctx = build(ModelShape(1, 1536, 12, 2, 8960, 65536), 65536, 16, batch=32)
+    toks = np.random.default_rng(0).integers(0, 65536, (32, 10)).astype(np.int32)
+
+    def seconds(lens):
+        best = 1e9
+        for _ in range(11):
+            t0 = time.perf_counter()
+            R.rsd_forward(ctx, 0, toks, lens, 5)
+            best = min(best, time.perf_counter() - t0)
+        return best
+
+    even, odd = np.full(32, 10, np.int32), np.full(32, 10, np.int32)
+    odd[13] = 6
+    assert seconds(odd) < 1.3 * seconds(even)
+    R.rsd_destroy(ctx)
