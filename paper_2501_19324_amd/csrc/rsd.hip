@@ -2325,11 +2325,13 @@ int forward_impl(rsd_ctx* c, int which, const int32_t* tokens_host, const int32_
                 if (!lm) reward_rows<WT>(c, m, c->h, M, nullptr, c->tmp_reward);
                 // Short pieces of several sequences go through the head together, by way of the gate/up workspace, instead of
                 // reading its weights once per piece (four pieces of 8 rows, a head of 16384 x 3584: 96 -> 32 us); the copy costs more than that from
-                // about 64 rows a piece.  Single rows keep the kernel that takes their activations in fp32: it writes over the place that
-                // the common product has filled.
-                size_t n_many = 0, many = 0;         // pieces of two or more rows, and their rows
+                // about 64 rows a piece.  Pieces of few enough rows for the vector kernel (one; fp32 weights: eight) keep it, for its fp32
+                // activations and its sums over 64 lanes (fp32, four pieces of 4 rows, 1536 wide: 1.75e-6 off, 1.89e-6 in the common product, and
+                // 1462 us against 1617): they write over the places that the common product has filled.
+                auto by_vector = [&](int n) { return n <= 8 && !rows_path<WT>(m, n); };
+                size_t n_many = 0, many = 0;         // the other pieces, and their rows
                 for (const Piece& pc : pass)
-                    if (pc.end - pc.start > 1) { ++n_many; many += pc.end - pc.start; }
+                    if (!by_vector(pc.end - pc.start)) { ++n_many; many += pc.end - pc.start; }
                 const bool shared = lm && n_many > 1 && many < 64 * n_many && (size_t)M * V <= (size_t)c->ws_rows * 2 * m.s.d_ffn;
                 if (shared) {
                     lm_head<WT>(c, m, c->h, M, c->gu, V);
@@ -2339,7 +2341,7 @@ int forward_impl(rsd_ctx* c, int which, const int32_t* tokens_host, const int32_
                 for (size_t i = 0; i < pass.size(); ++i) {
                     const Piece& pc = pass[i];
                     const int n = pc.end - pc.start;
-                    if (shared && n > 1) continue;
+                    if (shared && !by_vector(n)) continue;
                     if (lm) lm_head<WT>(c, m, c->h + (size_t)first[i] * m.s.d_model, n, out + ((size_t)pc.b * T + pc.start) * V, V);
                     else HIPCHK(c, hipMemcpyAsync(out + (size_t)pc.b * T + pc.start, c->tmp_reward + first[i], n * sizeof(float), hipMemcpyDeviceToDevice, c->st));
                 }

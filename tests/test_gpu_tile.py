@@ -243,3 +243,38 @@ def test_a_piece_of_one_row_leaves_the_others_their_shared_head():
     odd[13] = 6
     assert seconds(odd) < 1.3 * seconds(even)
     R.rsd_destroy(ctx)
+
+
+@pytest.mark.parametrize("chunk", [2, 3, 8, 9])
+def test_fp32_pieces_of_few_rows_keep_their_head(chunk):
+    """fp32 weights: pieces of up to eight rows go through the output head by themselves, in the kernel whose sums are more accurate,
+    beside a piece of one row and (chunk 9) longer ones that share theirs.  All layer weights are zero, so that the hidden
+    rows are the embeddings bit for bit, and the logits of such a piece do not depend on its neighbours either."""
+    import torch
+    from dataclasses import replace
+    from rsd_inputs import ModelShape, blob_layout
+    from paper_2501_19324_amd import binding as R
+    vocab, B = 1000, 5
+    shape = ModelShape(1, 1536, 12, 2, 64, vocab, "f32")
+    layout, total = blob_layout(shape)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    blob = torch.zeros(total, device="cuda")
+    for name, r, c, off in layout:
+        if not name.startswith("l0.") or "norm" in name:
+            blob[off:off + r * c].normal_(1.0 if "norm" in name else 0.0, 0.02, generator=g)
+    stub = ModelShape(1, 128, 1, 1, 64, vocab, "f32")
+    shapes = [shape, stub, replace(stub, head_kind="reward")]
+    blobs = [blob] + [torch.zeros(blob_layout(s)[1], device="cuda") for s in shapes[1:]]
+    torch.cuda.synchronize()
+    ctx, one = (R.rsd_init(shapes, blobs, batch=b, delta=0.5, sep_id=vocab - 1, step_cap=1, max_steps=1, max_ctx=40) for b in (B, 1))
+    toks = np.random.default_rng(chunk).integers(0, vocab, (B, 2 * chunk)).astype(np.int32)
+    lens = np.array([2 * chunk, 2 * chunk - 1, 2 * chunk, chunk + 1, 2 * chunk], np.int32)
+    out = R.rsd_forward(ctx, 0, toks, lens, chunk)
+    for b, n in enumerate(lens):
+        ref = R.rsd_forward(one, 0, toks[b:b + 1, :n].copy(), lens[b:b + 1], chunk)[0]
+        for s in range(0, n, chunk):
+            e = min(s + chunk, n)
+            assert torch.equal(out[b, s:e], ref[s:e]) if e - s <= 8 else float((out[b, s:e] - ref[s:e]).abs().max()) < 1e-5, (b, s)
+        assert bool(torch.isnan(out[b, n:]).all())
+    R.rsd_destroy(ctx)
+    R.rsd_destroy(one)
