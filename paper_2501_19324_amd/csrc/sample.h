@@ -402,6 +402,11 @@ __global__ __launch_bounds__(SMP_T) void sample_hist_kernel(SampleArgs a) {
     const int lane = threadIdx.x & 63;
     int n = 0;
     auto add = [&](uint32_t key) { atomicAdd(&lh[smp_bin(key)], smp_fix(__uint_as_float(key))); };
+    // the list is exchanged between the lanes of a wave, whose LDS operations stay in order: this keeps the compiler's (no instruction)
+    auto order = [] {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
     smp_scan<U, false>(a, lg, s0, s1, tid, T, __builtin_nanf(""), [&](int i, const float (&v)[U]) {
         if (s1 - (i - tid) <= U / 2 * T) {                  // (a short end: only what is there, as it comes)
 #pragma unroll
@@ -450,10 +455,12 @@ __global__ __launch_bounds__(SMP_T) void sample_hist_kernel(SampleArgs a) {
             at += in;
         }
         n += k;
+        order();                                           // other lanes' entries are read below ...
         while (n >= 64) {
             n -= 64;
             add(list[n + lane]);
         }
+        order();                                           // ... and written over by the next batch
     });
     if (lists && lane < n) add(list[lane]);
     // (eight lanes at a time: less than 2^32)
