@@ -2277,6 +2277,20 @@ extern "C" int rsd_debug_smp_exp(const float* d_dev, float* e_dev, float* lib_de
     hipLaunchKernelGGL(debug_smp_exp_kernel, dim3(ceil_div(n, 256)), dim3(256), 0, nullptr, d_dev, e_dev, lib_dev, n);
     return hipDeviceSynchronize() == hipSuccess ? RSD_OK : RSD_EHIP;
 }
+// the sampler's division by one number: q[i] = v[i] / T, n a multiple of 8 (a thread's values)
+__global__ void debug_smp_divide_kernel(const float* __restrict__ v, float T, float* __restrict__ q, int n) {
+    const int i = (blockIdx.x * blockDim.x + threadIdx.x) * 8;
+    if (i >= n) return;
+    float a[8], x[8];
+    for (int u = 0; u < 8; ++u) a[u] = v[i + u];
+    smp_divide<8>(a, x, T, 1.0f / T);
+    for (int u = 0; u < 8; ++u) q[i + u] = x[u];
+}
+extern "C" int rsd_debug_smp_divide(const float* v_dev, float T, float* q_dev, int32_t n) {
+    if (!v_dev || !q_dev || n < 8 || n % 8) return RSD_EINVAL;
+    hipLaunchKernelGGL(debug_smp_divide_kernel, dim3(ceil_div(n / 8, 256)), dim3(256), 0, nullptr, v_dev, T, q_dev, n);
+    return hipDeviceSynchronize() == hipSuccess ? RSD_OK : RSD_EHIP;
+}
 #endif
 
 // --------------------------------------------------------------------------- rsd_forward

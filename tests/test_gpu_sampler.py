@@ -132,9 +132,10 @@ def test_tokens_too_light_for_a_bin(kind, n, V, T, top_p):
     test_draws_lie_where_the_distribution_puts_them(kind, n, V, T, top_p)
 
 
-@pytest.mark.parametrize("n,V", [(2, 151936), (20, 151936), (33, 1027)])
-def test_quotients_do_not_depend_on_the_way_they_are_formed(n, V):
-    """Logits and temperature times 2^61 have the same quotients, but leave the range of the division by reciprocal."""
+@pytest.mark.parametrize("n,V", [(2, 151936), (20, 151936), (33, 30000)])
+def test_draws_do_not_depend_on_the_way_quotients_are_formed(n, V):
+    """Logits and temperature times 2^61 have the same quotients, but leave the range of the division by reciprocal.  (Spans of 2374
+    tokens by blocks and by waves, and of 469 by waves: all have batches of more than half their size, which it serves.)"""
     import torch
     from paper_2501_19324_amd import binding as R
     rng = np.random.default_rng(n)
@@ -199,3 +200,33 @@ def test_exponential_is_as_accurate_as_the_library_s():
     e, _ = run(d)
     assert e[0] == 1.0 and e[1] == 1.0 and abs(e[2] / np.exp(-27.0) - 1.0) < 1.1e-7
     assert (e[3:] < 2.0 ** -40).all() and (e[3:] > 0.0).all()
+
+
+@pytest.mark.parametrize("T", [0.7, 1.3, 1.0, 3.0, 1e-3, 2.0 ** -20, 2.0 ** 20, 1.0 - 2.0 ** -24, 1.0 + 2.0 ** -23, 2.0 - 2.0 ** -23, 2.0 ** -7 * (2.0 - 2.0 ** -22),
+                               2.0 ** -21, 2.0 ** 21])
+def test_quotients_are_correctly_rounded(T):
+    """The division of the histogram pass (the debug build exposes it) bit for bit against numpy's, which rounds correctly: mantissas
+    at random, all ones, all zeros and next to these, magnitudes from 2^-100 (below, the remainder of a quotient
+    leaves the range) to 2^60, where a wave changes to the plain division, and beyond; products of T that lie next to the
+    middle between two quotients.  T of 2^-21 and 2^21 take the plain division throughout."""
+    import ctypes
+    import torch
+    T = np.float32(T)
+    rng = np.random.default_rng(1)
+    n = 1 << 20
+    m = rng.integers(0, 1 << 23, n)
+    m[: n // 4] = rng.choice([0, 1, 2, (1 << 23) - 1, (1 << 23) - 2, 1 << 22, (1 << 22) - 1], n // 4)
+    e = rng.integers(27, 187, n)                                  # 2^-100 .. 2^59
+    e[-n // 8:] = rng.integers(185, 190, n // 8)                  # 2^58 .. 2^62: waves of either way
+    v = ((rng.integers(0, 2, n) << 31) | (e << 23) | m).astype(np.uint32).view(np.float32)
+    mid = rng.integers(1 << 24, 1 << 25, n // 4).astype(np.float64) * 2.0 ** -24      # 25 bits: every other one a middle
+    v[n // 4: n // 2] = (mid * np.float64(T)).astype(np.float32)
+    v[-8:] = [np.inf, -np.inf, 0.0, -0.0, 3e38, -3e38, 1.0, -1.0]
+    with np.errstate(over="ignore"):
+        want = v / T
+    d = torch.from_numpy(v).cuda()
+    q = torch.empty_like(d)
+    torch.cuda.synchronize()
+    assert debug_library().rsd_debug_smp_divide(ctypes.c_void_p(d.data_ptr()), ctypes.c_float(T), ctypes.c_void_p(q.data_ptr()), n) == 0
+    bad = np.nonzero(q.cpu().numpy().view(np.uint32) != want.view(np.uint32))[0]
+    assert bad.size == 0, (bad.size, [(float(v[i]), float(q[i]), float(want[i])) for i in bad[:4]])
