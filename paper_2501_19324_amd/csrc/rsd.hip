@@ -2277,6 +2277,23 @@ extern "C" int rsd_debug_smp_exp(const float* d_dev, float* e_dev, float* lib_de
     hipLaunchKernelGGL(debug_smp_exp_kernel, dim3(ceil_div(n, 256)), dim3(256), 0, nullptr, d_dev, e_dev, lib_dev, n);
     return hipDeviceSynchronize() == hipSuccess ? RSD_OK : RSD_EHIP;
 }
+// One many-row product with a given block tile, number of K slices and epilogue.  EPI_STORE with ks > 1: slice z to Y + z * M * N (ldy = N).
+// EPI_SWIGLU: halves to Oh / Ol [M][N / 2].
+extern "C" int rsd_debug_tile(const void* W_dev, int32_t N, int32_t K, const void* Xh_dev, const void* Xl_dev, int32_t M, int32_t epi, int32_t bm,
+                              int32_t bn, int32_t ks, float* Y_dev, int32_t ldy, void* Oh_dev, void* Ol_dev) {
+    bool known = false;
+#define RSD_TILE_KNOWN(BM, BN) known |= bm == BM && bn == BN;
+    RSD_TILE_SIZES(RSD_TILE_KNOWN)
+#undef RSD_TILE_KNOWN
+    if (!known || !W_dev || !Xh_dev || !Xl_dev || M < 1 || N < 1 || K < 64 || K % 64 || ks < 1) return RSD_EINVAL;
+    if (epi == EPI_SWIGLU ? (!Oh_dev || !Ol_dev || N % 128 || ks != 1) : (epi != EPI_STORE && epi != EPI_RESID)) return RSD_EINVAL;
+    if (epi != EPI_SWIGLU && (!Y_dev || ldy < N || (ks > 1 && (epi != EPI_STORE || ldy != N)))) return RSD_EINVAL;
+    if (gemm_tile_raise() != hipSuccess) return RSD_EHIP;
+    gemm_tile_launch(nullptr, epi, TilePlan{bm, bn, ks}, static_cast<const bf16_t*>(W_dev), N, K, static_cast<const uint16_t*>(Xh_dev),
+                     static_cast<const uint16_t*>(Xl_dev), M, ks > 1 ? nullptr : Y_dev, ldy, ks > 1 ? Y_dev : nullptr,
+                     static_cast<uint16_t*>(Oh_dev), static_cast<uint16_t*>(Ol_dev));
+    return hipDeviceSynchronize() == hipSuccess ? RSD_OK : RSD_EHIP;
+}
 // the sampler's division by one number: q[i] = v[i] / T, n a multiple of 8 (a thread's values)
 __global__ void debug_smp_divide_kernel(const float* __restrict__ v, float T, float* __restrict__ q, int n) {
     const int i = (blockIdx.x * blockDim.x + threadIdx.x) * 8;

@@ -278,3 +278,72 @@ def test_fp32_pieces_of_few_rows_keep_their_head(chunk):
         assert bool(torch.isnan(out[b, n:]).all())
     R.rsd_destroy(ctx)
     R.rsd_destroy(one)
+
+
+def tile_product(dbg, w, xh, xl, epi, bm, bn, ks=1, y=None, ldy=0, oh=None, ol=None):
+    import ctypes
+    import torch
+    torch.cuda.synchronize()
+    ptr = [ctypes.c_void_p(t.data_ptr() if t is not None else None) for t in (w, xh, xl, y, oh, ol)]
+    rc = dbg.rsd_debug_tile(ptr[0], w.shape[0], w.shape[1], ptr[1], ptr[2], xh.shape[0], epi, bm, bn, ks, ptr[3], ldy, ptr[4], ptr[5])
+    assert rc == 0
+
+
+def tile_operands(M, N, K, seed):
+    """bf16 W [N][K], and fp32 X [M][K] as hi + lo bf16 halves; the product and the sum of the terms' magnitudes in 64 bits"""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    w = torch.randn(N, K, generator=g, device="cuda").bfloat16()
+    x = torch.randn(M, K, generator=g, device="cuda")
+    xh = x.bfloat16()
+    xl = (x - xh.float()).bfloat16()
+    x64, w64 = xh.double() + xl.double(), w.double()
+    return w, xh, xl, x64 @ w64.T, x64.abs() @ w64.abs().T
+
+
+TILES = [(256, 256), (256, 192), (128, 256), (128, 192), (128, 128)]
+STORE, RESID, SWIGLU = 0, 1, 2
+
+
+@pytest.mark.parametrize("bm,bn", TILES)
+@pytest.mark.parametrize("K", [64, 128, 192, 448])
+def test_every_tile_and_epilogue(bm, bn, K):
+    """Each instance of the many-row kernel by itself (the debug build launches it), whatever the plan would choose: one, two, three and
+    seven K blocks in its ring, rows and columns just below, at and above the tile, N no multiple of four, an output at an odd
+    address or row pitch (values are then stored one by one), K in slices, among them an empty one; nothing is written beside
+    the output.  Bound of a product: 2 K terms summed in fp32 in any order, 2 K 2^-24 times the sum of their magnitudes, once more
+    for the residual; SwiGLU: silu has a slope below 1.1, 5 x 2^-24 of its own, and its result is kept in two halves (2^-17)."""
+    import torch
+    import ctypes
+    import os
+    from paper_2501_19324_amd import binding as R
+    dbg = ctypes.CDLL(os.path.join(os.path.dirname(R.LIB_PATH), "librsd_debug.so"))
+    eps = 2 * K * 2.0 ** -24
+    for i, (M, N) in enumerate([(bm - 1, bn + 4), (bm, bn), (bm + 1, bn - 1), (2 * bm + 17, 2 * bn + 30), (1, 1), (3, 2 * bn + 20)]):
+        w, xh, xl, want, mag = tile_operands(M, N, K, i)
+        for pitch, off in ((N, 0), (N + 3, 1), (N + 4, 0)):
+            for epi in (STORE, RESID):
+                buf = torch.randn(M * pitch + 64, device="cuda")
+                kept = buf.clone()
+                rows = torch.arange(M, device="cuda")[:, None] * pitch + torch.arange(N, device="cuda")[None, :] + off
+                y0 = kept[rows].double() if epi == RESID else 0.0
+                tile_product(dbg, w, xh, xl, epi, bm, bn, y=buf[off:], ldy=pitch)
+                bound = eps * mag + (2.0 ** -23 * (want.abs() + y0.abs()) if epi == RESID else 0.0)
+                assert bool(((buf[rows].double() - (want + y0)).abs() <= bound).all()), (M, N, pitch, off, epi)
+                buf[rows] = kept[rows]
+                assert torch.equal(buf, kept), (M, N, pitch, off, epi)
+        for ks in (2, 3, 4):
+            buf = torch.full((ks * M * N + 64,), 7.0, device="cuda")
+            tile_product(dbg, w, xh, xl, STORE, bm, bn, ks=ks, y=buf, ldy=N)
+            got = buf[:ks * M * N].view(ks, M, N).double().sum(0)
+            assert bool(((got - want).abs() <= eps * mag).all()) and bool((buf[ks * M * N:] == 7.0).all()), (M, N, ks)
+    for i, (M, F) in enumerate([(bm - 1, 64), (bm + 1, bn // 2 // 64 * 64 + 64), (2 * bm, 192)]):
+        w, xh, xl, want, mag = tile_operands(M, 2 * F, K, 9 + i)
+        oh, ol = (torch.full((M * F + 64,), 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        tile_product(dbg, w, xh, xl, SWIGLU, bm, bn, oh=oh, ol=ol)
+        g, u = want[:, :F], want[:, F:]
+        silu = g * torch.sigmoid(g)
+        got = (oh.double() + ol.double())[:M * F].view(M, F)
+        bound = eps * (1.1 * mag[:, :F] * u.abs() + silu.abs() * mag[:, F:] + 1.1 * eps * mag[:, :F] * mag[:, F:]) + (2.0 ** -17 + 5 * 2.0 ** -24) * (silu * u).abs()
+        assert bool(((got - silu * u).abs() <= bound + 1e-30).all()), (M, F)
+        assert bool((oh[M * F:] == 7.0).all()) and bool((ol[M * F:] == 7.0).all())
