@@ -74,6 +74,18 @@ __device__ __forceinline__ u64_t wave_incl_scan_u64(u64_t v, int lane) {
     }
     return v;
 }
+// the same for 32 bits in vector instructions: shifts inside the rows of 16 lanes, then the last lane of a row to the rows behind it
+__device__ __forceinline__ int wave_incl_scan(int x) {
+    using std::integral_constant;
+    auto add = [&](auto ctrl, auto rows) { x += __builtin_amdgcn_update_dpp(0, x, decltype(ctrl)::value, decltype(rows)::value, 0xF, false); };
+    add(integral_constant<int, 0x111>{}, integral_constant<int, 0xF>{});       // row_shr by 1, 2, 4, 8
+    add(integral_constant<int, 0x112>{}, integral_constant<int, 0xF>{});
+    add(integral_constant<int, 0x114>{}, integral_constant<int, 0xF>{});
+    add(integral_constant<int, 0x118>{}, integral_constant<int, 0xF>{});
+    add(integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});       // row_bcast 15 into rows 1 and 3
+    add(integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});       // row_bcast 31 into rows 2 and 3
+    return x;
+}
 // inclusive scan over the 256 threads of a block; wtot is 4 u64 of LDS
 __device__ __forceinline__ u64_t block256_incl_scan_u64(u64_t v, u64_t* wtot) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -301,7 +313,7 @@ __device__ void smp_append(const SampleArgs& a, const AppendArgs& ap, int row, i
 
 // ---- phase A: max of every span of x (sampling) or arg max of the biased logits (greedy).  x = logit / temperature
 // grows with the logit, so the division is done once per span
-template <int WPS>
+template <int WPS, bool GREEDY>
 __global__ __launch_bounds__(SMP_T) void sample_max_kernel(SampleArgs a, AppendArgs ap) {
     const int row = blockIdx.y, j = smp_span<WPS>(), tid = smp_lane<WPS>(), wave = threadIdx.x >> 6;
     const int seq = smp_seq(a, row);
@@ -309,18 +321,24 @@ __global__ __launch_bounds__(SMP_T) void sample_max_kernel(SampleArgs a, AppendA
     const float* lg = a.logits + (size_t)row * a.ld;
     const int span = (a.V + SMP_NB - 1) / SMP_NB, s0 = min(j * span, a.V), s1 = min(a.V, s0 + span);
     constexpr int T = WPS * 64, U = SMP_U<WPS>;
-    if (a.temperature != 0.0f) {                           // for phases B and C
+    if constexpr (!GREEDY) {                               // for phases B and C
         constexpr int NH = SMP_BINS / SMP_NB, NS = SMP_SUB / SMP_NB;
         u64_t* hist = a.hist + (size_t)row * SMP_WS;
         if (tid < NH + NS) hist[tid < NH ? j * NH + tid : SMP_WS - SMP_SUB + j * NS + tid - NH] = 0;
         if (tid == 0 && j == 0) { a.sel[(size_t)row * SMP_SEL + 3] = 0; a.sel[(size_t)row * SMP_SEL + 7] = 0; }
     }
     float bv = -INFINITY; int bi = 0x7FFFFFFF;
-    smp_scan<U, false>(a, lg, s0, s1, tid, T, -INFINITY, [&](int i, const float (&v)[U]) {
+    for (int i0 = s0 + tid; i0 < s1; i0 += T * U) {
+        float v[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (v[u] > bv) { bv = v[u]; bi = i + u * T; }
-    });
+        for (int u = 0; u < U; ++u) v[u] = lg[min(i0 + u * T, s1 - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = min(i0 + u * T, s1 - 1);
+            if (i == a.sep_id) v[u] += a.sep_bias;
+            if (v[u] > bv) { bv = v[u]; bi = i; }
+        }
+    }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
         const float ov = __shfl_xor(bv, off, RSD_WAVE);
@@ -336,11 +354,8 @@ __global__ __launch_bounds__(SMP_T) void sample_max_kernel(SampleArgs a, AppendA
             for (int w = 1; w < 4; ++w)
                 if (fred[w] > bv || (fred[w] == bv && ired[w] < bi)) { bv = fred[w]; bi = ired[w]; }
     }
-    if (a.temperature != 0.0f) {
-        if (tid == 0) {
-            a.pmax[(size_t)row * SMP_NB + j] = bv / a.temperature;
-            a.pidx[(size_t)row * SMP_NB + j] = bi;
-        }
+    if constexpr (!GREEDY) {
+        if (tid == 0) a.pmax[(size_t)row * SMP_NB + j] = bv / a.temperature;
         return;
     }
     // Greedy: the block that finishes a row's last span chooses among the spans and appends the token, instead of a launch of its
@@ -372,7 +387,7 @@ __global__ __launch_bounds__(SMP_T) void sample_max_kernel(SampleArgs a, AppendA
 }
 
 // ---- phase B: the histogram of masses
-template <int WPS>
+template <int WPS, bool PLAIN>
 __global__ __launch_bounds__(SMP_T) void sample_hist_kernel(SampleArgs a) {
     const int row = blockIdx.y, j = smp_span<WPS>(), tid = smp_lane<WPS>();
     if (smp_seq(a, row) < 0) return;
@@ -384,24 +399,37 @@ __global__ __launch_bounds__(SMP_T) void sample_hist_kernel(SampleArgs a) {
     for (int b = threadIdx.x; b < SMP_BINS; b += SMP_T) lh[b] = 0;
     const float mx = smp_row_max(a, row, fred);           // (holds a barrier)
     constexpr int T = WPS * 64, U = SMP_U<WPS>;
-    const float rT = 1.0f / a.temperature;
     // The mass reached from the top is at least top_p of a total of at least 1 (the maximum's own e), so tokens that even all together
     // have less than 1 - top_p need no bin of their own: those below `tail` are only added up, in registers (exactly: less than
     // 2^28 + 2^26 units a lane) and at the end in the lowest bin.  For 151936 tokens and 0.95 that is e < 2^-22: nearly all of them
     const float rest = 0.99f * (1.0f - a.top_p) / (float)a.V;
     const uint32_t tail = min(max(__float_as_uint(rest) & 0x7F800000u, SMP_UNIT), 0x38800000u);      // (2^-14)
     uint32_t low = 0;
+    auto add = [&](uint32_t key) { atomicAdd(&lh[smp_bin(key)], smp_fix(__uint_as_float(key))); };
+    if constexpr (PLAIN) {
+        for (int i0 = s0 + tid; i0 < s1; i0 += T * U) {
+            float x[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) x[u] = smp_x(a, lg, min(i0 + u * T, s1 - 1));
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (i0 + u * T >= s1) continue;
+                const float e = smp_exp(x[u] - mx);
+                if (__float_as_uint(e) >= tail) add(__float_as_uint(e));
+                else low += (uint32_t)(e * 1099511627776.0f);
+            }
+        }
+    } else {
     // the others are few, then, in most waves: a batch's are listed, without a branch (lanes with nothing to list write to a slot
     // nobody reads), and added to the histogram 64 at a time; where half of a batch is above the tail, at once
-    // (few rows and short spans are bound by latency, which the sum over the lanes adds to: there, and where there is no tail, all are
-    // added at once)
+    // (few rows are bound by latency, which the sum over the lanes adds to: there, and where there is no tail, all are added at once)
+    const float rT = 1.0f / a.temperature;
     constexpr int LIST = WPS == 1 ? 64 + 32 * U : 0;
-    const bool lists = WPS == 1 && tail > SMP_UNIT && span > U * T;
+    const bool lists = WPS == 1 && tail > SMP_UNIT;
     __shared__ uint32_t s_list[4][LIST + 64];
     uint32_t* list = s_list[threadIdx.x >> 6];
     const int lane = threadIdx.x & 63;
     int n = 0;
-    auto add = [&](uint32_t key) { atomicAdd(&lh[smp_bin(key)], smp_fix(__uint_as_float(key))); };
     // the list is exchanged between the lanes of a wave, whose LDS operations stay in order: this keeps the compiler's (no instruction)
     auto order = [] {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -434,12 +462,7 @@ __global__ __launch_bounds__(SMP_T) void sample_hist_kernel(SampleArgs a) {
             for (int u = 0; u < U; ++u) if (key[u] >= tail) add(key[u]);
             return;
         }
-        int at = above;                                    // inclusive sum over the lanes
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int o = __shfl_up(at, d, RSD_WAVE);
-            if (lane >= d) at += o;
-        }
+        int at = wave_incl_scan(above);
         const int k = __builtin_amdgcn_readlane(at, 63);
         if (k == 0) return;
         if (k > 32 * U) {
@@ -463,6 +486,7 @@ __global__ __launch_bounds__(SMP_T) void sample_hist_kernel(SampleArgs a) {
         order();                                           // ... and written over by the next batch
     });
     if (lists && lane < n) add(list[lane]);
+    }
     // (eight lanes at a time: less than 2^32)
     auto dpp = [](uint32_t x, auto ctrl) { return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, 0xF, 0xF, true); };
     low = dpp(low, std::integral_constant<int, 0xB1>{});       // quad_perm [1,0,3,2]
@@ -476,7 +500,7 @@ __global__ __launch_bounds__(SMP_T) void sample_hist_kernel(SampleArgs a) {
 
 // ---- phase C: the bin in which the mass reaches top_p of the total; per span the mass above it, and the keys inside it (dense
 // rows: their masses by sub-bin)
-template <int WPS>
+template <int WPS, bool PLAIN>
 __global__ __launch_bounds__(SMP_T) void sample_select_kernel(SampleArgs a) {
     const int row = blockIdx.y, j = smp_span<WPS>(), tid = smp_lane<WPS>(), wave = threadIdx.x >> 6;
     if (smp_seq(a, row) < 0) return;
@@ -530,16 +554,28 @@ __global__ __launch_bounds__(SMP_T) void sample_select_kernel(SampleArgs a) {
     u64_t acc = 0;
     constexpr int T = WPS * 64, U = WPS == 4 ? SMP_U<4> : 6;        // (eight spill)
     auto scan = [&](auto inside) {
-        smp_scan<U, true>(a, lg, s0, s1, tid, T, -INFINITY, [&](int, const float (&v)[U]) {
+        auto take = [&](float x) {
+            const float e = smp_exp(x - mx);
+            const uint32_t key = __float_as_uint(e);
+            if (key >= hi) acc += smp_fix(e);
+            else if (key >= lo) inside(key);
+        };
+        if constexpr (PLAIN) {
+            for (int i0 = s0 + tid; i0 < s1; i0 += T * U) {
+                float x[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (!__any(!(v[u] < cut))) continue;
-                const float e = smp_exp(v[u] / a.temperature - mx);
-                const uint32_t key = __float_as_uint(e);
-                if (key >= hi) acc += smp_fix(e);
-                else if (key >= lo) inside(key);
+                for (int u = 0; u < U; ++u) x[u] = smp_x(a, lg, min(i0 + u * T, s1 - 1));
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (i0 + u * T < s1) take(x[u]);
             }
-        });
+        } else {
+            smp_scan<U, true>(a, lg, s0, s1, tid, T, -INFINITY, [&](int, const float (&v)[U]) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (__any(!(v[u] < cut))) take(v[u] / a.temperature);
+            });
+        }
     };
     if (dense)
         scan([&](uint32_t key) { smp_add_tied(&lds[(key - lo) >> 8], key, smp_fix(__uint_as_float(key))); });
@@ -794,13 +830,23 @@ __global__ __launch_bounds__(SMP_T) void sample_finish_kernel(SampleArgs a, Appe
 // line: us of the four launches, span per block / per wave: 151936 tokens, 16 rows 32.7 / 33.8, 24 rows 38.1 / 36.8; 100000, 8 rows 25.5 /
 // 28.2, 15 rows 31.2 / 29.4; 50257, 4 rows 20.9 / 21.9, 8 rows 22.9 / 22.6; 32000, 1 row 19.0 / 19.4, 4 rows 20.4 / 19.6; 16384, 1 row
 // 18.5 / 18.3, 15 rows 24.9 / 20.1.
+// Short spans take plain passes over the tokens, without the steps that only pay where a wave has many: a histogram pass of up to two
+// batches without lists and the division by reciprocal, a selection of up to 1280 tokens without skipping.  64 rows of 32000, a third
+// of the tokens not masked: 28.0 us, 30.3 with the long spans' passes (27.8 before there were such passes); 16 rows 21.4, 22.3 (21.2); 64
+// rows of 1000 normal logits 21.1, 22.4 (23.4); the logits of a trained model, 17 rows of 151936: 28.3, 28.4 (33.1); 64 of 32000: 25.2, 26.1 (27.9).
 template <int WPS>
 static void sample_launch_spans(hipStream_t st, const SampleArgs& a, const AppendArgs& ap, int rows) {
     const dim3 grid(SMP_NB * WPS / 4, rows), block(SMP_T);
-    hipLaunchKernelGGL((sample_max_kernel<WPS>), grid, block, 0, st, a, ap);
-    if (a.temperature == 0.0f) return;
-    hipLaunchKernelGGL((sample_hist_kernel<WPS>), grid, block, 0, st, a);
-    hipLaunchKernelGGL((sample_select_kernel<WPS>), grid, block, 0, st, a);
+    if (a.temperature == 0.0f) {
+        hipLaunchKernelGGL((sample_max_kernel<WPS, true>), grid, block, 0, st, a, ap);
+        return;
+    }
+    const int span = (a.V + SMP_NB - 1) / SMP_NB;
+    hipLaunchKernelGGL((sample_max_kernel<WPS, false>), grid, block, 0, st, a, ap);
+    if (span <= 2 * SMP_U<WPS> * WPS * 64) hipLaunchKernelGGL((sample_hist_kernel<WPS, true>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((sample_hist_kernel<WPS, false>), grid, block, 0, st, a);
+    if (span <= 1280) hipLaunchKernelGGL((sample_select_kernel<WPS, true>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((sample_select_kernel<WPS, false>), grid, block, 0, st, a);
 }
 static void sample_launch(hipStream_t st, const SampleArgs& a, const AppendArgs& ap, int rows) {
     if (rows * 8192LL < a.V) sample_launch_spans<4>(st, a, ap, rows);

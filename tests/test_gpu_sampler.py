@@ -132,10 +132,17 @@ def test_tokens_too_light_for_a_bin(kind, n, V, T, top_p):
     test_draws_lie_where_the_distribution_puts_them(kind, n, V, T, top_p)
 
 
-@pytest.mark.parametrize("n,V", [(2, 151936), (20, 151936), (33, 30000)])
+@pytest.mark.parametrize("kind", ["normal", "low", "masked"])
+@pytest.mark.parametrize("n,V", [(20, 65536), (20, 65537), (20, 81920), (20, 81921), (2, 81920), (2, 81921), (2, 163840), (2, 163841)])
+def test_spans_at_the_change_between_plain_and_longer_passes(kind, n, V):
+    """Histogram: spans of 1024 tokens (one per wave) and 2560 (one per block) are the last that take the plain pass; selection: 1280."""
+    test_draws_lie_where_the_distribution_puts_them(kind, n, V, 0.7, 0.95)
+
+
+@pytest.mark.parametrize("n,V", [(2, 151936), (20, 151936), (33, 70000)])
 def test_draws_do_not_depend_on_the_way_quotients_are_formed(n, V):
     """Logits and temperature times 2^61 have the same quotients, but leave the range of the division by reciprocal.  (Spans of 2374
-    tokens by blocks and by waves, and of 469 by waves: all have batches of more than half their size, which it serves.)"""
+    and 1094 tokens by waves, whose histogram pass divides that way; by blocks spans of 2374 take the plain pass.)"""
     import torch
     from paper_2501_19324_amd import binding as R
     rng = np.random.default_rng(n)
