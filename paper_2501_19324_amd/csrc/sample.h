@@ -15,14 +15,15 @@
 //   B  histogram of masses over 1792 bins of 1/32 and 1/64 octave (exponent and five or six mantissa bits, 2^-40 .. 1); tokens so
 //      light that the threshold cannot lie among them are only added up
 //   C  every block finds the bin tau lies in, sums what lies above it per span and lists the keys inside it (a bin is
-//      1 or 2 % wide: mostly a few hundred keys)
+//      1 or 2 % wide: mostly a few hundred keys).  (B and C each have a plain form for short spans: sample_launch_spans)
 //   D  one block per row resolves tau among the listed keys (10 + 9 bits), forms the nucleus mass of every span, locates
 //      the draw and appends the token to its sequence.
 // So the logits are read three times and everything after C works on a few hundred keys.  (Three radix levels over the
 // whole row and a fifth pass for the masses, with a 2048-bin histogram cleared and flushed for every 2400 tokens, took
-// 109 us on 64 rows of 151936 logits and 36 on one.)  What bounds it on many rows: vector instructions of B (9 of 10 cycles) and the
-// reading of the logits, on few rows the chain of block scans in D.  Launches of 64 rows, A to D: 9.5 / 14.8 / 10.6 / 9.3 us; with a
-// bin for every token, a full division and expf for each in B and C 9.5 / 18.2 / 17.2 / 9.3.
+// 109 us on 64 rows of 151936 logits and 36 on one.)  What bounds it on many rows: in B the vector instructions (1530 a wave on 64 rows; the
+// vector units are busy 46 % of the counted cycles, the start and end of the launch among them, and 17 % in A and C), in A and C the
+// reading of the logits, on few rows the chain of block scans in D.  Launches of 64 rows with logits as a trained model gives them, not read before,
+// A to D: 11.6 / 15.3 / 10.4 / 8.9 us; with a bin for every token, a full division and expf for each in B and C 11.0 / 18.3 / 17.0 / 9.3.
 // A bin that may hold more keys than there is room for (nearly equal logits; the bin's mass tells in advance) makes the row
 // "dense": C then adds up sub-bins of 256 keys instead of listing, and D is SMP_FB blocks, which count the keys of the deciding
 // sub-bin span by span; the last of them to finish resolves tau from these counts and goes on alone.  A call on 64 rows
@@ -200,7 +201,8 @@ __device__ __forceinline__ void smp_scan(const SampleArgs& a, const float* lg, i
 }
 // exp(d) of a difference to the maximum, d <= 0: 2^n times the hardware's exponential of the rest of d log2 e, which is known to more than
 // a float's digits (product, its rounding error and the low part of log2 e); n is rounded and shifted into the exponent by one
-// addition each.  Below -80 (no mass; NaN as well) 2^-115.  Three instructions fewer than expf, which also looks after the ends of its range.
+// addition each.  Below -80 (no mass; NaN as well) 2^-115.  Three instructions fewer than expf, which also looks after the ends of its range,
+// and as accurate (largest relative error 8.32e-8, rms 2.10e-8 over all floats of -28 .. -1e-6 for both; they differ in five of them).
 // No contraction: y stands for the rounded product in both of its places.  (Fused into y - n, the product would bring in there the
 // rounding error that the other term adds: 1.4e-6 off at -28, 7e-7 at -15.)
 __device__ __forceinline__ float smp_exp(float d) {
@@ -359,7 +361,8 @@ __global__ __launch_bounds__(SMP_T) void sample_max_kernel(SampleArgs a, AppendA
         return;
     }
     // Greedy: the block that finishes a row's last span chooses among the spans and appends the token, instead of a launch of its
-    // own (one row of 151936 logits: 10.2 -> 7.3 us a call).  Results go past the L2 of this XCD and have arrived before they are counted,
+    // own (one row of 151936 logits, kernels alone: 5.8 -> 5.2 us, 6.4 -> 5.8 when the logits have not been read before; a call 10.2 -> 7.3 us,
+    // the gap between the launches included).  Results go past the L2 of this XCD and have arrived before they are counted,
     // as in smp_dense.  The count only ever grows, by 64 a call, so that it needs no clearing.
     __shared__ int s_last;
     if (tid == 0) {
@@ -420,72 +423,72 @@ __global__ __launch_bounds__(SMP_T) void sample_hist_kernel(SampleArgs a) {
             }
         }
     } else {
-    // the others are few, then, in most waves: a batch's are listed, without a branch (lanes with nothing to list write to a slot
-    // nobody reads), and added to the histogram 64 at a time; where half of a batch is above the tail, at once
-    // (few rows are bound by latency, which the sum over the lanes adds to: there, and where there is no tail, all are added at once)
-    const float rT = 1.0f / a.temperature;
-    constexpr int LIST = WPS == 1 ? 64 + 32 * U : 0;
-    const bool lists = WPS == 1 && tail > SMP_UNIT;
-    __shared__ uint32_t s_list[4][LIST + 64];
-    uint32_t* list = s_list[threadIdx.x >> 6];
-    const int lane = threadIdx.x & 63;
-    int n = 0;
-    // the list is exchanged between the lanes of a wave, whose LDS operations stay in order: this keeps the compiler's (no instruction)
-    auto order = [] {
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    };
-    smp_scan<U, false>(a, lg, s0, s1, tid, T, __builtin_nanf(""), [&](int i, const float (&v)[U]) {
-        if (s1 - (i - tid) <= U / 2 * T) {                  // (a short end: only what is there, as it comes)
+        // the others are few, then, in most waves: a batch's are listed, without a branch (lanes with nothing to list write to a slot
+        // nobody reads), and added to the histogram 64 at a time; where half of a batch is above the tail, at once
+        // (few rows are bound by latency, which the sum over the lanes adds to: there, and where there is no tail, all are added at once)
+        const float rT = 1.0f / a.temperature;
+        constexpr int LIST = WPS == 1 ? 64 + 32 * U : 0;
+        const bool lists = WPS == 1 && tail > SMP_UNIT;
+        __shared__ uint32_t s_list[4][LIST + 64];
+        uint32_t* list = s_list[threadIdx.x >> 6];
+        const int lane = threadIdx.x & 63;
+        int n = 0;
+        // the list is exchanged between the lanes of a wave, whose LDS operations stay in order: this keeps the compiler's (no instruction)
+        auto order = [] {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        };
+        smp_scan<U, false>(a, lg, s0, s1, tid, T, __builtin_nanf(""), [&](int i, const float (&v)[U]) {
+            if (s1 - (i - tid) <= U / 2 * T) {                  // (a short end: only what is there, as it comes)
 #pragma unroll
-            for (int u = 0; u < U / 2; ++u) {
-                if (s1 - (i - tid) <= u * T) break;
-                const uint32_t key = __float_as_uint(smp_exp(v[u] / a.temperature - mx));
-                low += key >= tail ? 0u : (uint32_t)(__uint_as_float(key) * 1099511627776.0f);
-                if (key >= tail) add(key);
+                for (int u = 0; u < U / 2; ++u) {
+                    if (s1 - (i - tid) <= u * T) break;
+                    const uint32_t key = __float_as_uint(smp_exp(v[u] / a.temperature - mx));
+                    low += key >= tail ? 0u : (uint32_t)(__uint_as_float(key) * 1099511627776.0f);
+                    if (key >= tail) add(key);
+                }
+                return;
             }
-            return;
-        }
-        float x[U];
-        uint32_t key[U];
-        int above = 0;
-        smp_divide<U>(v, x, a.temperature, rT);
+            float x[U];
+            uint32_t key[U];
+            int above = 0;
+            smp_divide<U>(v, x, a.temperature, rT);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const float e = smp_exp(x[u] - mx);
-            key[u] = __float_as_uint(e);
-            above += key[u] >= tail;
-            low += key[u] >= tail ? 0u : (uint32_t)(e * 1099511627776.0f);
-        }
-        if (!lists) {
+            for (int u = 0; u < U; ++u) {
+                const float e = smp_exp(x[u] - mx);
+                key[u] = __float_as_uint(e);
+                above += key[u] >= tail;
+                low += key[u] >= tail ? 0u : (uint32_t)(e * 1099511627776.0f);
+            }
+            if (!lists) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) if (key[u] >= tail) add(key[u]);
-            return;
-        }
-        int at = wave_incl_scan(above);
-        const int k = __builtin_amdgcn_readlane(at, 63);
-        if (k == 0) return;
-        if (k > 32 * U) {
+                for (int u = 0; u < U; ++u) if (key[u] >= tail) add(key[u]);
+                return;
+            }
+            int at = wave_incl_scan(above);
+            const int k = __builtin_amdgcn_readlane(at, 63);
+            if (k == 0) return;
+            if (k > 32 * U) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) if (key[u] >= tail) add(key[u]);
-            return;
-        }
-        at += n - above;
+                for (int u = 0; u < U; ++u) if (key[u] >= tail) add(key[u]);
+                return;
+            }
+            at += n - above;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const bool in = key[u] >= tail;
-            list[in ? at : LIST + lane] = key[u];
-            at += in;
-        }
-        n += k;
-        order();                                           // other lanes' entries are read below ...
-        while (n >= 64) {
-            n -= 64;
-            add(list[n + lane]);
-        }
-        order();                                           // ... and written over by the next batch
-    });
-    if (lists && lane < n) add(list[lane]);
+            for (int u = 0; u < U; ++u) {
+                const bool in = key[u] >= tail;
+                list[in ? at : LIST + lane] = key[u];
+                at += in;
+            }
+            n += k;
+            order();                                           // other lanes' entries are read below ...
+            while (n >= 64) {
+                n -= 64;
+                add(list[n + lane]);
+            }
+            order();                                           // ... and written over by the next batch
+        });
+        if (lists && lane < n) add(list[lane]);
     }
     // (eight lanes at a time: less than 2^32)
     auto dpp = [](uint32_t x, auto ctrl) { return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, 0xF, 0xF, true); };
