@@ -28,6 +28,7 @@ namespace {
 
 constexpr int kMaxRows = 8192;   // rows of one chunked-prefill pass (bounds the workspaces)
 constexpr int kPoll = 16;        // decode iterations between looks at the active counter
+constexpr int kRepackRows = 32;  // ... and, above this many rows, at which sequences are still active
 constexpr int kPfSplitRows = 128;   // chunked-prefill passes of at most this many rows may split the context
 constexpr int kPfSplits = 16;       // ... into at most this many parts
 
@@ -983,8 +984,9 @@ int gen_stage(rsd_ctx* c, int which, const float* u, const int* forced, int mode
         fill_packed_rows(seqs, c->dec_rows, c->dec_seq_h);
         HIPCHK(c, hipMemcpyAsync(c->dec_seq_dev, c->dec_seq_h, c->dec_rows * sizeof(int), hipMemcpyHostToDevice, c->st));
     }
-    const int M = c->dec_rows ? c->dec_rows : B;
+    int M = c->dec_rows ? c->dec_rows : B;
     int iters = 0;
+    long long row_iters = 0;
     // decode-loop accounting (steps of the reasoning loop only): contexts before the stage
     const bool count = mode == 1 && which < 2;
     std::vector<int> ctx0;
@@ -1033,10 +1035,27 @@ int gen_stage(rsd_ctx* c, int which, const float* u, const int* forced, int mode
             c->decode_warm[which] = true;
         }
         ++iters;
+        row_iters += M;
         if (iters % kPoll == 0 || iters == cap) {
             HIPCHK(c, hipMemcpyAsync(c->poll_h, c->ds.n_active, sizeof(int), hipMemcpyDeviceToHost, c->st));
+            // (the flags too while there are rows to give up)
+            const bool look = mode == 1 && M > kRepackRows && iters < cap;
+            if (look) HIPCHK(c, hipMemcpyAsync(c->poll_h + 4, c->ds.active, B * sizeof(int), hipMemcpyDeviceToHost, c->st));
             HIPCHK(c, hipStreamSynchronize(c->st));
             if (*c->poll_h <= 0) break;
+            // Steps end at different lengths: the sequences still at work move together as soon as they fit fewer row tiles.  Never
+            // below one MFMA tile: the launches read the weights in the same time there, and every further count is a graph.
+            const int rows = look ? packed_rows(std::max(*c->poll_h, kRepackRows), M) : 0;
+            if (rows) {
+                std::vector<int> seqs;
+                for (int b = 0; b < B; ++b)
+                    if (c->poll_h[4 + b]) seqs.push_back(b);
+                if ((int)seqs.size() <= rows) {
+                    fill_packed_rows(seqs, rows, c->dec_seq_h);
+                    HIPCHK(c, hipMemcpyAsync(c->dec_seq_dev, c->dec_seq_h, rows * sizeof(int), hipMemcpyHostToDevice, c->st));
+                    c->dec_rows = M = rows;
+                }
+            }
         }
     }
     c->in_decode_loop = false;
@@ -1051,7 +1070,7 @@ int gen_stage(rsd_ctx* c, int which, const float* u, const int* forced, int mode
             HIPCHK(c, hipEventElapsedTime(&ms, is.e0, is.e1));
             is.ms += ms;
             is.iters += iters - first;
-            is.row_iters += (long long)(iters - first) * M;
+            is.row_iters += row_iters;
             for (int b = 0; b < B; ++b) {
                 if (!was_active[b]) continue;
                 // tokens this sequence sampled inside the loop; its j-th one attends to ctx0 + first + j keys
@@ -1496,7 +1515,7 @@ int rsd_init(rsd_ctx** out, const rsd_model_shape shape[3], const rsd_weights w[
     HIPCHK(c, pin_alloc(&c->dec_seq_h, (size_t)B));
     HIPCHK(c, pin_alloc(&c->chk_h, (size_t)B + 4));
     HIPCHK(c, pin_alloc(&c->steptok_h, (size_t)B * p->step_cap));
-    HIPCHK(c, pin_alloc(&c->poll_h, 4));
+    HIPCHK(c, pin_alloc(&c->poll_h, 4 + (size_t)B));
     if (bon) {
         HIPCHK(c, pin_alloc(&c->bon_copy_h, (size_t)4 * B));        // [model 0: B pairs][model 2: B pairs]
         HIPCHK(c, dev_alloc(&c->bon_copy_dev, (size_t)4 * B));
