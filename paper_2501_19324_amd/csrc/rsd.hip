@@ -20,6 +20,7 @@
 #include "gemv.h"
 #include "gemm.h"
 #include "attn.h"
+#include "tiny.h"
 #include "misc.h"
 #include "sample.h"
 #include "specdec.h"
@@ -760,7 +761,6 @@ AppendArgs append_args(rsd_ctx* c, int which, const int* forced, int mode = 1) {
     return ap;
 }
 
-// One single-token iteration of an LM model over all sequences: forward, head, sample, append.
 // logits[b][:] -> q[b * k + (ctx_len[b] - sd_base[b])][:] for the active sequences: the distribution a
 // sampled proposal is about to be drawn from, kept for its acceptance test
 __global__ void sd_stash_kernel(const float* __restrict__ logits, int V, SeqState st, int k, float* __restrict__ q) {
@@ -779,13 +779,55 @@ void propose_stash(rsd_ctx* c, int mode) {
                        c->p.sd_k, c->sd_qlogits);
 }
 
+// Which single-token iterations the two-launch layers of tiny.h serve: fp32 weights of the widths that fit their registers, contexts that
+// the attention does not split either, and up to eight rows - every row reads the weights for itself there, which the
+// kernels for more rows share.  The head as far as a block per 64 tokens and row is less than the chip holds at once.
+// An iteration whose launches are timed takes the general path, where the launches the probes name exist.
+bool tiny_path(rsd_ctx* c, const Model& m, int M) {
+    const rsd_model_shape& s = m.s;
+    if (s.dtype != RSD_F32 || M > 8 || m.hd != 32 || (s.d_model != 128 && s.d_model != 256) || s.d_ffn % kTinyUnits ||
+        s.d_ffn / kTinyUnits > (s.d_model == 128 ? TinyRow<128>::kMaxParts : TinyRow<256>::kMaxParts) || s.n_heads > TinyRow<256>::kMaxParts ||
+        s.vocab > 8192 || m.splits > 1 || m.max_pages * RSD_PAGE > kTinyPos)
+        return false;
+    for (const auto& q : c->probe)
+        if (q.iter_on) return false;
+    return true;
+}
+template <int D>
+void tiny_iter(rsd_ctx* c, Model& m, int M, const RowMap& rm) {
+    const int F = m.s.d_ffn, H = m.s.n_heads, V = m.s.vocab, units = F / kTinyUnits;
+    const float scale = 1.0f / std::sqrt(32.0f);
+    const float* embed = wptr<float>(m, m.off_embed);
+    float *ha = c->h, *hb = c->xn, *heads = c->att, *mlp = c->gu;      // residual stream (two buffers), partial sums
+    for (int l = 0; l < m.s.n_layers; ++l) {
+        const LayerOff& o = m.layers[l];
+        float* pool_l = reinterpret_cast<float*>(m.pool) + (size_t)l * m.pool_pages * m.page_elts;
+        hipLaunchKernelGGL((tiny_attn_kernel<D>), dim3(M, H), dim3(kTinyT), 0, c->st,
+                           TinyIn{l ? ha : embed, mlp, l ? units : 0, wptr<float>(m, o.attn_norm), m.s.rms_eps, hb}, wptr<float>(m, o.wqkv),
+                           wptr<float>(m, o.wo), pool_l, m.bt_dev, m.max_pages, rm, l ? (const int*)nullptr : c->ds.tokens, c->p.max_ctx,
+                           m.rope, H, m.s.n_kv_heads, scale, heads);
+        hipLaunchKernelGGL((tiny_mlp_kernel<D>), dim3(M, units), dim3(kTinyT), 0, c->st,
+                           TinyIn{hb, heads, H, wptr<float>(m, o.ffn_norm), m.s.rms_eps, ha}, wptr<float>(m, o.wgu), wptr<float>(m, o.wdown), F,
+                           rm, mlp);
+    }
+    hipLaunchKernelGGL((tiny_head_kernel<D>), dim3(M, ceil_div(V, kTinyVocab)), dim3(kTinyT), 0, c->st,
+                       TinyIn{ha, mlp, units, wptr<float>(m, m.off_final_norm), m.s.rms_eps, nullptr}, wptr<float>(m, m.off_head), V, rm,
+                       c->logits);
+}
+
+// One single-token iteration of an LM model over all sequences: forward, head, sample, append.
 // mode 1: the token belongs to a reasoning step; mode 2: it is a proposal of speculative regeneration.
 template <typename WT>
 void decode_iter(rsd_ctx* c, int which, const float* u, const int* forced, int mode = 1) {
     Model& m = c->m[which];
     const int M = c->dec_rows ? c->dec_rows : c->B;
-    run_layers<WT>(c, m, M, decode_map(c, which), true);
-    lm_head<WT>(c, m, c->h, M, c->logits, m.s.vocab);
+    if (tiny_path(c, m, M)) {
+        if (m.s.d_model == 128) tiny_iter<128>(c, m, M, decode_map(c, which));
+        else tiny_iter<256>(c, m, M, decode_map(c, which));
+    } else {
+        run_layers<WT>(c, m, M, decode_map(c, which), true);
+        lm_head<WT>(c, m, c->h, M, c->logits, m.s.vocab);
+    }
     propose_stash(c, mode);
     sample_rows(c, c->logits, m.s.vocab, m.s.vocab, u, c->ds.ctx_len, c->p.max_ctx, c->p.temperature, c->p.top_p,
                 c->p.sep_id, c->p.sep_logit_bias, c->ds.active, M, nullptr, append_args(c, which, forced, mode), decode_seq(c));
