@@ -123,7 +123,15 @@ struct rsd_ctx {
     float *hl = nullptr, *xl = nullptr, *logits = nullptr, *tmp_reward = nullptr;
     int *chosen = nullptr, *steptok_dev = nullptr;
     int *row_seq_dev = nullptr, *row_pos_dev = nullptr, *last_row_dev = nullptr;
-    int *row_seq_h = nullptr, *row_pos_h = nullptr, *last_row_h = nullptr, *steptok_h = nullptr;
+    int* steptok_h = nullptr;
+    // tables of a chunked pass, one behind the other in one device array, so that they travel as one copy: sequence and position of
+    // every row, last row of every sequence, first row and row count of every attention item (row_seq_dev ... item_n_dev point into it).
+    // They are built in one of two pinned arrays, which is free again when the copy out of it (pf_ev) is over.
+    int* pf_dev = nullptr;
+    int* pf_h[2] = {nullptr, nullptr};
+    hipEvent_t pf_ev[2] = {nullptr, nullptr};
+    int pf_slot = 0;
+    bool mirror_busy = false;                // a copy out of the other pinned arrays may be under way (set with the copy)
     // decode iterations over packed rows: row r stands for sequence dec_seq[r] (-1: unused); 0 rows = one row per sequence
     int *dec_seq_dev = nullptr, *dec_seq_h = nullptr;
     int dec_rows = 0;
@@ -132,13 +140,14 @@ struct rsd_ctx {
     // halves the next MFMA GEMM reads instead of xs_h / xs_l (set by a producer that could not write there; used once)
     const uint16_t *xin_h = nullptr, *xin_l = nullptr;
     // chunked-prefill attention work items: first row and row count (<= kPfItemRows rows of one sequence)
-    int *item_row0_dev = nullptr, *item_n_dev = nullptr, *item_row0_h = nullptr, *item_n_h = nullptr;
+    int *item_row0_dev = nullptr, *item_n_dev = nullptr;
     int n_items = 0;
     int pf_rows = 0, pf_max_end = 0;     // rows of the chunked pass in flight and the longest context among its pieces
     // last layer of chunked passes, evaluated for the rows that are read only (Keep): the layer's input of these rows, and their
     // sequences, positions, item tables and (by sequence) places ([5][B]; pinned + device)
     float* tail_h = nullptr;
     int *tail_dev = nullptr, *tail_ints = nullptr;
+    hipEvent_t tail_ev = nullptr;            // the copy out of tail_ints
     int *poll_h = nullptr;
     double stage_ms[4] = {0, 0, 0, 0};
     // kernel timing probes
@@ -293,12 +302,14 @@ int upload_tables(rsd_ctx* c, Model& m) {
     if (!m.bt_dirty) return RSD_OK;
     HIPCHK(c, hipMemcpyAsync(m.bt_dev, m.bt_host, (size_t)c->B * m.max_pages * sizeof(int), hipMemcpyHostToDevice, c->st));
     m.bt_dirty = false;
+    c->mirror_busy = true;
     return RSD_OK;
 }
 
 int push_state(rsd_ctx* c) {
     *c->cur_step() = c->steps_done;
     HIPCHK(c, hipMemcpyAsync(c->sb_dev, c->sb, c->sb_ints * sizeof(int), hipMemcpyHostToDevice, c->st));
+    c->mirror_busy = true;
     return RSD_OK;
 }
 int pull_state(rsd_ctx* c) {
@@ -887,8 +898,8 @@ int prefill(rsd_ctx* c, int which, std::vector<Piece> pieces, AfterPass after_pa
     if (m.bt_dirty) return fail(c, RSD_ESTATE, "internal: block table of model %d not uploaded before a pass", which);
     int *t_seq = c->tail_ints, *t_pos = t_seq + c->B, *t_row0 = t_pos + c->B, *t_n = t_row0 + c->B, *t_place = t_n + c->B;
     int n_kept = 0, put_aside = 0, kept_end = 0;
-    HIPCHK(c, hipStreamSynchronize(c->st));              // staging buffers of the previous pass are free again
     if (keep == kKeepLast) {
+        HIPCHK(c, hipEventSynchronize(c->tail_ev));          // the copy out of the tables below is over
         long long n_rows = 0;
         bool whole = true;                               // (an empty piece has no last row)
         std::fill(t_place, t_place + c->B, -1);
@@ -904,43 +915,58 @@ int prefill(rsd_ctx* c, int which, std::vector<Piece> pieces, AfterPass after_pa
             ++n_kept;
         }
         if (!whole || n_rows <= (std::is_same<WT, bf16_t>::value ? 64 : 8) || 2LL * n_kept > n_rows) keep = kKeepAll;
-        else HIPCHK(c, hipMemcpyAsync(c->tail_dev, c->tail_ints, (size_t)5 * c->B * sizeof(int), hipMemcpyHostToDevice, c->st));
+        else {
+            HIPCHK(c, hipMemcpyAsync(c->tail_dev, c->tail_ints, (size_t)5 * c->B * sizeof(int), hipMemcpyHostToDevice, c->st));
+            HIPCHK(c, hipEventRecord(c->tail_ev, c->st));
+        }
+    }
+    if (c->mirror_busy) {       // callers go on to change the pinned arrays (state, block tables, row maps)
+        HIPCHK(c, hipStreamSynchronize(c->st));
+        c->mirror_busy = false;
     }
     size_t i = 0;
     std::vector<Piece> pass;
     std::vector<int> first_row;
-    bool first_pass = true;
     while (i < pieces.size()) {
         pass.clear();
         first_row.clear();
         int ends = 0;                                // sequences whose last row is in this pass
         int M = 0, n_items = 0;
-        if (!first_pass) HIPCHK(c, hipStreamSynchronize(c->st));      // (see above)
-        first_pass = false;
-        std::fill(c->last_row_h, c->last_row_h + c->B, -1);
-        while (i < pieces.size() && M < kMaxRows) {
+        for (size_t j = i; j < pieces.size() && M < kMaxRows; ++j) {
+            const int n = std::min(pieces[j].end - pieces[j].start, kMaxRows - M);
+            M += n;
+            n_items += ceil_div(n, kPfItemRows);
+        }
+        const int slot = c->pf_slot;
+        c->pf_slot ^= 1;
+        HIPCHK(c, hipEventSynchronize(c->pf_ev[slot]));
+        const size_t at[5] = {0, (size_t)M, (size_t)2 * M, (size_t)2 * M + c->B, (size_t)2 * M + c->B + n_items}, ints = at[4] + n_items;
+        int* const t = c->pf_h[slot];
+        int *row_seq = t + at[0], *row_pos = t + at[1], *last_row = t + at[2], *item_row0 = t + at[3], *item_n = t + at[4];
+        c->row_seq_dev = c->pf_dev + at[0]; c->row_pos_dev = c->pf_dev + at[1]; c->last_row_dev = c->pf_dev + at[2];
+        c->item_row0_dev = c->pf_dev + at[3]; c->item_n_dev = c->pf_dev + at[4];
+        std::fill(last_row, last_row + c->B, -1);
+        int m_at = 0, it = 0;
+        while (i < pieces.size() && m_at < kMaxRows) {
             Piece pc = pieces[i];
-            const int room = kMaxRows - M;
+            const int room = kMaxRows - m_at;
             Piece take = pc;
             if (pc.end - pc.start > room) take.end = pc.start + room;
-            first_row.push_back(M);
+            first_row.push_back(m_at);
             pass.push_back(take);
             for (int r = 0; r < take.end - take.start; r += kPfItemRows) {
-                c->item_row0_h[n_items] = M + r;
-                c->item_n_h[n_items++] = std::min(kPfItemRows, take.end - take.start - r);
+                item_row0[it] = m_at + r;
+                item_n[it++] = std::min(kPfItemRows, take.end - take.start - r);
             }
-            for (int p = take.start; p < take.end; ++p, ++M) { c->row_seq_h[M] = take.b; c->row_pos_h[M] = p; }
+            for (int p = take.start; p < take.end; ++p, ++m_at) { row_seq[m_at] = take.b; row_pos[m_at] = p; }
             // "last row" of a sequence: the final position of its final piece
             const bool final_piece = take.end == pc.end && (i + 1 == pieces.size() || pieces[i + 1].b != pc.b);
-            if (final_piece) { c->last_row_h[take.b] = M - 1; ++ends; }
+            if (final_piece) { last_row[take.b] = m_at - 1; ++ends; }
             if (take.end < pc.end) { pieces[i].start = take.end; break; }
             ++i;
         }
-        HIPCHK(c, hipMemcpyAsync(c->row_seq_dev, c->row_seq_h, M * sizeof(int), hipMemcpyHostToDevice, c->st));
-        HIPCHK(c, hipMemcpyAsync(c->row_pos_dev, c->row_pos_h, M * sizeof(int), hipMemcpyHostToDevice, c->st));
-        HIPCHK(c, hipMemcpyAsync(c->last_row_dev, c->last_row_h, c->B * sizeof(int), hipMemcpyHostToDevice, c->st));
-        HIPCHK(c, hipMemcpyAsync(c->item_row0_dev, c->item_row0_h, n_items * sizeof(int), hipMemcpyHostToDevice, c->st));
-        HIPCHK(c, hipMemcpyAsync(c->item_n_dev, c->item_n_h, n_items * sizeof(int), hipMemcpyHostToDevice, c->st));
+        HIPCHK(c, hipMemcpyAsync(c->pf_dev, t, ints * sizeof(int), hipMemcpyHostToDevice, c->st));
+        HIPCHK(c, hipEventRecord(c->pf_ev[slot], c->st));
         c->n_items = n_items;
         c->pf_rows = M;
         c->pf_max_end = 0;
@@ -1025,6 +1051,7 @@ int gen_stage(rsd_ctx* c, int which, const float* u, const int* forced, int mode
         for (const Piece& pc : pieces) seqs.push_back(pc.b);
         fill_packed_rows(seqs, c->dec_rows, c->dec_seq_h);
         HIPCHK(c, hipMemcpyAsync(c->dec_seq_dev, c->dec_seq_h, c->dec_rows * sizeof(int), hipMemcpyHostToDevice, c->st));
+        c->mirror_busy = true;
     }
     int M = c->dec_rows ? c->dec_rows : B;
     int iters = 0;
@@ -1369,7 +1396,7 @@ void rsd_destroy(rsd_ctx* c) {
                    c->sd_ws[0].pmax, c->sd_ws[0].pidx, c->sd_ws[0].hist, c->sd_ws[0].psum, c->sd_ws[0].sel,
                    c->sd_ws[1].pmax, c->sd_ws[1].pidx, c->sd_ws[1].hist, c->sd_ws[1].psum, c->sd_ws[1].sel, c->h, c->xn, c->qkv, c->att, c->gu, c->act,
                    c->part_acc, c->part_ml, c->part_k, c->xs_h, c->xs_l, c->smp_pmax, c->smp_pidx, c->smp_hist, c->smp_psum, c->smp_sel, c->hl, c->xl, c->logits, c->tmp_reward, c->chosen, c->steptok_dev,
-                   c->row_seq_dev, c->row_pos_dev, c->last_row_dev, c->item_row0_dev, c->item_n_dev, c->tail_h, c->tail_dev, c->bon_copy_dev, c->bon_src_dev, c->dec_seq_dev, c->chk_n_pages_dev, c->chk_err_dev, c->clk_dev};
+                   c->pf_dev, c->tail_h, c->tail_dev, c->bon_copy_dev, c->bon_src_dev, c->dec_seq_dev, c->chk_n_pages_dev, c->chk_err_dev, c->clk_dev};
     for (void* p : dev) if (p) (void)hipFree(p);
     for (auto& q : c->probe)
         for (hipEvent_t e : q.ev) (void)hipEventDestroy(e);
@@ -1379,7 +1406,8 @@ void rsd_destroy(rsd_ctx* c) {
     }
     for (auto& g : c->graphs) { (void)hipGraphExecDestroy(g.exec); (void)hipGraphDestroy(g.graph); }
     if (c->cap_st) (void)hipStreamDestroy(c->cap_st);
-    void* pin[] = {c->sb, c->sd_rows_h, c->sd_aux_h, c->item_row0_h, c->item_n_h, c->row_seq_h, c->row_pos_h, c->last_row_h, c->steptok_h, c->poll_h,
+    for (hipEvent_t e : {c->pf_ev[0], c->pf_ev[1], c->tail_ev}) if (e) (void)hipEventDestroy(e);
+    void* pin[] = {c->sb, c->sd_rows_h, c->sd_aux_h, c->pf_h[0], c->pf_h[1], c->steptok_h, c->poll_h,
                    c->bon_copy_h, c->bon_src_h, c->dec_seq_h, c->chk_h, c->tail_ints};
     for (void* p : pin) if (p) (void)hipHostFree(p);
     delete c;
@@ -1506,6 +1534,7 @@ int rsd_init(rsd_ctx** out, const rsd_model_shape shape[3], const rsd_weights w[
     HIPCHK(c, dev_alloc(&c->tail_h, (size_t)B * d));
     HIPCHK(c, dev_alloc(&c->tail_dev, (size_t)5 * B));
     HIPCHK(c, pin_alloc(&c->tail_ints, (size_t)5 * B));
+    HIPCHK(c, hipEventCreateWithFlags(&c->tail_ev, hipEventDisableTiming));
     HIPCHK(c, dev_alloc(&c->logits, (size_t)B * V));
     HIPCHK(c, dev_alloc(&c->tmp_reward, R));
     if (p->sd_k > 0) {
@@ -1541,19 +1570,14 @@ int rsd_init(rsd_ctx** out, const rsd_model_shape shape[3], const rsd_weights w[
     }
     HIPCHK(c, dev_alloc(&c->chosen, (size_t)B));
     HIPCHK(c, dev_alloc(&c->steptok_dev, (size_t)B * p->step_cap));
-    HIPCHK(c, dev_alloc(&c->row_seq_dev, R));
-    HIPCHK(c, dev_alloc(&c->row_pos_dev, R));
-    HIPCHK(c, dev_alloc(&c->last_row_dev, (size_t)B));
+    HIPCHK(c, dev_alloc(&c->pf_dev, 4 * R + B));
+    for (int i = 0; i < 2; ++i) {
+        HIPCHK(c, pin_alloc(&c->pf_h[i], 4 * R + B));
+        HIPCHK(c, hipEventCreateWithFlags(&c->pf_ev[i], hipEventDisableTiming));
+    }
     HIPCHK(c, dev_alloc(&c->dec_seq_dev, (size_t)B));
     HIPCHK(c, dev_alloc(&c->chk_n_pages_dev, (size_t)B));
     HIPCHK(c, dev_alloc(&c->chk_err_dev, (size_t)4));
-    HIPCHK(c, dev_alloc(&c->item_row0_dev, R));
-    HIPCHK(c, dev_alloc(&c->item_n_dev, R));
-    HIPCHK(c, pin_alloc(&c->item_row0_h, R));
-    HIPCHK(c, pin_alloc(&c->item_n_h, R));
-    HIPCHK(c, pin_alloc(&c->row_seq_h, R));
-    HIPCHK(c, pin_alloc(&c->row_pos_h, R));
-    HIPCHK(c, pin_alloc(&c->last_row_h, (size_t)B));
     HIPCHK(c, pin_alloc(&c->dec_seq_h, (size_t)B));
     HIPCHK(c, pin_alloc(&c->chk_h, (size_t)B + 4));
     HIPCHK(c, pin_alloc(&c->steptok_h, (size_t)B * p->step_cap));
@@ -2323,11 +2347,10 @@ int rsd_check_rows(rsd_ctx* c, int32_t model, const int32_t* seq_host, const int
     if (model < 0 || model > 2 || n < 1 || n > kMaxRows) return fail(c, RSD_EINVAL, "bad model or row count");
     if (!c->m[model].bt_dev) return fail(c, RSD_EINVAL, "model %d has no cache", model);
     HIPCHK(c, hipStreamSynchronize(c->st));          // the staging arrays of the last pass are free
-    std::copy(seq_host, seq_host + n, c->row_seq_h);
-    std::copy(pos_host, pos_host + n, c->row_pos_h);
-    HIPCHK(c, hipMemcpyAsync(c->row_seq_dev, c->row_seq_h, n * sizeof(int), hipMemcpyHostToDevice, c->st));
-    HIPCHK(c, hipMemcpyAsync(c->row_pos_dev, c->row_pos_h, n * sizeof(int), hipMemcpyHostToDevice, c->st));
-    return check_rows(c, model, RowMap{c->row_seq_dev, c->row_pos_dev, nullptr, nullptr}, n);
+    std::copy(seq_host, seq_host + n, c->pf_h[0]);
+    std::copy(pos_host, pos_host + n, c->pf_h[0] + n);
+    HIPCHK(c, hipMemcpyAsync(c->pf_dev, c->pf_h[0], (size_t)2 * n * sizeof(int), hipMemcpyHostToDevice, c->st));
+    return check_rows(c, model, RowMap{c->pf_dev, c->pf_dev + n, nullptr, nullptr}, n);
 }
 
 int rsd_probe_attention(rsd_ctx* c, int32_t model, const int32_t* ctx_len_host, int32_t reps, double* total_ms) {
