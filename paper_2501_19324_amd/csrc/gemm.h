@@ -1209,20 +1209,25 @@ static TilePlan gemm_tile_plan(int epi, int N, int K, int M, size_t part_floats)
 // The gate/up projection with its SwiGLU, and the output head, without K slices: a block owns BN rows of W (the gate and the up
 // rows of BN / 2 units) over all of K, so there are no partial sums to write and read back and no finish kernel.  BN is
 // chosen so that the blocks make one round on 256 compute units (stream_bn).  X and W tiles of 64 k go straight into a ring
-// of up to six LDS stages, all but one of them in flight; the waves divide a K block by (32 columns, K part) and add the K
-// parts through LDS at the end.  Bound by what the copies pull through L2: W once and, per block, all of X (217 MB beside
-// 272 MB at 64 rows of the 7B shape).  Measured against K slices plus their finish kernel (us; 7B gate/up, 1.5B gate/up, a
+// of up to six LDS stages, all but one of them in flight; the waves divide a K block among themselves and add their K parts
+// through LDS at the end.  Bound by what the copies pull through L2: W once and, per block, all of X (217 MB beside
+// 272 MB at 64 rows of the 7B shape, 435 at 128: 8.5 to 9 TB/s together).  Above 32 rows a wave takes all columns, half of the rows and a
+// quarter of the K block: an operand is read from LDS by one or two waves only (72 KB a K block at 128 rows and 160 columns; 180 with 32
+// columns and half of K per wave).  128 rows 80.7 -> 76.4, 27.9 -> 26.6, head 25.7 -> 23.6 us; 64 rows 56.7 / 56.8, 19.7 / 19.8, 17.7 ->
+// 17.0.  Measured against K slices plus their finish kernel (us; 7B gate/up, 1.5B gate/up, a
 // head of 16384 x 1536): 16 rows 48.4 / 51.6, 14.8 / 18.3, 12.1 / 17.4; 32 rows 50.2 / 55.6, 16.7 / 20.3, 13.7 / 19.5; 64 rows 58.8 /
 // 68.6, 21.3 / 24.7, 19.2 / 25.8; 128 rows (against the tile kernel) 84.6 / 93.1, 30.3 / 35.6, 30.3 / 34.9.  Matrices that give no
 // single round of blocks stay with the slices: [59136][8192] at 16 rows 182 against 159.
 template <int MT, int BN> struct StreamCfg {
     static constexpr int BK = 64;
-    static constexpr int TN = 1, WN = BN / 32, KW = BN == 64 ? 4 : 2, NW = WN * KW;      // waves along the columns / along K
+    // up to 32 rows: a wave per 32 columns and half (quarter) of the K block; more: all columns, half of the rows, a quarter of K
+    static constexpr int TN = MT == 1 ? 1 : BN / 32, WN = BN / 32 / TN, WM = MT == 1 ? 1 : 2, KW = MT > 1 || BN == 64 ? 4 : 2;
+    static constexpr int TM = MT / WM, NW = WN * WM * KW;             // row tiles of a wave; waves
     static constexpr int XREQ = MT * 8, REQ = XREQ + BN / 8;          // 1 KB requests of a K block: X hi, X lo, W
     static constexpr int NS = (160 * 1024) / (REQ * 1024) > 6 ? 6 : (160 * 1024) / (REQ * 1024);
     static constexpr int CNT = REQ / NW, EXTRA = REQ % NW;
     static constexpr int LDS = NS * REQ * 1024;
-    static_assert(NS >= 2 && (KW - 1) * WN * MT * TN * 4096 <= LDS, "");
+    static_assert(NS >= 2 && (KW - 1) * WN * WM * TN * 4096 <= LDS, "");
 };
 template <int EPI, int MT, int BN>
 __global__ __launch_bounds__((StreamCfg<MT, BN>::NW * 64)) void gemm_stream_kernel(const bf16_t* __restrict__ W, int N, int K,
@@ -1230,11 +1235,11 @@ __global__ __launch_bounds__((StreamCfg<MT, BN>::NW * 64)) void gemm_stream_kern
                                                              float* __restrict__ Y, int ldy,
                                                              uint16_t* __restrict__ Oh, uint16_t* __restrict__ Ol) {
     using C = StreamCfg<MT, BN>;
-    constexpr int BK = C::BK, TN = C::TN, WN = C::WN, KW = C::KW, NW = C::NW, NS = C::NS, CNT = C::CNT, EXTRA = C::EXTRA;
+    constexpr int BK = C::BK, TM = C::TM, TN = C::TN, WN = C::WN, WM = C::WM, KW = C::KW, NW = C::NW, NS = C::NS, CNT = C::CNT, EXTRA = C::EXTRA;
     constexpr int STAGE = C::REQ * 512;                       // bf16 elements of a stage
     extern __shared__ __attribute__((aligned(16))) uint16_t tile_sm[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wn = wave % WN, kw = wave / WN;
+    const int wn = wave % WN, wm = wave / WN % WM, kw = wave / (WN * WM);
     const int bx = blockIdx.x, n0 = bx * BN, nk = K / BK;
     const int F = N / 2;
     auto wrow = [&](int r) { return EPI == EPI_SWIGLU ? ((r >> 4) & 1) * F + min(bx * (BN / 2) + (r >> 5) * 16 + (r & 15), F - 1) : min(n0 + r, N - 1); };
@@ -1262,9 +1267,9 @@ __global__ __launch_bounds__((StreamCfg<MT, BN>::NW * 64)) void gemm_stream_kern
         for (int i = 0; i < CNT; ++i) copy16_to_lds(lds0 + s * (STAGE * 2) + i * (NW * 1024), voff[i], base[i] + ko);
         if (extra) copy16_to_lds(lds0 + s * (STAGE * 2) + CNT * (NW * 1024), voff[CNT], base[CNT] + ko);
     };
-    f32x16_t acc[MT][TN];
+    f32x16_t acc[TM][TN];
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -1288,9 +1293,9 @@ __global__ __launch_bounds__((StreamCfg<MT, BN>::NW * 64)) void gemm_stream_kern
 #pragma unroll
             for (int j = 0; j < TN; ++j) w[j] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(b + j * 32 * BK + off));
 #pragma unroll
-            for (int i = 0; i < MT; ++i) {
-                const bf16x8_t xl = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(a + (MT + i) * 32 * BK + off));
-                const bf16x8_t xh = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(a + i * 32 * BK + off));
+            for (int i = 0; i < TM; ++i) {
+                const bf16x8_t xl = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(a + (MT + wm * TM + i) * 32 * BK + off));
+                const bf16x8_t xh = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(a + (wm * TM + i) * 32 * BK + off));
 #pragma unroll
                 for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl, w[j], acc[i][j], 0, 0, 0);
 #pragma unroll
@@ -1301,58 +1306,56 @@ __global__ __launch_bounds__((StreamCfg<MT, BN>::NW * 64)) void gemm_stream_kern
         cur = cur == NS - 1 ? 0 : cur + 1;
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    // add the K parts in ascending order through LDS
-    float* red = reinterpret_cast<float*>(tile_sm);
-    if (kw > 0) {
+    // Add the K parts through LDS: the waves of one (row, column) part share the 16 values a lane has of a tile, 8 / KW pairs
+    // (v, v + 8) each, and add the others' to their own, ascending.  One row tile of every wave at a time.
+    constexpr int PV = 8 / KW;                                // pairs per wave
+    float2* red = reinterpret_cast<float2*>(tile_sm);        // [owner][source][wn, wm][j][pair][lane]
+    auto at = [&](int owner, int src, int j, int p) {
+        return red + ((((owner * (KW - 1) + (src < owner ? src : src - 1)) * (WN * WM) + wave % (WN * WM)) * TN + j) * PV + p) * 64 + lane;
+    };
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+    for (int i = 0; i < TM; ++i) {
+        if (i > 0) __syncthreads();
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+        for (int o = 0; o < KW; ++o)
+            if (o != kw)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) red[((((kw - 1) * WN + wn) * MT + i) * TN + j) * 1024 + v * 64 + lane] = acc[i][j][v];
-    }
-    __syncthreads();
-    if (kw > 0) return;
+                for (int j = 0; j < TN; ++j)
 #pragma unroll
-    for (int p = 0; p < KW - 1; ++p)
+                    for (int p = 0; p < PV; ++p) *at(o, kw, j, p) = make_float2(acc[i][j][o * PV + p], acc[i][j][o * PV + p + 8]);
+        __syncthreads();
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+            for (int p = 0; p < PV; ++p) {
+                float2 x = make_float2(0.0f, 0.0f);           // the wave's own pair (its registers have constant indices only)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][j][v] += red[(((p * WN + wn) * MT + i) * TN + j) * 1024 + v * 64 + lane];
-    if (EPI == EPI_SWIGLU) {
+                for (int o = 0; o < KW; ++o)
+                    if (o == kw) x = make_float2(acc[i][j][o * PV + p], acc[i][j][o * PV + p + 8]);
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int col = bx * (BN / 2) + (wn * TN + j) * 16 + (lane & 15);
-#pragma unroll
-                for (int v = 0; v < 8; ++v) {
-                    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[i][j][v]), __float_as_uint(acc[i][j][v + 8]), false, false);
+                for (int q = 0; q < KW - 1; ++q) {
+                    const float2 y = *at(kw, q < kw ? q : q + 1, j, p);
+                    x.x += y.x; x.y += y.y;
+                }
+                const int v = kw * PV + p, m0 = (wm * TM + i) * 32 + 8 * (v >> 2) + 4 * kg + (v & 3);       // x.y: row m0 + 16
+                if (EPI == EPI_SWIGLU) {
+                    const int col = bx * (BN / 2) + (wn * TN + j) * 16 + (lane & 15);
+                    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x.x), __float_as_uint(x.y), false, false);
                     const float g = __uint_as_float(s[0]), u = __uint_as_float(s[1]);
-                    const int m = i * 32 + 8 * (v >> 2) + 4 * kg + (v & 3) + ((lane & 16) ? 16 : 0);
+                    const int m = m0 + ((lane & 16) ? 16 : 0);
                     if (m < M && col < F) {
-                        const float x = silu_mul(g, u);
-                        const uint16_t hi = f2bf(x);
+                        const float z = silu_mul(g, u);
+                        const uint16_t hi = f2bf(z);
                         Oh[(size_t)m * F + col] = hi;
-                        Ol[(size_t)m * F + col] = f2bf(x - bf2f(hi));
+                        Ol[(size_t)m * F + col] = f2bf(z - bf2f(hi));
                     }
+                } else {
+                    const int n = n0 + (wn * TN + j) * 32 + l32;
+                    if (m0 < M && n < N) Y[(size_t)m0 * ldy + n] = x.x;
+                    if (m0 + 16 < M && n < N) Y[(size_t)(m0 + 16) * ldy + n] = x.y;
                 }
             }
-        return;
     }
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int n = n0 + (wn * TN + j) * 32 + l32;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int m = i * 32 + 8 * (v >> 2) + 4 * kg + (v & 3);
-                if (m < M && n < N) Y[(size_t)m * ldy + n] = acc[i][j][v];
-            }
-        }
 }
 
 // BN for which an [N][K] matrix gives 160..256 blocks, as many as possible; 0: none
