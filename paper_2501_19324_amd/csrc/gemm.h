@@ -74,55 +74,73 @@ __global__ __launch_bounds__(256) void sgemm_nt_kernel(const float* __restrict__
 }
 
 // The same for products whose 64x64 tiles would leave most of the chip idle (the tiny configuration: 128 rows of 128..1024
-// columns are 4 to 32 of them): 32x32 tiles, 2x2 outputs per thread, K in blocks of 64 with the next block requested while the
-// present one is multiplied.  Those passes are bound by the latency of their K steps: 128 rows x 256 columns, K = 256 and 1024
-// in turn, 42 -> 27 us on average; 128 columns, K = 128 and 512, 23.0 -> 14.9.  Sums run over ascending k in both.
+// columns are 4 to 32 of them): 32x32 tiles, K in blocks of 64 with the next block requested while the present one is multiplied.
+// Every wave multiplies the whole tile on its quarter of a K block, 4x4 outputs per lane (eight 16-byte LDS reads for 64
+// multiply-adds), and the quarters are added at the end.  Bound by the latency of the K steps and, within one, by the FMAs.
+// 128 rows x 256 columns, K = 256 and 1024 in turn: 27.0 -> 16.6 us on average against 2x2 outputs per thread and all of K (two LDS
+// reads for every four multiply-adds); 128 columns, K = 128 and 512, 15.2 -> 9.3.
 template <int EPI>
 __global__ __launch_bounds__(256) void sgemm32_nt_kernel(const float* __restrict__ W, int N, int K,
                                                          const float* __restrict__ X, int ldx,
                                                          float* __restrict__ Y, int ldy, int M) {
-    constexpr int BK = 64;
-    __shared__ float As[BK][32 + 1];
-    __shared__ float Bs[BK][32 + 1];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+    constexpr int BK = 64, LD = BK + 4;                      // row stride 68: eight rows of 16 bytes touch all 32 banks
+    __shared__ __attribute__((aligned(16))) float sm[2 * 32 * LD];
+    float *Xs = sm, *Ws = sm + 32 * LD;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tx = lane & 7, ty = lane >> 3;
     const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
     // copies: 16 threads per row of 64 k, rows tid / 16 and tid / 16 + 16
     const int row = tid >> 4, kq = (tid & 15) * 4;
     const float* xa[2] = {X + (size_t)min(m0 + row, M - 1) * ldx + kq, X + (size_t)min(m0 + row + 16, M - 1) * ldx + kq};
     const float* wb[2] = {W + (size_t)min(n0 + row, N - 1) * K + kq, W + (size_t)min(n0 + row + 16, N - 1) * K + kq};
-    float acc[2][2] = {};
-    float4 a[2], b[2];
+    float acc[4][4] = {};
+    f32x4_t a[2], b[2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) { a[i] = *reinterpret_cast<const float4*>(xa[i]); b[i] = *reinterpret_cast<const float4*>(wb[i]); }
+    for (int i = 0; i < 2; ++i) { a[i] = *reinterpret_cast<const f32x4_t*>(xa[i]); b[i] = *reinterpret_cast<const f32x4_t*>(wb[i]); }
     for (int k0 = 0; k0 < K; k0 += BK) {                     // (K is a multiple of 64)
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            const int r = row + 16 * i;
-            As[kq][r] = a[i].x; As[kq + 1][r] = a[i].y; As[kq + 2][r] = a[i].z; As[kq + 3][r] = a[i].w;
-            Bs[kq][r] = b[i].x; Bs[kq + 1][r] = b[i].y; Bs[kq + 2][r] = b[i].z; Bs[kq + 3][r] = b[i].w;
+            *reinterpret_cast<f32x4_t*>(Xs + (row + 16 * i) * LD + kq) = a[i];
+            *reinterpret_cast<f32x4_t*>(Ws + (row + 16 * i) * LD + kq) = b[i];
         }
         __syncthreads();
         const int kn = min(k0 + BK, K - BK);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) { a[i] = *reinterpret_cast<const float4*>(xa[i] + kn); b[i] = *reinterpret_cast<const float4*>(wb[i] + kn); }
-#pragma unroll 16
-        for (int k = 0; k < BK; ++k) {
-            const float x0 = As[k][ty * 2], x1 = As[k][ty * 2 + 1], w0 = Bs[k][tx * 2], w1 = Bs[k][tx * 2 + 1];
-            acc[0][0] += x0 * w0; acc[0][1] += x0 * w1;
-            acc[1][0] += x1 * w0; acc[1][1] += x1 * w1;
+        for (int i = 0; i < 2; ++i) { a[i] = *reinterpret_cast<const f32x4_t*>(xa[i] + kn); b[i] = *reinterpret_cast<const f32x4_t*>(wb[i] + kn); }
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            const int k = wave * 16 + kk * 4;
+            f32x4_t x[4], w[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                x[i] = *reinterpret_cast<const f32x4_t*>(Xs + (ty + 8 * i) * LD + k);
+                w[i] = *reinterpret_cast<const f32x4_t*>(Ws + (tx + 8 * i) * LD + k);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[i][j] += x[i].x * w[j].x + x[i].y * w[j].y + x[i].z * w[j].z + x[i].w * w[j].w;
         }
     }
+    // wave i takes row part i of all four quarters
+    __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int m = m0 + ty * 2 + i, n = n0 + tx * 2 + j;
-            if (m < M && n < N) {
-                float* yp = Y + (size_t)m * ldy + n;
-                *yp = (EPI == EPI_RESID) ? (*yp + acc[i][j]) : acc[i][j];
-            }
+        for (int j = 0; j < 4; ++j) sm[((wave * 4 + i) * 4 + j) * 64 + lane] = acc[i][j];
+    __syncthreads();
+    const int m = m0 + ty + 8 * wave;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int n = n0 + tx + 8 * j;
+        float v = 0.0f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v += sm[((q * 4 + wave) * 4 + j) * 64 + lane];
+        if (m < M && n < N) {
+            float* yp = Y + (size_t)m * ldy + n;
+            *yp = (EPI == EPI_RESID) ? (*yp + v) : v;
         }
+    }
 }
 
 // ---------------------------------------------------------------- bf16 MFMA, 2..64 rows, pre-split activations

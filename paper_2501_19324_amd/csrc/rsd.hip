@@ -747,6 +747,15 @@ void reward_rows(rsd_ctx* c, Model& m, const float* H, int n, const int* rows, f
                        wptr<WT>(t, t.off_final_norm), t.s.rms_eps, wptr<WT>(m, m.off_head), wptr<WT>(m, m.off_br), out);
 }
 
+// The sampler's arguments for rows from r0 on
+SampleArgs sample_args(rsd_ctx* c, const float* logits, int ld, int V, const float* u, const int* u_index, int u_stride, float temperature,
+                       float top_p, int sep_id, float sep_bias, const int* active, int* out, const int* row_seq, int r0) {
+    const int s0 = row_seq ? 0 : r0;             // per-sequence arrays keep their base under a row map
+    return SampleArgs{logits + (size_t)r0 * ld, ld, V, u ? u + (size_t)s0 * u_stride : nullptr,
+                      u_index ? u_index + s0 : nullptr, u_stride, temperature, top_p, sep_id, sep_bias,
+                      active ? active + s0 : nullptr, out ? out + r0 : nullptr,
+                      c->smp_pmax, c->smp_pidx, c->smp_hist, c->smp_psum, c->smp_sel, row_seq ? row_seq + r0 : nullptr};
+}
 // Sample one token per row; with `ap` the chosen token is also appended to its sequence.
 // row_seq (packed rows): u, u_index, active and the appended state are indexed by the sequence of a row
 void sample_rows(rsd_ctx* c, const float* logits, int ld, int V, const float* u, const int* u_index, int u_stride,
@@ -754,12 +763,8 @@ void sample_rows(rsd_ctx* c, const float* logits, int ld, int V, const float* u,
                  const AppendArgs& ap, const int* row_seq = nullptr) {
     for (int r0 = 0; r0 < n; r0 += c->smp_rows) {
         const int rows = std::min(c->smp_rows, n - r0);
-        const int s0 = row_seq ? 0 : r0;         // per-sequence arrays keep their base under a row map
-        SampleArgs a{logits + (size_t)r0 * ld, ld, V, u ? u + (size_t)s0 * u_stride : nullptr,
-                     u_index ? u_index + s0 : nullptr, u_stride, temperature, top_p, sep_id, sep_bias,
-                     active ? active + s0 : nullptr, out ? out + r0 : nullptr,
-                     c->smp_pmax, c->smp_pidx, c->smp_hist, c->smp_psum, c->smp_sel, row_seq ? row_seq + r0 : nullptr};
-        sample_launch(c->st, a, ap, rows);
+        sample_launch(c->st, sample_args(c, logits, ld, V, u, u_index, u_stride, temperature, top_p, sep_id, sep_bias, active, out, row_seq, r0),
+                      ap, rows);
     }
 }
 
@@ -804,8 +809,9 @@ bool tiny_path(rsd_ctx* c, const Model& m, int M) {
         if (q.iter_on) return false;
     return true;
 }
+// true: the token has been chosen and appended as well
 template <int D>
-void tiny_iter(rsd_ctx* c, Model& m, int M, const RowMap& rm) {
+bool tiny_iter(rsd_ctx* c, Model& m, int M, const RowMap& rm, const SampleArgs& sa, const AppendArgs& ap) {
     const int F = m.s.d_ffn, H = m.s.n_heads, V = m.s.vocab, units = F / kTinyUnits;
     const float scale = 1.0f / std::sqrt(32.0f);
     const float* embed = wptr<float>(m, m.off_embed);
@@ -821,9 +827,12 @@ void tiny_iter(rsd_ctx* c, Model& m, int M, const RowMap& rm) {
                            TinyIn{hb, heads, H, wptr<float>(m, o.ffn_norm), m.s.rms_eps, ha}, wptr<float>(m, o.wgu), wptr<float>(m, o.wdown), F,
                            rm, mlp);
     }
-    hipLaunchKernelGGL((tiny_head_kernel<D>), dim3(M, ceil_div(V, kTinyVocab)), dim3(kTinyT), 0, c->st,
-                       TinyIn{ha, mlp, units, wptr<float>(m, m.off_final_norm), m.s.rms_eps, nullptr}, wptr<float>(m, m.off_head), V, rm,
-                       c->logits);
+    const TinyIn in{ha, mlp, units, wptr<float>(m, m.off_final_norm), m.s.rms_eps, nullptr};
+    const dim3 grid(M, ceil_div(V, kTinyVocab));
+    const bool choose = sa.temperature == 0.0f && grid.y <= SMP_NB;
+    if (choose) hipLaunchKernelGGL((tiny_head_kernel<D, true>), grid, dim3(kTinyT), 0, c->st, in, wptr<float>(m, m.off_head), V, rm, c->logits, sa, ap);
+    else hipLaunchKernelGGL((tiny_head_kernel<D, false>), grid, dim3(kTinyT), 0, c->st, in, wptr<float>(m, m.off_head), V, rm, c->logits, sa, ap);
+    return choose;
 }
 
 // One single-token iteration of an LM model over all sequences: forward, head, sample, append.
@@ -832,16 +841,19 @@ template <typename WT>
 void decode_iter(rsd_ctx* c, int which, const float* u, const int* forced, int mode = 1) {
     Model& m = c->m[which];
     const int M = c->dec_rows ? c->dec_rows : c->B;
+    const AppendArgs ap = append_args(c, which, forced, mode);
     if (tiny_path(c, m, M)) {
-        if (m.s.d_model == 128) tiny_iter<128>(c, m, M, decode_map(c, which));
-        else tiny_iter<256>(c, m, M, decode_map(c, which));
+        const SampleArgs sa = sample_args(c, c->logits, m.s.vocab, m.s.vocab, u, c->ds.ctx_len, c->p.max_ctx, c->p.temperature, c->p.top_p,
+                                          c->p.sep_id, c->p.sep_logit_bias, c->ds.active, nullptr, decode_seq(c), 0);
+        const RowMap rm = decode_map(c, which);
+        if (m.s.d_model == 128 ? tiny_iter<128>(c, m, M, rm, sa, ap) : tiny_iter<256>(c, m, M, rm, sa, ap)) return;
     } else {
         run_layers<WT>(c, m, M, decode_map(c, which), true);
         lm_head<WT>(c, m, c->h, M, c->logits, m.s.vocab);
     }
     propose_stash(c, mode);
     sample_rows(c, c->logits, m.s.vocab, m.s.vocab, u, c->ds.ctx_len, c->p.max_ctx, c->p.temperature, c->p.top_p,
-                c->p.sep_id, c->p.sep_logit_bias, c->ds.active, M, nullptr, append_args(c, which, forced, mode), decode_seq(c));
+                c->p.sep_id, c->p.sep_logit_bias, c->ds.active, M, nullptr, ap, decode_seq(c));
 }
 
 // The graph of one decode iteration of model `which`, recorded on first use.  Everything an

@@ -9,13 +9,15 @@
 //     rotary embedding; cache write (the first head of a group); attention; the head's share of the output projection -> partials
 //   tiny_mlp_kernel, block (row, 32 hidden units): x = h + sum of the heads' partials; RMSNorm; gate and up; SiLU; the units' share of
 //     the down projection -> partials
-//   tiny_head_kernel, block (row, 64 tokens): x = h + sum of the MLP's partials; RMSNorm; logits
+//   tiny_head_kernel, block (row, 64 tokens): x = h + sum of the MLP's partials; RMSNorm; logits; greedy: the arg max as well, chosen
+//     and appended by the block that finishes a row, as in sample_max_kernel
 // One block of a row writes the new residual stream, into the other of two buffers (every block of the launch reads the old one).
 // Everything a block reads that does not depend on the launch before it - its weights - is requested first and kept in registers.
 // Partials are added in a fixed order: results do not depend on timing.
 #pragma once
 #include "attn.h"
 #include "common.h"
+#include "sample.h"
 
 constexpr int kTinyT = 512;                  // threads of a block: 32 groups of 16 lanes, or 64 of 8
 constexpr int kTinyPos = 128;                // positions a block holds in registers (two a lane group)
@@ -258,9 +260,11 @@ __global__ __launch_bounds__(kTinyT) void tiny_mlp_kernel(TinyIn in, const float
     }
 }
 
-// W: [V][D]; logits [M][V]
-template <int D>
-__global__ __launch_bounds__(kTinyT) void tiny_head_kernel(TinyIn in, const float* __restrict__ W, int V, RowMap rm, float* __restrict__ logits) {
+// W: [V][D]; logits [M][V].  CHOOSE (at most SMP_NB blocks a row): the sampler's phase A with a block as a span; its workspace and counter
+// are used as sample_max_kernel uses them (64 more on the row's counter with every call)
+template <int D, bool CHOOSE>
+__global__ __launch_bounds__(kTinyT) void tiny_head_kernel(TinyIn in, const float* __restrict__ W, int V, RowMap rm, float* __restrict__ logits,
+                                                           SampleArgs sa, AppendArgs ap) {
     constexpr int NX = D / 64, NV = kTinyVocab / 32;
     __shared__ TinyLds<D> s;
     const int r = blockIdx.x, tid = threadIdx.x, sub16 = tid & 15, row16 = tid >> 4;
@@ -284,10 +288,44 @@ __global__ __launch_bounds__(kTinyT) void tiny_head_kernel(TinyIn in, const floa
 #pragma unroll
         for (int a = 0; a < NV; ++a) y[a] += dot4(w[a][i], x);
     }
+    float bv = -INFINITY; int bi = 0x7FFFFFFF;
 #pragma unroll
     for (int a = 0; a < NV; ++a) {
         const int n = blockIdx.y * kTinyVocab + a * 32 + row16;
-        const float z = sum16(y[a]) * rs;
+        float z = sum16(y[a]) * rs;
         if (sub16 == 0 && n < V) logits[(size_t)r * V + n] = z;
+        if (n == sa.sep_id) z += sa.sep_bias;
+        if (n < V && z > bv) { bv = z; bi = n; }
     }
+    if constexpr (!CHOOSE) return;
+    auto better = [&](float ov, int oi) { if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; } };
+    __shared__ float fred[kTinyT / 64];
+    __shared__ int ired[kTinyT / 64];
+#pragma unroll
+    for (int off = 16; off < 64; off <<= 1) better(__shfl_xor(bv, off, RSD_WAVE), __shfl_xor(bi, off, RSD_WAVE));
+    if ((tid & 63) == 0) { fred[tid >> 6] = bv; ired[tid >> 6] = bi; }
+    __syncthreads();
+    if (tid >= 64) return;
+    if (tid == 0) {
+#pragma unroll
+        for (int i = 1; i < kTinyT / 64; ++i) better(fred[i], ired[i]);
+        __hip_atomic_store(&sa.pmax[(size_t)r * SMP_NB + blockIdx.y], bv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&sa.pidx[(size_t)r * SMP_NB + blockIdx.y], bi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    int last = 0;
+    if (tid == 0) {
+        const unsigned mine = blockIdx.y ? 1u : SMP_NB + 1u - gridDim.y;
+        last = (__hip_atomic_fetch_add(reinterpret_cast<unsigned*>(sa.sel + (size_t)r * SMP_SEL + 8), mine, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT) + mine) % SMP_NB == 0;
+    }
+    if (!__builtin_amdgcn_readfirstlane(last)) return;
+    bv = -INFINITY; bi = 0x7FFFFFFF;
+    if (tid < (int)gridDim.y) {
+        bv = __hip_atomic_load(&sa.pmax[(size_t)r * SMP_NB + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        bi = __hip_atomic_load(&sa.pidx[(size_t)r * SMP_NB + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) better(__shfl_xor(bv, off, RSD_WAVE), __shfl_xor(bi, off, RSD_WAVE));
+    if (tid == 0) smp_append(sa, ap, r, seq, bi);
 }
