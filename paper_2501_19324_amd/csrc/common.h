@@ -46,28 +46,21 @@ __device__ __forceinline__ float ld1(const bf16_t* p) { return bf2f(p->v); }
 __device__ __forceinline__ void st1(float* p, float v) { *p = v; }
 __device__ __forceinline__ void st1(bf16_t* p, float v) { p->v = f2bf(v); }
 
+// ---- Reductions over a wave by cross-lane register moves.  A shuffle (ds_bpermute) is a trip through the LDS of more than a hundred
+// cycles, and the six of a reduction wait for one another: about 0.4 us, in launches of 4 to 10.  All 64 lanes must be active; every lane gets the result.
+template <int CTRL> __device__ __forceinline__ uint32_t dpp_move(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
+}
+// f(ctrl) for the four moves that bring together the 16 lanes of a row: quad_perm [1,0,3,2], [2,3,0,1], row_half_mirror, row_mirror
+template <typename F> __device__ __forceinline__ void row16_moves(F f) {
+    f(std::integral_constant<int, 0xB1>{});
+    f(std::integral_constant<int, 0x4E>{});
+    f(std::integral_constant<int, 0x141>{});
+    f(std::integral_constant<int, 0x140>{});
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, RSD_WAVE);
-    return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, RSD_WAVE));
-    return v;
-}
-
-// Sum over the 64 lanes with cross-lane register moves (no LDS traffic).  All 64 lanes must be
-// active; every lane gets the result.
-__device__ __forceinline__ float wave_sum_dpp(float v) {
-    auto dpp_add = [](float x, auto ctrl) {
-        return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xF, 0xF, true));
-    };
-    v = dpp_add(v, std::integral_constant<int, 0xB1>{});    // quad_perm [1,0,3,2]
-    v = dpp_add(v, std::integral_constant<int, 0x4E>{});    // quad_perm [2,3,0,1]
-    v = dpp_add(v, std::integral_constant<int, 0x141>{});   // row_half_mirror
-    v = dpp_add(v, std::integral_constant<int, 0x140>{});   // row_mirror: each row of 16 lanes holds its sum
-    const int bits = __float_as_int(v);
+    row16_moves([&](auto c) { v += __uint_as_float(dpp_move<decltype(c)::value>(__float_as_uint(v))); });
+    const int bits = __float_as_int(v);                     // each row of 16 lanes holds its sum
     return (__int_as_float(__builtin_amdgcn_readlane(bits, 0)) + __int_as_float(__builtin_amdgcn_readlane(bits, 16))) +
            (__int_as_float(__builtin_amdgcn_readlane(bits, 32)) + __int_as_float(__builtin_amdgcn_readlane(bits, 48)));
 }
@@ -85,6 +78,45 @@ __device__ __forceinline__ float rows4_sum(float v) {
     v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
     const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+__device__ __forceinline__ float wave_max(float v) {
+    row16_moves([&](auto c) { v = fmaxf(v, __uint_as_float(dpp_move<decltype(c)::value>(__float_as_uint(v)))); });
+    return rows4_max(v);
+}
+// arg max: the largest value, on ties the lowest index.  wave_argmax_rows: lanes that agree within the 16-lane rows already
+__device__ __forceinline__ void take_better(float& v, int& i, float ov, int oi) { if (ov > v || (ov == v && oi < i)) { v = ov; i = oi; } }
+__device__ __forceinline__ void wave_argmax_rows(float& v, int& i) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap((uint32_t)i, (uint32_t)i, false, false);
+    v = __uint_as_float(a[0]); i = (int)b[0];
+    take_better(v, i, __uint_as_float(a[1]), (int)b[1]);
+    const auto c = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    const auto d = __builtin_amdgcn_permlane32_swap((uint32_t)i, (uint32_t)i, false, false);
+    v = __uint_as_float(c[0]); i = (int)d[0];
+    take_better(v, i, __uint_as_float(c[1]), (int)d[1]);
+}
+__device__ __forceinline__ void wave_argmax(float& v, int& i) {
+    row16_moves([&](auto c) {
+        constexpr int C = decltype(c)::value;
+        const float ov = __uint_as_float(dpp_move<C>(__float_as_uint(v)));
+        take_better(v, i, ov, (int)dpp_move<C>((uint32_t)i));
+    });
+    wave_argmax_rows(v, i);
+}
+// 64-bit sums
+typedef unsigned long long u64_t;
+__device__ __forceinline__ u64_t u64_of(uint32_t lo, uint32_t hi) { return ((u64_t)hi << 32) | lo; }
+__device__ __forceinline__ u64_t wave_sum_u64(u64_t v) {
+    row16_moves([&](auto c) {
+        constexpr int C = decltype(c)::value;
+        v += u64_of(dpp_move<C>((uint32_t)v), dpp_move<C>((uint32_t)(v >> 32)));
+    });
+    u64_t s = 0;
+#pragma unroll
+    for (int r = 0; r < 64; r += 16)
+        s += u64_of((uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, r), (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), r));
+    return s;
 }
 
 // Sum over a 256-thread block; `red` is 4 floats of LDS. All threads get the result.

@@ -34,8 +34,6 @@
 #include "common.h"
 #include "misc.h"
 
-typedef unsigned long long u64_t;
-
 constexpr int SMP_NB = 64;      // spans a row is cut into
 constexpr int SMP_T = 256;      // threads per block
 constexpr uint32_t SMP_UNIT = 0x2B800000u;                // key of 2^-40, the smallest e with a mass
@@ -54,28 +52,27 @@ static_assert(SMP_DENSE > 0 && SMP_BINS + SMP_SUB <= SMP_WS, "");
 constexpr int SMP_SEL = 9;                                // words of a row's `sel`
 constexpr int SMP_FB = SMP_NB / 4;                        // blocks of phase D of a dense row: a span per wave
 
-__device__ __forceinline__ u64_t shfl_up_u64(u64_t v, int d) {
-    const unsigned lo = __shfl_up((unsigned)v, d, RSD_WAVE), hi = __shfl_up((unsigned)(v >> 32), d, RSD_WAVE);
-    return ((u64_t)hi << 32) | lo;
-}
 __device__ __forceinline__ u64_t shfl_xor_u64(u64_t v, int d) {
     const unsigned lo = __shfl_xor((unsigned)v, d, RSD_WAVE), hi = __shfl_xor((unsigned)(v >> 32), d, RSD_WAVE);
     return ((u64_t)hi << 32) | lo;
 }
-__device__ __forceinline__ u64_t wave_sum_u64(u64_t v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += shfl_xor_u64(v, off);
-    return v;
+// Inclusive scans over the lanes in vector instructions: shifts inside the rows of 16 lanes, then the last lane of a row to the rows behind it
+// (by shuffles the four scans of phase D alone took 1.5 us of its 9)
+__device__ __forceinline__ u64_t wave_incl_scan_u64(u64_t x) {
+    using std::integral_constant;
+    auto add = [&](auto ctrl, auto rows) {
+        constexpr int C = decltype(ctrl)::value, R = decltype(rows)::value;
+        x += u64_of((uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, C, R, 0xF, false),
+                    (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), C, R, 0xF, false));
+    };
+    add(integral_constant<int, 0x111>{}, integral_constant<int, 0xF>{});       // row_shr by 1, 2, 4, 8
+    add(integral_constant<int, 0x112>{}, integral_constant<int, 0xF>{});
+    add(integral_constant<int, 0x114>{}, integral_constant<int, 0xF>{});
+    add(integral_constant<int, 0x118>{}, integral_constant<int, 0xF>{});
+    add(integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});       // row_bcast 15 into rows 1 and 3
+    add(integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});       // row_bcast 31 into rows 2 and 3
+    return x;
 }
-__device__ __forceinline__ u64_t wave_incl_scan_u64(u64_t v, int lane) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const u64_t o = shfl_up_u64(v, d);
-        if (lane >= d) v += o;
-    }
-    return v;
-}
-// the same for 32 bits in vector instructions: shifts inside the rows of 16 lanes, then the last lane of a row to the rows behind it
 __device__ __forceinline__ int wave_incl_scan(int x) {
     using std::integral_constant;
     auto add = [&](auto ctrl, auto rows) { x += __builtin_amdgcn_update_dpp(0, x, decltype(ctrl)::value, decltype(rows)::value, 0xF, false); };
@@ -90,7 +87,7 @@ __device__ __forceinline__ int wave_incl_scan(int x) {
 // inclusive scan over the 256 threads of a block; wtot is 4 u64 of LDS
 __device__ __forceinline__ u64_t block256_incl_scan_u64(u64_t v, u64_t* wtot) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const u64_t incl = wave_incl_scan_u64(v, lane);
+    const u64_t incl = wave_incl_scan_u64(v);
     __syncthreads();
     if (lane == 63) wtot[wave] = incl;
     __syncthreads();
@@ -341,12 +338,7 @@ __global__ __launch_bounds__(SMP_T) void sample_max_kernel(SampleArgs a, AppendA
             if (v[u] > bv) { bv = v[u]; bi = i; }
         }
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const float ov = __shfl_xor(bv, off, RSD_WAVE);
-        const int oi = __shfl_xor(bi, off, RSD_WAVE);
-        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-    }
+    wave_argmax(bv, bi);
     if (WPS == 4) {
         __shared__ float fred[4];
         __shared__ int ired[4];
@@ -380,12 +372,7 @@ __global__ __launch_bounds__(SMP_T) void sample_max_kernel(SampleArgs a, AppendA
     if (!s_last || threadIdx.x >= SMP_NB) return;
     bv = __hip_atomic_load(&a.pmax[(size_t)row * SMP_NB + threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     bi = __hip_atomic_load(&a.pidx[(size_t)row * SMP_NB + threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const float ov = __shfl_xor(bv, off, RSD_WAVE);
-        const int oi = __shfl_xor(bi, off, RSD_WAVE);
-        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-    }
+    wave_argmax(bv, bi);
     if (threadIdx.x == 0) smp_append(a, ap, row, seq, bi);
 }
 

@@ -25,11 +25,12 @@ constexpr int kTinyUnits = 32;               // hidden units of an MLP block
 constexpr int kTinyVocab = 64;               // tokens of a head block
 
 // sums over the 8 or 16 lanes of a group; every lane gets the result
-template <int CTRL> __device__ __forceinline__ float dpp_plus(float x) {
-    return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
-}
+template <int CTRL> __device__ __forceinline__ float dpp_plus(float x) { return x + __uint_as_float(dpp_move<CTRL>(__float_as_uint(x))); }
 __device__ __forceinline__ float sum8(float v) { return dpp_plus<0x141>(dpp_plus<0x4E>(dpp_plus<0xB1>(v))); }   // quad_perm [1,0,3,2], [2,3,0,1], row_half_mirror
 __device__ __forceinline__ float sum16(float v) { return dpp_plus<0x140>(sum8(v)); }                            // row_mirror
+// over the eight groups of 8 lanes: row_ror by 8, then the four rows
+__device__ __forceinline__ float sum_groups(float v) { return rows4_sum(dpp_plus<0x128>(v)); }
+__device__ __forceinline__ float max_groups(float v) { return rows4_max(fmaxf(v, __uint_as_float(dpp_move<0x128>(__float_as_uint(v))))); }
 __device__ __forceinline__ float dot4(const float4& a, const float4& b) { return a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w; }
 
 struct TinyIn {
@@ -77,7 +78,7 @@ template <int D> struct TinyRow {
             for (int i = 0; i < GR; ++i) x += s.part[i][tid];
             if (write && in.h_out) in.h_out[(size_t)r * D + tid] = x;
             s.xs[tid] = x * gn;
-            ss = wave_sum_dpp(x * x);
+            ss = wave_sum(x * x);
         }
         if ((tid & 63) == 0) s.red[tid >> 6] = ss;
         __syncthreads();
@@ -174,8 +175,7 @@ __global__ __launch_bounds__(kTinyT) void tiny_attn_kernel(TinyIn in, const floa
         if (p > pos) sc[i] = -INFINITY;
         mx = fmaxf(mx, sc[i]);
     }
-#pragma unroll
-    for (int off = 8; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, RSD_WAVE));
+    mx = max_groups(mx);
     float l = 0.0f;
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
@@ -185,12 +185,8 @@ __global__ __launch_bounds__(kTinyT) void tiny_attn_kernel(TinyIn in, const floa
         l += p;
         a.x += p * v.x; a.y += p * v.y; a.z += p * v.z; a.w += p * v.w;
     }
-#pragma unroll
-    for (int off = 8; off < 64; off <<= 1) {
-        l += __shfl_xor(l, off, RSD_WAVE);
-        a.x += __shfl_xor(a.x, off, RSD_WAVE); a.y += __shfl_xor(a.y, off, RSD_WAVE);
-        a.z += __shfl_xor(a.z, off, RSD_WAVE); a.w += __shfl_xor(a.w, off, RSD_WAVE);
-    }
+    l = sum_groups(l);
+    a = make_float4(sum_groups(a.x), sum_groups(a.y), sum_groups(a.z), sum_groups(a.w));
     if (lane < 8) *reinterpret_cast<float4*>(&s_acc[wave][lane * 4]) = a;
     if (lane == 0) { s_m[wave] = mx; s_l[wave] = l; }
     __syncthreads();
@@ -298,17 +294,15 @@ __global__ __launch_bounds__(kTinyT) void tiny_head_kernel(TinyIn in, const floa
         if (n < V && z > bv) { bv = z; bi = n; }
     }
     if constexpr (!CHOOSE) return;
-    auto better = [&](float ov, int oi) { if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; } };
     __shared__ float fred[kTinyT / 64];
     __shared__ int ired[kTinyT / 64];
-#pragma unroll
-    for (int off = 16; off < 64; off <<= 1) better(__shfl_xor(bv, off, RSD_WAVE), __shfl_xor(bi, off, RSD_WAVE));
+    wave_argmax_rows(bv, bi);                                // (a row of 16 lanes has one token at a time)
     if ((tid & 63) == 0) { fred[tid >> 6] = bv; ired[tid >> 6] = bi; }
     __syncthreads();
     if (tid >= 64) return;
     if (tid == 0) {
 #pragma unroll
-        for (int i = 1; i < kTinyT / 64; ++i) better(fred[i], ired[i]);
+        for (int i = 1; i < kTinyT / 64; ++i) take_better(bv, bi, fred[i], ired[i]);
         __hip_atomic_store(&sa.pmax[(size_t)r * SMP_NB + blockIdx.y], bv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&sa.pidx[(size_t)r * SMP_NB + blockIdx.y], bi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -325,7 +319,6 @@ __global__ __launch_bounds__(kTinyT) void tiny_head_kernel(TinyIn in, const floa
         bv = __hip_atomic_load(&sa.pmax[(size_t)r * SMP_NB + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         bi = __hip_atomic_load(&sa.pidx[(size_t)r * SMP_NB + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) better(__shfl_xor(bv, off, RSD_WAVE), __shfl_xor(bi, off, RSD_WAVE));
+    wave_argmax(bv, bi);
     if (tid == 0) smp_append(sa, ap, r, seq, bi);
 }
