@@ -120,8 +120,8 @@ struct rsd_ctx {
     int smp_rows = 0;
     float* smp_pmax = nullptr; int* smp_pidx = nullptr;
     u64_t *smp_hist = nullptr, *smp_psum = nullptr, *smp_sel = nullptr;
-    float *hl = nullptr, *xl = nullptr, *logits = nullptr, *tmp_reward = nullptr;
-    int *chosen = nullptr, *steptok_dev = nullptr;
+    float *hl = nullptr, *logits = nullptr, *tmp_reward = nullptr;
+    int* steptok_dev = nullptr;
     int *row_seq_dev = nullptr, *row_pos_dev = nullptr, *last_row_dev = nullptr;
     int* steptok_h = nullptr;
     // tables of a chunked pass, one behind the other in one device array, so that they travel as one copy: sequence and position of
@@ -1407,8 +1407,8 @@ void rsd_destroy(rsd_ctx* c) {
                    c->sd_kept_own, c->sd_where, c->sd_acc_own, c->sd_acc_rec, c->sd_rpart,
                    c->sd_ws[0].pmax, c->sd_ws[0].pidx, c->sd_ws[0].hist, c->sd_ws[0].psum, c->sd_ws[0].sel,
                    c->sd_ws[1].pmax, c->sd_ws[1].pidx, c->sd_ws[1].hist, c->sd_ws[1].psum, c->sd_ws[1].sel, c->h, c->xn, c->qkv, c->att, c->gu, c->act,
-                   c->part_acc, c->part_ml, c->part_k, c->xs_h, c->xs_l, c->smp_pmax, c->smp_pidx, c->smp_hist, c->smp_psum, c->smp_sel, c->hl, c->xl, c->logits, c->tmp_reward, c->chosen, c->steptok_dev,
-                   c->pf_dev, c->tail_h, c->tail_dev, c->bon_copy_dev, c->bon_src_dev, c->dec_seq_dev, c->chk_n_pages_dev, c->chk_err_dev, c->clk_dev};
+                   c->part_acc, c->part_ml, c->part_k, c->xs_h, c->xs_l, c->smp_pmax, c->smp_pidx, c->smp_hist, c->smp_psum, c->smp_sel, c->hl, c->logits, c->tmp_reward, c->steptok_dev,
+                   c->pf_dev, c->tail_h, c->bon_copy_dev, c->bon_src_dev, c->dec_seq_dev, c->chk_n_pages_dev, c->chk_err_dev, c->clk_dev};
     for (void* p : dev) if (p) (void)hipFree(p);
     for (auto& q : c->probe)
         for (hipEvent_t e : q.ev) (void)hipEventDestroy(e);
@@ -1419,8 +1419,8 @@ void rsd_destroy(rsd_ctx* c) {
     for (auto& g : c->graphs) { (void)hipGraphExecDestroy(g.exec); (void)hipGraphDestroy(g.graph); }
     if (c->cap_st) (void)hipStreamDestroy(c->cap_st);
     for (hipEvent_t e : {c->pf_ev[0], c->pf_ev[1], c->tail_ev}) if (e) (void)hipEventDestroy(e);
-    void* pin[] = {c->sb, c->sd_rows_h, c->sd_aux_h, c->pf_h[0], c->pf_h[1], c->steptok_h, c->poll_h,
-                   c->bon_copy_h, c->bon_src_h, c->dec_seq_h, c->chk_h, c->tail_ints};
+    void* pin[] = {c->sb, c->sd_rows_h, c->sd_aux_h, c->pf_h[0], c->steptok_h, c->poll_h,
+                   c->bon_copy_h, c->bon_src_h, c->dec_seq_h, c->chk_h};
     for (void* p : pin) if (p) (void)hipHostFree(p);
     delete c;
 }
@@ -1542,10 +1542,7 @@ int rsd_init(rsd_ctx** out, const rsd_model_shape shape[3], const rsd_weights w[
     HIPCHK(c, dev_alloc(&c->smp_sel, (size_t)c->smp_rows * SMP_SEL));
     HIPCHK(c, hipMemsetAsync(c->smp_sel, 0, (size_t)c->smp_rows * SMP_SEL * sizeof(u64_t), c->st));
     HIPCHK(c, dev_alloc(&c->hl, (size_t)B * d));
-    HIPCHK(c, dev_alloc(&c->xl, (size_t)B * d));
     HIPCHK(c, dev_alloc(&c->tail_h, (size_t)B * d));
-    HIPCHK(c, dev_alloc(&c->tail_dev, (size_t)5 * B));
-    HIPCHK(c, pin_alloc(&c->tail_ints, (size_t)5 * B));
     HIPCHK(c, hipEventCreateWithFlags(&c->tail_ev, hipEventDisableTiming));
     HIPCHK(c, dev_alloc(&c->logits, (size_t)B * V));
     HIPCHK(c, dev_alloc(&c->tmp_reward, R));
@@ -1580,13 +1577,13 @@ int rsd_init(rsd_ctx** out, const rsd_model_shape shape[3], const rsd_weights w[
             HIPCHK(c, dev_alloc(&c->sd_rpart, (size_t)B * SMP_NB));
         }
     }
-    HIPCHK(c, dev_alloc(&c->chosen, (size_t)B));
     HIPCHK(c, dev_alloc(&c->steptok_dev, (size_t)B * p->step_cap));
-    HIPCHK(c, dev_alloc(&c->pf_dev, 4 * R + B));
-    for (int i = 0; i < 2; ++i) {
-        HIPCHK(c, pin_alloc(&c->pf_h[i], 4 * R + B));
-        HIPCHK(c, hipEventCreateWithFlags(&c->pf_ev[i], hipEventDisableTiming));
-    }
+    HIPCHK(c, dev_alloc(&c->pf_dev, 4 * R + 6 * B));             // (and the tables of the last layer's rows)
+    HIPCHK(c, pin_alloc(&c->pf_h[0], 2 * (4 * R + B) + 5 * B));
+    c->pf_h[1] = c->pf_h[0] + 4 * R + B;
+    c->tail_dev = c->pf_dev + 4 * R + B;
+    c->tail_ints = c->pf_h[1] + 4 * R + B;
+    for (hipEvent_t& e : c->pf_ev) HIPCHK(c, hipEventCreateWithFlags(&e, hipEventDisableTiming));
     HIPCHK(c, dev_alloc(&c->dec_seq_dev, (size_t)B));
     HIPCHK(c, dev_alloc(&c->chk_n_pages_dev, (size_t)B));
     HIPCHK(c, dev_alloc(&c->chk_err_dev, (size_t)4));
