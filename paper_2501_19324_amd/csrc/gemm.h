@@ -502,7 +502,7 @@ __global__ __launch_bounds__(512, D == 2 ? 2 : 1) void gemm_rows_sk_kernel(const
 // K parts in a fixed order through LDS at the end.  Same partial-result layout and finish kernels.
 // Measured at 64 rows (kernel alone, against the 256-row kernel): 7B output projection 17.0 -> 11.7 us,
 // 7B QKV 16.7 -> 14.1, 1.5B down 16.4 -> 13.6, 1.5B QKV 7.8 -> 4.8; large matrices (7B down) lose.
-template <int MT>
+template <int MT, bool LONG>
 __global__ __launch_bounds__(512, 2) void gemm_rows64_kernel(const bf16_t* __restrict__ W, int N, int K,
                                                              const uint16_t* __restrict__ Xh,
                                                              const uint16_t* __restrict__ Xl,
@@ -541,22 +541,24 @@ __global__ __launch_bounds__(512, 2) void gemm_rows64_kernel(const bf16_t* __res
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
 
-    u32x4_t w0, w1, w2, w3, x0, x1;       // W: four K blocks requested ahead; activations (L2-resident): one
-#define R64_FETCH_W(kb, R) { R = load_w16(wr + (size_t)min((kb), kb_last) * BK); }
-#define R64_FETCH_X(kb)                                                                          \
+    // requested ahead: W four K blocks, the thread's activation chunks x, y as far in long slices, else one block (set 0)
+    u32x4_t w0, w1, w2, w3, x0, x1, x2, x3, y0, y1, y2, y3;
+#define R64_FETCH_W(kb, S) { w##S = load_w16(wr + (size_t)min((kb), kb_last) * BK); }
+#define R64_FETCH_X(kb, S)                                                                       \
     {                                                                                            \
         const size_t k0_ = (size_t)min((kb), kb_last) * BK;                                      \
-        x0 = *reinterpret_cast<const u32x4_t*>(xp0 + k0_);                                       \
-        if (MT == 2) x1 = *reinterpret_cast<const u32x4_t*>(xp1 + k0_);                          \
+        x##S = *reinterpret_cast<const u32x4_t*>(xp0 + k0_);                                     \
+        if (MT == 2) y##S = *reinterpret_cast<const u32x4_t*>(xp1 + k0_);                        \
     }
-#define R64_STAGE(buf, R)                                                                        \
+#define R64_FETCH(kb, S) R64_FETCH_W(kb, S) R64_FETCH_X(kb, S)
+#define R64_STAGE(buf, S, X)                                                                     \
     {                                                                                            \
-        *reinterpret_cast<u32x4_t*>(Ws + (buf) * WS_E + w_st) = R;                               \
+        *reinterpret_cast<u32x4_t*>(Ws + (buf) * WS_E + w_st) = w##S;                            \
         if (MT == 2) {                                                                           \
-            *reinterpret_cast<u32x4_t*>(Ah + (buf) * XS_E + x_st) = x0;                          \
-            *reinterpret_cast<u32x4_t*>(Al + (buf) * XS_E + x_st) = x1;                          \
+            *reinterpret_cast<u32x4_t*>(Ah + (buf) * XS_E + x_st) = x##X;                        \
+            *reinterpret_cast<u32x4_t*>(Al + (buf) * XS_E + x_st) = y##X;                        \
         } else {                                                                                 \
-            *reinterpret_cast<u32x4_t*>((tid < 256 ? Ah : Al) + (buf) * XS_E + x_st) = x0;       \
+            *reinterpret_cast<u32x4_t*>((tid < 256 ? Ah : Al) + (buf) * XS_E + x_st) = x##X;     \
         }                                                                                        \
     }
 #define R64_COMPUTE(buf)                                                                         \
@@ -571,39 +573,49 @@ __global__ __launch_bounds__(512, 2) void gemm_rows64_kernel(const bf16_t* __res
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah_, b_, acc, 0, 0, 0);                \
         }                                                                                        \
     }
-    // step i: block i + 1 (W in set S, activations in x0/x1) moves into the LDS buffer block i - 1 has
-    // left; S at once takes the request of W block i + 5 and x0/x1 that of activation block i + 2; block i
-    // is multiplied
+    // step i: block i + 1 (W in set S) moves into the LDS buffer that block i - 1 has left; S at once takes the request of W block
+    // i + 5, the activation set that has become free that of block i + 5 or i + 2; block i is multiplied
 #define R64_STEP(i_step, S)                                                                      \
-    {                                                                                            \
-        R64_STAGE(((i_step) + 1) & 1, S)                                                         \
-        R64_FETCH_W(kb0 + (i_step) + 5, S)                                                       \
-        R64_FETCH_X(kb0 + (i_step) + 2)                                                          \
-        R64_COMPUTE((i_step) & 1)                                                                \
-        __syncthreads();                                                                         \
+    {                                                                                        \
+        if (LONG) {                                                              \
+            R64_STAGE(((i_step) + 1) & 1, S, S)                                              \
+            R64_FETCH(kb0 + (i_step) + 5, S)                                                 \
+        } else {                                                                             \
+            R64_STAGE(((i_step) + 1) & 1, S, 0)                                              \
+            R64_FETCH_W(kb0 + (i_step) + 5, S)                                               \
+            R64_FETCH_X(kb0 + (i_step) + 2, 0)                                               \
+        }                                                                                    \
+        R64_COMPUTE((i_step) & 1)                                                            \
+        __syncthreads();                                                                     \
     }
-    R64_FETCH_W(kb0, w0)
-    R64_FETCH_X(kb0)
-    R64_FETCH_W(kb0 + 1, w1)
-    R64_FETCH_W(kb0 + 2, w2)
-    R64_FETCH_W(kb0 + 3, w3)
-    R64_STAGE(0, w0)
-    R64_FETCH_W(kb0 + 4, w0)
-    R64_FETCH_X(kb0 + 1)
+    R64_FETCH(kb0, 0)
+    if (LONG) {
+        R64_FETCH(kb0 + 1, 1)
+        R64_FETCH(kb0 + 2, 2)
+        R64_FETCH(kb0 + 3, 3)
+    } else {
+        R64_FETCH_W(kb0 + 1, 1)
+        R64_FETCH_W(kb0 + 2, 2)
+        R64_FETCH_W(kb0 + 3, 3)
+    }
+    R64_STAGE(0, 0, 0)
+    R64_FETCH_W(kb0 + 4, 0)
+    if (LONG) R64_FETCH_X(kb0 + 4, 0) else R64_FETCH_X(kb0 + 1, 0)
     __syncthreads();
     int i = 0;
     for (; i + 3 < nk; i += 4) {
-        R64_STEP(i, w1)
-        R64_STEP(i + 1, w2)
-        R64_STEP(i + 2, w3)
-        R64_STEP(i + 3, w0)
+        R64_STEP(i, 1)
+        R64_STEP(i + 1, 2)
+        R64_STEP(i + 2, 3)
+        R64_STEP(i + 3, 0)
     }
-    if (i < nk) { R64_STEP(i, w1) ++i; }
-    if (i < nk) { R64_STEP(i, w2) ++i; }
-    if (i < nk) { R64_STEP(i, w3) }
+    if (i < nk) { R64_STEP(i, 1) ++i; }
+    if (i < nk) { R64_STEP(i, 2) ++i; }
+    if (i < nk) { R64_STEP(i, 3) }
 #undef R64_STEP
 #undef R64_COMPUTE
 #undef R64_STAGE
+#undef R64_FETCH
 #undef R64_FETCH_W
 #undef R64_FETCH_X
 
@@ -885,12 +897,20 @@ static void gemm_rows_sk_launch(hipStream_t st, const bf16_t* W, int N, int K, c
     else         hipLaunchKernelGGL((gemm_rows_sk_kernel<2, D>), dim3(g.G), dim3(512), 0, st, W, N, K, Xh, Xl, part, g, M);
 }
 
+// K blocks per slice from which gemm_rows64_kernel requests the activations as far ahead as the weights: a step of one block ahead lasts as
+// long as an L2 read, which a long slice pays many times (1536 x 8960, 18 blocks: 4 rows 10.9 -> 8.2 us, 16 rows 11.0 -> 9.0, 32 rows
+// 11.4 -> 10.2, 64 rows 14.1 -> 13.4); short ones re-read their last block for the requests beyond it (7 blocks, 3584 x 3584: 64 rows
+// 11.9 -> 13.5; 10 blocks, 4608 x 3584: 15.2 -> 16.6).
+constexpr int kLongSlice = 14;
 static void gemm_rows_launch(hipStream_t st, const bf16_t* W, int N, int K, const uint16_t* Xh, const uint16_t* Xl,
                              int M, float* part, int ks) {
     if (gemm_rows_small(N, K)) {
         const dim3 grid((N + 63) / 64, ks), block(512);
-        if (M <= 32) hipLaunchKernelGGL((gemm_rows64_kernel<1>), grid, block, 0, st, W, N, K, Xh, Xl, part, M);
-        else         hipLaunchKernelGGL((gemm_rows64_kernel<2>), grid, block, 0, st, W, N, K, Xh, Xl, part, M);
+#define RSD_R64(LONG)                                                                                                \
+    if (M <= 32) hipLaunchKernelGGL((gemm_rows64_kernel<1, LONG>), grid, block, 0, st, W, N, K, Xh, Xl, part, M);     \
+    else         hipLaunchKernelGGL((gemm_rows64_kernel<2, LONG>), grid, block, 0, st, W, N, K, Xh, Xl, part, M);
+        if ((K / 64 + ks - 1) / ks >= kLongSlice) { RSD_R64(true) } else { RSD_R64(false) }
+#undef RSD_R64
         return;
     }
     const dim3 grid((N + 255) / 256, ks), block(512);
