@@ -242,6 +242,30 @@ __device__ __forceinline__ int smp_find_bin(const u64_t* hist, u64_t thr, u64_t&
     return *s_bin;
 }
 
+__device__ __forceinline__ u64_t readlane_u64(u64_t v, int lane) {
+    return u64_of((uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane), (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane));
+}
+// The same on n_bins = 64 * P bins by one wave (every wave of a block for itself: no barriers); 0 where there is no such bin
+template <int P>
+__device__ __forceinline__ int smp_find_bin_wave(const u64_t* hist, u64_t thr, u64_t& above) {
+    const int lane = threadIdx.x & 63, top = 64 * P - 1 - lane * P;
+    u64_t h[P], loc = 0;
+#pragma unroll
+    for (int j = 0; j < P; ++j) { h[j] = hist[top - j]; loc += h[j]; }
+    u64_t run = above + (wave_incl_scan_u64(loc) - loc), at = 0;
+    int bin = -1;
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+        if (run < thr && run + h[j] >= thr) { bin = top - j; at = run; }
+        run += h[j];
+    }
+    const u64_t hit = __ballot(bin >= 0);
+    if (!hit) return 0;
+    const int l = __builtin_ctzll(hit);
+    above = readlane_u64(at, l);
+    return __builtin_amdgcn_readlane(bin, l);
+}
+
 // bin of the key of an e with a mass
 __device__ __forceinline__ int smp_bin(uint32_t key) {      // (2 i - SMP_FINE overtakes i at i = SMP_FINE)
     return min(max((int)(key >> 18) - SMP_BIN0, (int)(key >> 17) - 2 * SMP_BIN0 - SMP_FINE), SMP_BINS - 1);
@@ -686,8 +710,8 @@ __global__ __launch_bounds__(SMP_T) void sample_finish_kernel(SampleArgs a, Appe
     if (seq < 0) return;
     __shared__ u64_t wtot[4];
     __shared__ float fred[4];
-    __shared__ int s_tok, s_blk, s_bin;
-    __shared__ u64_t s_base, s_above;
+    __shared__ int s_tok, s_bin;
+    __shared__ u64_t s_above;
     int token;
     {
         u64_t* sel = a.sel + (size_t)row * SMP_SEL;
@@ -738,7 +762,6 @@ __global__ __launch_bounds__(SMP_T) void sample_finish_kernel(SampleArgs a, Appe
             };
             if (tid < SMP_NB) s_mass[tid] = mass_above;
             for (int b = tid; b < 768 + 512; b += SMP_T) lh[b] = 0;
-            if (tid == 0) { s_bin = 0; s_above = above; }
             mx = smp_row_max(a, row, fred);                // (holds a barrier)
             if (bin >= 0) {
                 const uint32_t lo = smp_lo(bin);
@@ -748,55 +771,61 @@ __global__ __launch_bounds__(SMP_T) void sample_finish_kernel(SampleArgs a, Appe
                 // bits 9..18, then 0..8 of the keys' distance from the bin's first
                 each_key([&](uint32_t w) { atomicAdd(&lh[off(w) >> 9], mass(w)); });
                 __syncthreads();
-                const uint32_t up = (uint32_t)smp_find_bin<3>(lh, thr, run, wtot, &s_bin, &s_above);
-                __syncthreads();
+                const uint32_t up = (uint32_t)smp_find_bin_wave<12>(lh, thr, run);
                 each_key([&](uint32_t w) { if (off(w) >> 9 == up) atomicAdd(&lh[768 + (off(w) & 0x1FFu)], mass(w)); });
                 __syncthreads();
-                const uint32_t rel = (up << 9) | (uint32_t)smp_find_bin<2>(lh + 768, thr, run, wtot, &s_bin, &s_above);
+                const uint32_t rel = (up << 9) | (uint32_t)smp_find_bin_wave<8>(lh + 768, thr, run);
                 tau = lo + rel;
                 each_key([&](uint32_t w) { if (off(w) >= rel) atomicAdd(&s_mass[w >> 19], mass(w)); });
             }
         }
+        if (tid == 0) s_tok = -1;
         __syncthreads();
-        const u64_t pv = (tid < SMP_NB) ? s_mass[tid] : 0;
-        if (tid < SMP_NB) a.psum[(size_t)row * SMP_NB + tid] = pv;
-        const u64_t pincl = block256_incl_scan_u64(pv, wtot);
-        const u64_t zs = wtot[0] + wtot[1] + wtot[2] + wtot[3];
+        // (every wave finds the span for itself)
+        const u64_t pv = s_mass[lane], pincl = wave_incl_scan_u64(pv), zs = readlane_u64(pincl, 63);
         const u64_t target = (u64_t)floor((double)uu * (double)zs);      // running > u * Z  <=>  running > floor(u * Z)
-        if (tid == 0) { s_blk = -1; s_tok = -1; sel[5] = tau; sel[6] = target; }
-        __syncthreads();
-        if (tid < SMP_NB && pincl > target && pincl - pv <= target) { s_blk = tid; s_base = pincl - pv; }
-        __syncthreads();
-        // if rounding of u * Z left no crossing, the draw is the last member: of the last span with a mass.  Every thread finds
-        // it for itself (writing it to s_blk / s_base would race with the waves that still read these)
-        int blk = s_blk;
-        u64_t base = s_base;
-        if (blk < 0) {
-            u64_t run = 0;
-            blk = 0; base = 0;
-            for (int b = 0; b < SMP_NB; ++b) { const u64_t v = s_mass[b]; if (v) { blk = b; base = run; } run += v; }
-        }
+        if (wave == 0) a.psum[(size_t)row * SMP_NB + lane] = pv;
+        if (tid == 0) { sel[5] = tau; sel[6] = target; }
+        // if rounding of u * Z left no crossing, the draw is the last member: of the last span with a mass
+        u64_t at = __ballot(pincl > target && pincl - pv <= target);
+        if (!at) at = __ballot(pv != 0);
+        const int blk = at ? 63 - __builtin_clzll(at) : 0;
+        const u64_t base = at ? readlane_u64(pincl - pv, blk) : 0;
         // every thread takes a run of consecutive tokens of the span; the one whose run holds the crossing walks it
         const int s0 = min(blk * span, a.V), s1 = min(a.V, s0 + span);
         const int per = (s1 - s0 + SMP_T - 1) / SMP_T, t0 = min(s1, s0 + tid * per), t1 = min(s1, t0 + per);
         u64_t mine = 0;
         int last_member = -1;
-        for (int i0 = t0; i0 < t1; i0 += 10) {                 // (spans of 2374: one batch)
-            float x[10];
+        constexpr int NB = 10;                                 // (spans of 2374: one batch, which is kept)
+        float kept_e[NB];
+        for (int i0 = t0; i0 < t1; i0 += NB) {
+            float x[NB];
 #pragma unroll
-            for (int u = 0; u < 10; ++u) x[u] = smp_x(a, lg, min(i0 + u, t1 - 1));
+            for (int u = 0; u < NB; ++u) x[u] = smp_x(a, lg, min(i0 + u, t1 - 1));
 #pragma unroll
-            for (int u = 0; u < 10; ++u) {
+            for (int u = 0; u < NB; ++u) {
                 const float e = smp_exp(x[u] - mx);
-                if (i0 + u < t1 && __float_as_uint(e) >= tau) { mine += smp_fix(e); last_member = i0 + u; }
+                const bool in = i0 + u < t1 && __float_as_uint(e) >= tau;
+                kept_e[u] = in ? e : 0.0f;
+                if (in) { mine += smp_fix(e); last_member = i0 + u; }
             }
         }
         const u64_t incl = base + block256_incl_scan_u64(mine, wtot);
         if (mine && incl > target && incl - mine <= target) {
             u64_t run = incl - mine;
-            for (int i = t0; i < t1; ++i) {
-                const float e = smp_exp(smp_x(a, lg, i) - mx);
-                if (__float_as_uint(e) >= tau) { run += smp_fix(e); if (run > target) { s_tok = i; break; } }
+            if (per <= NB) {
+                int tok = -1;
+#pragma unroll
+                for (int u = 0; u < NB; ++u) {
+                    run += smp_fix(kept_e[u]);
+                    if (tok < 0 && run > target) tok = t0 + u;
+                }
+                s_tok = tok;
+            } else {
+                for (int i = t0; i < t1; ++i) {
+                    const float e = smp_exp(smp_x(a, lg, i) - mx);
+                    if (__float_as_uint(e) >= tau) { run += smp_fix(e); if (run > target) { s_tok = i; break; } }
+                }
             }
         }
         __syncthreads();
