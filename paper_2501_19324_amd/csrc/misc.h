@@ -68,13 +68,14 @@ __global__ void gather_rows_kernel(const float* __restrict__ src, const int* __r
         *reinterpret_cast<float4*>(dst + (size_t)i * d + k) = *reinterpret_cast<const float4*>(src + (size_t)r * d + k);
 }
 
-// Rows of V values, row r to place row_seq[r] * T + row_pos[r] of dst: the logits of a pass over several sequences, multiplied together,
-// at the places of their tokens.  Grid (rows, parts of a row).
-__global__ __launch_bounds__(256) void scatter_rows_kernel(const float* __restrict__ src, int V, const int* __restrict__ row_seq,
-                                                           const int* __restrict__ row_pos, int T, float* __restrict__ dst) {
+// Rows of V values, row r to place (sequence * T + position) of dst, rows without a token nowhere: the logits of a pass over several
+// sequences, multiplied together, at the places of their tokens.  Grid (rows, parts of a row).
+__global__ __launch_bounds__(256) void scatter_rows_kernel(const float* __restrict__ src, int V, RowMap rm, int T, float* __restrict__ dst) {
     const int r = blockIdx.x, step = blockDim.x * gridDim.y, i0 = blockIdx.y * blockDim.x + threadIdx.x;
+    int seq, pos;
+    if (!row_lookup(rm, r, seq, pos)) return;
     const float* s = src + (size_t)r * V;
-    float* d = dst + ((size_t)row_seq[r] * T + row_pos[r]) * V;
+    float* d = dst + ((size_t)seq * T + pos) * V;
     if (V % 4 == 0 && (reinterpret_cast<uintptr_t>(dst) & 15) == 0) {
         for (int i = i0 * 4; i < V; i += step * 4) *reinterpret_cast<float4*>(d + i) = *reinterpret_cast<const float4*>(s + i);
     } else {
@@ -139,6 +140,14 @@ __global__ __launch_bounds__(256) void reward_head_kernel(const float* __restric
         const float z = dot / sqrtf(ss / (float)d + eps) + ld1(b_r);
         out[i] = 1.0f / (1.0f + expf(-z));
     }
+}
+
+// The state of token t of an evaluation token by token: position t in every sequence, in use as long as there are tokens
+__global__ void forward_state_kernel(int* __restrict__ kv_len, int* __restrict__ active, const int* __restrict__ ctx_len, int B, int t) {
+    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b >= B) return;
+    kv_len[b] = t;
+    active[b] = t < ctx_len[b];
 }
 
 // Device-side sequence state, one int per sequence unless noted.
