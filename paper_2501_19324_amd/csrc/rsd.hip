@@ -892,8 +892,8 @@ enum Keep { kKeepAll, kKeepLast, kKeepNone };
 // output projection, MLP), and a prompt or a scored step is read at its last token alone, the context of Best-of-N candidates not
 // at all.  The passes then end with the last layer's keys and values (kUpToCache); that layer's input of the rows in question is put
 // aside, and behind the last pass the layer runs once on all of them together (kLastLayer), with one after_pass on the result
-// (the arguments name no rows; c->h and last_row_dev do).  A layer of the 7B shape over 8192 rows of prompts takes 6.4 ms, its keys and
-// values 0.2 and one pass over up to 64 kept rows 0.15.
+// (the arguments name no rows; c->h and last_row_dev do).  A layer of the 7B shape over 8192 rows of prompts takes 5.6 ms, its keys and
+// values 0.12 and one pass over up to 64 kept rows 0.15.
 // bf16 weights: from 65 rows on, for up to half of the rows.  Up to 64 rows a pass is a reading of the weights either way, and reading
 // the key and value weights twice only adds launches.  fp32 weights: from 9 rows, where the tile kernels begin, which take as long for a
 // few rows as for many, several times what the kept rows take on the vector kernels.
