@@ -333,7 +333,8 @@ int rsd_decode_stats(rsd_ctx *c, int64_t *eager_iters, int64_t *graph_replays, i
  * max_samples pairs.  phase RSD_PROBE_DECODE: launches of the single-token decode iteration (Algorithm 1's
  * token-by-token generation of a step; inside the decode loop every stride-th *iteration* is launched kernel
  * by kernel with its launch timed, the others are replayed from the recorded graph); phase RSD_PROBE_PREFILL:
- * launches of chunked passes (reward scoring of a step, catch-up).  Only the matrix kernel itself is timed
+ * launches of chunked passes (reward scoring of a step, catch-up; the last layer of a pass that is read at
+ * single rows runs on these rows, and its launches count with the rows they have).  Only the matrix kernel itself is timed
  * (not the kernels that add K slices or apply the epilogue).  rsd_probe_read synchronises, returns the
  * number of timed launches, their summed duration, and over the same launches the summed algorithmic bytes
  * (weights once + activations in and out) and floating-point operations (2 * rows * N * K), and disarms. */

@@ -46,8 +46,9 @@ __device__ __forceinline__ float ld1(const bf16_t* p) { return bf2f(p->v); }
 __device__ __forceinline__ void st1(float* p, float v) { *p = v; }
 __device__ __forceinline__ void st1(bf16_t* p, float v) { p->v = f2bf(v); }
 
-// ---- Reductions over a wave by cross-lane register moves.  A shuffle (ds_bpermute) is a trip through the LDS of more than a hundred
-// cycles, and the six of a reduction wait for one another: about 0.4 us, in launches of 4 to 10.  All 64 lanes must be active; every lane gets the result.
+// ---- Reductions over a wave by cross-lane register moves.  A shuffle (ds_bpermute) is a trip through the LDS, and the six of a
+// reduction wait for one another, in launches of 4 to 10 us: the tiny target's MLP launch 4.7 -> 3.8, a token of the 1.5B model 1.06 -> 1.04 ms.
+// All 64 lanes must be active; every lane gets the result.
 template <int CTRL> __device__ __forceinline__ uint32_t dpp_move(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
 }

@@ -23,7 +23,7 @@
 // 109 us on 64 rows of 151936 logits and 36 on one.)  What bounds it on many rows: in B the vector instructions (1530 a wave on 64 rows; the
 // vector units are busy 46 % of the counted cycles, the start and end of the launch among them, and 17 % in A and C), in A and C the
 // reading of the logits, on few rows the chain of block scans in D.  Launches of 64 rows with logits as a trained model gives them, not read before,
-// A to D: 11.6 / 15.3 / 10.4 / 8.9 us; with a bin for every token, a full division and expf for each in B and C 11.0 / 18.3 / 17.0 / 9.3.
+// A to D: 11.6 / 15.3 / 10.4 / 6.9 us (D 8.9 with block-wide searches); with a bin for every token, a full division and expf for each in B and C 11.0 / 18.3 / 17.0 / 9.3.
 // A bin that may hold more keys than there is room for (nearly equal logits; the bin's mass tells in advance) makes the row
 // "dense": C then adds up sub-bins of 256 keys instead of listing, and D is SMP_FB blocks, which count the keys of the deciding
 // sub-bin span by span; the last of them to finish resolves tau from these counts and goes on alone.  A call on 64 rows
@@ -57,7 +57,7 @@ __device__ __forceinline__ u64_t shfl_xor_u64(u64_t v, int d) {
     return ((u64_t)hi << 32) | lo;
 }
 // Inclusive scans over the lanes in vector instructions: shifts inside the rows of 16 lanes, then the last lane of a row to the rows behind it
-// (by shuffles the four scans of phase D alone took 1.5 us of its 9)
+// (phase D on one row with shuffles 9.1 us, this way 7.7)
 __device__ __forceinline__ u64_t wave_incl_scan_u64(u64_t x) {
     using std::integral_constant;
     auto add = [&](auto ctrl, auto rows) {
