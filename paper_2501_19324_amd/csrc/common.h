@@ -59,7 +59,22 @@ template <typename F> __device__ __forceinline__ void row16_moves(F f) {
     f(std::integral_constant<int, 0x141>{});
     f(std::integral_constant<int, 0x140>{});
 }
+// Lanes 32, 16, 8, 4, 2, 1 apart in turn, the order of wave_sums (gemv.h): a bf16 cache entry near the middle between two numbers is
+// rounded one way or the other with the last bit of a sum, so the order is part of the result and does not depend on how lanes exchange.
+// (After the steps over 32, 16 and 8 lanes a value repeats every 8 lanes: the rotation by 4 brings the lane 4 apart.)
 __device__ __forceinline__ float wave_sum(float v) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+    v += __uint_as_float(dpp_move<0x128>(__float_as_uint(v)));       // row_ror by 8
+    v += __uint_as_float(dpp_move<0x124>(__float_as_uint(v)));       // row_ror by 4
+    v += __uint_as_float(dpp_move<0x4E>(__float_as_uint(v)));        // quad_perm [2,3,0,1]
+    v += __uint_as_float(dpp_move<0xB1>(__float_as_uint(v)));        // quad_perm [1,0,3,2]
+    return v;
+}
+// Neighbours first: the order gemv_flat_kernel has
+__device__ __forceinline__ float wave_sum_near(float v) {
     row16_moves([&](auto c) { v += __uint_as_float(dpp_move<decltype(c)::value>(__float_as_uint(v))); });
     const int bits = __float_as_int(v);                     // each row of 16 lanes holds its sum
     return (__int_as_float(__builtin_amdgcn_readlane(bits, 0)) + __int_as_float(__builtin_amdgcn_readlane(bits, 16))) +

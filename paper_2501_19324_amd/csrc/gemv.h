@@ -523,7 +523,7 @@ __global__ __launch_bounds__(NW * 64) void gemv_flat_kernel(const WT* __restrict
             if (i < n_my && (s == CPR - 1 || i == n_my - 1)) {
 #pragma unroll
                 for (int a = 0; a < NA; ++a) {
-                    const float t = wave_sum(acc[a]);
+                    const float t = wave_sum_near(acc[a]);
                     if (lane == 0) red[(wave * NA + a) * V + v] = t;
                     acc[a] = 0.0f;
                 }

@@ -2449,6 +2449,20 @@ extern "C" int rsd_debug_smp_exp(const float* d_dev, float* e_dev, float* lib_de
     hipLaunchKernelGGL(debug_smp_exp_kernel, dim3(ceil_div(n, 256)), dim3(256), 0, nullptr, d_dev, e_dev, lib_dev, n);
     return hipDeviceSynchronize() == hipSuccess ? RSD_OK : RSD_EHIP;
 }
+// the sums over a wave alone, one wave per 64 values: what a test of their order calls
+__global__ __launch_bounds__(64) void debug_wave_sum_kernel(const float* __restrict__ v, float* __restrict__ far, float* __restrict__ vec,
+                                                            float* __restrict__ near) {
+    const int i = blockIdx.x * 64 + threadIdx.x;
+    float one[1] = {v[i]};
+    far[i] = wave_sum(v[i]);
+    vec[i] = wave_sums<1>(one);
+    near[i] = wave_sum_near(v[i]);
+}
+extern "C" int rsd_debug_wave_sum(const float* v_dev, float* far_dev, float* vec_dev, float* near_dev, int32_t n) {
+    if (!v_dev || !far_dev || !vec_dev || !near_dev || n < 64 || n % 64) return RSD_EINVAL;
+    hipLaunchKernelGGL(debug_wave_sum_kernel, dim3(n / 64), dim3(64), 0, nullptr, v_dev, far_dev, vec_dev, near_dev);
+    return hipDeviceSynchronize() == hipSuccess ? RSD_OK : RSD_EHIP;
+}
 // One many-row product with a given block tile, number of K slices and epilogue.  EPI_STORE with ks > 1: slice z to Y + z * M * N (ldy = N).
 // EPI_SWIGLU: halves to Oh / Ol [M][N / 2].
 extern "C" int rsd_debug_tile(const void* W_dev, int32_t N, int32_t K, const void* Xh_dev, const void* Xl_dev, int32_t M, int32_t epi, int32_t bm,
