@@ -1345,7 +1345,8 @@ __global__ __launch_bounds__((StreamCfg<MT, BN>::NW * 64)) void gemm_stream_kern
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     // Add the K parts through LDS: the waves of one (row, column) part share the 16 values a lane has of a tile, 8 / KW pairs
-    // (v, v + 8) each, and add the others' to their own, ascending.  One row tile of every wave at a time.
+    // (v, v + 8) each.  Whoever adds a value adds the parts in ascending order: every row of a product is the same sum, wherever it
+    // stands in the tile.  One row tile of every wave at a time.
     constexpr int PV = 8 / KW;                                // pairs per wave
     float2* red = reinterpret_cast<float2*>(tile_sm);        // [owner][source][wn, wm][j][pair][lane]
     auto at = [&](int owner, int src, int j, int p) {
@@ -1366,14 +1367,17 @@ __global__ __launch_bounds__((StreamCfg<MT, BN>::NW * 64)) void gemm_stream_kern
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int p = 0; p < PV; ++p) {
-                float2 x = make_float2(0.0f, 0.0f);           // the wave's own pair (its registers have constant indices only)
+                float2 own = make_float2(0.0f, 0.0f), y[KW - 1];   // the wave's own pair (its registers have constant indices only)
 #pragma unroll
                 for (int o = 0; o < KW; ++o)
-                    if (o == kw) x = make_float2(acc[i][j][o * PV + p], acc[i][j][o * PV + p + 8]);
+                    if (o == kw) own = make_float2(acc[i][j][o * PV + p], acc[i][j][o * PV + p + 8]);
 #pragma unroll
-                for (int q = 0; q < KW - 1; ++q) {
-                    const float2 y = *at(kw, q < kw ? q : q + 1, j, p);
-                    x.x += y.x; x.y += y.y;
+                for (int q = 0; q < KW - 1; ++q) y[q] = *at(kw, q < kw ? q : q + 1, j, p);
+                float2 x = kw == 0 ? own : y[0];
+#pragma unroll
+                for (int q = 1; q < KW; ++q) {
+                    const float2 z = q == kw ? own : q < kw ? y[min(q, KW - 2)] : y[q - 1];
+                    x.x += z.x; x.y += z.y;
                 }
                 const int v = kw * PV + p, m0 = (wm * TM + i) * 32 + 8 * (v >> 2) + 4 * kg + (v & 3);       // x.y: row m0 + 16
                 if (EPI == EPI_SWIGLU) {
