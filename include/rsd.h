@@ -335,9 +335,12 @@ int rsd_decode_stats(rsd_ctx *c, int64_t *eager_iters, int64_t *graph_replays, i
  * by kernel with its launch timed, the others are replayed from the recorded graph); phase RSD_PROBE_PREFILL:
  * launches of chunked passes (reward scoring of a step, catch-up; the last layer of a pass that is read at
  * single rows runs on these rows, and its launches count with the rows they have).  Only the matrix kernel itself is timed
- * (not the kernels that add K slices or apply the epilogue).  rsd_probe_read synchronises, returns the
- * number of timed launches, their summed duration, and over the same launches the summed algorithmic bytes
- * (weights once + activations in and out) and floating-point operations (2 * rows * N * K), and disarms. */
+ * (not the kernels that add K slices or apply the epilogue).  Small fp32 models whose single-token layers are two
+ * launches (qkv to attention output, gate+up and down): a probe of either projection times the launch that holds
+ * both and counts the bytes and operations of both.  Timing an iteration does not change what it computes.
+ * rsd_probe_read synchronises, returns the number of timed launches, their summed duration, and over the same
+ * launches the summed algorithmic bytes (weights once + activations in and out) and floating-point operations
+ * (2 * rows * N * K), and disarms. */
 #define RSD_PROBE_SLOTS 4
 enum { RSD_PROBE_DECODE = 0, RSD_PROBE_PREFILL = 1 };
 int rsd_probe_start(rsd_ctx *c, int32_t slot, int32_t model, int32_t phase, int32_t op, int32_t max_samples,

@@ -798,16 +798,12 @@ void propose_stash(rsd_ctx* c, int mode) {
 // Which single-token iterations the two-launch layers of tiny.h serve: fp32 weights of the widths that fit their registers, contexts that
 // the attention does not split either, and up to eight rows - every row reads the weights for itself there, which the
 // kernels for more rows share.  The head as far as a block per 64 tokens and row is less than the chip holds at once.
-// An iteration whose launches are timed takes the general path, where the launches the probes name exist.
-bool tiny_path(rsd_ctx* c, const Model& m, int M) {
+// It does not depend on whether an iteration is timed: the other kernels add in another order, and a measured generation is the same generation.
+bool tiny_path(const Model& m, int M) {
     const rsd_model_shape& s = m.s;
-    if (s.dtype != RSD_F32 || M > 8 || m.hd != 32 || (s.d_model != 128 && s.d_model != 256) || s.d_ffn % kTinyUnits ||
-        s.d_ffn / kTinyUnits > (s.d_model == 128 ? TinyRow<128>::kMaxParts : TinyRow<256>::kMaxParts) || s.n_heads > TinyRow<256>::kMaxParts ||
-        s.vocab > 8192 || m.splits > 1 || m.max_pages * RSD_PAGE > kTinyPos)
-        return false;
-    for (const auto& q : c->probe)
-        if (q.iter_on) return false;
-    return true;
+    return s.dtype == RSD_F32 && M <= 8 && m.hd == 32 && (s.d_model == 128 || s.d_model == 256) && s.d_ffn % kTinyUnits == 0 &&
+           s.d_ffn / kTinyUnits <= (s.d_model == 128 ? TinyRow<128>::kMaxParts : TinyRow<256>::kMaxParts) &&
+           s.n_heads <= TinyRow<256>::kMaxParts && s.vocab <= 8192 && m.splits == 1 && m.max_pages * RSD_PAGE <= kTinyPos;
 }
 // true: the token has been chosen and appended as well
 template <int D>
@@ -816,13 +812,20 @@ bool tiny_iter(rsd_ctx* c, Model& m, int M, const RowMap& rm, const SampleArgs& 
     const float scale = 1.0f / std::sqrt(32.0f);
     const float* embed = wptr<float>(m, m.off_embed);
     float *ha = c->h, *hb = c->xn, *heads = c->att, *mlp = c->gu;      // residual stream (two buffers), partial sums
+    c->cur_phase = RSD_PROBE_DECODE;
+    // (a probe of a projection times the launch that holds it: both projections of the launch are in the bytes and operations)
+    const long long wa = (long long)D * (m.n_qkv + m.q_dim), wm = 3LL * D * F, wh = (long long)D * V;
     for (int l = 0; l < m.s.n_layers; ++l) {
         const LayerOff& o = m.layers[l];
         float* pool_l = reinterpret_cast<float*>(m.pool) + (size_t)l * m.pool_pages * m.page_elts;
-        hipLaunchKernelGGL((tiny_attn_kernel<D>), dim3(M, H), dim3(kTinyT), 0, c->st,
-                           TinyIn{l ? ha : embed, mlp, l ? units : 0, wptr<float>(m, o.attn_norm), m.s.rms_eps, hb}, wptr<float>(m, o.wqkv),
-                           wptr<float>(m, o.wo), pool_l, m.bt_dev, m.max_pages, rm, l ? (const int*)nullptr : c->ds.tokens, c->p.max_ctx,
-                           m.rope, H, m.s.n_kv_heads, scale, heads);
+        {
+            ProbeScope qkv(c, m, 0, 4 * wa + 8LL * M * D, 2 * M * wa), out(c, m, 1, 4 * wa + 8LL * M * D, 2 * M * wa);
+            hipLaunchKernelGGL((tiny_attn_kernel<D>), dim3(M, H), dim3(kTinyT), 0, c->st,
+                               TinyIn{l ? ha : embed, mlp, l ? units : 0, wptr<float>(m, o.attn_norm), m.s.rms_eps, hb}, wptr<float>(m, o.wqkv),
+                               wptr<float>(m, o.wo), pool_l, m.bt_dev, m.max_pages, rm, l ? (const int*)nullptr : c->ds.tokens, c->p.max_ctx,
+                               m.rope, H, m.s.n_kv_heads, scale, heads);
+        }
+        ProbeScope gate_up(c, m, 2, 4 * wm + 8LL * M * D, 2 * M * wm), down(c, m, 3, 4 * wm + 8LL * M * D, 2 * M * wm);
         hipLaunchKernelGGL((tiny_mlp_kernel<D>), dim3(M, units), dim3(kTinyT), 0, c->st,
                            TinyIn{hb, heads, H, wptr<float>(m, o.ffn_norm), m.s.rms_eps, ha}, wptr<float>(m, o.wgu), wptr<float>(m, o.wdown), F,
                            rm, mlp);
@@ -830,6 +833,7 @@ bool tiny_iter(rsd_ctx* c, Model& m, int M, const RowMap& rm, const SampleArgs& 
     const TinyIn in{ha, mlp, units, wptr<float>(m, m.off_final_norm), m.s.rms_eps, nullptr};
     const dim3 grid(M, ceil_div(V, kTinyVocab));
     const bool choose = sa.temperature == 0.0f && grid.y <= SMP_NB;
+    ProbeScope head(c, m, 4, 4 * wh + 4LL * M * (D + V), 2 * M * wh);
     if (choose) hipLaunchKernelGGL((tiny_head_kernel<D, true>), grid, dim3(kTinyT), 0, c->st, in, wptr<float>(m, m.off_head), V, rm, c->logits, sa, ap);
     else hipLaunchKernelGGL((tiny_head_kernel<D, false>), grid, dim3(kTinyT), 0, c->st, in, wptr<float>(m, m.off_head), V, rm, c->logits, sa, ap);
     return choose;
@@ -842,7 +846,7 @@ void decode_iter(rsd_ctx* c, int which, const float* u, const int* forced, int m
     Model& m = c->m[which];
     const int M = c->dec_rows ? c->dec_rows : c->B;
     const AppendArgs ap = append_args(c, which, forced, mode);
-    if (tiny_path(c, m, M)) {
+    if (tiny_path(m, M)) {
         const SampleArgs sa = sample_args(c, c->logits, m.s.vocab, m.s.vocab, u, c->ds.ctx_len, c->p.max_ctx, c->p.temperature, c->p.top_p,
                                           c->p.sep_id, c->p.sep_logit_bias, c->ds.active, nullptr, decode_seq(c), 0);
         const RowMap rm = decode_map(c, which);

@@ -57,3 +57,55 @@ def test_chunked_pass_probe_counts_flops_and_reads_the_clock(gpu):
     r = R.rsd_probe_read(s.ctx, 0)
     assert r["n"] == L and c["launches"] == 0 and c["shader_ticks"] == 0
     s.close()
+
+
+def test_timed_iterations_of_the_tiny_configuration(gpu):
+    """A generation with every second iteration timed chooses the same tokens as one that is not timed.  The heads make the order of the
+    additions visible: their rows hold pairs v, -v in drawn places, so that a logit is nothing but the rounding errors of its sum.  All
+    layers add zero to a state of ones."""
+    import torch
+    from dataclasses import replace
+    from rsd_inputs import workload
+
+    R = gpu["R"]
+    w = workload("cfg0", max_steps=2, deltas=(1.01,), sep_logit_bias=-100.0)      # (no separator: steps of step_cap tokens)
+    w = replace(w, draft=replace(w.draft, rms_eps=0.0), target=replace(w.target, rms_eps=0.0))
+    rng = np.random.default_rng(7)
+    weights = []
+    for i, s in enumerate(w.shapes):
+        d, kv, V = s.d_model, s.n_kv_heads * 32, s.vocab
+        layers = s.n_layers * (2 * d + 2 * d * d + 2 * kv * d + 3 * d * s.d_ffn)
+        if i == 2:
+            weights.append(np.zeros(V * d + layers + d + d + 8, dtype=np.float32))
+            continue
+        v = rng.standard_normal((V, d // 2))
+        head = rng.permuted(np.concatenate([v, -v], axis=1), axis=1)
+        weights.append(np.concatenate([np.ones(V * d), np.zeros(layers), np.ones(d), head.reshape(-1)]).astype(np.float32))
+    weights = [torch.from_numpy(b).cuda() for b in weights]
+    torch.cuda.synchronize()
+
+    def generate(model):
+        s = gpu["Session"](w, weights=weights)
+        ops = (0, 1, 2, 4)
+        if model is not None:
+            for slot, op in enumerate(ops):
+                R.rsd_probe_start(s.ctx, slot, model, DECODE, op, 1024, 2)
+        toks = [R.rsd_step(s.ctx) for _ in range(w.max_steps)]
+        rec = [R.rsd_probe_read(s.ctx, slot) for slot in range(len(ops))] if model is not None else None
+        s.close()
+        return np.stack([t["draft_tokens"] for t in toks]), np.stack([t["final_tokens"] for t in toks]), rec
+
+    plain = generate(None)
+    assert (plain[0] >= 0).all() and (plain[1] >= 0).all()
+    for model in (0, 1):
+        timed = generate(model)
+        assert (timed[0] == plain[0]).all() and (timed[1] == plain[1]).all(), model
+        s, (qkv, out, gate_up, head) = w.shapes[model], timed[2]
+        # iterations 0, 2, ... of the decode loops: 15 and 15 of the draft, which begins both steps with a chunked pass, 15 and 16 of the target
+        n = -(-(2 * w.step_cap - 2 + model) // 2)
+        d, B = s.d_model, w.batch
+        assert qkv["n"] == out["n"] == gate_up["n"] == n * s.n_layers and head["n"] == n
+        assert qkv["total_flops"] == out["total_flops"] == n * s.n_layers * 2 * B * d * (2 * d + 2 * s.n_kv_heads * 32)
+        assert gate_up["total_flops"] == n * s.n_layers * 2 * B * 3 * d * s.d_ffn
+        assert head["total_flops"] == n * 2 * B * d * s.vocab
+        assert min(r["total_ms"] for r in timed[2]) > 0
