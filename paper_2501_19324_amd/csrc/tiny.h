@@ -43,9 +43,10 @@ struct TinyIn {
     float eps;
     float* h_out;            // [M][D] where the sum goes (nullptr: nowhere)
 };
+// (LDS arrays that are read or written 16 bytes at a time say so: a float array alone need only be aligned to 4)
 template <int D> struct TinyLds {
-    float xs[D];             // the staged row times the gain, before 1 / rms
-    float part[kTinyT / (D / 4)][D];
+    alignas(16) float xs[D];                                // the staged row times the gain, before 1 / rms
+    alignas(16) float part[kTinyT / (D / 4)][D];
     float red[kTinyT / 64];
 };
 // What a thread holds of the row to be staged: one column and its gain, four columns of the partials i = g, g + GR, ...
@@ -104,8 +105,8 @@ __global__ __launch_bounds__(kTinyT) void tiny_attn_kernel(TinyIn in, const floa
                                                            float* __restrict__ out) {
     constexpr int HD = 32, NX = D / 64, NO = D / 64;         // float4s per lane of a weight row (16 lanes); passes of 64 rows of wo
     __shared__ TinyLds<D> s;
-    __shared__ float s_q[3][HD], s_att[HD];
-    __shared__ float s_acc[kTinyT / 64][HD], s_m[kTinyT / 64], s_l[kTinyT / 64];
+    __shared__ __attribute__((aligned(16))) float s_q[3][HD], s_att[HD], s_acc[kTinyT / 64][HD];
+    __shared__ float s_m[kTinyT / 64], s_l[kTinyT / 64];
     const int r = blockIdx.x, h = blockIdx.y, G = H / Hkv, hk = h / G, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int sub16 = tid & 15, row16 = tid >> 4, sub8 = tid & 7, row8 = tid >> 3;
     int seq, pos;
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(kTinyT) void tiny_mlp_kernel(TinyIn in, const float
                                                           RowMap rm, float* __restrict__ out) {
     constexpr int NX = D / 64, NO = D / 64;
     __shared__ TinyLds<D> s;
-    __shared__ float s_act[kTinyUnits];
+    __shared__ __attribute__((aligned(16))) float s_act[kTinyUnits];
     const int r = blockIdx.x, u0 = blockIdx.y * kTinyUnits, tid = threadIdx.x;
     const int sub16 = tid & 15, row16 = tid >> 4, sub8 = tid & 7, row8 = tid >> 3;
     int seq, pos;
