@@ -1,23 +1,56 @@
 """Decode stages whose sequences end at different lengths: every 16 iterations the sequences still at work move together into fewer rows
 (200 -> 128 -> 64 -> 32, 70 -> 64 -> 32).  The step is fixed by a teacher; every token the models would have chosen themselves is compared
-with rsd_forward on the same tokens, evaluated in one chunk.  A token may differ where the two best logits are closer than 2e-2 (both
-ways are within 3e-3 of the 64-bit value; a cache entry may be rounded either way)."""
+with rsd_forward on the same tokens, evaluated in one chunk.  A greedy token may differ where the two best logits are closer than 2e-2 (both
+ways are within 3e-3 of the 64-bit value; a cache entry may be rounded either way).  A sampled token must be the one that the sequence's own
+uniform draws: its interval of the distribution function reaches the uniform within 2e-2 (logits 6e-3 apart at T 0.7 move every mass by
+at most 0.9 %, a sum of masses and its total by as much each; another sequence's uniform would pass one time in 25), and its mass is
+at least 0.98 of the nucleus' smallest (the same 0.9 %, twice).  The rows launched are counted exactly."""
 import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
 
 
+def launched_rows(n, batch, cap, first):
+    """Rows launched by a decode loop over ``batch`` rows whose sequences end after n[b] tokens, ``first`` of them sampled before the loop:
+    at every 16th iteration the rows fall to the next of 32, 64, 128, ... that holds the sequences still at work."""
+    rows, total = batch, 0
+    for i in range(first + 1, cap + 1):
+        total += rows
+        if i % 16 == 0 and i < cap:
+            alive = int((n > i).sum())
+            if not alive:
+                break
+            if rows > 32:
+                rows = min(rows, 32 if alive <= 32 else 64 if alive <= 64 else -(-alive // 128) * 128)
+    return total
+
+
+def off_by(logits, tokens, u, w):
+    """How far u is from the interval of the distribution function that draws each token, and the token's mass over the nucleus' smallest"""
+    import torch
+    p = torch.softmax(logits.double() / w.temperature, -1)
+    desc = p.sort(-1, descending=True).values
+    at = (desc.cumsum(-1) < w.top_p).sum(-1, keepdim=True).clamp(max=p.shape[-1] - 1)
+    tau = desc.gather(1, at)
+    run = torch.where(p >= tau, p, 0.0)
+    z = run.sum(-1)
+    hi = run.cumsum(-1).gather(1, tokens[:, None])[:, 0] / z
+    lo = hi - run.gather(1, tokens[:, None])[:, 0] / z
+    return torch.maximum(lo - u, u - hi).clamp(min=0.0), p.gather(1, tokens[:, None])[:, 0] / tau[:, 0]
+
+
+@pytest.mark.parametrize("sampled", [False, True], ids=["greedy", "sampled"])
 @pytest.mark.parametrize("batch,cap,alive", [(70, 40, (60, 20)), (200, 70, (190, 120, 50, 3)), (40, 33, (32, 1))])
-def test_rows_given_up_by_finished_sequences(batch, cap, alive):
+def test_rows_given_up_by_finished_sequences(batch, cap, alive, sampled):
     import torch
     assert torch.cuda.is_available(), "these tests need the MI355X"
     from paper_2501_19324_amd import binding as R
     from paper_2501_19324_amd.harness import Session
     from rsd_inputs import workload
 
-    w = workload("cfg1", n_layers=1, vocab=4096, batch=batch, prompt_len_min=3, prompt_len_max=9, step_cap=cap, max_steps=1, temperature=0.0,
-                 top_p=1.0, deltas=(0.5,), sep_logit_bias=0.0)
+    w = workload("cfg1", n_layers=1, vocab=4096, batch=batch, prompt_len_min=3, prompt_len_max=9, step_cap=cap, max_steps=1,
+                 temperature=0.7 if sampled else 0.0, top_p=0.95 if sampled else 1.0, deltas=(0.5,), sep_logit_bias=0.0)
     s = Session(w)
     rng = np.random.default_rng(batch)
 
@@ -44,7 +77,7 @@ def test_rows_given_up_by_finished_sequences(batch, cap, alive):
     assert list(rec["draft_len"]) == list(nd) and list(rec["final_len"]) == list(nt)
     own = R.rsd_export_sampled(s.ctx)
     rows = [R.rsd_iter_rows(s.ctx, m) for m in (0, 1)]
-    assert max(rows) < batch * (cap - 1)                            # (rows were given up)
+    assert rows == [launched_rows(n, batch, cap, 1) for n in (nd, nt)] and max(rows) < batch * (cap - 1)
     T = int(s.prompt_len.max()) + cap
     for which, toks, n, mine in ((0, fd, nd, own[0]), (1, ft, nt, own[1])):
         full = np.zeros((batch, T), dtype=np.int32)
@@ -55,7 +88,45 @@ def test_rows_given_up_by_finished_sequences(batch, cap, alive):
         best = out.max(dim=-1).values.cpu().numpy()
         for b, p in enumerate(s.prompt_len):
             idx = torch.from_numpy(np.array(mine[b, 0, :n[b]], dtype=np.int64)).cuda()
+            if sampled:
+                u = s.u["U_DRAFT" if which == 0 else "U_TARGET"][b, p:p + n[b]].double()
+                off, mass = off_by(out[b, p - 1:p - 1 + n[b]], idx, u, w)
+                assert float(off.max()) <= 2e-2 and float(mass.min()) >= 0.98, (which, b)
+                continue
             got = out[b, p - 1:p - 1 + n[b]].gather(1, idx[:, None])[:, 0].cpu().numpy()
             assert (best[b, p - 1:p - 1 + n[b]] - got <= 2e-2).all(), (which, b)
     R.rsd_set_teacher(s.ctx, None, None, None)
+    s.close()
+
+
+def test_best_of_n_lanes_given_up():
+    """48 candidate lanes that share their prompts' pages, sampled, steps that end at drawn separators: 48 -> 32 rows in the step."""
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2501_19324_amd import binding as R
+    from paper_2501_19324_amd.harness import BonSession
+    from rsd_inputs import workload
+
+    lanes, n, cap = 48, 4, 40
+    w = workload("cfg1", n_layers=1, vocab=4096, batch=lanes // n, prompt_len_min=20, prompt_len_max=45, step_cap=cap, max_steps=1,
+                 temperature=0.7, top_p=0.95, deltas=(0.5,), sep_logit_bias=3.5)
+    s = BonSession(w, n)
+    rec = R.rsd_bon_step(s.ctx)
+    assert R.rsd_bon_stats(s.ctx)["pages_shared"] > 0
+    length, toks = rec["cand_len"].reshape(-1), rec["cand_tokens"].reshape(lanes, cap)
+    rows = R.rsd_iter_rows(s.ctx, 0)
+    assert rows == launched_rows(length, lanes, cap, 0) and (length > 16).sum() in range(1, 33) and length.max() > 17
+    plen = np.repeat(s.prompt_len, n)
+    T = int(plen.max()) + cap
+    full = np.zeros((lanes, T), dtype=np.int32)
+    for i, p in enumerate(plen):
+        full[i, :p] = s.tokens_host[i // n, :p]
+        full[i, p:p + length[i]] = toks[i, :length[i]]
+    out = R.rsd_forward(s.ctx, 0, full, (plen + length).astype(np.int32), T)
+    out[:, :, w.sep_id] += w.sep_logit_bias
+    for i, p in enumerate(plen):
+        k = int(length[i])
+        idx = torch.from_numpy(toks[i, :k].astype(np.int64)).cuda()
+        off, mass = off_by(out[i, p - 1:p - 1 + k], idx, s.u[i, p:p + k].double(), w)
+        assert float(off.max()) <= 2e-2 and float(mass.min()) >= 0.98, i
     s.close()
