@@ -371,8 +371,10 @@ int rsd_iter_stats(rsd_ctx *c, int32_t model, int64_t *iterations, double *gpu_m
 /* Rows launched by the iterations rsd_iter_stats counts: the sum over those iterations of the number of
  * activation rows every kernel of the iteration was launched over.  A stage in which only some sequences
  * take part (the target's stage of Algorithm 1 after the reward model accepted the other sequences' steps)
- * packs its sequences into fewer rows than the batch has (1..8 exactly, then 32, 64, multiples of 128), so
- * row_iterations / iterations lies between the mean number of active sequences and the batch size.
+ * packs its sequences into fewer rows than the batch has (1..8 exactly, then 32, 64, multiples of 128).  Within
+ * a stage of more than 32 rows, after every 16th token of the step, the sequences still at work move into fewer
+ * rows as soon as they fit (multiples of 128, 64, 32; not below).  So row_iterations / iterations lies between
+ * the mean number of active sequences and the batch size.
  * Cleared together with rsd_iter_stats' counters.  Host output. */
 int rsd_iter_rows(rsd_ctx *c, int32_t model, int64_t *row_iterations);
 

@@ -899,8 +899,9 @@ static void gemm_rows_sk_launch(hipStream_t st, const bf16_t* W, int N, int K, c
 
 // K blocks per slice from which gemm_rows64_kernel requests the activations as far ahead as the weights: a step of one block ahead lasts as
 // long as an L2 read, which a long slice pays many times (1536 x 8960, 18 blocks: 4 rows 10.9 -> 8.2 us, 16 rows 11.0 -> 9.0, 32 rows
-// 11.4 -> 10.2, 64 rows 14.1 -> 13.4); short ones re-read their last block for the requests beyond it (7 blocks, 3584 x 3584: 64 rows
-// 11.9 -> 13.5; 10 blocks, 4608 x 3584: 15.2 -> 16.6).
+// 11.4 -> 10.2, 64 rows 14.1 -> 13.4); short ones re-read their last block for the requests beyond it, at 64 rows (7 blocks, 3584 x 3584:
+// 14.9 -> 15.9; 10 blocks, 4608 x 3584: 17.3 -> 18.4) as at fewer (4 / 16 / 32 rows: 8.8 -> 8.5, 9.6 -> 9.7, 11.0 -> 11.3 and 10.3 -> 10.1,
+// 11.2 -> 11.4, 13.0 -> 13.3; within whole passes).  No matrix with slices of 11 to 17 blocks has been measured: the line lies between.
 constexpr int kLongSlice = 14;
 static void gemm_rows_launch(hipStream_t st, const bf16_t* W, int N, int K, const uint16_t* Xh, const uint16_t* Xl,
                              int M, float* part, int ks) {

@@ -84,7 +84,8 @@ struct PageTable {
     }
 };
 
-// Rows of a decode iteration that serves n_act of B sequences, or 0 when one row per sequence is as cheap.
+// Rows of a decode iteration that serves n_act sequences, or 0 when that is not fewer than the B rows it would have otherwise: one per
+// sequence of the batch at the start of a stage, the rows in use when sequences have finished within it.
 // The sizes are those at which the matrix kernels change: up to 8 rows the exact count (single-row and
 // few-row vector kernels), 32 and 64 (one or two MFMA row tiles of the weight-streaming kernels), then whole
 // 128-row tiles.

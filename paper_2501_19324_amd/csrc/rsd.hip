@@ -795,9 +795,11 @@ void propose_stash(rsd_ctx* c, int mode) {
                        c->p.sd_k, c->sd_qlogits);
 }
 
-// Which single-token iterations the two-launch layers of tiny.h serve: fp32 weights of the widths that fit their registers, contexts that
-// the attention does not split either, and up to eight rows - every row reads the weights for itself there, which the
-// kernels for more rows share.  The head as far as a block per 64 tokens and row is less than the chip holds at once.
+// Which single-token iterations the two-launch layers of tiny.h serve: fp32 weights, head_dim 32, the widths they are built for (128 and
+// 256; a width has to cut 512 threads into whole groups of d_model / 4, and to be whole waves), an MLP whose partial sums a thread's
+// registers hold, up to eight rows - every row reads the weights for itself there, which the kernels for more rows share - and
+// contexts that can never exceed the 128 positions a block holds.  The capacity decides and not the positions in use: those live on the
+// device, and one recorded iteration serves them all.  The head as far as a block per 64 tokens and row is less than the chip holds at once.
 // It does not depend on whether an iteration is timed: the other kernels add in another order, and a measured generation is the same generation.
 bool tiny_path(const Model& m, int M) {
     const rsd_model_shape& s = m.s;
@@ -1055,8 +1057,8 @@ int gen_stage(rsd_ctx* c, int which, const float* u, const int* forced, int mode
     // A stage that only some sequences take part in (the target's, after the reward model has accepted the
     // others' steps) runs its iterations over packed rows: every launch then costs what the rows in use cost, not
     // what the batch costs.  The row count is rounded up to the next size at which the matrix kernels change
-    // (few counts, so few recorded graphs); unused rows are marked -1.  Sequences that finish their step early
-    // keep their row until the stage ends.
+    // (few counts, so few recorded graphs); unused rows are marked -1.  Above kRepackRows rows, sequences that
+    // finish their step early give their row up at the polls below; up to there they keep it until the stage ends.
     struct PackScope {
         rsd_ctx* c;
         ~PackScope() { c->dec_rows = 0; }
