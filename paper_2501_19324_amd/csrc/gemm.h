@@ -1368,17 +1368,23 @@ __global__ __launch_bounds__((StreamCfg<MT, BN>::NW * 64)) void gemm_stream_kern
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int p = 0; p < PV; ++p) {
-                float2 own = make_float2(0.0f, 0.0f), y[KW - 1];   // the wave's own pair (its registers have constant indices only)
+                // (scalars, chosen between with constant indices: float2 structs would be chosen by address, in scratch memory)
+                float xo = 0.0f, yo = 0.0f, xq[KW - 1], yq[KW - 1];      // the wave's own pair, the others'
 #pragma unroll
-                for (int o = 0; o < KW; ++o)
-                    if (o == kw) own = make_float2(acc[i][j][o * PV + p], acc[i][j][o * PV + p + 8]);
+                for (int o = 0; o < KW; ++o) {
+                    xo = o == kw ? acc[i][j][o * PV + p] : xo;
+                    yo = o == kw ? acc[i][j][o * PV + p + 8] : yo;
+                }
 #pragma unroll
-                for (int q = 0; q < KW - 1; ++q) y[q] = *at(kw, q < kw ? q : q + 1, j, p);
-                float2 x = kw == 0 ? own : y[0];
+                for (int q = 0; q < KW - 1; ++q) {
+                    const float2 y = *at(kw, q < kw ? q : q + 1, j, p);
+                    xq[q] = y.x; yq[q] = y.y;
+                }
+                float2 x = make_float2(kw == 0 ? xo : xq[0], kw == 0 ? yo : yq[0]);
 #pragma unroll
                 for (int q = 1; q < KW; ++q) {
-                    const float2 z = q == kw ? own : q < kw ? y[min(q, KW - 2)] : y[q - 1];
-                    x.x += z.x; x.y += z.y;
+                    x.x += q == kw ? xo : q < kw ? xq[q < KW - 1 ? q : 0] : xq[q - 1];
+                    x.y += q == kw ? yo : q < kw ? yq[q < KW - 1 ? q : 0] : yq[q - 1];
                 }
                 const int v = kw * PV + p, m0 = (wm * TM + i) * 32 + 8 * (v >> 2) + 4 * kg + (v & 3);       // x.y: row m0 + 16
                 if (EPI == EPI_SWIGLU) {
