@@ -49,6 +49,7 @@ template <int D> struct TinyLds {
     alignas(16) float part[kTinyT / (D / 4)][D];
     float red[kTinyT / 64];
 };
+static_assert(alignof(TinyLds<128>) == 16 && alignof(TinyLds<256>) == 16, "");
 // What a thread holds of the row to be staged: one column and its gain, four columns of the partials i = g, g + GR, ...
 // Requested before the weights: loads return in order, and staging would otherwise wait for all of them.
 template <int D> struct TinyRow {
